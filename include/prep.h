@@ -91,7 +91,8 @@ enum { PREP_FILTER_BILINEAR = 0, PREP_FILTER_ANTIALIAS = 1 };
  *   sample replication.  Reconstruction then takes two kernels and a chroma workspace a third
  *   of the RGB workspace's size; prep_debug_last_region leaves out the outermost chroma sample
  *   of the converted region where that does not end with the image.
- * PREP_FLAG_LARGE_WINDOWS: a call with little entropy-coded data (up to 1.5 MiB, and in
+ * PREP_FLAG_LARGE_WINDOWS: an image without restart markers is normally cut into pieces that
+ *   several workgroups decode side by side; with this flag one workgroup decodes it.  And a call with little entropy-coded data (up to 1.5 MiB, and in
  *   smaller pieces still up to 448 KiB) is normally cut into more and smaller pieces for the
  *   entropy decoder, which then finds the decoder states
  *   inside restart intervals by hypotheses over the block's place in the MCU, so that the

@@ -207,6 +207,8 @@ struct Plan {                         // what one call will run
     uint64_t rgb_bytes = 0;
     uint32_t max_region_pixels = 0;  // most pixels in the reconstructed region of one image
     uint32_t window_bytes = kWindowBytes;  // raw bytes between the decoder's workgroup starts
+    uint32_t n_streams = 0;     // windows of the streams without restart markers
+    uint32_t row_bytes = kStreamRowBytes;  // clean bytes of a row of such a window
 };
 
 }  // namespace
@@ -224,6 +226,9 @@ struct prep_handle {
     std::vector<uint32_t> table_hash;  // open-addressed: slot + 1 of a table set by the hash of its DHT bytes, 0 = free
     int32_t *d_status = nullptr;
     uint32_t *d_win_count = nullptr, *d_win_first = nullptr;
+    uint32_t *d_retry = nullptr;          // images whose windows did not link up: decoded in one piece
+    StreamWindow *d_streams = nullptr;    // cap_streams of them
+    uint64_t cap_streams = 0;
     Slot slot[kSlots];
     int next_slot = 0;
     // stage timing: one set of 5 events per call, kept for the last kTimedCalls calls
@@ -317,13 +322,15 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
     h->table_rep.clear();
     std::fill(h->table_hash.begin(), h->table_hash.end(), 0u);
     Plan P;
-    uint64_t entropy_total = 0;
+    uint64_t entropy_total = 0, unmarked_total = 0;
     for (int32_t i = 0; i < n; i++) {
         if (offsets[i + 1] < offsets[i]) return PREP_E_INVALID_ARG;
         ParsedImage &pi = h->parsed[(size_t)i];
         parse_image(bits + offsets[i], offsets[i + 1] - offsets[i], &pi);
         if (pi.info.status == PREP_OK) entropy_total += pi.info.entropy_bytes;
+        if (pi.info.status == PREP_OK && pi.info.restart_interval == 0) unmarked_total += pi.info.entropy_bytes;
     }
+    if (unmarked_total <= kStreamTinyBytes) P.row_bytes = kStreamTinyRowBytes;
     // a call with little data is cut into small windows, for the decoder variant that fills
     // the chip with hypotheses instead of walking whole restart intervals lane by lane
     if (entropy_total <= kSmallCallBytes && !(h->cfg.flags & PREP_FLAG_LARGE_WINDOWS))
@@ -341,6 +348,7 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
         R.window0 = P.n_windows;
         R.group0 = P.n_groups;
         R.coef_block0 = (uint32_t)P.n_blocks;
+        R.stream0 = P.n_streams;
         R.rgb_off = P.rgb_bytes;
         R.status = I.status;
         R.n_windows = 1;
@@ -354,6 +362,13 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
             R.rgb_pitch = (uint32_t)I.mcu_cols * 8u * hs * 3u;
             for (int t = 0; t < 4; t++) { R.dht_off[t] = pi.dht_off[t]; R.dht_nval[t] = pi.dht_nval[t]; }
             R.table_slot = table_slot_of(h, bits, offsets, i);
+            // Without restart markers the stream is cut into windows that several workgroups decode
+            // side by side.  (A workgroup that has to expand the tables itself spends longer on them
+            // than on a window: such a stream stays with one workgroup, which does so once.)
+            if (I.restart_interval == 0 && R.table_slot != kNoTableSlot && !(h->cfg.flags & PREP_FLAG_LARGE_WINDOWS)) {
+                const uint32_t step = stream_window_bytes((uint32_t)I.blocks_per_mcu, P.row_bytes);
+                R.n_streams = (uint32_t)std::max<uint64_t>((I.entropy_bytes + step - 1) / step, 1);
+            }
             for (int c = 0; c < 3; c++) R.dqt_off[c] = pi.dqt_off[c];
             R.width = (uint16_t)I.width;
             R.height = (uint16_t)I.height;
@@ -365,6 +380,7 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
             if (!make_resize_rec(I.width, I.height, params, R.rgb_off, R.rgb_pitch, &Z)) {
                 // the crop window does not fit this image after resizing
                 I.status = R.status = PREP_E_UNSUPPORTED;
+                R.n_streams = 0;
             }
         }
         if (R.status == PREP_OK) {
@@ -401,6 +417,7 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
                                                      region_cols * 8u * (uint32_t)luma_h(R.sampling) * (uint32_t)R.roi_rows * 8u * (uint32_t)luma_v(R.sampling));
         }
         P.n_windows += R.n_windows;
+        P.n_streams += R.n_streams;
     }
     P.n_tables = (uint32_t)h->table_rep.size();
     // A reconstruction workgroup takes several groups of its image when there are plenty, so
@@ -412,7 +429,8 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
         if (R.status == PREP_OK)
             P.recon_wgs += ((uint32_t)R.roi_gcols * R.roi_rows + P.groups_per_wg - 1) / P.groups_per_wg;
     }
-    if (P.n_blocks > h->cap_blocks || P.rgb_bytes > h->cap_rgb || P.n_windows > h->cap_windows)
+    if (P.n_blocks > h->cap_blocks || P.rgb_bytes > h->cap_rgb || P.n_windows > h->cap_windows ||
+        P.n_streams > h->cap_streams)
         return PREP_E_TOO_LARGE;
     *plan = P;
     return PREP_OK;
@@ -497,14 +515,18 @@ int run_batch(prep_handle *h, const uint8_t *bits_host, const uint8_t *bits_dev,
     } else {
         // (P.n_windows >= n > 0: the scan also sets every image's status)
         launch_scan_restart_markers(d_bits, s->d_recs, n, P.n_windows, P.window_bytes, h->d_win_count, h->d_win_first,
-                                    s->d_data_end,
+                                    s->d_data_end, h->d_retry,
                                     h->d_status, reinterpret_cast<const uint32_t *>(s->d_recs + n) + n,
                                     P.n_tables, h->d_tables, stream);
         if (timing) HIP_TRY(hipEventRecord(ev[1], stream));
+        launch_decode_streams(d_bits, s->d_recs, n, P.n_streams, P.row_bytes, s->d_data_end, h->d_retry, h->d_streams,
+                              h->d_coef, (uint32_t)(h->cap_blocks * 64), h->d_tables, stream);
         launch_decode_entropy(d_bits, s->d_recs, n, P.n_windows, h->d_win_count, h->d_win_first, s->d_data_end,
-                              h->d_coef, (uint32_t)(h->cap_blocks * 64), h->d_status, h->d_tables,
+                              h->d_retry, h->d_coef, (uint32_t)(h->cap_blocks * 64), h->d_status, h->d_tables,
                               P.window_bytes != (uint32_t)kWindowBytes,
                               P.window_bytes == (uint32_t)kTinyWindowBytes ? 256u : 512u, stream);
+        launch_finish_streams(s->d_recs, n, P.n_streams, h->d_retry, h->d_streams, h->d_coef,
+                              (uint32_t)(h->cap_blocks * 64), stream);
         if (timing) HIP_TRY(hipEventRecord(ev[2], stream));
     }
     launch_reconstruct(d_bits, s->d_recs, reinterpret_cast<const uint32_t *>(s->d_recs + n), n, P.recon_wgs,
@@ -556,6 +578,9 @@ int prep_create(prep_handle **out, const prep_config *cfg)
     h->cap_windows = std::max<uint64_t>(cfg->max_bitstream_bytes / kWindowBytes,
                                         std::max<uint64_t>(std::min<uint64_t>(cfg->max_bitstream_bytes, kSmallCallBytes) / kSmallWindowBytes,
                                                            std::min<uint64_t>(cfg->max_bitstream_bytes, kTinyCallBytes) / kTinyWindowBytes)) + n + 1;
+    // (the shortest stream windows are those of six blocks per MCU; an image ends with a partial one)
+    h->cap_streams = std::max<uint64_t>(cfg->max_bitstream_bytes / stream_window_bytes(6, kStreamRowBytes),
+                                        std::min<uint64_t>(cfg->max_bitstream_bytes, kStreamTinyBytes) / stream_window_bytes(6, kStreamTinyRowBytes)) + n + 1;
     h->cap_bits = cfg->max_bitstream_bytes + kBitsPad;
     // (the kernels index the workspace and its side array with 32-bit element offsets)
     if (h->cap_blocks * 65 > 0xFFFFFFFFull) { delete h; return PREP_E_TOO_LARGE; }
@@ -575,6 +600,8 @@ int prep_create(prep_handle **out, const prep_config *cfg)
     ok = ok && hipMalloc((void **)&h->d_status, sizeof(int32_t) * n) == hipSuccess;
     ok = ok && hipMalloc((void **)&h->d_win_count, sizeof(uint32_t) * h->cap_windows) == hipSuccess;
     ok = ok && hipMalloc((void **)&h->d_win_first, sizeof(uint32_t) * h->cap_windows) == hipSuccess;
+    ok = ok && hipMalloc((void **)&h->d_retry, sizeof(uint32_t) * n) == hipSuccess;
+    ok = ok && hipMalloc((void **)&h->d_streams, sizeof(StreamWindow) * h->cap_streams) == hipSuccess;
     for (int i = 0; ok && i < kSlots; i++) {
         Slot &s = h->slot[i];
         ok = ok && hipHostMalloc((void **)&s.h_bits, h->cap_bits, hipHostMallocDefault) == hipSuccess;
@@ -609,6 +636,8 @@ int prep_destroy(prep_handle *h)
     (void)hipFree(h->d_status);
     (void)hipFree(h->d_win_count);
     (void)hipFree(h->d_win_first);
+    (void)hipFree(h->d_retry);
+    (void)hipFree(h->d_streams);
     for (int i = 0; i < kSlots; i++) {
         Slot &s = h->slot[i];
         if (s.h_bits) (void)hipHostFree(s.h_bits);

@@ -687,8 +687,8 @@ struct DcWalk {
     }
 };
 
-__device__ inline void dc_prefix(DecodeShared &S, const Geometry &g, int16_t *coef, const int16_t *side,
-                                 uint32_t lo, uint32_t hi, int32_t carry[3])
+__device__ inline void dc_prefix(int32_t *scan_val, int32_t *scan_flag, const Geometry &g, int16_t *coef,
+                                 const int16_t *side, uint32_t lo, uint32_t hi, int32_t carry[3])
 {
     __syncthreads();  // the stores of every lane (zeros, coefficients, differences) are done and visible
     const uint32_t n = hi > lo ? hi - lo : 0u;
@@ -714,11 +714,11 @@ __device__ inline void dc_prefix(DecodeShared &S, const Geometry &g, int16_t *co
         }
     }
     int32_t out;
-    int32_t c0 = block_seg_excl_scan(s0, r0, carry[0], S.dc_val, S.dc_flag, &out);
+    int32_t c0 = block_seg_excl_scan(s0, r0, carry[0], scan_val, scan_flag, &out);
     carry[0] = out;
-    int32_t c1 = block_seg_excl_scan(s1, r1, carry[1], S.dc_val, S.dc_flag, &out);
+    int32_t c1 = block_seg_excl_scan(s1, r1, carry[1], scan_val, scan_flag, &out);
     carry[1] = out;
-    int32_t c2 = block_seg_excl_scan(s2, r2, carry[2], S.dc_val, S.dc_flag, &out);
+    int32_t c2 = block_seg_excl_scan(s2, r2, carry[2], scan_val, scan_flag, &out);
     carry[2] = out;
     wk.start(g, a);
     for (uint32_t i = a; i < b; i += 8) {
@@ -799,8 +799,8 @@ __device__ inline void classify16(const uint4 v, uint32_t prev, uint32_t nextb, 
 __global__ __launch_bounds__(kDecodeThreads) void scan_restart_markers(
     const uint8_t *__restrict__ bits, const ImageRec *__restrict__ recs, int n_images,
     uint32_t n_windows, uint32_t window_bytes, uint32_t *__restrict__ win_count,
-    uint32_t *__restrict__ win_first, uint32_t *__restrict__ data_end, int32_t *__restrict__ status,
-    const uint32_t *__restrict__ table_rep, uint4 *__restrict__ tables)
+    uint32_t *__restrict__ win_first, uint32_t *__restrict__ data_end, uint32_t *__restrict__ retry,
+    int32_t *__restrict__ status, const uint32_t *__restrict__ table_rep, uint4 *__restrict__ tables)
 {
     __shared__ uint32_t s_cnt[kT / 64], s_first[kT / 64];
     const uint32_t wg = blockIdx.x;
@@ -836,7 +836,10 @@ __global__ __launch_bounds__(kDecodeThreads) void scan_restart_markers(
     const ImageRec &R = recs[img];
     const uint32_t w = wg - R.window0;
     // the per-image verdict starts as the host parser's; the decoder may lower it
-    if (w == 0 && threadIdx.x == 0) status[img] = R.status;
+    if (w == 0 && threadIdx.x == 0) {
+        status[img] = R.status;
+        retry[img] = 0;
+    }
     uint32_t cnt = 0, first = kNoMarker, eoi = kNoMarker;
     if (R.status == PREP_OK && w < R.n_windows) {
         const bool count_rst = R.restart_interval != 0;
@@ -895,8 +898,8 @@ template <bool kHyp>
 __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
     const uint8_t *__restrict__ bits, const ImageRec *__restrict__ recs, int n_images,
     const uint32_t *__restrict__ win_count, const uint32_t *__restrict__ win_first,
-    const uint32_t *__restrict__ data_end, int16_t *__restrict__ coef_all, uint32_t side_off,
-    int32_t *__restrict__ status, const uint4 *__restrict__ tables, uint32_t hyp_span_bits)
+    const uint32_t *__restrict__ data_end, const uint32_t *__restrict__ retry, int16_t *__restrict__ coef_all,
+    uint32_t side_off, int32_t *__restrict__ status, const uint4 *__restrict__ tables, uint32_t hyp_span_bits)
 {
     __shared__ DecodeShared S;
     const int tid = threadIdx.x;
@@ -905,6 +908,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
     const ImageRec &R = recs[img];
     const uint32_t w = wg - R.window0;
     if (R.status != PREP_OK || w >= R.n_windows) return;
+    if (R.n_streams != 0 && retry[img] == 0) return;  // decoded by write_streams
 
     Geometry g;
     g.bpm = R.blocks_per_mcu;
@@ -1165,7 +1169,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
                 // DC values of the blocks whose DC was decoded here (the chunk may begin inside a block)
                 const uint32_t dc_lo = block_base + ((st0 & 63u) ? 1u : 0u);
                 block_base = min(block_base + rem0 + (n_iv - 1) * g.ri_blocks, block_end);
-                dc_prefix(S, g, coef, coef + side_rel, dc_lo, min(block_base, g.n_blocks), dc_carry);
+                dc_prefix(S.dc_val, S.dc_flag, g, coef, coef + side_rel, dc_lo, min(block_base, g.n_blocks), dc_carry);
             }
             st0 = pack_state(0, 0, 0);
             dc_carry[0] = dc_carry[1] = dc_carry[2] = 0;
@@ -1342,7 +1346,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
             // a block (DC decoded earlier) and end inside one (DC decoded here)
             const uint32_t dc_lo = block_base + ((st0 & 63u) ? 1u : 0u);
             const uint32_t dc_hi = block_base + total_blocks + ((fs & 63u) ? 1u : 0u);
-            dc_prefix(S, g, coef, coef + side_rel, dc_lo, min(dc_hi, g.n_blocks), dc_carry);
+            dc_prefix(S.dc_val, S.dc_flag, g, coef, coef + side_rel, dc_lo, min(dc_hi, g.n_blocks), dc_carry);
         }
 
         // carry the true end state into the next chunk
@@ -1389,35 +1393,643 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
     }
 }
 
+// ---- streams without restart markers ------------------------------------------------
+//
+// decode_entropy gives such a stream to one workgroup, which walks it chunk by chunk and, in
+// every chunk, iterates until the states at the subsequence borders settle: a chain as long as
+// the file (a full-HD still: 14 ms) on a chip that is idle otherwise.  Here the stream is cut
+// into windows, one workgroup each, that are decoded side by side without knowing the state in
+// which the stream enters them.  What takes long to fall into step is the block's place in the
+// MCU; bit position and zig-zag index do so within a block or two.  So:
+//
+//   resolve_streams  A window's clean bytes are cut into rows of row_bytes; lane (j, h) decodes
+//       row j from its first bit with the hypothesis "block h of an MCU begins here" (pass 0) and
+//       then row j + 1 from the state it reached (pass 1): a node.  A node's end state is looked
+//       up among the pass-0 ends of its own row: the equal one is where a node of the next row
+//       begins.  An end state that is none of them (1 to 10 % of the nodes) gets a node of its own
+//       in the next row, decoded in a further pass with the others of its kind.  The last
+//       rows, the overlap, are the first rows of the next window: where a chain of nodes meets
+//       one of the hypotheses there, the next window has the node that goes on from it.  So every
+//       entry (overlap row, hypothesis) leads to an exit of the same form and a count of blocks.
+//   chain_streams    follows the entries from window to window of an image: the true chain.
+//   write_streams    decodes every window's rows once more, from the true states.
+//   finish_streams   DC differences -> DC values.
+//
+// Whatever does not fit this scheme (a chain that meets no hypothesis within the overlap, markers
+// inside the data, a stream that ends in the wrong state) is set in retry[], and decode_entropy
+// decodes the image, and judges it, as if there were no windows.
+//
+// The work is 2 H + 1 decodes of every byte (H = blocks per MCU) against about ten by iteration
+// over 4:2:0, but none waits for another for longer than a row.  Whole calls, one workgroup per
+// image against windows: a 44 KB photograph 1068 -> 132 us, a 760 KB full-HD still 14 100 -> 199 us,
+// 128 photographs (5 MB) 1901 -> 461 us, 512 thumbnails of 4:4:4, 4:2:0 and gray (5.6 MB)
+// 1156 -> 465 us; no size was slower.  resolve_streams and write_streams are bound by a lane's
+// dependent symbols (about 0.1 us each when the chip is idle) and, where the chip is full, by
+// instruction issue: 167 and 108 us of the thumbnails' 465.
+
+namespace {
+
+constexpr uint32_t kToEnd = 254, kNoWay = 255;       // instead of an exit or an entry
+constexpr uint32_t kExit = 0x8000, kNodeToEnd = 0xFFFE, kNodeNoWay = 0xFFFF;  // instead of a next node
+constexpr uint32_t kOpenLimit = 1u << 22;            // bit limit of a window that the data go on after
+constexpr int kStreamSlack = 32;                     // raw bytes staged behind the overlap
+// clean words of a window: its own bytes and, where every byte is stuffed, the overlap's at half
+// their raw number, or twice as many where none is; then zeros
+constexpr int kStreamWords = (int)(stream_window_bytes(3, kStreamRowBytes) + 2 * stream_overlap(kStreamRowBytes) * kStreamRowBytes +
+                                   kStreamSlack + 64) / 4;
+static_assert(stream_rows(1) <= stream_rows(3) && stream_rows(4) <= stream_rows(3) && stream_rows(6) <= stream_rows(3),
+              "4:4:4 has the largest windows");
+
+struct StreamShared {
+    uint32_t clean[kStreamWords];    // the window's bytes without stuffing, big-endian packed
+    HuffTables tab;
+    uint32_t scan_a[kT / 64 + 1];
+    uint32_t bcast[4];
+};
+
+struct StreamPart {                  // what staging found
+    uint32_t own, total;             // clean bytes of the window itself, and with what follows
+    bool to_end;                     // the staged bytes reach the end of the data
+    bool marker;                     // a marker other than stuffing lies among them
+};
+
+// Stage the raw bytes [w * step, (w + 1) * step) of the segment and enough after them for the
+// overlap rows into S.clean.  All lanes must call.
+__device__ inline StreamPart stage_stream(StreamShared &S, const uint8_t *seg, uint32_t data_len, uint32_t w,
+                                          uint32_t step, uint32_t row_bytes)
+{
+    const int tid = threadIdx.x;
+    const int32_t cs = (int32_t)(w * step), own_end = (int32_t)min(w * step + step, data_len);
+    const int32_t ce = (int32_t)min(w * step + step + 2u * stream_overlap(row_bytes) * row_bytes + kStreamSlack, data_len);
+    StreamPart part;
+    part.to_end = ce == (int32_t)data_len;
+    // 16-byte aligned parts that cover [cs, ce), one or two to a lane
+    const int32_t a0 = cs - (int32_t)((uintptr_t)(seg + cs) & 15u);
+    const int32_t n_parts = (ce - a0 + 15) >> 4;
+    const int32_t per = n_parts > kT ? 2 : 1;
+    static_assert(kStreamWords * 4 <= 2 * kT * 16, "two parts a lane hold a window");
+    uint4 v[2];
+    uint32_t keep[2] = {0, 0}, bound = 0;
+    int32_t bad = 0;
+    const int32_t my_lo = a0 + tid * per * 16;
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+        const int32_t plo = my_lo + 16 * k;
+        v[k] = make_uint4(0, 0, 0, 0);
+        if (k < per && plo < ce) v[k] = *reinterpret_cast<const uint4 *>(seg + plo);
+    }
+    uint32_t n_own = 0, n_all = 0;
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+        const int32_t plo = my_lo + 16 * k;
+        if (k < per && plo < ce) {
+            // the byte before the part (the segment's first byte has none) and the one after it
+            // (at the end of the data, the FF of the marker there)
+            uint32_t prev = plo > 0 ? load_byte(seg + plo - 1) : 0u, b = 0;
+            const uint32_t after = plo + 16 < (int32_t)data_len ? load_byte(seg + plo + 16) : 0xFFu;
+            classify16(v[k], prev, after, plo, cs, ce, &keep[k], &b, &prev, &bad);
+            bound |= b;
+            const int32_t left = own_end - plo;
+            const uint32_t mine = left >= 16 ? 0xFFFFu : left > 0 ? (1u << left) - 1u : 0u;
+            n_own += (uint32_t)__popcll(keep[k] & mine);
+            n_all += (uint32_t)__popcll(keep[k]);
+        }
+    }
+    uint32_t totals;
+    const uint32_t before = block_excl_scan(n_all | (n_own << 16), S.scan_a, &totals) & 0xFFFFu;
+    part.total = totals & 0xFFFFu;
+    part.own = totals >> 16;
+    // zeros behind the data: the last word is written byte by byte, and lookups near the end
+    // read a few words past it
+    if (tid < 6) S.clean[(part.total >> 2) + (uint32_t)tid] = 0;
+    part.marker = __syncthreads_or(bound != 0 || bad != 0) != 0;
+    uint8_t *cb = reinterpret_cast<uint8_t *>(S.clean);
+    uint32_t o = before;
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+        const uint32_t wv[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+#pragma unroll
+        for (int i = 0; i < 16; i++)
+            if ((keep[k] >> i) & 1u) {
+                cb[o ^ 3u] = (uint8_t)(wv[i >> 2] >> (8 * (i & 3)));
+                o++;
+            }
+    }
+    __syncthreads();
+    return part;
+}
+
+// The rows of a window: row j < n_own holds clean bytes of the window itself, the rows after them
+// are the first of the next window.
+struct StreamRows {
+    uint32_t row_bytes, own, total, n_own, n, limit_bits;
+    bool to_end;  // the data end with the last row
+    __device__ inline StreamRows(const StreamPart &p, uint32_t rb) : row_bytes(rb), own(p.own), total(p.total)
+    {
+        n_own = (own + rb - 1) / rb;
+        n = n_own + min((total - own + rb - 1) / rb, stream_overlap(rb));
+        to_end = p.to_end && total - own <= stream_overlap(rb) * rb;
+        limit_bits = p.to_end ? total * 8u : kOpenLimit;
+    }
+    __device__ inline uint32_t start(uint32_t j) const { return 8u * (j < n_own ? j * row_bytes : own + (j - n_own) * row_bytes); }
+    __device__ inline uint32_t end(uint32_t j) const { return 8u * (j < n_own ? min((j + 1u) * row_bytes, own) : min(own + (j - n_own + 1u) * row_bytes, total)); }
+};
+
+// Decode from packed state `st` until the bit position reaches end_bit, or to limit_bits where no
+// further symbol fits before it (the padding at the end of the data).  The symbol loop of
+// decode_interval for a stream without restart boundaries.  Returns the end state.
+template <bool kWrite>
+__device__ __forceinline__ uint32_t decode_row(const StreamShared &S, const Geometry &g, uint32_t st, uint32_t end_bit,
+                                               uint32_t limit_bits, uint32_t *nblk, WriteCtx *wc)
+{
+    uint32_t p = st >> 9, slot = slot_of_block((st >> 6) & 7u);
+    const uint32_t first_block = kWrite ? wc->block : 0u;
+    uint32_t at = (first_block << 6) | (st & 63u);
+    const uint32_t last = kWrite ? g.n_blocks * 64u - 1u : 0u;
+    const uint16_t *lut = S.tab.lut;
+    const uint32_t ac_bit = 2u;  // tb: twice the number of the current table, see decode_span
+    uint32_t tb = __builtin_amdgcn_ubfe(g.chroma_at, slot, 3u) | ((st & 63u) ? ac_bit : 0u);
+    int32_t broken = 0;
+    uint32_t over = 0;
+    uint32_t w = p >> 5;
+    uint32_t hi = S.clean[w], lo = S.clean[w + 1], ahead = S.clean[w + 2];
+    auto lookup = [&](uint32_t win) {
+        uint32_t e = first_level(lut, tb, win);
+        if (__builtin_expect((e >> 11) == 0, 0)) {
+            e = second_level(S.tab, e, tb, win);
+            if (__builtin_expect((e >> 11) == 0, 0)) {
+                if (e == kUseLoop) e = lookup_by_search(S.tab, tb >> 1, win);
+                if ((e >> 11) == 0) {
+                    e = kInvalidEntry;
+                    if (kWrite && p < end_bit && p + (kInvalidEntry >> 11) <= limit_bits) broken = 1;
+                }
+            }
+        }
+        return e;
+    };
+    uint32_t win = window_at(hi, lo, p);
+    uint32_t e = lookup(win);
+    while (p < end_bit && p + (e >> 11) <= limit_bits) {
+        const uint32_t adv = e >> 11;
+        const uint32_t k = (at & 63u) + ((e >> 4) & 127u);  // index of the symbol's coefficient
+        const uint32_t here = (at & ~63u) | min(k, 63u);
+        if (kWrite) {
+            // every symbol stores (see decode_span); k = 0 is a DC difference: it goes to the side array
+            const uint32_t ci = min(here, last);
+            wc->coef[k == 0 ? wc->side_rel + (ci >> 6) : ci] = (int16_t)coefficient_value(win, adv, e & 15u);
+            over |= k;
+        }
+        at = here + 1u;
+        p += adv;
+        {
+            const bool moved = (p >> 5) != w;
+            hi = moved ? lo : hi;
+            lo = moved ? ahead : lo;
+            w += moved ? 1u : 0u;
+            ahead = S.clean[w + 2];
+        }
+        const bool endb = k >= 63u;  // the zig-zag index reaches 64
+        const uint32_t slot1 = __builtin_amdgcn_ubfe(g.next_slot, slot, 5u);
+        slot = endb ? slot1 : slot;
+        tb = endb ? __builtin_amdgcn_ubfe(g.chroma_at, slot1, 3u) : tb | ac_bit;
+        win = window_at(hi, lo, p);
+        e = lookup(win);
+    }
+    if (p < end_bit) {
+        // what is left is padding: fewer than eight bits, between MCUs
+        if (kWrite && (slot != 0 || (at & 63u) != 0 || limit_bits - p >= 8)) broken = 1;
+        p = limit_bits;
+    }
+    if (kWrite) wc->bad |= broken | (int32_t)((over >> 6) & 1u);
+    *nblk = (at >> 6) - first_block;
+    return pack_state(p, block_of_slot(slot), at & 63u);
+}
+
+__device__ inline void stream_geometry(Geometry &g, const ImageRec &R)
+{
+    g.bpm = R.blocks_per_mcu;
+    g.n_luma = (uint32_t)(luma_h(R.sampling) * luma_v(R.sampling));
+    g.ri_blocks = 0;
+    g.set_slots();
+    g.n_blocks = R.n_blocks;
+}
+
+// the expanded tables of an image with a table slot, into LDS (a barrier has to follow)
+__device__ inline void load_tables(HuffTables &tab, const uint4 *__restrict__ tables, uint32_t slot)
+{
+    constexpr uint32_t units = sizeof(HuffTables) / 16;
+    uint4 *dst = reinterpret_cast<uint4 *>(&tab);
+    for (uint32_t i = threadIdx.x; i < units; i += kT) dst[i] = tables[(size_t)slot * units + i];
+}
+
+// image of stream window wg: the last one whose first window does not exceed it (images without
+// stream windows share their number with the next one that has some)
+__device__ inline int image_of_stream(const ImageRec *recs, int n_images, uint32_t wg)
+{
+    return find_image(n_images, wg, [&](int i) { return recs[i].stream0; });
+}
+
+}  // namespace
+
+__global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
+    const uint8_t *__restrict__ bits, const ImageRec *__restrict__ recs, int n_images, uint32_t row_bytes,
+    const uint32_t *__restrict__ data_end, uint32_t *__restrict__ retry, const uint4 *__restrict__ tables,
+    StreamWindow *__restrict__ windows)
+{
+    __shared__ StreamShared S;
+    __shared__ uint32_t cand[kT];              // end states of pass 0
+    __shared__ uint32_t node_end[kStreamNodes];
+    __shared__ uint16_t node_blocks[kStreamNodes], node_next[kStreamNodes];
+    __shared__ uint16_t extra_from[kStreamExtras];  // the node whose end state the extra node begins in
+    __shared__ uint8_t extra_row[kStreamExtras];
+    __shared__ uint32_t n_extra;
+    const int tid = threadIdx.x;
+    const uint32_t wg = blockIdx.x;
+    const int img = image_of_stream(recs, n_images, wg);
+    const ImageRec &R = recs[img];
+    const uint32_t w = wg - R.stream0;
+    if (w >= R.n_streams) return;
+    Geometry g;
+    stream_geometry(g, R);
+    const uint32_t H = g.bpm, step = stream_window_bytes(H, row_bytes);
+    const uint32_t data_len = min(R.entropy_len, data_end[img]);
+    StreamWindow &W = windows[wg];
+    if (w * step >= data_len) {
+        // the data ended before this window; an empty segment is decode_entropy's to judge
+        if (tid == 0 && w == 0) retry[img] = 1;
+        if (tid < kStreamEntries) W.through[tid] = kNoWay;
+        return;
+    }
+    load_tables(S.tab, tables, R.table_slot);
+    if (tid == 0) n_extra = 0;
+    const StreamPart part = stage_stream(S, bits + R.file_off + R.entropy_rel, data_len, w, step, row_bytes);
+    if (part.marker && tid == 0) retry[img] = 1;
+    const StreamRows rows(part, row_bytes);
+
+    const uint32_t j = (uint32_t)tid / H, h = (uint32_t)tid - j * H;
+    const bool mine = j < rows.n && j < stream_rows(H);
+    uint32_t state = 0, nb = 0;
+    if (mine) {
+        state = decode_row<false>(S, g, pack_state(rows.start(j), h, 0), rows.end(j), rows.limit_bits, &nb, nullptr);
+        cand[tid] = state;
+    }
+    __syncthreads();
+    // where node id, whose row r ends in state s, goes on
+    auto link = [&](uint32_t id, uint32_t r, uint32_t s) {
+        uint32_t k = 0;
+        while (k < H && cand[r * H + k] != s) k++;
+        uint32_t to = kNodeNoWay;
+        if (k < H && r >= rows.n_own) {
+            to = kExit | ((r - rows.n_own) * H + k);  // in an overlap row: the next window goes on from there
+        } else if (r + 1u >= rows.n) {
+            if (rows.to_end) to = kNodeToEnd;
+        } else if (k < H) {
+            to = (r + 1u) * H + k;
+        } else {
+            const uint32_t x = atomicAdd(&n_extra, 1u);
+            if (x < (uint32_t)kStreamExtras) {
+                extra_from[x] = (uint16_t)id;
+                extra_row[x] = (uint8_t)(r + 1u);
+                to = (uint32_t)kT + x;
+            }
+        }
+        node_next[id] = (uint16_t)to;
+    };
+    // pass 1 (row 0 begins in a known state in window 0, and is not entered otherwise; an overlap
+    // row after the first is entered by extra nodes only)
+    const bool node = mine && j <= rows.n_own;
+    if (node) {
+        if (j != 0) {
+            const uint32_t from = cand[(uint32_t)tid - H];
+            state = from;
+            nb = 0;
+            // (a state past the row's end: the row before ran through it)
+            if ((from >> 9) < rows.end(j)) state = decode_row<false>(S, g, from, rows.end(j), rows.limit_bits, &nb, nullptr);
+        }
+        node_end[tid] = state;
+        node_blocks[tid] = (uint16_t)nb;
+        if (j == 0) node_next[tid] = (uint16_t)(rows.n > 1 ? (uint32_t)tid + H : rows.to_end ? kNodeToEnd : kNodeNoWay);
+        else link((uint32_t)tid, j, state);
+    } else {
+        node_next[tid] = kNodeNoWay;
+        node_blocks[tid] = 0;
+        node_end[tid] = 0;
+    }
+    __syncthreads();
+    // the extra nodes, a generation at a time (a generation's are at least one row further)
+    uint32_t done = 0;
+    for (uint32_t round = 0; round < (uint32_t)kStreamMaxRows; round++) {
+        const uint32_t have = min(n_extra, (uint32_t)kStreamExtras);
+        __syncthreads();
+        if (done >= have) break;
+        const uint32_t x = done + (uint32_t)tid;
+        if (x < have) {
+            const uint32_t from = node_end[extra_from[x]], r = extra_row[x];
+            uint32_t to = from, n = 0;
+            if ((from >> 9) < rows.end(r)) to = decode_row<false>(S, g, from, rows.end(r), rows.limit_bits, &n, nullptr);
+            node_end[kT + x] = to;
+            node_blocks[kT + x] = (uint16_t)n;
+            link((uint32_t)kT + x, r, to);
+        }
+        done = have;
+        __syncthreads();
+    }
+    const uint32_t n_nodes = (uint32_t)kT + done;
+    for (uint32_t i = (uint32_t)tid; i < n_nodes; i += kT) {
+        W.end[i] = node_end[i];
+        W.blocks[i] = node_blocks[i];
+        W.next[i] = node_next[i];
+    }
+    if (tid < kStreamEntries) {
+        // entry e = (overlap row i, hypothesis k) goes on with node (i + 1, k) here; window 0 is
+        // entered by node 0
+        const uint32_t e = (uint32_t)tid;
+        uint32_t at = w == 0 ? 0u : e + H, way = kNoWay, blocks = 0;
+        if (e < (w == 0 ? 1u : stream_overlap(row_bytes) * H)) {
+            W.entry_state[e] = w == 0 ? 0u : cand[e];
+            if (w != 0 && e / H + 1u >= rows.n) {
+                way = rows.to_end ? kToEnd : kNoWay;  // no such row: all was decoded in the window before
+            } else {
+                // (a chain has at most one node per row)
+                for (uint32_t r = 0; r <= (uint32_t)kStreamMaxRows; r++) {
+                    const uint32_t to = node_next[at];
+                    blocks += node_blocks[at];
+                    if (to == kNodeNoWay) break;
+                    if (to == kNodeToEnd) { way = kToEnd; break; }
+                    if (to & kExit) { way = to & ~kExit; break; }
+                    at = to;
+                }
+            }
+        }
+        W.through[e] = (blocks << 8) | way;
+    }
+}
+
+// One workgroup per image: which entry of each window the image's true chain takes, and the block
+// there.  Windows are taken kChainTile at a time; within a tile, lane (s, e) follows segment s from
+// entry e, one lane strings the segments together, and a lane per segment goes over it again.
+constexpr int kChainTile = 128;
+__global__ __launch_bounds__(kDecodeThreads) void chain_streams(
+    const ImageRec *__restrict__ recs, uint32_t row_bytes, uint32_t *__restrict__ retry, StreamWindow *__restrict__ windows)
+{
+    __shared__ uint32_t through[kChainTile * kStreamEntries];
+    __shared__ uint32_t seg_way[kT], seg_blocks[kT];
+    __shared__ uint32_t seg_entry[kT], seg_block[kT];
+    __shared__ uint32_t s_entry, s_block;
+    const ImageRec &R = recs[blockIdx.x];
+    const int tid = threadIdx.x;
+    const uint32_t n = R.n_streams;
+    if (n == 0 || R.status != PREP_OK) return;
+    const bool redo = retry[blockIdx.x] != 0;
+    StreamWindow *W = windows + R.stream0;
+    const uint32_t E = stream_overlap(row_bytes) * R.blocks_per_mcu, n_seg = (uint32_t)kT / E;
+    if (tid == 0) {
+        s_entry = redo ? kNoWay : 0u;
+        s_block = 0;
+    }
+    for (uint32_t w0 = 0; w0 < n; w0 += kChainTile) {
+        const uint32_t cnt = min(n - w0, (uint32_t)kChainTile);
+        for (uint32_t i = (uint32_t)tid; i < cnt * E; i += kT) through[i] = W[w0 + i / E].through[i % E];
+        __syncthreads();
+        const uint32_t len = (cnt + n_seg - 1) / n_seg;
+        const uint32_t s = (uint32_t)tid / E, e = (uint32_t)tid - s * E;
+        const uint32_t lo = min(s * len, cnt), hi = min(lo + len, cnt);
+        if (s < n_seg) {
+            uint32_t way = e, blocks = 0;
+            for (uint32_t i = lo; i < hi && way < E; i++) {
+                const uint32_t t = through[i * E + way];
+                blocks += t >> 8;
+                way = t & 255u;
+            }
+            seg_way[tid] = way;
+            seg_blocks[tid] = blocks;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            uint32_t way = s_entry, block = s_block;
+            for (uint32_t i = 0; i < n_seg; i++) {
+                seg_entry[i] = way;
+                seg_block[i] = block;
+                if (way < E) {
+                    block += seg_blocks[i * E + way];
+                    way = seg_way[i * E + way];
+                }
+            }
+            s_entry = way;
+            s_block = block;
+        }
+        __syncthreads();
+        if (e == 0 && s < n_seg) {
+            uint32_t way = seg_entry[s], block = seg_block[s];
+            for (uint32_t i = lo; i < hi; i++) {
+                W[w0 + i].entry = way;
+                W[w0 + i].block = block;
+                if (way < E) {
+                    const uint32_t t = through[i * E + way];
+                    block += t >> 8;
+                    way = t & 255u;
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // the chain has to reach the end of the data with all of the image's blocks
+    if (tid == 0 && (s_entry != kToEnd || s_block != R.n_blocks)) retry[blockIdx.x] = 1;
+}
+
+__global__ __launch_bounds__(kDecodeThreads) void write_streams(
+    const uint8_t *__restrict__ bits, const ImageRec *__restrict__ recs, int n_images, uint32_t row_bytes,
+    const uint32_t *__restrict__ data_end, uint32_t *__restrict__ retry, const uint4 *__restrict__ tables,
+    StreamWindow *__restrict__ windows, int16_t *__restrict__ coef_all, uint32_t side_off)
+{
+    __shared__ StreamShared S;
+    __shared__ uint32_t node_end[kStreamNodes];
+    __shared__ uint16_t node_blocks[kStreamNodes], node_next[kStreamNodes];
+    __shared__ uint16_t chain[kStreamMaxRows + 1];
+    const int tid = threadIdx.x;
+    const uint32_t wg = blockIdx.x;
+    const int img = image_of_stream(recs, n_images, wg);
+    const ImageRec &R = recs[img];
+    const uint32_t w = wg - R.stream0;
+    if (w >= R.n_streams || R.status != PREP_OK) return;
+    StreamWindow &W = windows[wg];
+    const uint32_t H = R.blocks_per_mcu, entry = W.entry;
+    // (an image that is to be decoded in one piece is left alone; other windows of it may find that
+    // out only now)
+    if (retry[img] != 0 || entry >= stream_overlap(row_bytes) * H) {
+        if (tid == 0) {
+            W.dc_lo = W.dc_hi = 0;
+            W.dc_sum[0] = W.dc_sum[1] = W.dc_sum[2] = 0;
+        }
+        return;
+    }
+    Geometry g;
+    stream_geometry(g, R);
+    const uint32_t step = stream_window_bytes(H, row_bytes);
+    const uint32_t data_len = min(R.entropy_len, data_end[img]);
+    load_tables(S.tab, tables, R.table_slot);
+    for (uint32_t i = (uint32_t)tid; i < (uint32_t)kStreamNodes; i += kT) {
+        node_end[i] = W.end[i];
+        node_blocks[i] = W.blocks[i];
+        node_next[i] = W.next[i];
+    }
+    const StreamPart part = stage_stream(S, bits + R.file_off + R.entropy_rel, data_len, w, step, row_bytes);
+    const StreamRows rows(part, row_bytes);
+    const uint32_t row0 = w == 0 ? 0u : entry / H + 1u;  // first row of the chain
+    if (tid == 0) {
+        uint32_t cnt = 0, at = w == 0 ? 0u : entry + H;
+        while (row0 + cnt < rows.n) {
+            chain[cnt++] = (uint16_t)at;
+            at = node_next[at];
+            if (at >= (uint32_t)kStreamNodes) break;  // an exit, or the end of the data
+        }
+        S.bcast[0] = cnt;
+    }
+    __syncthreads();
+    const uint32_t cnt = S.bcast[0];
+    const bool active = (uint32_t)tid < cnt;
+    const uint32_t row = row0 + (uint32_t)tid;
+    const uint32_t entry_state = W.entry_state[entry];
+    uint32_t nblk = 0, in_state = 0, out_state = 0;
+    if (active) {
+        in_state = tid == 0 ? entry_state : node_end[chain[tid - 1]];
+        out_state = node_end[chain[tid]];
+        nblk = node_blocks[chain[tid]];
+    }
+    uint32_t total_blocks;
+    const uint32_t block0 = W.block;
+    const uint32_t my_block = block0 + block_excl_scan(nblk, S.scan_a, &total_blocks);
+    const uint32_t exit_state = cnt ? node_end[chain[cnt - 1]] : entry_state;
+    int16_t *coef = coef_all + (size_t)R.coef_block0 * 64;
+    const uint32_t side_rel = side_off + R.coef_block0 - R.coef_block0 * 64u;
+    // Zeros over exactly the coefficients that this window decodes: a block that is under way at
+    // either end is shared with the workgroup next door, each with its own part of it.
+    const uint32_t all = g.n_blocks * 64u;
+    const uint32_t z_lo = min(block0 * 64u + (entry_state & 63u), all);
+    const uint32_t z_hi = max(z_lo, min((block0 + total_blocks) * 64u + (exit_state & 63u), all));
+    {
+        const uint32_t a = min((z_lo + 7u) & ~7u, z_hi), b = max(a, z_hi & ~7u);
+        if ((uint32_t)tid < a - z_lo) coef[z_lo + (uint32_t)tid] = 0;
+        for (uint32_t u = a + 8u * (uint32_t)tid; u < b; u += 8u * kT)
+            *reinterpret_cast<uint4 *>(coef + u) = make_uint4(0, 0, 0, 0);
+        if ((uint32_t)tid < z_hi - b) coef[b + (uint32_t)tid] = 0;
+    }
+    __syncthreads();  // (and only then does any lane store a coefficient)
+    WriteCtx wc;
+    wc.coef = coef;
+    wc.side_rel = side_rel;
+    wc.block = my_block;
+    wc.iv_rem = 0;
+    wc.bad = 0;
+    if (active) {
+        uint32_t fin = in_state, got = 0;
+        if ((in_state >> 9) < rows.end(row)) fin = decode_row<true>(S, g, in_state, rows.end(row), rows.limit_bits, &got, &wc);
+        if (fin != out_state || got != nblk) wc.bad = 1;
+        // the data end between MCUs
+        if (rows.end(row) == rows.limit_bits && ((fin & 511u) != 0 || (fin >> 9) != rows.limit_bits)) wc.bad = 1;
+    }
+    if (__syncthreads_or(wc.bad) && tid == 0) retry[img] = 1;
+    // the DC differences' sums, for the windows after this one
+    const uint32_t dc_lo = min(block0 + ((entry_state & 63u) ? 1u : 0u), g.n_blocks);
+    const uint32_t dc_hi = max(dc_lo, min(block0 + total_blocks + ((exit_state & 63u) ? 1u : 0u), g.n_blocks));
+    uint32_t sum[3] = {0, 0, 0};
+    const int16_t *side = coef + side_rel;
+    for (uint32_t i = dc_lo + (uint32_t)tid; i < dc_hi; i += kT) {
+        const uint32_t c = comp_of_block(g, i % H);
+        const uint32_t d = (uint32_t)(int32_t)side[i];
+        sum[0] += c == 0 ? d : 0u;
+        sum[1] += c == 1 ? d : 0u;
+        sum[2] += c == 2 ? d : 0u;
+    }
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+        sum[c] = block_sum(sum[c], S.scan_a);
+        if (tid == 0) W.dc_sum[c] = (int32_t)sum[c];
+    }
+    if (tid == 0) {
+        W.dc_lo = dc_lo;
+        W.dc_hi = dc_hi;
+    }
+}
+
+// DC differences -> DC values of the blocks whose DC was decoded in each window.
+__global__ __launch_bounds__(kDecodeThreads) void finish_streams(
+    const ImageRec *__restrict__ recs, int n_images, const uint32_t *__restrict__ retry,
+    const StreamWindow *__restrict__ windows, int16_t *__restrict__ coef_all, uint32_t side_off)
+{
+    __shared__ uint32_t scan_a[kT / 64 + 1];
+    __shared__ int32_t dc_val[kT / 64 + 1], dc_flag[kT / 64 + 1];
+    const uint32_t wg = blockIdx.x;
+    const int img = image_of_stream(recs, n_images, wg);
+    const ImageRec &R = recs[img];
+    const uint32_t w = wg - R.stream0;
+    if (w >= R.n_streams || R.status != PREP_OK || retry[img] != 0) return;
+    const StreamWindow *W = windows + R.stream0;
+    if (W[w].dc_hi <= W[w].dc_lo) return;
+    uint32_t before[3] = {0, 0, 0};
+    for (uint32_t i = threadIdx.x; i < w; i += kT)
+#pragma unroll
+        for (int c = 0; c < 3; c++) before[c] += (uint32_t)W[i].dc_sum[c];
+    int32_t carry[3];
+#pragma unroll
+    for (int c = 0; c < 3; c++) carry[c] = (int32_t)block_sum(before[c], scan_a);
+    Geometry g;
+    stream_geometry(g, R);
+    int16_t *coef = coef_all + (size_t)R.coef_block0 * 64;
+    dc_prefix(dc_val, dc_flag, g, coef, coef + (side_off + R.coef_block0 - R.coef_block0 * 64u), W[w].dc_lo, W[w].dc_hi, carry);
+}
+
+
 size_t huff_tables_bytes() { return sizeof(HuffTables); }
 static_assert(sizeof(HuffTables) % 16 == 0, "table slots are copied in 16-byte units");
 
 void launch_scan_restart_markers(const uint8_t *bits, const ImageRec *recs, int n_images,
                                  uint32_t n_windows, uint32_t window_bytes, uint32_t *win_count, uint32_t *win_first,
-                                 uint32_t *data_end,
+                                 uint32_t *data_end, uint32_t *retry,
                                  int32_t *status, const uint32_t *table_rep, uint32_t n_tables,
                                  uint8_t *tables, hipStream_t stream)
 {
     if (n_windows == 0) return;
     hipLaunchKernelGGL(scan_restart_markers, dim3(n_windows + 4 * n_tables), dim3(kDecodeThreads), 0, stream,
-                       bits, recs, n_images, n_windows, window_bytes, win_count, win_first, data_end, status, table_rep,
+                       bits, recs, n_images, n_windows, window_bytes, win_count, win_first, data_end, retry, status, table_rep,
                        reinterpret_cast<uint4 *>(tables));
 }
 
 void launch_decode_entropy(const uint8_t *bits, const ImageRec *recs, int n_images,
                            uint32_t n_windows, const uint32_t *win_count, const uint32_t *win_first,
-                           const uint32_t *data_end, int16_t *coef, uint32_t side_off, int32_t *status,
+                           const uint32_t *data_end, const uint32_t *retry, int16_t *coef, uint32_t side_off, int32_t *status,
                            const uint8_t *tables, bool small_windows, uint32_t hyp_span_bits, hipStream_t stream)
 {
     if (n_windows == 0) return;
     if (small_windows)
         hipLaunchKernelGGL(decode_entropy<true>, dim3(n_windows), dim3(kDecodeThreads), 0, stream, bits, recs,
-                           n_images, win_count, win_first, data_end, coef, side_off, status,
+                           n_images, win_count, win_first, data_end, retry, coef, side_off, status,
                            reinterpret_cast<const uint4 *>(tables), hyp_span_bits);
     else
         hipLaunchKernelGGL(decode_entropy<false>, dim3(n_windows), dim3(kDecodeThreads), 0, stream, bits, recs,
-                           n_images, win_count, win_first, data_end, coef, side_off, status,
+                           n_images, win_count, win_first, data_end, retry, coef, side_off, status,
                            reinterpret_cast<const uint4 *>(tables), hyp_span_bits);
+}
+
+void launch_decode_streams(const uint8_t *bits, const ImageRec *recs, int n_images, uint32_t n_streams, uint32_t row_bytes,
+                           const uint32_t *data_end, uint32_t *retry, StreamWindow *win, int16_t *coef, uint32_t side_off,
+                           const uint8_t *tables, hipStream_t stream)
+{
+    if (n_streams == 0) return;
+    const uint4 *tab = reinterpret_cast<const uint4 *>(tables);
+    hipLaunchKernelGGL(resolve_streams, dim3(n_streams), dim3(kDecodeThreads), 0, stream, bits, recs, n_images, row_bytes,
+                       data_end, retry, tab, win);
+    hipLaunchKernelGGL(chain_streams, dim3(n_images), dim3(kDecodeThreads), 0, stream, recs, row_bytes, retry, win);
+    hipLaunchKernelGGL(write_streams, dim3(n_streams), dim3(kDecodeThreads), 0, stream, bits, recs, n_images, row_bytes,
+                       data_end, retry, tab, win, coef, side_off);
+}
+
+void launch_finish_streams(const ImageRec *recs, int n_images, uint32_t n_streams, const uint32_t *retry,
+                           const StreamWindow *win, int16_t *coef, uint32_t side_off, hipStream_t stream)
+{
+    if (n_streams == 0) return;
+    hipLaunchKernelGGL(finish_streams, dim3(n_streams), dim3(kDecodeThreads), 0, stream, recs, n_images, retry, win, coef,
+                       side_off);
 }
 
 }  // namespace prep

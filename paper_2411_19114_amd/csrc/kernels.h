@@ -15,10 +15,10 @@ size_t huff_tables_bytes();
 // table_rep[s] = an image whose tables go into slot s of `tables` (n_tables slots);
 // window_bytes = raw bytes between workgroup starts (the ImageRecs' n_windows count such windows);
 // data_end[i] = length of image i's entropy-coded segment as the host found it, lowered by the
-// kernel to the offset of the first EOI marker inside it
+// kernel to the offset of the first EOI marker inside it; retry[i] = 0
 void launch_scan_restart_markers(const uint8_t *bits, const ImageRec *recs, int n_images,
                                  uint32_t n_windows, uint32_t window_bytes, uint32_t *win_count, uint32_t *win_first,
-                                 uint32_t *data_end,
+                                 uint32_t *data_end, uint32_t *retry,
                                  int32_t *status, const uint32_t *table_rep, uint32_t n_tables,
                                  uint8_t *tables, hipStream_t stream);
 // coef + side_off: one int16 per block of the coefficient workspace, in the same allocation
@@ -28,8 +28,16 @@ void launch_scan_restart_markers(const uint8_t *bits, const ImageRec *recs, int 
 // hyp_span_bits = what a lane of its hypothesis passes takes, 512 or 256 bits
 void launch_decode_entropy(const uint8_t *bits, const ImageRec *recs, int n_images,
                            uint32_t n_windows, const uint32_t *win_count, const uint32_t *win_first,
-                           const uint32_t *data_end, int16_t *coef, uint32_t side_off, int32_t *status,
+                           const uint32_t *data_end, const uint32_t *retry, int16_t *coef, uint32_t side_off, int32_t *status,
                            const uint8_t *tables, bool small_windows, uint32_t hyp_span_bits, hipStream_t stream);
+// The images whose ImageRec counts stream windows (n_streams of all images): three kernels before
+// launch_decode_entropy, which then does the images that they set in retry[] from the start, and
+// one after it.  row_bytes = kStreamRowBytes or kStreamTinyRowBytes.
+void launch_decode_streams(const uint8_t *bits, const ImageRec *recs, int n_images, uint32_t n_streams, uint32_t row_bytes,
+                           const uint32_t *data_end, uint32_t *retry, StreamWindow *win, int16_t *coef, uint32_t side_off,
+                           const uint8_t *tables, hipStream_t stream);
+void launch_finish_streams(const ImageRec *recs, int n_images, uint32_t n_streams, const uint32_t *retry,
+                           const StreamWindow *win, int16_t *coef, uint32_t side_off, hipStream_t stream);
 
 // reconstruct.hip
 // chroma: nullptr = subsampled chroma is replicated; else the workspace of the interpolating

@@ -28,6 +28,45 @@ constexpr uint64_t kSmallCallBytes = 1536 << 10;            // entropy-coded byt
 // at 32 = 375 KB, even at 48 = 562 KB, worse from there on).
 constexpr int kTinyWindowBytes = 512;
 constexpr uint64_t kTinyCallBytes = 448 << 10;
+// Streams without restart markers are cut into windows too, one workgroup each, whatever the
+// size of the call (see resolve_streams in entropy.hip).  A window is decoded in rows, a lane to
+// a row and hypothesis; its last rows, the overlap, are the first rows of the next window.
+constexpr int kStreamRowBytes = 68;                         // clean bytes per row: 17 words, so that rows begin in different LDS banks
+constexpr int kStreamTinyRowBytes = 36;                     // the same in calls with little data
+constexpr uint64_t kStreamTinyBytes = 1024 << 10;           // entropy-coded bytes of such streams in a call up to which rows are short
+// Overlap rows.  A decoder that comes out of a window agrees with none of the hypotheses of an
+// overlap row with a probability that falls with the row's length: full-HD stills of quality 95,
+// the slowest seen, 10 % for rows of 36 bytes and 1 % for rows of 68 (photographs of quality 90:
+// 3 and 1 %).  About 250 bytes leave one in 10^7 windows without a way on.
+constexpr int kStreamMaxOverlap = 7;
+inline constexpr uint32_t stream_overlap(uint32_t row_bytes) { return row_bytes == (uint32_t)kStreamTinyRowBytes ? 7 : 4; }
+constexpr int kStreamMaxRows = 85;                          // rows per window: 256 lanes over the hypotheses, at most this many
+inline constexpr uint32_t stream_rows(uint32_t blocks_per_mcu)
+{
+    return kDecodeThreads / blocks_per_mcu < (uint32_t)kStreamMaxRows ? kDecodeThreads / blocks_per_mcu : (uint32_t)kStreamMaxRows;
+}
+// raw bytes between window starts
+inline constexpr uint32_t stream_window_bytes(uint32_t blocks_per_mcu, uint32_t row_bytes)
+{
+    return (stream_rows(blocks_per_mcu) - stream_overlap(row_bytes)) * row_bytes;
+}
+// What the kernels of such streams hand on per window: its decoder states (nodes), where each
+// entry into the window leads, and what the chain through the image's windows found.
+constexpr int kStreamExtras = 128;                          // nodes besides one per lane
+constexpr int kStreamNodes = kDecodeThreads + kStreamExtras;
+constexpr int kStreamEntries = kStreamMaxOverlap * 6;         // entries into a window, or exits of it
+struct StreamWindow {
+    uint32_t end[kStreamNodes];        // state where the node's row ends
+    uint16_t blocks[kStreamNodes];     // blocks completed in the row
+    uint16_t next[kStreamNodes];       // node of the next row that begins in that state, or a code
+    uint32_t entry_state[kStreamEntries];  // state at entry e
+    uint32_t through[kStreamEntries];  // from entry e: blocks completed << 8 | exit or code
+    uint32_t entry;                    // the entry that the image's true chain takes, or a code
+    uint32_t block;                    // block of the image that is under way or next there
+    uint32_t dc_lo, dc_hi;             // blocks whose DC difference was decoded in this window
+    int32_t dc_sum[3];                 // sums of these differences per component
+    uint32_t pad_;
+};
 constexpr int kLutBits = 10;                                // first-level Huffman lookup width
 // Images of a batch mostly share their Huffman tables (encoders write the tables of T.81
 // Annex K unless asked to optimise): each distinct set of four tables is expanded once per
@@ -83,6 +122,8 @@ struct ImageRec {
     uint8_t blocks_per_mcu;
     int32_t status;             // host verdict; kernels skip images that are not PREP_OK
     uint32_t table_slot;        // expanded Huffman tables of this image, or kNoTableSlot
+    uint32_t stream0;           // first stream window of this image, and how many: 0 = the stream
+    uint32_t n_streams;         // is decode_entropy's alone (restart markers, no table slot)
 };
 static_assert(sizeof(ImageRec) % 8 == 0, "ImageRec must keep 8-byte alignment in arrays");
 

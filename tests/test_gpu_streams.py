@@ -1,0 +1,77 @@
+"""Streams without restart markers, cut into windows that are decoded side by side: coefficients,
+pixels and tensors against the oracle where the windows and their rows can go wrong."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from helpers import check_against_oracle, run_gpu
+from oracle import MODE_420, MODE_422, MODE_440, MODE_444, MODE_GRAY
+
+pytestmark = pytest.mark.gpu
+MODES = [MODE_444, MODE_420, MODE_GRAY, MODE_422, MODE_440]
+
+
+@pytest.fixture(scope="module")
+def pp():
+    import paper_2411_19114_amd as prep
+    h = prep.Preprocessor(device=0, max_batch=48, max_width=1024, max_height=1024, max_bitstream_bytes=24 << 20,
+                          flags=prep.FLAG_FULL_RGB)
+    yield h
+    h.close()
+
+
+def _file(seed, w, h, quality, mode, sigma=12.0, table_mode=0):
+    rgb = synth.gradient_noise_image(np.random.default_rng(seed), w, h, sigma)
+    return oracle.encode(rgb, quality, mode, 0, table_mode=table_mode)[0]
+
+
+@pytest.mark.parametrize("mode", MODES)
+def test_one_window_to_many_with_short_rows(pp, mode):
+    # 30 bytes to 60 KB of data each: no full row, a window's edge, an overlap that the data end in
+    files = [_file(10 * mode + k, w, h, q, mode, table_mode=k % 2)
+             for k, (w, h, q) in enumerate([(8, 8, 50), (33, 17, 60), (64, 64, 75), (96, 80, 85), (131, 117, 90),
+                                            (200, 160, 95), (255, 199, 50), (320, 240, 100)])]
+    assert sum(map(len, files)) < 1 << 20
+    check_against_oracle(pp, files, 0, 1, 1, "f32")
+
+
+@pytest.mark.parametrize("mode", MODES)
+def test_many_windows_with_long_rows(pp, mode):
+    # more than 1 MiB of data in the call; quality 100 falls into step most slowly
+    files = [_file(20 * mode + k, 700, 640, 100, mode) for k in range(2)]
+    files += [_file(20 * mode + 9 + k, 40 + 37 * k, 300 - 23 * k, 60 + 4 * k, mode) for k in range(8)]
+    while sum(map(len, files)) < (1 << 20) + 4096:
+        files.append(files[0])
+    check_against_oracle(pp, files, 0, 1, 1, "f32")
+
+
+def test_every_length_across_a_window_edge(pp):
+    # heights that move the end of the data by some tens of bytes over a window's 1260 and an overlap's 252
+    files = [_file(7, 64, 16 * k, 88, MODE_420) for k in range(1, 33)]
+    check_against_oracle(pp, files, 0, 1, 1, "f32")
+
+
+def test_streams_with_and_without_markers_in_one_batch(pp):
+    rgb = synth.gradient_noise_image(np.random.default_rng(3), 300, 251, 12.0)
+    files = [oracle.encode(rgb, 88, m, dri)[0] for m in MODES for dri in (0, 5, 0, 200)]
+    check_against_oracle(pp, files, 0, 1, 1, "f16")
+
+
+def test_markers_and_damage_inside_the_data(pp):
+    # a restart marker in a file that declares none, a cut file, bytes left over: refused as before,
+    # and the sound files around them are decoded
+    good = _file(5, 256, 256, 90, MODE_420)
+    mid = len(good) // 2
+    while good[mid - 1] == 0xFF or good[mid] == 0xFF:
+        mid += 1
+    marker = good[:mid] + b"\xff\xd0" + good[mid:]
+    cut = good[:mid] + b"\xff\xd9"
+    left = good[:-2] + b"\x55\x55\x55" + b"\xff\xd9"
+    status, tensor = run_gpu(pp, [good, marker, cut, good, left, good], 0, 64, 64, "f32")
+    assert [s == 0 for s in status] == [True, False, False, True, False, True], status
+    coef = oracle.decode(good)[0]
+    for i in (0, 3, 5):
+        assert np.array_equal(pp.debug_last_coefficients(i, coef.shape[0]), coef)
+    for i in (1, 2, 4):
+        assert not np.any(tensor[i])
