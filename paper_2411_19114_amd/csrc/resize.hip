@@ -85,6 +85,20 @@ __device__ __forceinline__ uint2 load_pixel_pair(const uint8_t *p)
     return v;
 }
 
+// The same for an image that ends with its last byte (callers' own images): near the right
+// edge the load starts earlier, so that it ends with the row, and the bytes are shifted down.
+// A row holds at least eight bytes; x is a column, row_bytes 3 x the width.  Where x is the last
+// column only the left pixel is valid (the callers' right tap is then the same pixel).
+__device__ __forceinline__ uint2 load_pixel_pair_inside(const uint8_t *row, int x, int row_bytes)
+{
+    const int at = x * 3, from = min(at, row_bytes - 8);
+    uint64_t v;
+    __builtin_memcpy(&v, row + from, 8);
+    v >>= 8 * (at - from);  // 0, 16 or 40 bits
+    return make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+}
+constexpr int kPairWidth = 3;  // narrowest image whose rows hold such a load
+
 // channel c of the left (i = 0) or right (i = 1) pixel of a pair
 __device__ __forceinline__ float pair_channel(const uint2 v, int i, int c)
 {
@@ -95,7 +109,10 @@ __device__ __forceinline__ float pair_channel(const uint2 v, int i, int c)
 
 // One thread produces kPx horizontally adjacent output pixels of all 3 planes.
 // kWide: the source rows may be read two bytes past a pixel pair (true for the library's
-// own RGB workspace, which keeps slack after every image); otherwise bytes are loaded singly.
+// own RGB workspace, which keeps slack after every image); otherwise the loads are moved back
+// to end with their rows, and images narrower than such a load are read byte by byte.
+// Bound by the number of load instructions: 32 full-HD frames to 384 x 384 take 35 us with twelve
+// byte loads a pixel, 27 us with two of eight bytes.
 template <typename OutT, bool kWide>
 __global__ __launch_bounds__(kResizeThreads) void resize_crop_normalize(
     const uint8_t *__restrict__ rgb, const ResizeRec *__restrict__ rr,
@@ -134,10 +151,11 @@ __global__ __launch_bounds__(kResizeThreads) void resize_crop_normalize(
             map_coord(R.off_x, R.scale_x, x0 + j, &ix, &fx);
             const int xa = min(max(ix, 0), R.src_w - 1);
             const int xb = min(max(ix + 1, 0), R.src_w - 1);
-            if (kWide) {
+            if (kWide || R.src_w >= kPairWidth) {
                 // the right tap is the next pixel except where clamping makes both taps one pixel
                 const int right = xb != xa;
-                const uint2 a = load_pixel_pair(ra + xa * 3), b = load_pixel_pair(rb + xa * 3);
+                const uint2 a = kWide ? load_pixel_pair(ra + xa * 3) : load_pixel_pair_inside(ra, xa, R.src_w * 3);
+                const uint2 b = kWide ? load_pixel_pair(rb + xa * 3) : load_pixel_pair_inside(rb, xa, R.src_w * 3);
 #pragma unroll
                 for (int c = 0; c < 3; c++) {
                     const float p00 = pair_channel(a, 0, c), p01 = right ? pair_channel(a, 1, c) : p00;
@@ -219,13 +237,16 @@ __device__ __forceinline__ Window make_window(uint64_t off, uint64_t scale, int 
 }
 
 // A pixel's three bytes as floats.  kWide: read as four bytes (the byte past the pixel is
-// readable); otherwise the bytes are loaded singly.
+// readable).  Otherwise the load starts one byte early at the last pixel of a row (last; rows
+// hold at least two pixels), and in an image one pixel wide (narrow) the bytes are loaded singly.
 template <bool kWide>
-__device__ __forceinline__ void load_pixel(const uint8_t *p, float v[3])
+__device__ __forceinline__ void load_pixel(const uint8_t *p, bool last, bool narrow, float v[3])
 {
-    if (kWide) {
+    if (kWide || !narrow) {
+        const int back = !kWide && last ? 1 : 0;
         uint32_t u;
-        __builtin_memcpy(&u, p, 4);
+        __builtin_memcpy(&u, p - back, 4);
+        u >>= 8 * back;
         v[0] = (float)(u & 255u);
         v[1] = (float)((u >> 8) & 255u);
         v[2] = (float)((u >> 16) & 255u);
@@ -287,6 +308,7 @@ __global__ __launch_bounds__(kResizeThreads) void resize_antialias_crop_normaliz
         const Window wx = make_window(R.off_x, R.scale_x, min(x, crop_w - 1), R.src_w);
         const Window wy = make_window(R.off_y, R.scale_y, min(y, crop_h - 1), R.src_h);
         const int nx = wx.end - wx.first, ny = wy.end - wy.first;
+        const bool narrow = R.src_w < 2;
         const float dx0 = (float)(wx.first - wx.whole) - wx.frac;  // then one more per tap
         // the columns under the triangles of this tile's outputs (windows move right with x)
         const int c_lo = make_window(R.off_x, R.scale_x, x_first, R.src_w).first;
@@ -302,13 +324,14 @@ __global__ __launch_bounds__(kResizeThreads) void resize_antialias_crop_normaliz
             if (y < crop_h) {
                 for (int c = c_lo + lane; c < c_hi; c += kTileW) {
                     const uint8_t *p = src + (size_t)wy.first * R.src_pitch + (size_t)c * 3;
+                    const bool last = c == R.src_w - 1;
                     float a[3] = {0.0f, 0.0f, 0.0f};
                     // two rows at a time, so that their loads are in flight together
                     for (int j = 0; j < ny; j += 2, p += 2 * (size_t)R.src_pitch) {
                         const bool two = j + 1 < ny;
                         float u[3], v[3];
-                        load_pixel<kWide>(p, u);
-                        load_pixel<kWide>(two ? p + R.src_pitch : p, v);  // a row of the window either way
+                        load_pixel<kWide>(p, last, narrow, u);
+                        load_pixel<kWide>(two ? p + R.src_pitch : p, last, narrow, v);  // a row of the window either way
                         const float w0 = row_weight[wave][j], w1 = two ? row_weight[wave][j + 1] : 0.0f;
 #pragma unroll
                         for (int ch = 0; ch < 3; ch++) a[ch] = fmaf(w0, u[ch], fmaf(w1, v[ch], a[ch]));
@@ -349,8 +372,9 @@ __global__ __launch_bounds__(kResizeThreads) void resize_antialias_crop_normaliz
                 for (int k = 0; k < nx; k++, p0 += 3, p1 += 3, d += 1.0f) {
                     const float w = fmaxf(0.0f, fmaf(-fabsf(d), wx.inv, 1.0f));
                     float u[3], v[3];
-                    load_pixel<kWide>(p0, u);
-                    load_pixel<kWide>(p1, v);
+                    const bool last = wx.first + k == R.src_w - 1;
+                    load_pixel<kWide>(p0, last, narrow, u);
+                    load_pixel<kWide>(p1, last, narrow, v);
 #pragma unroll
                     for (int ch = 0; ch < 3; ch++) {
                         a[ch] = fmaf(w, u[ch], a[ch]);

@@ -75,3 +75,20 @@ def test_static_entry_point_refuses_what_does_not_fit():
         prep.resize_normalize_static(0, dev.data_ptr(), np.zeros(1, dtype=np.uint64), [8], [8], [24],
                                      make_params(0, 16, 16, "f32", MEAN, STD), out.data_ptr(), 0)
     assert e.value.code == prep.E_INVALID_ARG
+
+
+@pytest.mark.parametrize("dt,aa,rs", [("f32", 0, 6), ("f32", 1, 6), ("f32", 0, 1), ("f32", 1, 1), ("f16", 1, 4)])
+def test_rows_at_the_edges_of_wide_loads(dt, aa, rs):
+    # rows of 3 to 33 bytes and one of 900, back to back and at odd addresses: loads that are moved
+    # back at the end of a row, images too narrow for them, reductions with tall windows.  Bars: those of
+    # the other test (fp32 sums of 8-bit samples, and half a unit of fp16 at a magnitude below 4).
+    rng = np.random.default_rng(43)
+    shapes = [(w, h) for w in range(1, 12) for h in (1, 2, 9)] + [(300, 17), (9, 64), (3, 5)]
+    imgs = [rng.integers(0, 256, size=(h, w, 3), dtype=np.uint8) for w, h in shapes]
+    pp = prep.Preprocessor(device=0, max_batch=len(imgs), max_width=320, max_height=320, max_bitstream_bytes=1 << 20)
+    want, got = _run_both(pp, imgs, shapes, rs, rs, rs, dt, aa)
+    pp.close()
+    assert np.array_equal(want, got)
+    for im, g in zip(imgs, got):
+        ref = oracle.preprocess(im, rs, rs, rs, MEAN, STD, bool(aa))
+        assert np.abs(g.astype(np.float64) - ref).max() <= (0.02 if dt == "f16" else 1e-4), im.shape
