@@ -95,7 +95,10 @@ __device__ __forceinline__ uint2 load_pixel_pair_inside(const uint8_t *row, int 
     uint64_t v;
     __builtin_memcpy(&v, row + from, 8);
     v >>= 8 * (at - from);  // 0, 16 or 40 bits
-    return make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+    uint2 pair;
+    pair.x = (uint32_t)v;
+    pair.y = (uint32_t)(v >> 32);
+    return pair;
 }
 constexpr int kPairWidth = 3;  // narrowest image whose rows hold such a load
 
