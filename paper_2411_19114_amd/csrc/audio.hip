@@ -34,7 +34,7 @@ constexpr double kRolloff = 0.99;
 constexpr float kLogGuard = 5.9604644775390625e-08f;  // 2^-24
 constexpr float kStdGuard = 1e-5f;
 constexpr int kFft = 512;                             // the transform the kernel is built for
-constexpr int kFrameThreads = 256;                    // four frames per workgroup, one wave each
+constexpr int kFrameThreads = 128;                    // two pairs of frames per workgroup, one wave each
 constexpr int kMaxMels = 128;
 
 struct Utterance {
@@ -182,31 +182,44 @@ __device__ __forceinline__ void dft8(double2 v[8])
 __device__ __forceinline__ int padded(int i) { return i + (i >> 3); }
 constexpr int kFramePadded = kFft + kFft / 8;
 
-// One wave per frame; a 512-point transform in three radix-8 passes (self-sorting: pass s reads
-// element j + 64 r, multiplies by W512^(r k 512 / (8 Ns)), k = j mod Ns, Ns = 8^s, transforms
-// the eight values and writes them Ns apart from (j / Ns) 8 Ns + k), each lane holding eight
-// values in registers; the first pass reads the signal itself.  frame_start[u] = first frame of
-// utterance u among all frames.  Sample is double for a resampled signal, float where the
-// input is framed as it is.
+// One wave per two adjacent frames a, b of an utterance, transformed together as a + i b: a
+// 512-point transform in three radix-8 passes (self-sorting: pass s reads element j + 64 r,
+// multiplies by W512^(r k 512 / (8 Ns)), k = j mod Ns, Ns = 8^s, transforms the eight values and
+// writes them Ns apart from (j / Ns) 8 Ns + k), each lane holding eight values in registers; the
+// first pass reads the signal itself.  Its outputs Z hold both spectra of the real frames,
+// A[k] = (Z[k] + conj Z[512 - k]) / 2 and i B[k] = (Z[k] - conj Z[512 - k]) / 2.  Bound by fp64
+// arithmetic and LDS passes, which a pair pays once: 117 000 frames 394 -> 240 us.
+// A pair never spans two utterances (a NaN would cross over); the last of an odd number of
+// frames is transformed alone.  Two waves a workgroup, so that one utterance of some seconds
+// still has a workgroup for every compute unit.  pair_start[u] = first pair of utterance u among
+// all pairs.  Sample is double for a resampled signal, float where the input is framed as it is.
 template <typename Sample>
 __global__ __launch_bounds__(kFrameThreads) void log_mel_kernel(
-    const Sample *__restrict__ mid, const Utterance *__restrict__ utt, const uint64_t *__restrict__ frame_start,
-    int n_utt, uint64_t n_frames, int hop, const double *__restrict__ window, const double2 *__restrict__ twiddle,
+    const Sample *__restrict__ mid, const Utterance *__restrict__ utt, const uint64_t *__restrict__ pair_start,
+    int n_utt, uint64_t n_pairs, int hop, const double *__restrict__ window, const double2 *__restrict__ twiddle,
     MelTable mel, const double *__restrict__ mel_weights, int n_mels, float *__restrict__ out)
 {
     __shared__ double2 s_x[kFrameThreads / 64][kFramePadded];
-    __shared__ double s_power[kFrameThreads / 64][kFft / 2 + 1];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const uint64_t f = (uint64_t)blockIdx.x * (kFrameThreads / 64) + wave;
-    if (f >= n_frames) return;   // no workgroup-wide barrier below: a wave works on its own frame
+    if (f >= n_pairs) return;    // no workgroup-wide barrier below: a wave works on its own pair
     int lo = 0, hi = n_utt - 1;
     while (lo < hi) {
         const int m = (lo + hi + 1) >> 1;
-        if (frame_start[m] <= f) lo = m; else hi = m - 1;
+        if (pair_start[m] <= f) lo = m; else hi = m - 1;
     }
     const Utterance u = utt[lo];
-    const uint32_t t = (uint32_t)(f - frame_start[lo]);
+    const uint32_t t = 2 * (uint32_t)(f - pair_start[lo]);
+    const bool two = t + 1 < u.frames;
     double2 *x = s_x[wave];
+    // the factors of the last two passes, under way while the signal arrives
+    double2 factor[2][8];
+#pragma unroll
+    for (int pass = 1; pass < 3; pass++) {
+        const int ns = pass == 1 ? 8 : 64, k = lane & (ns - 1);
+#pragma unroll
+        for (int r = 1; r < 8; r++) factor[pass - 1][r] = twiddle[r * k * (kFft / (8 * ns))];
+    }
     double2 v[8];
     {
         const Sample *sig = mid + u.mid_off;
@@ -214,10 +227,15 @@ __global__ __launch_bounds__(kFrameThreads) void log_mel_kernel(
 #pragma unroll
         for (int r = 0; r < 8; r++) {
             const int j = lane + 64 * r;
-            int64_t s = (int64_t)t * hop + j - kFft / 2;
-            if (s < 0) s = -s;                       // reflection about the first sample
-            if (s >= len) s = 2 * (len - 1) - s;     // and about the last (len > n_fft / 2)
-            v[r] = make_double2((double)sig[s] * window[j], 0.0);
+            double ab[2];
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                int64_t s = ((int64_t)t + (two ? i : 0)) * hop + j - kFft / 2;
+                if (s < 0) s = -s;                       // reflection about the first sample
+                if (s >= len) s = 2 * (len - 1) - s;     // and about the last (len > n_fft / 2)
+                ab[i] = (double)sig[s] * window[j];
+            }
+            v[r] = make_double2(ab[0], two ? ab[1] : 0.0);
         }
     }
     dft8(v);
@@ -233,7 +251,7 @@ __global__ __launch_bounds__(kFrameThreads) void log_mel_kernel(
 #pragma unroll
         for (int r = 0; r < 8; r++) v[r] = x[padded(lane + 64 * r)];
 #pragma unroll
-        for (int r = 1; r < 8; r++) v[r] = cmul(v[r], twiddle[r * k * (kFft / (8 * ns))]);
+        for (int r = 1; r < 8; r++) v[r] = cmul(v[r], factor[pass - 1][r]);
         dft8(v);
         if (pass == 1) {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -243,10 +261,19 @@ __global__ __launch_bounds__(kFrameThreads) void log_mel_kernel(
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
     }
-    // after the last pass value r of lane j is bin j + 64 r: bins 0 .. 255, and 256 in lane 0
+    // After the last pass value r of lane j is Z[j + 64 r].  Z[512 - k] is value 7 - r of lane
+    // 64 - j, in lane 0 its own value 8 - r.  The powers of both frames, bins 0 .. 256, replace
+    // the values of the last pass in LDS (all lanes have read theirs: the fence).
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
-    for (int r = 0; r < 4; r++) s_power[wave][lane + 64 * r] = v[r].x * v[r].x + v[r].y * v[r].y;
-    if (lane == 0) s_power[wave][kFft / 2] = v[4].x * v[4].x + v[4].y * v[4].y;
+    for (int r = 0; r < 4; r++) {
+        double2 w = make_double2(__shfl(v[7 - r].x, (64 - lane) & 63), __shfl(v[7 - r].y, (64 - lane) & 63));
+        if (lane == 0) w = v[(8 - r) & 7];
+        const double ax = v[r].x + w.x, ay = v[r].y - w.y, bx = v[r].x - w.x, by = v[r].y + w.y;
+        x[lane + 64 * r] = make_double2(0.25 * (ax * ax + ay * ay), 0.25 * (bx * bx + by * by));
+    }
+    // bin 256 is its own partner: both spectra are real there
+    if (lane == 0) x[kFft / 2] = make_double2(v[4].x * v[4].x, v[4].y * v[4].y);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     // The triangles widen with their number, so a lane takes a narrow one and then the wide one
     // that mirrors it (m and n_mels - 1 - m): every busy lane sums about the same number of bins.
@@ -256,10 +283,22 @@ __global__ __launch_bounds__(kFrameThreads) void log_mel_kernel(
             const int m = side == 0 ? i : n_mels - 1 - i;
             if (side == 1 && m == i) break;  // the middle one of an odd number
             const double *w = mel_weights + mel.first_weight[m];
-            const double *pw = s_power[wave] + mel.start[m];
-            double acc = 0.0;
-            for (int k = 0; k < mel.count[m]; k++) acc = fma(w[k], pw[k], acc);
-            out[u.out_off + (uint64_t)m * u.frames + t] = (float)log(acc + (double)kLogGuard);
+            const double2 *pw = x + mel.start[m];
+            double a = 0.0, b = 0.0;
+            // four bins at a time, so that their loads are under way together
+            const int count = mel.count[m];
+            for (int k = 0; k < count; k += 4) {
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const int at = min(k + i, count - 1);
+                    const double weight = w[at], wk = k + i < count ? weight : 0.0;
+                    a = fma(wk, pw[at].x, a);
+                    b = fma(wk, pw[at].y, b);
+                }
+            }
+            float *o = out + u.out_off + (uint64_t)m * u.frames + t;
+            o[0] = (float)log(a + (double)kLogGuard);
+            if (two) o[1] = (float)log(b + (double)kLogGuard);
         }
     }
 }
@@ -347,7 +386,7 @@ struct prep_audio {
     uint64_t calls = 0;
     // per call
     Utterance *h_utt = nullptr, *d_utt = nullptr;
-    uint64_t *h_starts = nullptr, *d_starts = nullptr;  // [mid_start n][frame_start n][tile_start n]
+    uint64_t *h_starts = nullptr, *d_starts = nullptr;  // [mid_start n][pair_start n][tile_start n]
     double *d_mid = nullptr;
     hipEvent_t done = nullptr;
     bool pending = false;
@@ -525,7 +564,7 @@ int prep_audio_features(prep_audio *h, const float *waveforms, const uint64_t *o
         AUDIO_TRY(hipEventSynchronize(h->done));
         h->pending = false;
     }
-    uint64_t mid_total = 0, frames_total = 0, out_total = 0, tiles_total = 0;
+    uint64_t mid_total = 0, pairs_total = 0, out_total = 0, tiles_total = 0;
     // threads per workgroup of the resampler that keeps its taps in registers: a multiple of q
     const uint32_t phase_threads = q <= 320 ? (uint32_t)q * (uint32_t)std::max(1, 320 / q) : 0u;
     const uint64_t per_wg = (uint64_t)phase_threads * kTilesPerWg;
@@ -543,11 +582,11 @@ int prep_audio_features(prep_audio *h, const float *waveforms, const uint64_t *o
         u.out_off = out_total;
         u.pad_ = 0;
         h->h_starts[i] = mid_total;
-        h->h_starts[(size_t)n + i] = frames_total;
+        h->h_starts[(size_t)n + i] = pairs_total;
         h->h_starts[2 * (size_t)n + i] = tiles_total;
         if (per_wg) tiles_total += (len + per_wg - 1) / per_wg;
         mid_total += len;
-        frames_total += u.frames;
+        pairs_total += (u.frames + 1) / 2;
         out_total += (uint64_t)u.frames * (uint64_t)h->cfg.n_mels;
         out_offsets[i + 1] = out_total;
     }
@@ -591,14 +630,15 @@ int prep_audio_features(prep_audio *h, const float *waveforms, const uint64_t *o
         hipLaunchKernelGGL(resample_kernel, dim3((unsigned)((mid_total + 255) / 256)), dim3(256), 0, stream, waveforms,
                            h->d_utt, h->d_starts, n, taps->d_taps, taps->d_first, p, q, taps->n_taps, h->d_mid, mid_total);
     }
-    const dim3 frame_grid((unsigned)((frames_total + 3) / 4));
+    const uint64_t pairs_per_wg = kFrameThreads / 64;
+    const dim3 pair_grid((unsigned)((pairs_total + pairs_per_wg - 1) / pairs_per_wg));
     if (p == q)
-        hipLaunchKernelGGL(log_mel_kernel<float>, frame_grid, dim3(kFrameThreads), 0, stream, waveforms, h->d_utt,
-                           h->d_starts + n, n, frames_total, h->cfg.hop, h->d_window, h->d_twiddle, h->mel,
+        hipLaunchKernelGGL(log_mel_kernel<float>, pair_grid, dim3(kFrameThreads), 0, stream, waveforms, h->d_utt,
+                           h->d_starts + n, n, pairs_total, h->cfg.hop, h->d_window, h->d_twiddle, h->mel,
                            h->d_mel_weights, h->cfg.n_mels, out);
     else
-        hipLaunchKernelGGL(log_mel_kernel<double>, frame_grid, dim3(kFrameThreads), 0, stream, (const double *)h->d_mid,
-                           h->d_utt, h->d_starts + n, n, frames_total, h->cfg.hop, h->d_window, h->d_twiddle, h->mel,
+        hipLaunchKernelGGL(log_mel_kernel<double>, pair_grid, dim3(kFrameThreads), 0, stream, (const double *)h->d_mid,
+                           h->d_utt, h->d_starts + n, n, pairs_total, h->cfg.hop, h->d_window, h->d_twiddle, h->mel,
                            h->d_mel_weights, h->cfg.n_mels, out);
     hipLaunchKernelGGL(normalize_kernel, dim3((unsigned)n * (unsigned)h->cfg.n_mels), dim3(256), 0, stream, h->d_utt,
                        h->cfg.n_mels, out);

@@ -111,3 +111,26 @@ def test_argument_errors(prep):
         ap.close()
     with pytest.raises(prep.PrepError):
         prep.AudioPreprocessor(max_batch=1, max_total_samples=1000, n_fft=1024)
+
+
+def test_frames_in_pairs(prep):
+    """Two frames share a transform: odd and even counts of frames (from two on: the shortest signal
+    that can be reflected holds 257 samples), a frame of silence beside loud ones, and a NaN that
+    stays in its own utterance."""
+    rate = 16000
+    waves = [speech_like(700 + k, rate, 1.0)[:n] for k, n in enumerate((257, 319, 320, 479, 480, 481, 4000, 4160))]
+    waves.append(np.concatenate([waves[-1], np.zeros(1600, np.float32), waves[-1]]))
+    bad = waves[3].copy()
+    bad[100] = np.nan
+    ap = prep.AudioPreprocessor(max_batch=16, max_total_samples=sum(len(w) for w in waves) * 3)
+    try:
+        plain = run(ap, waves, rate)
+        for w, g in zip(waves, plain):
+            ref = audio.preprocess(w.astype(np.float64), rate)
+            assert g.shape == ref.shape and np.abs(g - ref).max() <= FEATURE_TOL
+        got = run(ap, waves[:3] + [bad] + waves[4:], rate)
+        assert np.isnan(got[3]).any()
+        for i in range(len(waves)):
+            assert i == 3 or np.array_equal(got[i], plain[i])
+    finally:
+        ap.close()
