@@ -43,6 +43,8 @@ struct Utterance {
     uint64_t out_off;   // first output element
     uint32_t in_len, mid_len, frames, pad_;
 };
+constexpr size_t kRecordBytes = sizeof(Utterance) + 3 * sizeof(uint64_t);  // of one utterance and its starts
+static_assert(sizeof(Utterance) % sizeof(uint64_t) == 0, "the starts behind the records are aligned");
 
 // ---- resample -----------------------------------------------------------------------------
 // Output m = a q + r of an utterance (r < q) is sum_j x[a p + first[r] + j] taps[j][r]: the
@@ -385,8 +387,9 @@ struct prep_audio {
     int32_t *h_first_pinned = nullptr;
     uint64_t calls = 0;
     // per call
+    // a call's n records, and behind them [mid_start n][pair_start n][tile_start n]: they go up in
+    // one copy
     Utterance *h_utt = nullptr, *d_utt = nullptr;
-    uint64_t *h_starts = nullptr, *d_starts = nullptr;  // [mid_start n][pair_start n][tile_start n]
     double *d_mid = nullptr;
     hipEvent_t done = nullptr;
     bool pending = false;
@@ -499,10 +502,8 @@ int prep_audio_create(prep_audio **out, const prep_audio_config *cfg)
     ok = ok && hipMalloc((void **)&h->d_window, sizeof(double) * kFft) == hipSuccess;
     ok = ok && hipMalloc((void **)&h->d_twiddle, sizeof(double2) * kFft) == hipSuccess;
     ok = ok && hipMalloc((void **)&h->d_mel_weights, sizeof(double) * weights.size()) == hipSuccess;
-    ok = ok && hipMalloc((void **)&h->d_utt, sizeof(Utterance) * n) == hipSuccess;
-    ok = ok && hipMalloc((void **)&h->d_starts, sizeof(uint64_t) * 3 * n) == hipSuccess;
-    ok = ok && hipHostMalloc((void **)&h->h_utt, sizeof(Utterance) * n, hipHostMallocDefault) == hipSuccess;
-    ok = ok && hipHostMalloc((void **)&h->h_starts, sizeof(uint64_t) * 3 * n, hipHostMallocDefault) == hipSuccess;
+    ok = ok && hipMalloc((void **)&h->d_utt, kRecordBytes * n) == hipSuccess;
+    ok = ok && hipHostMalloc((void **)&h->h_utt, kRecordBytes * n, hipHostMallocDefault) == hipSuccess;
     // the resampled signal is never longer than max_total_samples scaled by the largest ratio accepted
     ok = ok && hipMalloc((void **)&h->d_mid, sizeof(double) * (cfg->max_total_samples + n)) == hipSuccess;
     for (auto &ts : h->slot) {
@@ -533,7 +534,6 @@ int prep_audio_destroy(prep_audio *h)
     (void)hipFree(h->d_twiddle);
     (void)hipFree(h->d_mel_weights);
     (void)hipFree(h->d_utt);
-    (void)hipFree(h->d_starts);
     (void)hipFree(h->d_mid);
     for (auto &ts : h->slot) {
         (void)hipFree(ts.d_taps);
@@ -542,7 +542,6 @@ int prep_audio_destroy(prep_audio *h)
     if (h->h_taps_pinned) (void)hipHostFree(h->h_taps_pinned);
     if (h->h_first_pinned) (void)hipHostFree(h->h_first_pinned);
     if (h->h_utt) (void)hipHostFree(h->h_utt);
-    if (h->h_starts) (void)hipHostFree(h->h_starts);
     if (h->done) (void)hipEventDestroy(h->done);
     delete h;
     return PREP_OK;
@@ -564,6 +563,8 @@ int prep_audio_features(prep_audio *h, const float *waveforms, const uint64_t *o
         AUDIO_TRY(hipEventSynchronize(h->done));
         h->pending = false;
     }
+    uint64_t *h_starts = reinterpret_cast<uint64_t *>(h->h_utt + n);
+    const uint64_t *d_starts = reinterpret_cast<const uint64_t *>(h->d_utt + n);
     uint64_t mid_total = 0, pairs_total = 0, out_total = 0, tiles_total = 0;
     // threads per workgroup of the resampler that keeps its taps in registers: a multiple of q
     const uint32_t phase_threads = q <= 320 ? (uint32_t)q * (uint32_t)std::max(1, 320 / q) : 0u;
@@ -581,9 +582,9 @@ int prep_audio_features(prep_audio *h, const float *waveforms, const uint64_t *o
         u.mid_off = mid_total;
         u.out_off = out_total;
         u.pad_ = 0;
-        h->h_starts[i] = mid_total;
-        h->h_starts[(size_t)n + i] = pairs_total;
-        h->h_starts[2 * (size_t)n + i] = tiles_total;
+        h_starts[i] = mid_total;
+        h_starts[(size_t)n + i] = pairs_total;
+        h_starts[2 * (size_t)n + i] = tiles_total;
         if (per_wg) tiles_total += (len + per_wg - 1) / per_wg;
         mid_total += len;
         pairs_total += (u.frames + 1) / 2;
@@ -621,24 +622,23 @@ int prep_audio_features(prep_audio *h, const float *waveforms, const uint64_t *o
         // same rate: the frames read the input itself; utterance offsets are the input's
         for (int32_t i = 0; i < n; i++) h->h_utt[i].mid_off = h->h_utt[i].in_off;
     }
-    AUDIO_TRY(hipMemcpyAsync(h->d_utt, h->h_utt, sizeof(Utterance) * (size_t)n, hipMemcpyHostToDevice, stream));
-    AUDIO_TRY(hipMemcpyAsync(h->d_starts, h->h_starts, sizeof(uint64_t) * 3 * (size_t)n, hipMemcpyHostToDevice, stream));
+    AUDIO_TRY(hipMemcpyAsync(h->d_utt, h->h_utt, kRecordBytes * (size_t)n, hipMemcpyHostToDevice, stream));
     if (p != q && phase_threads && taps->n_taps <= kMaxTaps && tiles_total <= 0x7FFFFFFFull) {
         hipLaunchKernelGGL(resample_phase_kernel, dim3((unsigned)tiles_total), dim3(phase_threads), 0, stream, waveforms,
-                           h->d_utt, h->d_starts + 2 * n, n, taps->d_taps, taps->d_first, p, q, taps->n_taps, h->d_mid);
+                           h->d_utt, d_starts + 2 * n, n, taps->d_taps, taps->d_first, p, q, taps->n_taps, h->d_mid);
     } else if (p != q) {
         hipLaunchKernelGGL(resample_kernel, dim3((unsigned)((mid_total + 255) / 256)), dim3(256), 0, stream, waveforms,
-                           h->d_utt, h->d_starts, n, taps->d_taps, taps->d_first, p, q, taps->n_taps, h->d_mid, mid_total);
+                           h->d_utt, d_starts, n, taps->d_taps, taps->d_first, p, q, taps->n_taps, h->d_mid, mid_total);
     }
     const uint64_t pairs_per_wg = kFrameThreads / 64;
     const dim3 pair_grid((unsigned)((pairs_total + pairs_per_wg - 1) / pairs_per_wg));
     if (p == q)
         hipLaunchKernelGGL(log_mel_kernel<float>, pair_grid, dim3(kFrameThreads), 0, stream, waveforms, h->d_utt,
-                           h->d_starts + n, n, pairs_total, h->cfg.hop, h->d_window, h->d_twiddle, h->mel,
+                           d_starts + n, n, pairs_total, h->cfg.hop, h->d_window, h->d_twiddle, h->mel,
                            h->d_mel_weights, h->cfg.n_mels, out);
     else
         hipLaunchKernelGGL(log_mel_kernel<double>, pair_grid, dim3(kFrameThreads), 0, stream, (const double *)h->d_mid,
-                           h->d_utt, h->d_starts + n, n, pairs_total, h->cfg.hop, h->d_window, h->d_twiddle, h->mel,
+                           h->d_utt, d_starts + n, n, pairs_total, h->cfg.hop, h->d_window, h->d_twiddle, h->mel,
                            h->d_mel_weights, h->cfg.n_mels, out);
     hipLaunchKernelGGL(normalize_kernel, dim3((unsigned)n * (unsigned)h->cfg.n_mels), dim3(256), 0, stream, h->d_utt,
                        h->cfg.n_mels, out);
