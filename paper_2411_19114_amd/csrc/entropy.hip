@@ -1848,7 +1848,11 @@ __global__ __launch_bounds__(kDecodeThreads) void chain_streams(
         __syncthreads();
     }
     // the chain has to reach the end of the data with all of the image's blocks
-    if (tid == 0 && (s_entry != kToEnd || s_block != R.n_blocks)) retry[blockIdx.x] = 1;
+    if (tid == 0) {
+        const bool linked = s_entry == kToEnd && s_block == R.n_blocks;
+        W[0].linked = linked;
+        if (!linked) retry[blockIdx.x] = 1;
+    }
 }
 
 __global__ __launch_bounds__(kDecodeThreads) void write_streams(
@@ -1868,9 +1872,11 @@ __global__ __launch_bounds__(kDecodeThreads) void write_streams(
     if (w >= R.n_streams || R.status != PREP_OK) return;
     StreamWindow &W = windows[wg];
     const uint32_t H = R.blocks_per_mcu, entry = W.entry;
-    // (an image that is to be decoded in one piece is left alone; other windows of it may find that
-    // out only now)
-    if (retry[img] != 0 || entry >= stream_overlap(row_bytes) * H) {
+    // An image that is to be decoded in one piece is left alone.  Other windows of it may find that
+    // out only now and set retry[img]: that is for the next kernels to read.  Here the waves of this
+    // workgroup would read it at different times, and some would leave where others go on to
+    // the barriers; what chain_streams wrote is the same for all of them.
+    if (!windows[R.stream0].linked || entry >= stream_overlap(row_bytes) * H) {
         if (tid == 0) {
             W.dc_lo = W.dc_hi = 0;
             W.dc_sum[0] = W.dc_sum[1] = W.dc_sum[2] = 0;

@@ -3,7 +3,7 @@
 
 namespace hip_emul {
 
-void launch(dim3 grid, dim3 block, const std::function<void()> &fn)
+void launch(dim3 grid, dim3 block, const std::function<void()> &fn, const std::function<void()> &intrude)
 {
     const unsigned n = block.x * block.y * block.z;
     for (unsigned bz = 0; bz < grid.z; bz++)
@@ -12,7 +12,11 @@ void launch(dim3 grid, dim3 block, const std::function<void()> &fn)
                 BlockCtx ctx(n);
                 std::vector<std::thread> lanes;
                 lanes.reserve(n);
-                for (unsigned t = 0; t < n; t++)
+                for (unsigned t = 0; t < n; t++) {
+                    if (t == 64 && intrude) {
+                        while (ctx.wave0_settled.load() < 64) std::this_thread::yield();
+                        intrude();
+                    }
                     lanes.emplace_back([&, t]() {
                         ThreadState &s = tls;
                         s.tid = dim3(t % block.x, (t / block.x) % block.y, t / (block.x * block.y));
@@ -21,11 +25,15 @@ void launch(dim3 grid, dim3 block, const std::function<void()> &fn)
                         s.gdim = grid;
                         s.ctx = &ctx;
                         s.or_calls = 0;
+                        s.settled = false;
                         fn();
+                        s.settle();
+                        ctx.ended++;
                         // a lane that has returned no longer takes part in barriers
                         ctx.wave_bar[t >> 6]->arrive_and_drop();
                         ctx.bar.arrive_and_drop();
                     });
+                }
                 for (auto &l : lanes) l.join();
             }
 }

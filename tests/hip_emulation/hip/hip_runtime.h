@@ -11,12 +11,14 @@
 #include <cmath>
 #include <condition_variable>
 #include <cstdint>
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <functional>
 #include <memory>
 #include <mutex>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 #define __global__
@@ -51,6 +53,8 @@ struct BlockCtx {
     std::vector<std::unique_ptr<std::barrier<>>> wave_bar;
     std::vector<uint64_t> xchg;
     std::atomic<int> orflag[2];
+    std::atomic<unsigned> ended{0};         // lanes that have returned
+    std::atomic<unsigned> wave0_settled{0}; // lanes of wave 0 that have come to a barrier or returned
     explicit BlockCtx(unsigned n) : nthreads(n), bar(n), xchg(n)
     {
         orflag[0] = orflag[1] = 0;
@@ -63,12 +67,54 @@ struct ThreadState {
     dim3 tid, bid, bdim, gdim;
     BlockCtx *ctx = nullptr;
     unsigned or_calls = 0;
+    bool settled = false;
+    void settle()
+    {
+        if (!settled && tid.x < 64) ctx->wave0_settled++;
+        settled = true;
+    }
 };
 inline thread_local ThreadState tls;
 
 // Run fn once per lane of every workgroup of the grid; workgroups run one after another
-// because __shared__ variables are function-level statics here.
-void launch(dim3 grid, dim3 block, const std::function<void()> &fn);
+// because __shared__ variables are function-level statics here.  intrude: what another
+// workgroup would do to memory, done when the first wave of every workgroup has come to its first
+// barrier (or has returned) and the other waves have not begun.
+void launch(dim3 grid, dim3 block, const std::function<void()> &fn, const std::function<void()> &intrude = {});
+
+// PREP_EMUL_INTRUDE=kernel: a launch of that kernel gets all of its first `uint32_t *` argument's
+// entries (one an image, PREP_EMUL_IMAGES of them) set to 1 in that way
+inline bool intruded(const char *kernel)
+{
+    const char *v = getenv("PREP_EMUL_INTRUDE");
+    return v && strcmp(v, kernel) == 0;
+}
+inline uint32_t *first_flags() { return nullptr; }
+template <typename A, typename... Rest>
+inline uint32_t *first_flags(A a, Rest... rest)
+{
+    if constexpr (std::is_same_v<A, uint32_t *>) return a;
+    else return first_flags(rest...);
+}
+template <typename... Args>
+inline std::function<void()> intruder(const char *kernel, Args... args)
+{
+    uint32_t *flags = first_flags(args...);
+    if (!flags || !intruded(kernel)) return {};
+    const int n = atoi(getenv("PREP_EMUL_IMAGES"));
+    return [flags, n]() { for (int i = 0; i < n; i++) flags[i] = 1; };
+}
+
+// Every lane of a workgroup has to come to each of its barriers: one that has returned never will.
+inline void meet(std::barrier<> &bar)
+{
+    tls.settle();
+    if (tls.ctx->ended.load() != 0) {
+        fprintf(stderr, "hip_emul: a barrier that some lanes of the workgroup never reach\n");
+        abort();
+    }
+    bar.arrive_and_wait();
+}
 
 template <typename T>
 inline uint64_t to_bits(T v) { uint64_t b = 0; memcpy(&b, &v, sizeof(T)); return b; }
@@ -97,16 +143,16 @@ inline T shuffle(T v, F src_of)
 #define blockDim (hip_emul::tls.bdim)
 #define gridDim (hip_emul::tls.gdim)
 
-inline void __syncthreads() { hip_emul::tls.ctx->bar.arrive_and_wait(); }
+inline void __syncthreads() { hip_emul::meet(hip_emul::tls.ctx->bar); }
 inline int __syncthreads_or(int p)
 {
     hip_emul::ThreadState &t = hip_emul::tls;
     hip_emul::BlockCtx &c = *t.ctx;
     const int slot = (int)(t.or_calls++ & 1u);
     if (p) c.orflag[slot].store(1);
-    c.bar.arrive_and_wait();
+    hip_emul::meet(c.bar);
     const int r = c.orflag[slot].load();
-    c.bar.arrive_and_wait();
+    hip_emul::meet(c.bar);
     if (t.tid.x == 0) c.orflag[slot].store(0);
     return r;
 }
@@ -185,7 +231,7 @@ template <typename T> inline T min(T a, T b) { return b < a ? b : a; }
 template <typename T> inline T max(T a, T b) { return a < b ? b : a; }
 
 #define hipLaunchKernelGGL(kernel, grid, block, shmem, stream, ...) \
-    hip_emul::launch((grid), (block), [&]() { kernel(__VA_ARGS__); })
+    hip_emul::launch((grid), (block), [&]() { kernel(__VA_ARGS__); }, hip_emul::intruder(#kernel, __VA_ARGS__))
 
 // ---- runtime API: the "device" is the host heap --------------------------------------
 inline hipError_t hipGetDeviceCount(int *n) { *n = 1; return hipSuccess; }

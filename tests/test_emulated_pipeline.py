@@ -171,3 +171,13 @@ def test_damaged_entropy_data_stays_in_bounds(windows):
     per, ten = emul.run(streams, 32, 24, 24, "f32", MEAN, STD, timeout=3000, flags=windows)
     refused = helpers.check_damaged(streams, [p[0] for p in per], lambda i, nb: per[i][1], ten)
     assert refused >= len(streams) // 2
+
+
+def test_a_window_that_another_gives_up_meanwhile(monkeypatch):
+    # another window of the image finds damage and sends the image to the decoder for whole streams
+    # while this one is at work: its lanes must stay together at their barriers, and the image is
+    # decoded again
+    streams = [oracle.encode(_img(90 + k, 112, 96), 88, mode, 0)[0] for k, mode in enumerate((MODE_420, MODE_444, MODE_GRAY))]
+    monkeypatch.setenv("PREP_EMUL_INTRUDE", "write_streams")
+    monkeypatch.setenv("PREP_EMUL_IMAGES", str(len(streams)))
+    _check(streams, 0, 1, 1, "f32", flags=2)
