@@ -1450,7 +1450,8 @@ struct StreamShared {
 struct StreamPart {                  // what staging found
     uint32_t own, total;             // clean bytes of the window itself, and with what follows
     bool to_end;                     // the staged bytes reach the end of the data
-    bool marker;                     // a marker other than stuffing lies among them
+    bool marker;                     // a marker other than stuffing lies among them, or too little
+                                     // is left between long runs of fill bytes
 };
 
 // Stage the raw bytes [w * step, (w + 1) * step) of the segment and enough after them for the
@@ -1515,6 +1516,12 @@ __device__ inline StreamPart stage_stream(StreamShared &S, const uint8_t *seg, u
                 o++;
             }
     }
+    // Windows are joined at rows that both hold whole, with the bytes of a symbol that begins at
+    // their end.  Stuffing leaves at least half of the bytes, which is enough (see ce), but a
+    // run of fill bytes (FF FF .. FF 00) may leave any number, behind this window or in it.
+    const uint32_t shared = stream_overlap(row_bytes) * row_bytes;
+    if ((!part.to_end && part.total - part.own < shared + 8u) || (own_end < (int32_t)data_len && part.own < shared))
+        part.marker = true;
     __syncthreads();
     return part;
 }

@@ -181,3 +181,24 @@ def test_a_window_that_another_gives_up_meanwhile(monkeypatch):
     monkeypatch.setenv("PREP_EMUL_INTRUDE", "write_streams")
     monkeypatch.setenv("PREP_EMUL_IMAGES", str(len(streams)))
     _check(streams, 0, 1, 1, "f32", flags=2)
+
+
+def test_long_runs_of_fill_bytes_before_stuffing():
+    # hundreds of FF in front of an FF 00, inside the rows that two windows share, at several places
+    # in them: the windows then hold too little of each other's data to be joined.  Seeds and places
+    # whose pixels came out wrong, and some on either side.
+    streams = []
+    for mode, w, h, step, places in ((MODE_420, 112, 96, 1260, [(77, 1), (197, 1), (361, 1), (54, 1), (377, 1)]),
+                                     (MODE_GRAY, 160, 128, 2808, [(1, 1), (85, 1), (305, 1), (116, 1)])):
+        for seed, k in places:
+            f = oracle.encode(_img(seed, w, h, sigma=9.0), 90, mode, 0)[0]
+            start = f.index(b"\xff\xda") + 2
+            start += int.from_bytes(f[start:start + 2], "big")
+            at = f.index(b"\xff\x00", start + k * step + 26)
+            assert at < start + k * step + 37, (mode, seed)
+            for run in (620, 290) if seed in (77, 1) else (620,):
+                streams.append((f, f[:at] + b"\xff" * run + f[at:]))
+    per, _ = emul.run([s for _, s in streams], 0, 1, 1, "f32", MEAN, STD)
+    for i, (f, _) in enumerate(streams):
+        # (the files without the run: the oracle does not take fill bytes before stuffing)
+        assert per[i][0] == 0 and np.array_equal(per[i][1], oracle.decode(f)[0]), f"image {i}"
