@@ -281,6 +281,14 @@ int64_t prep_debug_last_rgb(prep_handle *h, int32_t image, uint8_t *host_out_hwc
  * it was refused, or PREP_E_INVALID_ARG.                                      */
 int prep_debug_last_region(prep_handle *h, int32_t image, int32_t rect[4]);
 
+/* How the last call decoded the stream of image `image`: PREP_STREAM_WINDOWS = it
+ * has no restart markers and was cut into windows that were decoded side by side;
+ * PREP_STREAM_UNJOINED = the windows could not be joined, and one workgroup then
+ * decoded the whole stream (which costs both); PREP_STREAM_WHOLE = otherwise.  A
+ * negative code as above where the image was refused before it was decoded.    */
+enum { PREP_STREAM_WHOLE = 0, PREP_STREAM_WINDOWS = 1, PREP_STREAM_UNJOINED = 2 };
+int prep_debug_last_stream(prep_handle *h, int32_t image);
+
 /* Stage timing.  While enabled, every batch call brackets its GPU stages with
  * events on the call's stream (calls that enqueue no decode are not counted).
  * prep_stage_ms waits for the call made `calls_back` timed calls ago (0 = the

@@ -16,6 +16,7 @@ FLAG_FULL_RGB = 2
 FLAG_SMOOTH_CHROMA = 4
 FLAG_LARGE_WINDOWS = 8
 FILTER_BILINEAR, FILTER_ANTIALIAS = 0, 1
+STREAM_WHOLE, STREAM_WINDOWS, STREAM_UNJOINED = 0, 1, 2
 
 
 def lib_path():
@@ -88,7 +89,7 @@ EXPORTS = [
     "prep_create", "prep_destroy", "prep_decode_resize_batch", "prep_decode_resize_batch_resident",
     "prep_get_status", "prep_strerror", "prep_parse_headers", "prep_interval_descriptors",
     "prep_resize_normalize", "prep_resize_normalize_static", "prep_reconstruct_from_coefficients", "prep_debug_last_coefficients",
-    "prep_debug_last_rgb", "prep_debug_last_region", "prep_stage_ms", "prep_set_timing",
+    "prep_debug_last_rgb", "prep_debug_last_region", "prep_debug_last_stream", "prep_stage_ms", "prep_set_timing",
     "prep_policy_create", "prep_policy_destroy", "prep_policy_arrive", "prep_policy_deadline",
     "prep_policy_take", "prep_policy_pending", "prep_server_create", "prep_server_destroy",
     "prep_server_submit", "prep_server_next", "prep_server_release", "prep_server_next_many",
@@ -137,6 +138,7 @@ def lib():
         L.prep_debug_last_rgb.argtypes = [vp, C.c_int32, vp, C.c_uint64]
         L.prep_debug_last_rgb.restype = C.c_int64
         L.prep_debug_last_region.argtypes = [vp, C.c_int32, C.POINTER(C.c_int32)]
+        L.prep_debug_last_stream.argtypes = [vp, C.c_int32]
         L.prep_stage_ms.argtypes = [vp, C.c_int32, C.POINTER(C.c_float)]
         L.prep_set_timing.argtypes = [vp, C.c_int32]
         L.prep_policy_create.argtypes = [C.POINTER(vp), C.c_int32, C.c_int64]
@@ -312,6 +314,13 @@ class Preprocessor:
         rect = (C.c_int32 * 4)()
         _check(lib().prep_debug_last_region(self._h, image, rect), "prep_debug_last_region")
         return tuple(rect)
+
+    def debug_last_stream(self, image):
+        """STREAM_*: how the last call decoded the image's stream."""
+        r = lib().prep_debug_last_stream(self._h, image)
+        if r < 0:
+            raise PrepError(int(r), "prep_debug_last_stream")
+        return int(r)
 
     def set_timing(self, enabled):
         _check(lib().prep_set_timing(self._h, int(bool(enabled))), "prep_set_timing")

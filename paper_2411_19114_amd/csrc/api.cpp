@@ -237,6 +237,7 @@ struct prep_handle {
     uint64_t timed_calls = 0;
     // last call
     int32_t last_n = 0;
+    bool last_decoded = false;         // (its coefficients were not the caller's)
     hipStream_t last_stream = nullptr;
     std::vector<ParsedImage> parsed;
     std::vector<ImageRec> recs;
@@ -541,6 +542,7 @@ int run_batch(prep_handle *h, const uint8_t *bits_host, const uint8_t *bits_dev,
     s->pending = true;
     if (timing) h->timed_calls++;
     h->last_n = n;
+    h->last_decoded = !coef_host;
     h->last_stream = stream;
     return PREP_OK;
 }
@@ -822,6 +824,19 @@ int prep_debug_last_region(prep_handle *h, int32_t image, int32_t rect[4])
         if (R.roi_row0 + R.roi_rows < R.mcu_rows) rect[3] -= fy;
     }
     return PREP_OK;
+}
+
+int prep_debug_last_stream(prep_handle *h, int32_t image)
+{
+    if (!h || image < 0 || image >= h->last_n) return PREP_E_INVALID_ARG;
+    const ImageRec &R = h->recs[(size_t)image];
+    if (R.status != PREP_OK) return R.status;
+    if (R.n_streams == 0 || !h->last_decoded) return PREP_STREAM_WHOLE;
+    HIP_TRY(hipSetDevice(h->cfg.device));
+    HIP_TRY(hipStreamSynchronize(h->last_stream));
+    uint32_t retry;
+    HIP_TRY(hipMemcpy(&retry, h->d_retry + image, sizeof retry, hipMemcpyDeviceToHost));
+    return retry ? PREP_STREAM_UNJOINED : PREP_STREAM_WINDOWS;
 }
 
 int prep_set_timing(prep_handle *h, int32_t enabled)

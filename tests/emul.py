@@ -12,6 +12,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 EMU = os.path.join(ROOT, "tests", "hip_emulation")
 CSRC = os.path.join(ROOT, "paper_2411_19114_amd", "csrc")
 BINARY = os.environ.get("PREP_EMUL_BIN", os.path.join(EMU, "prep_emul"))
+streams_decoded = []  # of the last run: how each image's stream was decoded (PREP_STREAM_*)
 KERNELS = ["entropy.hip", "reconstruct.hip", "resize.hip", "api.cpp", "parser.cpp"]
 
 
@@ -56,12 +57,14 @@ def run(streams, resize_short, crop_h, crop_w, out_dtype, mean, std, timeout=600
         blob = open(fout, "rb").read()
     pos = 0
     per_image = []
+    streams_decoded.clear()
     for _ in range(n):
         status, = struct.unpack_from("<i", blob, pos); pos += 4
         nc, = struct.unpack_from("<q", blob, pos); pos += 8
         coef = np.frombuffer(blob, dtype=np.int16, count=nc, offset=pos).reshape(-1, 64) if nc else None
         pos += 2 * nc
         rect = struct.unpack_from("<4i", blob, pos); pos += 16
+        streams_decoded.append(struct.unpack_from("<i", blob, pos)[0]); pos += 4
         nr, = struct.unpack_from("<q", blob, pos); pos += 8
         rgb = np.frombuffer(blob, dtype=np.uint8, count=nr, offset=pos) if nr else None
         pos += nr

@@ -2,8 +2,8 @@
 // runs the C ABI end to end on host threads and dumps every checkpoint.
 //   in : int32 n, resize_short, crop_h, crop_w, out_dtype; float mean[3], std[3];
 //        uint64 offsets[n+1]; bytes
-//   out: per image int32 status, int64 n_coef, int16 coef[], int64 n_rgb, uint8 rgb[];
-//        then the output tensor
+//   out: per image int32 status, int64 n_coef, int16 coef[], int32 region[4], int32 PREP_STREAM_*,
+//        int64 n_rgb, uint8 rgb[]; then the output tensor
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -85,6 +85,8 @@ int main(int argc, char **argv)
         fwrite(&nc, 8, 1, o);
         if (nc) fwrite(coef.data(), 2, (size_t)nc, o);
         fwrite(rect, 4, 4, o);
+        const int32_t stream = info[i].status == PREP_OK ? prep_debug_last_stream(h, i) : 0;
+        fwrite(&stream, 4, 1, o);
         fwrite(&nr, 8, 1, o);
         if (nr) fwrite(rgb.data(), 1, (size_t)nr, o);
     }

@@ -202,3 +202,16 @@ def test_long_runs_of_fill_bytes_before_stuffing():
     for i, (f, _) in enumerate(streams):
         # (the files without the run: the oracle does not take fill bytes before stuffing)
         assert per[i][0] == 0 and np.array_equal(per[i][1], oracle.decode(f)[0]), f"image {i}"
+
+
+def test_how_a_stream_was_decoded_is_reported():
+    # without markers in windows, with markers not, and a stream whose windows show damage is
+    # decoded again in one piece, which refuses it
+    good = oracle.encode(_img(95, 112, 96), 85, MODE_420, 0)[0]
+    cut = good[:len(good) // 2] + b"\xff\xd9"
+    streams = [good, oracle.encode(_img(96, 64, 48), 85, MODE_420, 2)[0], cut, b"not a jpeg"]
+    per, _ = emul.run(streams, 32, 24, 24, "f32", MEAN, STD)
+    assert [p[0] for p in per][:3] == [0, 0, -5] and emul.streams_decoded == [1, 0, 2, 0]
+    assert np.array_equal(per[0][1], oracle.decode(good)[0])
+    emul.run(streams, 32, 24, 24, "f32", MEAN, STD, flags=8)
+    assert emul.streams_decoded == [0, 0, 0, 0]
