@@ -1406,8 +1406,10 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
 //       row j from its first bit with the hypothesis "block h of an MCU begins here" (pass 0) and
 //       then row j + 1 from the state it reached (pass 1): a node.  A node's end state is looked
 //       up among the pass-0 ends of its own row: the equal one is where a node of the next row
-//       begins.  An end state that is none of them (1 to 10 % of the nodes) gets a node of its own
-//       in the next row, decoded in a further pass with the others of its kind.  The last
+//       begins.  An end state that is none of them (1 to 10 % of the nodes, in dense streams most)
+//       gets an extra node in the next row, one for all that end in it, decoded in a further
+//       pass with the others of its kind.  (Of 24 windows in which most nodes needed one, each with
+//       one of its own needed 200 to 450, which the 128 places did not hold; shared, 20 to 80.)  The last
 //       rows, the overlap, are the first rows of the next window: where a chain of nodes meets
 //       one of the hypotheses there, the next window has the node that goes on from it.  So every
 //       entry (overlap row, hypothesis) leads to an exit of the same form and a count of blocks.
@@ -1431,6 +1433,9 @@ namespace {
 
 constexpr uint32_t kToEnd = 254, kNoWay = 255;       // instead of an exit or an entry
 constexpr uint32_t kExit = 0x8000, kNodeToEnd = 0xFFFE, kNodeNoWay = 0xFFFF;  // instead of a next node
+// Extra nodes are kept by the state they begin in and their row, in a table with open addressing.
+constexpr uint32_t kStateBits = 25, kNoKey = 0xFFFFFFFFu;
+constexpr int kExtraProbes = kStreamExtras;          // places looked at; a node without one has no way on
 constexpr uint32_t kOpenLimit = 1u << 22;            // bit limit of a window that the data go on after
 constexpr int kStreamSlack = 32;                     // raw bytes staged behind the overlap
 // clean words of a window: its own bytes and, where every byte is stuffed, the overlap's at half
@@ -1439,6 +1444,9 @@ constexpr int kStreamWords = (int)(stream_window_bytes(3, kStreamRowBytes) + 2 *
                                    kStreamSlack + 64) / 4;
 static_assert(stream_rows(1) <= stream_rows(3) && stream_rows(4) <= stream_rows(3) && stream_rows(6) <= stream_rows(3),
               "4:4:4 has the largest windows");
+
+static_assert(kStreamWords * 32 < (1 << (kStateBits - 9)) && kStreamMaxRows < (1 << (32 - kStateBits)) && kStreamExtras == 128,
+              "a state and its row fit a key, and seven bits index the table");
 
 struct StreamShared {
     uint32_t clean[kStreamWords];    // the window's bytes without stuffing, big-endian packed
@@ -1647,9 +1655,7 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
     __shared__ uint32_t cand[kT];              // end states of pass 0
     __shared__ uint32_t node_end[kStreamNodes];
     __shared__ uint16_t node_blocks[kStreamNodes], node_next[kStreamNodes];
-    __shared__ uint16_t extra_from[kStreamExtras];  // the node whose end state the extra node begins in
-    __shared__ uint8_t extra_row[kStreamExtras];
-    __shared__ uint32_t n_extra;
+    __shared__ uint32_t extra_key[kStreamExtras];  // extra nodes: row << 25 | state in which it begins, or kNoKey
     const int tid = threadIdx.x;
     const uint32_t wg = blockIdx.x;
     const int img = image_of_stream(recs, n_images, wg);
@@ -1668,7 +1674,7 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
         return;
     }
     load_tables(S.tab, tables, R.table_slot);
-    if (tid == 0) n_extra = 0;
+    if (tid < kStreamExtras) extra_key[tid] = kNoKey;
     const StreamPart part = stage_stream(S, bits + R.file_off + R.entropy_rel, data_len, w, step, row_bytes);
     if (part.marker && tid == 0) retry[img] = 1;
     const StreamRows rows(part, row_bytes);
@@ -1693,11 +1699,16 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
         } else if (k < H) {
             to = (r + 1u) * H + k;
         } else {
-            const uint32_t x = atomicAdd(&n_extra, 1u);
-            if (x < (uint32_t)kStreamExtras) {
-                extra_from[x] = (uint16_t)id;
-                extra_row[x] = (uint8_t)(r + 1u);
-                to = (uint32_t)kT + x;
+            // (nodes that begin alike are one: all decoders that are in step come here in the same
+            // state where no hypothesis of the row has fallen into step by its end)
+            const uint32_t key = ((r + 1u) << kStateBits) | s;
+            uint32_t x = (s * 0x9E3779B1u) >> 25;
+            for (int probe = 0; probe < kExtraProbes; probe++, x = (x + 1u) & (uint32_t)(kStreamExtras - 1)) {
+                const uint32_t was = atomicCAS(&extra_key[x], kNoKey, key);
+                if (was == kNoKey || was == key) {
+                    to = (uint32_t)kT + x;
+                    break;
+                }
             }
         }
         node_next[id] = (uint16_t)to;
@@ -1723,26 +1734,26 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
         node_end[tid] = 0;
     }
     __syncthreads();
-    // the extra nodes, a generation at a time (a generation's are at least one row further)
-    uint32_t done = 0;
+    // the extra nodes, a lane each, a generation at a time (a generation's are at least one row further)
+    static_assert(kStreamExtras <= kT, "a lane per extra node");
+    bool done = false;
     for (uint32_t round = 0; round < (uint32_t)kStreamMaxRows; round++) {
-        const uint32_t have = min(n_extra, (uint32_t)kStreamExtras);
-        __syncthreads();
-        if (done >= have) break;
-        const uint32_t x = done + (uint32_t)tid;
-        if (x < have) {
-            const uint32_t from = node_end[extra_from[x]], r = extra_row[x];
+        const uint32_t key = tid < kStreamExtras ? extra_key[tid] : kNoKey;
+        const bool fresh = key != kNoKey && !done;
+        if (!__syncthreads_or(fresh)) break;
+        if (fresh) {
+            const uint32_t from = key & ((1u << kStateBits) - 1u), r = key >> kStateBits;
             uint32_t to = from, n = 0;
             if ((from >> 9) < rows.end(r)) to = decode_row<false>(S, g, from, rows.end(r), rows.limit_bits, &n, nullptr);
-            node_end[kT + x] = to;
-            node_blocks[kT + x] = (uint16_t)n;
-            link((uint32_t)kT + x, r, to);
+            node_end[kT + tid] = to;
+            node_blocks[kT + tid] = (uint16_t)n;
+            link((uint32_t)(kT + tid), r, to);
+            done = true;
         }
-        done = have;
         __syncthreads();
     }
-    const uint32_t n_nodes = (uint32_t)kT + done;
-    for (uint32_t i = (uint32_t)tid; i < n_nodes; i += kT) {
+    for (uint32_t i = (uint32_t)tid; i < (uint32_t)kStreamNodes; i += kT) {
+        if (i >= (uint32_t)kT && extra_key[i - (uint32_t)kT] == kNoKey) continue;
         W.end[i] = node_end[i];
         W.blocks[i] = node_blocks[i];
         W.next[i] = node_next[i];

@@ -180,6 +180,11 @@ template <typename T>
 inline T __shfl_xor(T v, int d, int = 64) { return hip_emul::shuffle(v, [d](int l) { return l ^ d; }); }
 
 inline uint32_t atomicOr(uint32_t *p, uint32_t v) { return __atomic_fetch_or(p, v, __ATOMIC_SEQ_CST); }
+inline uint32_t atomicCAS(uint32_t *p, uint32_t expected, uint32_t v)
+{
+    __atomic_compare_exchange_n(p, &expected, v, false, __ATOMIC_SEQ_CST, __ATOMIC_SEQ_CST);
+    return expected;
+}
 inline uint32_t atomicAdd(uint32_t *p, uint32_t v) { return __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST); }
 inline int32_t atomicMin(int32_t *p, int32_t v)
 {

@@ -215,3 +215,14 @@ def test_how_a_stream_was_decoded_is_reported():
     assert np.array_equal(per[0][1], oracle.decode(good)[0])
     emul.run(streams, 32, 24, 24, "f32", MEAN, STD, flags=8)
     assert emul.streams_decoded == [0, 0, 0, 0]
+
+
+def test_dense_streams_are_joined_too():
+    # about twenty bytes per block (noise at quality 95): many rows do not fall into step with a
+    # hypothesis within their own length, and their nodes lead to extra nodes, which must not run out
+    streams = [oracle.encode(_img(5, 192, 160, sigma), 95, mode, 0, table_mode=tables)[0]
+               for sigma, mode, tables in ((9.0, MODE_420, 0), (9.0, MODE_444, 0), (9.0, MODE_422, 0), (10.0, MODE_444, 1))]
+    per, _ = emul.run(streams, 0, 1, 1, "f32", MEAN, STD)
+    for i, s in enumerate(streams):
+        assert per[i][0] == 0 and np.array_equal(per[i][1], oracle.decode(s)[0]), f"image {i}"
+    assert emul.streams_decoded == [1, 1, 1, 1]
