@@ -313,6 +313,57 @@ uint32_t table_slot_of(prep_handle *h, const uint8_t *bits, const uint64_t *offs
     }
 }
 
+// Which of a call's streams without restart markers are cut into windows that several workgroups
+// decode side by side (the others take a workgroup each), and in rows of which length.
+//   - A stream is cut only if it is sparse enough for its windows to be joined
+//     (stream_density_limit).  A call with a denser one that is more than a quarter as long as the
+//     longest sparse stream is not cut at all: it waits for that one either way.
+//   - Windows pay by the length of the longest stream (7, 8, 12 and 25 us per KB in one workgroup
+//     with 1, 3, 4 and 6 blocks per MCU) and cost four launches and about 60 us for every MB.  Where no
+//     stream is longer than one chunk, no MCU has six blocks and the streams occupy the chip by
+//     themselves, a workgroup each is faster: batches of 256 gray images of 256 x 256
+//     174 against 219 us (1.6 MB), of 384 4:4:4 images of 192 x 192 238 against 293 us (2.1 MB), of 512
+//     4:2:2 images of 64 x 64 258 against 295 us.  It is not for smaller batches (64 of these:
+//     139 against 129, 152 against 146, 163 against 103 us).
+//   - A stream of one subsequence is decoded by one lane (a gray image of 16 x 16: 45 against 55 us),
+//     and batches of streams of a few wait for their launches (512 4:2:0 images of 32 x 32: 270 against 288).
+struct StreamCut {
+    uint32_t n = 0, blocks_per_mcu = 0;  // streams that may be cut, and the most blocks in an MCU of theirs
+    uint64_t total = 0, longest = 0, longest_dense = 0;
+    bool short_rows = true;
+
+    static bool denser(const ParsedImage &p, uint32_t row_bytes)
+    {
+        const prep_image_info &I = p.info;
+        const uint32_t limit = stream_density_limit((uint32_t)I.blocks_per_mcu, p.dht_nval[1] < kAnnexKAcSymbols, row_bytes);
+        return I.entropy_bytes * 10 > (uint64_t)I.mcu_cols * (uint64_t)I.mcu_rows * (uint64_t)I.blocks_per_mcu * limit;
+    }
+    static bool may(const ParsedImage &p) { return p.info.restart_interval == 0 && !denser(p, kStreamRowBytes); }
+    void add(const ParsedImage &p)
+    {
+        const prep_image_info &I = p.info;
+        if (I.restart_interval != 0) return;
+        if (!may(p)) {
+            longest_dense = std::max(longest_dense, I.entropy_bytes);
+            return;
+        }
+        n++;
+        blocks_per_mcu = std::max(blocks_per_mcu, (uint32_t)I.blocks_per_mcu);
+        total += I.entropy_bytes;
+        longest = std::max(longest, I.entropy_bytes);
+        if (denser(p, kStreamTinyRowBytes)) short_rows = false;
+    }
+    bool pays() const
+    {
+        if (longest <= (uint64_t)kSubseqBytes || longest <= 4 * longest_dense) return false;
+        if (n >= kStreamFewBytesCall && longest <= kStreamFewBytes) return false;
+        const bool full = n >= stream_full_chip(blocks_per_mcu) ||
+                          (n >= kStreamHalfChip && blocks_per_mcu <= 3 && total > kStreamTinyBytes);
+        return !(full && longest <= (uint64_t)kChunkRaw);
+    }
+    uint32_t row_bytes() const { return short_rows && total <= kStreamTinyBytes ? kStreamTinyRowBytes : kStreamRowBytes; }
+};
+
 // Parse every file and lay the batch out in the workspace.
 int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int32_t n,
                const prep_params *params, Plan *plan)
@@ -323,15 +374,19 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
     h->table_rep.clear();
     std::fill(h->table_hash.begin(), h->table_hash.end(), 0u);
     Plan P;
-    uint64_t entropy_total = 0, unmarked_total = 0;
+    uint64_t entropy_total = 0;
+    StreamCut streams;
     for (int32_t i = 0; i < n; i++) {
         if (offsets[i + 1] < offsets[i]) return PREP_E_INVALID_ARG;
         ParsedImage &pi = h->parsed[(size_t)i];
         parse_image(bits + offsets[i], offsets[i + 1] - offsets[i], &pi);
-        if (pi.info.status == PREP_OK) entropy_total += pi.info.entropy_bytes;
-        if (pi.info.status == PREP_OK && pi.info.restart_interval == 0) unmarked_total += pi.info.entropy_bytes;
+        if (pi.info.status == PREP_OK) {
+            entropy_total += pi.info.entropy_bytes;
+            streams.add(pi);
+        }
     }
-    if (unmarked_total <= kStreamTinyBytes) P.row_bytes = kStreamTinyRowBytes;
+    const bool cut = streams.pays() && !(h->cfg.flags & PREP_FLAG_LARGE_WINDOWS);
+    P.row_bytes = streams.row_bytes();
     // a call with little data is cut into small windows, for the decoder variant that fills
     // the chip with hypotheses instead of walking whole restart intervals lane by lane
     if (entropy_total <= kSmallCallBytes && !(h->cfg.flags & PREP_FLAG_LARGE_WINDOWS))
@@ -363,10 +418,9 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
             R.rgb_pitch = (uint32_t)I.mcu_cols * 8u * hs * 3u;
             for (int t = 0; t < 4; t++) { R.dht_off[t] = pi.dht_off[t]; R.dht_nval[t] = pi.dht_nval[t]; }
             R.table_slot = table_slot_of(h, bits, offsets, i);
-            // Without restart markers the stream is cut into windows that several workgroups decode
-            // side by side.  (A workgroup that has to expand the tables itself spends longer on them
-            // than on a window: such a stream stays with one workgroup, which does so once.)
-            if (I.restart_interval == 0 && R.table_slot != kNoTableSlot && !(h->cfg.flags & PREP_FLAG_LARGE_WINDOWS)) {
+            // (A workgroup that has to expand the tables itself spends longer on them than on a
+            // window: such a stream stays with one workgroup, which does so once.)
+            if (cut && StreamCut::may(pi) && R.table_slot != kNoTableSlot) {
                 const uint32_t step = stream_window_bytes((uint32_t)I.blocks_per_mcu, P.row_bytes);
                 R.n_streams = (uint32_t)std::max<uint64_t>((I.entropy_bytes + step - 1) / step, 1);
             }

@@ -1408,8 +1408,8 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
 //       up among the pass-0 ends of its own row: the equal one is where a node of the next row
 //       begins.  An end state that is none of them (1 to 10 % of the nodes, in dense streams most)
 //       gets an extra node in the next row, one for all that end in it, decoded in a further
-//       pass with the others of its kind.  (Of 24 windows in which most nodes needed one, each with
-//       one of its own needed 200 to 450, which the 128 places did not hold; shared, 20 to 80.)  The last
+//       pass with the others of its kind.  (There are 128 places.  A window of a 4:2:0 stream of 23
+//       bytes per block took 200 to 320 with one for each node, of 19 bytes 36 to 76 shared.)  The last
 //       rows, the overlap, are the first rows of the next window: where a chain of nodes meets
 //       one of the hypotheses there, the next window has the node that goes on from it.  So every
 //       entry (overlap row, hypothesis) leads to an exit of the same form and a count of blocks.

@@ -28,12 +28,18 @@ constexpr uint64_t kSmallCallBytes = 1536 << 10;            // entropy-coded byt
 // at 32 = 375 KB, even at 48 = 562 KB, worse from there on).
 constexpr int kTinyWindowBytes = 512;
 constexpr uint64_t kTinyCallBytes = 448 << 10;
-// Streams without restart markers are cut into windows too, one workgroup each, whatever the
-// size of the call (see resolve_streams in entropy.hip).  A window is decoded in rows, a lane to
+// Streams without restart markers are cut into windows too, one workgroup each, where that pays
+// (StreamCut in api.cpp; the kernels: resolve_streams in entropy.hip).  A window is decoded in rows, a lane to
 // a row and hypothesis; its last rows, the overlap, are the first rows of the next window.
 constexpr int kStreamRowBytes = 68;                         // clean bytes per row: 17 words, so that rows begin in different LDS banks
 constexpr int kStreamTinyRowBytes = 36;                     // the same in calls with little data
-constexpr uint64_t kStreamTinyBytes = 1024 << 10;           // entropy-coded bytes of such streams in a call up to which rows are short
+// Entropy-coded bytes of such streams in a call up to which rows are short.  Short rows make more
+// workgroups, whose lanes have less to do one after the other; once the chip is full, their longer
+// overlaps only add work.  Whole calls, short against long rows, us: photographs of 44 KB 126
+// against 182 (one), 149 against 197 (1.0 MB), 184 against 212 (1.7 MB), 225 against 216 (2.0 MB);
+// full-HD stills of 0.7 MB 170 against 211 (one), 221 against 215 (two).  (Where fewer hypotheses are
+// decoded, 4:2:2 and 4:4:4, the two meet later, at 2.5 and 4.7 MB.)
+constexpr uint64_t kStreamTinyBytes = 1024 << 10;
 // Overlap rows.  A decoder that comes out of a window agrees with none of the hypotheses of an
 // overlap row with a probability that falls with the row's length: full-HD stills of quality 95,
 // the slowest seen, 10 % for rows of 36 bytes and 1 % for rows of 68 (photographs of quality 90:
@@ -41,6 +47,30 @@ constexpr uint64_t kStreamTinyBytes = 1024 << 10;           // entropy-coded byt
 constexpr int kStreamMaxOverlap = 7;
 inline constexpr uint32_t stream_overlap(uint32_t row_bytes) { return row_bytes == (uint32_t)kStreamTinyRowBytes ? 7 : 4; }
 constexpr int kStreamMaxRows = 85;                          // rows per window: 256 lanes over the hypotheses, at most this many
+// Streams with more bytes per block than this (in tenths; b = blocks per MCU) are not cut.  The
+// longer the blocks, the longer a decoder runs before it falls into step with a hypothesis, and
+// beyond these densities too many chains come through an overlap without: the image is then
+// decoded twice, which costs 2 to 8 % for one image and a quarter for a batch.  Codes made for the
+// image (own; an AC table that leaves symbols out) are nearer to its statistics and take longer to
+// fall into step than the codes of T.81 Annex K do.  Measured on 8 000 images of noise and of shapes, qualities 90 to
+// 97, each with short and with long rows: up to the limits all windows were joined in 99 % of those of
+// 256 x 256 and 98 % of those of 512 x 384, in the next two bytes in 97 and 90 % (Annex K, long rows) to
+// none (own, short); of those of 1600 x 1200 near the limits in 80 %, which decode 100 times faster
+// then.  Photographs of quality 90 have 6 to 12 bytes, stills of quality 95 15 to 18, noise of 8
+// levels at quality 95 19 (gray 24), with own codes 18 (22).
+inline constexpr uint32_t stream_density_limit(uint32_t b, bool own, uint32_t row_bytes)
+{
+    const bool short_rows = row_bytes == (uint32_t)kStreamTinyRowBytes;
+    if (own) return short_rows ? (b == 1 ? 240 : 175) : (b == 1 ? 260 : 210);
+    return short_rows ? (b == 1 ? 260 : 230) : (b == 1 ? 280 : 245);
+}
+constexpr uint32_t kAnnexKAcSymbols = 162;                  // symbols of an AC table that leaves none out
+// Streams of one chunk (kChunkRaw) that are many enough to occupy the chip with a workgroup each
+// settle there in few rounds, unless an MCU has six blocks; see StreamCut in api.cpp.
+inline constexpr uint32_t stream_full_chip(uint32_t b) { return b <= 3 ? 192 : b == 4 ? 384 : 0xFFFFFFFFu; }
+constexpr uint32_t kStreamHalfChip = 128;                   // the same for b <= 3 where the call is past kStreamTinyBytes
+constexpr uint32_t kStreamFewBytesCall = 256;               // the same for any b where no stream is longer than
+constexpr uint64_t kStreamFewBytes = 512;                   // a few subsequences
 inline constexpr uint32_t stream_rows(uint32_t blocks_per_mcu)
 {
     return kDecodeThreads / blocks_per_mcu < (uint32_t)kStreamMaxRows ? kDecodeThreads / blocks_per_mcu : (uint32_t)kStreamMaxRows;

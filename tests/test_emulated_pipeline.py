@@ -226,3 +226,18 @@ def test_dense_streams_are_joined_too():
     for i, s in enumerate(streams):
         assert per[i][0] == 0 and np.array_equal(per[i][1], oracle.decode(s)[0]), f"image {i}"
     assert emul.streams_decoded == [1, 1, 1, 1]
+
+
+def test_streams_that_windows_would_slow_down_are_not_cut():
+    # noise at quality 100, whose windows could not be joined; it also keeps the call's other
+    # streams whole unless it is less than a quarter as long as the longest of them; and a stream
+    # that a single lane decodes
+    dense = oracle.encode(_img(6, 96, 80, 25.0), 100, MODE_420, 0)[0]
+    small_dense = oracle.encode(_img(6, 24, 24, 25.0), 100, MODE_GRAY, 0, table_mode=1)[0]
+    sparse = oracle.encode(_img(7, 192, 160, 8.0), 85, MODE_420, 0)[0]
+    tiny = oracle.encode(_img(8, 8, 8), 50, MODE_GRAY, 0)[0]
+    for streams, want in (([dense], [0]), ([sparse, dense], [0, 0]), ([sparse, small_dense, tiny], [1, 0, 1]), ([tiny], [0])):
+        per, _ = emul.run(streams, 0, 1, 1, "f32", MEAN, STD)
+        assert emul.streams_decoded == want
+        for i, s in enumerate(streams):
+            assert per[i][0] == 0 and np.array_equal(per[i][1], oracle.decode(s)[0]), f"image {i}"

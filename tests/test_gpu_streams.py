@@ -7,6 +7,7 @@ import oracle
 import synth
 from helpers import check_against_oracle, run_gpu
 from oracle import MODE_420, MODE_422, MODE_440, MODE_444, MODE_GRAY
+from paper_2411_19114_amd import STREAM_UNJOINED, STREAM_WHOLE, STREAM_WINDOWS
 
 pytestmark = pytest.mark.gpu
 MODES = [MODE_444, MODE_420, MODE_GRAY, MODE_422, MODE_440]
@@ -21,6 +22,11 @@ def pp():
     h.close()
 
 
+def _decoded(pp, n):
+    """How the last call decoded its n streams, without repetitions."""
+    return {pp.debug_last_stream(i) for i in range(n)}
+
+
 def _file(seed, w, h, quality, mode, sigma=12.0, table_mode=0):
     rgb = synth.gradient_noise_image(np.random.default_rng(seed), w, h, sigma)
     return oracle.encode(rgb, quality, mode, 0, table_mode=table_mode)[0]
@@ -29,33 +35,78 @@ def _file(seed, w, h, quality, mode, sigma=12.0, table_mode=0):
 @pytest.mark.parametrize("mode", MODES)
 def test_one_window_to_many_with_short_rows(pp, mode):
     # 30 bytes to 60 KB of data each: no full row, a window's edge, an overlap that the data end in
-    files = [_file(10 * mode + k, w, h, q, mode, table_mode=k % 2)
+    files = [_file(10 * mode + k, w, h, q, mode, sigma=6.0, table_mode=k % 2)
              for k, (w, h, q) in enumerate([(8, 8, 50), (33, 17, 60), (64, 64, 75), (96, 80, 85), (131, 117, 90),
-                                            (200, 160, 95), (255, 199, 50), (320, 240, 100)])]
+                                            (200, 160, 92), (255, 199, 50), (640, 480, 90)])]
     assert sum(map(len, files)) < 1 << 20
     check_against_oracle(pp, files, 0, 1, 1, "f32")
+    assert _decoded(pp, len(files)) == {STREAM_WINDOWS}
 
 
 @pytest.mark.parametrize("mode", MODES)
 def test_many_windows_with_long_rows(pp, mode):
-    # more than 1 MiB of data in the call; quality 100 falls into step most slowly
-    files = [_file(20 * mode + k, 700, 640, 100, mode) for k in range(2)]
+    # more than 1 MiB of data in the call
+    files = [_file(20 * mode + k, 1000, 900, 94, mode, sigma=7.0) for k in range(2)]
     files += [_file(20 * mode + 9 + k, 40 + 37 * k, 300 - 23 * k, 60 + 4 * k, mode) for k in range(8)]
     while sum(map(len, files)) < (1 << 20) + 4096:
         files.append(files[0])
     check_against_oracle(pp, files, 0, 1, 1, "f32")
+    assert _decoded(pp, len(files)) == {STREAM_WINDOWS}
+
+
+@pytest.mark.parametrize("sigma,table_mode", [(9.0, 0), (9.0, 1), (30.0, 0)])
+@pytest.mark.parametrize("mode", MODES)
+def test_dense_streams(pp, mode, sigma, table_mode):
+    # noise near the densities up to which streams are cut, where most rows need extra nodes, and
+    # far beyond, where one workgroup takes each
+    files = [_file(30 * mode + k, 200 + 40 * k, 160, 95, mode, sigma, table_mode) for k in range(4)]
+    check_against_oracle(pp, files, 0, 1, 1, "f32")
+    assert _decoded(pp, len(files)) <= ({STREAM_WHOLE} if sigma > 20 else {STREAM_WHOLE, STREAM_WINDOWS})
+
+
+def test_an_image_of_many_chain_tiles():
+    # 2400 x 2000: more than 128 windows several times over, and a tile that is not full
+    import paper_2411_19114_amd as prep
+    f = _file(40, 2400, 2000, 92, MODE_420, sigma=7.0)
+    assert len(f) > 3 * 128 * 2584
+    with_one = prep.Preprocessor(device=0, max_batch=1, max_width=2400, max_height=2000, max_bitstream_bytes=len(f))
+    try:
+        check_against_oracle(with_one, [f], 0, 64, 64, "f32")
+        assert _decoded(with_one, 1) == {STREAM_WINDOWS}
+    finally:
+        with_one.close()
+
+
+@pytest.mark.parametrize("mode,n,w,h,quality,how", [
+    (MODE_GRAY, 191, 40, 40, 80, STREAM_WINDOWS), (MODE_GRAY, 192, 40, 40, 80, STREAM_WHOLE),
+    (MODE_444, 192, 40, 40, 80, STREAM_WHOLE), (MODE_422, 383, 80, 80, 80, STREAM_WINDOWS),
+    (MODE_440, 384, 80, 80, 80, STREAM_WHOLE), (MODE_420, 256, 96, 80, 85, STREAM_WINDOWS),
+    (MODE_420, 256, 16, 16, 60, STREAM_WHOLE), (MODE_GRAY, 192, 256, 224, 92, STREAM_WINDOWS)])
+def test_batches_on_either_side_of_the_rules(mode, n, w, h, quality, how):
+    # many streams of one chunk take a workgroup each; from one chunk (the last case) on they do not
+    import paper_2411_19114_amd as prep
+    files = [_file(50 + k, w - k % 3, h, quality, mode) for k in range(16)]
+    files = (files * (n // 16 + 1))[:n]
+    many = prep.Preprocessor(device=0, max_batch=n, max_width=w, max_height=h, max_bitstream_bytes=sum(map(len, files)))
+    try:
+        check_against_oracle(many, files, 0, 1, 1, "f16")
+        assert _decoded(many, n) == {how}
+    finally:
+        many.close()
 
 
 def test_every_length_across_a_window_edge(pp):
     # heights that move the end of the data by some tens of bytes over a window's 1260 and an overlap's 252
     files = [_file(7, 64, 16 * k, 88, MODE_420) for k in range(1, 33)]
     check_against_oracle(pp, files, 0, 1, 1, "f32")
+    assert _decoded(pp, len(files)) == {STREAM_WINDOWS}
 
 
 def test_streams_with_and_without_markers_in_one_batch(pp):
     rgb = synth.gradient_noise_image(np.random.default_rng(3), 300, 251, 12.0)
     files = [oracle.encode(rgb, 88, m, dri)[0] for m in MODES for dri in (0, 5, 0, 200)]
     check_against_oracle(pp, files, 0, 1, 1, "f16")
+    assert [pp.debug_last_stream(i) for i in range(4)] == [STREAM_WINDOWS, STREAM_WHOLE, STREAM_WINDOWS, STREAM_WHOLE]
 
 
 def test_markers_and_damage_inside_the_data(pp):
@@ -70,6 +121,8 @@ def test_markers_and_damage_inside_the_data(pp):
     left = good[:-2] + b"\x55\x55\x55" + b"\xff\xd9"
     status, tensor = run_gpu(pp, [good, marker, cut, good, left, good], 0, 64, 64, "f32")
     assert [s == 0 for s in status] == [True, False, False, True, False, True], status
+    assert [pp.debug_last_stream(i) for i in range(6)] == [STREAM_WINDOWS, STREAM_UNJOINED, STREAM_UNJOINED,
+                                                           STREAM_WINDOWS, STREAM_UNJOINED, STREAM_WINDOWS]
     coef = oracle.decode(good)[0]
     for i in (0, 3, 5):
         assert np.array_equal(pp.debug_last_coefficients(i, coef.shape[0]), coef)
