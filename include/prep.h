@@ -108,7 +108,11 @@ enum { PREP_SAMPLING_444 = 0, PREP_SAMPLING_420 = 1, PREP_SAMPLING_GRAY = 2, PRE
 
 typedef struct prep_handle prep_handle;
 
-/* Capacity of a handle; all device and pinned host memory is reserved here. */
+/* Capacity of a handle; all device and pinned host memory is reserved here.  The
+ * windows of images without restart markers take 4/3 of max_bitstream_bytes of
+ * device memory among it (up to 8/3 below 1 MiB, and 4 KB per image of max_batch); none with
+ * PREP_FLAG_LARGE_WINDOWS or PREP_FLAG_TABLES_PER_WORKGROUP.  Where that much is not left the
+ * handle is created without, and decodes such images with one workgroup each.   */
 typedef struct {
     int32_t device;               /* HIP device ordinal                              */
     int32_t max_batch;            /* largest n of one call                           */

@@ -385,7 +385,7 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
             streams.add(pi);
         }
     }
-    const bool cut = streams.pays() && !(h->cfg.flags & PREP_FLAG_LARGE_WINDOWS);
+    const bool cut = h->cap_streams != 0 && streams.pays();
     P.row_bytes = streams.row_bytes();
     // a call with little data is cut into small windows, for the decoder variant that fills
     // the chip with hypotheses instead of walking whole restart intervals lane by lane
@@ -634,9 +634,11 @@ int prep_create(prep_handle **out, const prep_config *cfg)
     h->cap_windows = std::max<uint64_t>(cfg->max_bitstream_bytes / kWindowBytes,
                                         std::max<uint64_t>(std::min<uint64_t>(cfg->max_bitstream_bytes, kSmallCallBytes) / kSmallWindowBytes,
                                                            std::min<uint64_t>(cfg->max_bitstream_bytes, kTinyCallBytes) / kTinyWindowBytes)) + n + 1;
-    // (the shortest stream windows are those of six blocks per MCU; an image ends with a partial one)
-    h->cap_streams = std::max<uint64_t>(cfg->max_bitstream_bytes / stream_window_bytes(6, kStreamRowBytes),
-                                        std::min<uint64_t>(cfg->max_bitstream_bytes, kStreamTinyBytes) / stream_window_bytes(6, kStreamTinyRowBytes)) + n + 1;
+    // (the shortest stream windows are those of six blocks per MCU; an image ends with a partial one;
+    // a handle whose streams are never cut needs none)
+    if (!(cfg->flags & (PREP_FLAG_LARGE_WINDOWS | PREP_FLAG_TABLES_PER_WORKGROUP)))
+        h->cap_streams = std::max<uint64_t>(cfg->max_bitstream_bytes / stream_window_bytes(6, kStreamRowBytes),
+                                            std::min<uint64_t>(cfg->max_bitstream_bytes, kStreamTinyBytes) / stream_window_bytes(6, kStreamTinyRowBytes)) + n + 1;
     h->cap_bits = cfg->max_bitstream_bytes + kBitsPad;
     // (the kernels index the workspace and its side array with 32-bit element offsets)
     if (h->cap_blocks * 65 > 0xFFFFFFFFull) { delete h; return PREP_E_TOO_LARGE; }
@@ -657,7 +659,6 @@ int prep_create(prep_handle **out, const prep_config *cfg)
     ok = ok && hipMalloc((void **)&h->d_win_count, sizeof(uint32_t) * h->cap_windows) == hipSuccess;
     ok = ok && hipMalloc((void **)&h->d_win_first, sizeof(uint32_t) * h->cap_windows) == hipSuccess;
     ok = ok && hipMalloc((void **)&h->d_retry, sizeof(uint32_t) * n) == hipSuccess;
-    ok = ok && hipMalloc((void **)&h->d_streams, sizeof(StreamWindow) * h->cap_streams) == hipSuccess;
     for (int i = 0; ok && i < kSlots; i++) {
         Slot &s = h->slot[i];
         ok = ok && hipHostMalloc((void **)&s.h_bits, h->cap_bits, hipHostMallocDefault) == hipSuccess;
@@ -671,6 +672,12 @@ int prep_create(prep_handle **out, const prep_config *cfg)
     h->ev.assign((size_t)kTimedCalls * 5, nullptr);
     for (size_t i = 0; ok && i < h->ev.size(); i++) ok = hipEventCreate(&h->ev[i]) == hipSuccess;
     if (ok) ok = hipMemset(h->d_status, 0, sizeof(int32_t) * n) == hipSuccess;
+    // Last, as a handle can do without: it then decodes every stream without restart markers whole.
+    if (ok && h->cap_streams && hipMalloc((void **)&h->d_streams, sizeof(StreamWindow) * h->cap_streams) != hipSuccess) {
+        (void)hipGetLastError();
+        h->d_streams = nullptr;
+        h->cap_streams = 0;
+    }
     if (!ok) {
         (void)hipGetLastError();
         prep_destroy(h);

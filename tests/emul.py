@@ -13,6 +13,7 @@ EMU = os.path.join(ROOT, "tests", "hip_emulation")
 CSRC = os.path.join(ROOT, "paper_2411_19114_amd", "csrc")
 BINARY = os.environ.get("PREP_EMUL_BIN", os.path.join(EMU, "prep_emul"))
 streams_decoded = []  # of the last run: how each image's stream was decoded (PREP_STREAM_*)
+device_bytes = []     # of the last run: [device memory that the handle took]
 KERNELS = ["entropy.hip", "reconstruct.hip", "resize.hip", "api.cpp", "parser.cpp"]
 
 
@@ -54,6 +55,7 @@ def run(streams, resize_short, crop_h, crop_w, out_dtype, mean, std, timeout=600
             print(r.stderr[-6000:])
         if r.returncode != 0:
             raise RuntimeError(f"prep_emul exit {r.returncode}\n{r.stderr[-4000:]}")
+        device_bytes[:] = [int(line.split()[2]) for line in r.stderr.splitlines() if line.startswith("device bytes")]
         blob = open(fout, "rb").read()
     pos = 0
     per_image = []

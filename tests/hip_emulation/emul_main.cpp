@@ -8,6 +8,8 @@
 #include <cstdlib>
 #include <vector>
 
+#include <hip/hip_runtime.h>
+
 #include "../../include/prep.h"
 
 static void die(const char *what, int rc)
@@ -95,5 +97,6 @@ int main(int argc, char **argv)
     for (size_t k = out.size() - 16; k < out.size(); k++)
         if (out[k] != 0xAB) { fprintf(stderr, "prep_emul: wrote past the output tensor\n"); return 3; }
     prep_destroy(h);
+    fprintf(stderr, "device bytes %zu\n", hip_emul::device_bytes);
     return 0;
 }

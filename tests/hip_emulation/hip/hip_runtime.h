@@ -243,9 +243,21 @@ inline hipError_t hipGetDeviceCount(int *n) { *n = 1; return hipSuccess; }
 inline hipError_t hipSetDevice(int) { return hipSuccess; }
 inline hipError_t hipGetLastError() { return hipSuccess; }
 inline hipError_t hipDeviceSynchronize() { return hipSuccess; }
-inline hipError_t hipMalloc(void **p, size_t n) { *p = malloc(n ? n : 1); return *p ? hipSuccess : hipErrorUnknown; }
+namespace hip_emul {
+inline size_t device_bytes = 0;  // asked for and granted (freeing is not counted)
+}
+// PREP_EMUL_DEVICE_BYTES: all that hipMalloc grants
+inline hipError_t hipMalloc(void **p, size_t n)
+{
+    const char *most = getenv("PREP_EMUL_DEVICE_BYTES");
+    *p = nullptr;
+    if (most && hip_emul::device_bytes + n > strtoull(most, nullptr, 10)) return hipErrorUnknown;
+    hip_emul::device_bytes += n;
+    *p = malloc(n ? n : 1);
+    return *p ? hipSuccess : hipErrorUnknown;
+}
 inline hipError_t hipFree(void *p) { free(p); return hipSuccess; }
-inline hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return hipMalloc(p, n); }
+inline hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = malloc(n ? n : 1); return *p ? hipSuccess : hipErrorUnknown; }
 inline hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
 inline hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
 inline hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }

@@ -241,3 +241,24 @@ def test_streams_that_windows_would_slow_down_are_not_cut():
         assert emul.streams_decoded == want
         for i, s in enumerate(streams):
             assert per[i][0] == 0 and np.array_equal(per[i][1], oracle.decode(s)[0]), f"image {i}"
+
+
+def test_a_handle_without_memory_for_windows(monkeypatch):
+    # what the windows need is not taken by a handle that never cuts a stream, and a handle that
+    # does not get it decodes such streams whole
+    streams = [oracle.encode(_img(95, 112, 96), 85, MODE_420, 0)[0], oracle.encode(_img(96, 64, 48), 85, MODE_420, 2)[0]]
+    emul.run(streams, 32, 24, 24, "f32", MEAN, STD)
+    assert emul.streams_decoded == [1, 0]
+    whole = emul.device_bytes[0]
+    for flags in (8, 1):
+        emul.run(streams, 32, 24, 24, "f32", MEAN, STD, flags=flags)
+        assert emul.streams_decoded == [0, 0]
+        if flags == 8:
+            without = emul.device_bytes[0]
+    assert without < whole
+    monkeypatch.setenv("PREP_EMUL_DEVICE_BYTES", str(without))
+    _check(streams, 32, 24, 24, "f32")
+    assert emul.streams_decoded == [0, 0]
+    monkeypatch.setenv("PREP_EMUL_DEVICE_BYTES", str(without - 1))
+    with pytest.raises(RuntimeError, match="out of memory"):
+        emul.run(streams, 32, 24, 24, "f32", MEAN, STD)
