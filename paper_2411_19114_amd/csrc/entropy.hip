@@ -1446,7 +1446,7 @@ static_assert(stream_rows(1) <= stream_rows(3) && stream_rows(4) <= stream_rows(
               "4:4:4 has the largest windows");
 
 static_assert(kStreamWords * 32 < (1 << (kStateBits - 9)) && kStreamMaxRows < (1 << (32 - kStateBits)) && kStreamExtras == 128,
-              "a state and its row fit a key, and seven bits index the table");
+              "a state and its row fit a key, and the table's size wraps by a mask");
 
 struct StreamShared {
     uint32_t clean[kStreamWords];    // the window's bytes without stuffing, big-endian packed
@@ -1644,6 +1644,18 @@ __device__ inline int image_of_stream(const ImageRec *recs, int n_images, uint32
     return find_image(n_images, wg, [&](int i) { return recs[i].stream0; });
 }
 
+// The extra node of key (see kStateBits), made if there is none yet; x = where to look first.  Out of
+// line: inlined, it cost resolve_streams 3 % in calls that need few.
+__device__ __attribute__((noinline)) uint32_t extra_node(uint32_t *keys, uint32_t *n_extra, uint32_t key, uint32_t x)
+{
+    for (int probe = 0; probe < kExtraProbes; probe++, x = (x + 1u) & (uint32_t)(kStreamExtras - 1)) {
+        const uint32_t was = atomicCAS(&keys[x], kNoKey, key);
+        if (was == kNoKey) atomicAdd(n_extra, 1u);
+        if (was == kNoKey || was == key) return (uint32_t)kT + x;
+    }
+    return kNodeNoWay;
+}
+
 }  // namespace
 
 __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
@@ -1656,6 +1668,7 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
     __shared__ uint32_t node_end[kStreamNodes];
     __shared__ uint16_t node_blocks[kStreamNodes], node_next[kStreamNodes];
     __shared__ uint32_t extra_key[kStreamExtras];  // extra nodes: row << 25 | state in which it begins, or kNoKey
+    __shared__ uint32_t n_extra;
     const int tid = threadIdx.x;
     const uint32_t wg = blockIdx.x;
     const int img = image_of_stream(recs, n_images, wg);
@@ -1675,6 +1688,7 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
     }
     load_tables(S.tab, tables, R.table_slot);
     if (tid < kStreamExtras) extra_key[tid] = kNoKey;
+    if (tid == 0) n_extra = 0;
     const StreamPart part = stage_stream(S, bits + R.file_off + R.entropy_rel, data_len, w, step, row_bytes);
     if (part.marker && tid == 0) retry[img] = 1;
     const StreamRows rows(part, row_bytes);
@@ -1701,15 +1715,7 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
         } else {
             // (nodes that begin alike are one: all decoders that are in step come here in the same
             // state where no hypothesis of the row has fallen into step by its end)
-            const uint32_t key = ((r + 1u) << kStateBits) | s;
-            uint32_t x = (s * 0x9E3779B1u) >> 25;
-            for (int probe = 0; probe < kExtraProbes; probe++, x = (x + 1u) & (uint32_t)(kStreamExtras - 1)) {
-                const uint32_t was = atomicCAS(&extra_key[x], kNoKey, key);
-                if (was == kNoKey || was == key) {
-                    to = (uint32_t)kT + x;
-                    break;
-                }
-            }
+            to = extra_node(extra_key, &n_extra, ((r + 1u) << kStateBits) | s, (s * 0x9E3779B1u) >> 26);
         }
         node_next[id] = (uint16_t)to;
     };
@@ -1736,20 +1742,22 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
     __syncthreads();
     // the extra nodes, a lane each, a generation at a time (a generation's are at least one row further)
     static_assert(kStreamExtras <= kT, "a lane per extra node");
-    bool done = false;
+    bool mine_done = false;
+    uint32_t done = 0;
     for (uint32_t round = 0; round < (uint32_t)kStreamMaxRows; round++) {
-        const uint32_t key = tid < kStreamExtras ? extra_key[tid] : kNoKey;
-        const bool fresh = key != kNoKey && !done;
-        if (!__syncthreads_or(fresh)) break;
-        if (fresh) {
+        const uint32_t have = n_extra, key = tid < kStreamExtras ? extra_key[tid] : kNoKey;
+        __syncthreads();
+        if (done == have) break;
+        if (key != kNoKey && !mine_done) {
             const uint32_t from = key & ((1u << kStateBits) - 1u), r = key >> kStateBits;
             uint32_t to = from, n = 0;
             if ((from >> 9) < rows.end(r)) to = decode_row<false>(S, g, from, rows.end(r), rows.limit_bits, &n, nullptr);
             node_end[kT + tid] = to;
             node_blocks[kT + tid] = (uint16_t)n;
             link((uint32_t)(kT + tid), r, to);
-            done = true;
+            mine_done = true;
         }
+        done = have;
         __syncthreads();
     }
     for (uint32_t i = (uint32_t)tid; i < (uint32_t)kStreamNodes; i += kT) {
@@ -1866,10 +1874,10 @@ __global__ __launch_bounds__(kDecodeThreads) void chain_streams(
         __syncthreads();
     }
     // the chain has to reach the end of the data with all of the image's blocks
-    if (tid == 0) {
-        const bool linked = s_entry == kToEnd && s_block == R.n_blocks;
-        W[0].linked = linked;
-        if (!linked) retry[blockIdx.x] = 1;
+    // (all lanes have come here past the last barrier: they see the same)
+    if (s_entry != kToEnd || s_block != R.n_blocks) {
+        for (uint32_t i = (uint32_t)tid; i < n; i += kT) W[i].entry = kNoWay;
+        if (tid == 0) retry[blockIdx.x] = 1;
     }
 }
 
@@ -1894,7 +1902,7 @@ __global__ __launch_bounds__(kDecodeThreads) void write_streams(
     // out only now and set retry[img]: that is for the next kernels to read.  Here the waves of this
     // workgroup would read it at different times, and some would leave where others go on to
     // the barriers; what chain_streams wrote is the same for all of them.
-    if (!windows[R.stream0].linked || entry >= stream_overlap(row_bytes) * H) {
+    if (entry >= stream_overlap(row_bytes) * H) {
         if (tid == 0) {
             W.dc_lo = W.dc_hi = 0;
             W.dc_sum[0] = W.dc_sum[1] = W.dc_sum[2] = 0;

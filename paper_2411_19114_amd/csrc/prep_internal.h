@@ -95,7 +95,7 @@ struct StreamWindow {
     uint32_t block;                    // block of the image that is under way or next there
     uint32_t dc_lo, dc_hi;             // blocks whose DC difference was decoded in this window
     int32_t dc_sum[3];                 // sums of these differences per component
-    uint32_t linked;                   // in an image's first window: its chain holds together
+    uint32_t pad_;
 };
 constexpr int kLutBits = 10;                                // first-level Huffman lookup width
 // Images of a batch mostly share their Huffman tables (encoders write the tables of T.81
