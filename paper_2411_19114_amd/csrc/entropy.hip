@@ -2,7 +2,8 @@
 //
 // The first half of the "Decode" functional unit (PREBA section 4.2, Table 1).
 // The FPGA decodes one stream serially per compute unit; here one workgroup owns
-// a run of whole restart intervals (T.81 E.2.4) of one image:
+// a run of whole restart intervals (T.81 E.2.4) of one image, or a window of a stream
+// that has none:
 //
 //   1. scan_restart_markers counts the RSTn markers in fixed windows of every
 //      image's entropy-coded segment, so that a workgroup starting at the first
@@ -22,7 +23,11 @@
 //        and a segmented scan turns DC differences into absolute values.
 //      - calls with little data (small windows, kHyp): the states at the subsequence
 //        borders inside restart intervals are found by phase hypotheses in two passes
-//        (resolve_by_hypotheses) instead of by iteration, then written as above.
+//        (the by_hypotheses branch) instead of by iteration, then written as above.
+//   3. Streams without restart markers are mostly cut into windows that several workgroups decode
+//      side by side (resolve_streams and the kernels after it, which run on either side of
+//      decode_entropy).  decode_entropy iterates over those that are not (StreamCut in api.cpp) or
+//      whose windows cannot be joined.
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -1423,11 +1428,11 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
 //
 // The work is 2 H + 1 decodes of every byte (H = blocks per MCU) against about ten by iteration
 // over 4:2:0, but none waits for another for longer than a row.  Whole calls, one workgroup per
-// image against windows: a 44 KB photograph 1068 -> 132 us, a 760 KB full-HD still 14 100 -> 199 us,
-// 128 photographs (5 MB) 1901 -> 461 us, 512 thumbnails of 4:4:4, 4:2:0 and gray (5.6 MB)
-// 1156 -> 465 us; no size was slower.  resolve_streams and write_streams are bound by a lane's
-// dependent symbols (about 0.1 us each when the chip is idle) and, where the chip is full, by
-// instruction issue: 167 and 108 us of the thumbnails' 465.
+// image against windows: a 44 KB photograph 1099 -> 132 us, a 760 KB full-HD still 14 639 -> 175 us,
+// 128 photographs (5 MB) 1879 -> 455 us, 512 thumbnails of 4:4:4, 4:2:0 and gray (5.6 MB)
+// 1062 -> 443 us.  Where windows do not pay, api.cpp does not cut (StreamCut).  resolve_streams and
+// write_streams are bound by a lane's dependent symbols (about 0.1 us each when the chip is idle)
+// and, where the chip is full, by instruction issue: 182 and 94 us of the 128 photographs' 455.
 
 namespace {
 

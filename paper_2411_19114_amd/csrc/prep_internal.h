@@ -29,8 +29,8 @@ constexpr uint64_t kSmallCallBytes = 1536 << 10;            // entropy-coded byt
 constexpr int kTinyWindowBytes = 512;
 constexpr uint64_t kTinyCallBytes = 448 << 10;
 // Streams without restart markers are cut into windows too, one workgroup each, where that pays
-// (StreamCut in api.cpp; the kernels: resolve_streams in entropy.hip).  A window is decoded in rows, a lane to
-// a row and hypothesis; its last rows, the overlap, are the first rows of the next window.
+// (StreamCut in api.cpp; the kernels: resolve_streams in entropy.hip).  A window is decoded in rows,
+// a lane to a row and hypothesis; its last rows, the overlap, are the first rows of the next window.
 constexpr int kStreamRowBytes = 68;                         // clean bytes per row: 17 words, so that rows begin in different LDS banks
 constexpr int kStreamTinyRowBytes = 36;                     // the same in calls with little data
 // Entropy-coded bytes of such streams in a call up to which rows are short.  Short rows make more
@@ -38,12 +38,14 @@ constexpr int kStreamTinyRowBytes = 36;                     // the same in calls
 // overlaps only add work.  Whole calls, short against long rows, us: photographs of 44 KB 126
 // against 182 (one), 149 against 197 (1.0 MB), 184 against 212 (1.7 MB), 225 against 216 (2.0 MB);
 // full-HD stills of 0.7 MB 170 against 211 (one), 221 against 215 (two).  (Where fewer hypotheses are
-// decoded, 4:2:2 and 4:4:4, the two meet later, at 2.5 and 4.7 MB.)
+// decoded, 4:2:2 and 4:4:4, the two meet later, at 2.5 and 4.7 MB: the line is below all of these.)
 constexpr uint64_t kStreamTinyBytes = 1024 << 10;
 // Overlap rows.  A decoder that comes out of a window agrees with none of the hypotheses of an
 // overlap row with a probability that falls with the row's length: full-HD stills of quality 95,
 // the slowest seen, 10 % for rows of 36 bytes and 1 % for rows of 68 (photographs of quality 90:
-// 3 and 1 %).  About 250 bytes leave one in 10^7 windows without a way on.
+// 3 and 1 %).  About 250 bytes leave one in 10^7 windows without a way on, if rows were
+// independent of one another; counted, the sparsest streams that failed had 20 bytes per block and
+// lost one window in 500 (see stream_density_limit).
 constexpr int kStreamMaxOverlap = 7;
 inline constexpr uint32_t stream_overlap(uint32_t row_bytes) { return row_bytes == (uint32_t)kStreamTinyRowBytes ? 7 : 4; }
 constexpr int kStreamMaxRows = 85;                          // rows per window: 256 lanes over the hypotheses, at most this many
@@ -52,12 +54,11 @@ constexpr int kStreamMaxRows = 85;                          // rows per window: 
 // beyond these densities too many chains come through an overlap without: the image is then
 // decoded twice, which costs 2 to 8 % for one image and a quarter for a batch.  Codes made for the
 // image (own; an AC table that leaves symbols out) are nearer to its statistics and take longer to
-// fall into step than the codes of T.81 Annex K do.  Measured on 8 000 images of noise and of shapes, qualities 90 to
-// 97, each with short and with long rows: up to the limits all windows were joined in 99 % of those of
-// 256 x 256 and 98 % of those of 512 x 384, in the next two bytes in 97 and 90 % (Annex K, long rows) to
-// none (own, short); of those of 1600 x 1200 near the limits in 80 %, which decode 100 times faster
-// then.  Photographs of quality 90 have 6 to 12 bytes, stills of quality 95 15 to 18, noise of 8
-// levels at quality 95 19 (gray 24), with own codes 18 (22).
+// fall into step than the codes of T.81 Annex K do.  Of 9 700 images of noise and of shapes, qualities
+// 90 to 97, each with short and with long rows, all windows were joined: up to the limits in 99.7 % of
+// those of 256 x 256, 99 % of 512 x 384 and 93 % of 1600 x 1200 (which decode 100 times faster then), in
+// the next two bytes in 94, 85 and 40 %.  Photographs of quality 90 have 6 to 12 bytes, stills of
+// quality 95 15 to 18, noise of 8 levels at quality 95 19 (gray 24), with own codes 18 (22).
 inline constexpr uint32_t stream_density_limit(uint32_t b, bool own, uint32_t row_bytes)
 {
     const bool short_rows = row_bytes == (uint32_t)kStreamTinyRowBytes;
