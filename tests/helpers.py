@@ -130,14 +130,19 @@ DAMAGE_BASES = [(96, 64, oracle.MODE_420, 2, 85), (96, 64, oracle.MODE_420, 0, 9
                 (320, 240, oracle.MODE_420, 0, 96)]
 
 
-def damaged_streams(seed, per_base, n_bases=len(DAMAGE_BASES)):
+# streams without markers, sparse enough to be cut into windows (one to eleven of them)
+WINDOW_BASES = [(96, 64, oracle.MODE_420, 0, 85), (112, 96, oracle.MODE_420, 0, 88), (160, 120, oracle.MODE_444, 0, 85),
+                (160, 128, oracle.MODE_GRAY, 0, 88), (120, 112, oracle.MODE_422, 0, 85), (240, 200, oracle.MODE_420, 0, 88)]
+
+
+def damaged_streams(seed, per_base, n_bases=None, bases=DAMAGE_BASES):
     """Sound oracle-encoded files whose entropy-coded segment is then damaged at random: bit
     flips, inserted marker bytes, deleted runs, garbage runs, truncation, runs of FF, restart
     markers with a wrong number or two of them swapped.
     Headers stay intact, so every file reaches the decoder kernels."""
     rng = np.random.default_rng(seed)
     out = []
-    for k, (w, h, mode, dri, q) in enumerate(DAMAGE_BASES[:n_bases]):
+    for k, (w, h, mode, dri, q) in enumerate(bases[:n_bases]):
         rgb = synth.gradient_noise_image(np.random.default_rng(50 + k), w, h, 14.0)
         b = oracle.encode(rgb, q, mode, dri, table_mode=k % 2)[0]
         sos = b.index(b"\xff\xda")

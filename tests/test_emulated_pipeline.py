@@ -262,3 +262,10 @@ def test_a_handle_without_memory_for_windows(monkeypatch):
     monkeypatch.setenv("PREP_EMUL_DEVICE_BYTES", str(without - 1))
     with pytest.raises(RuntimeError, match="out of memory"):
         emul.run(streams, 32, 24, 24, "f32", MEAN, STD)
+
+
+def test_damage_in_streams_that_are_cut():
+    streams = helpers.damaged_streams(21, 3, n_bases=5, bases=helpers.WINDOW_BASES)
+    per, ten = emul.run(streams, 32, 24, 24, "f32", MEAN, STD, timeout=3000)
+    helpers.check_damaged(streams, [p[0] for p in per], lambda i, nb: per[i][1], ten)
+    assert set(emul.streams_decoded) == {1, 2}

@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 import synth
-from helpers import check_against_oracle, run_gpu
+from helpers import WINDOW_BASES, check_against_oracle, check_damaged, damaged_streams, run_gpu
 from oracle import MODE_420, MODE_422, MODE_440, MODE_444, MODE_GRAY
 from paper_2411_19114_amd import STREAM_UNJOINED, STREAM_WHOLE, STREAM_WINDOWS
 
@@ -128,3 +128,13 @@ def test_markers_and_damage_inside_the_data(pp):
         assert np.array_equal(pp.debug_last_coefficients(i, coef.shape[0]), coef)
     for i in (1, 2, 4):
         assert not np.any(tensor[i])
+
+
+@pytest.mark.parametrize("seed", [31, 32])
+def test_random_damage(pp, seed):
+    # every stream is cut; those whose windows show the damage are decoded again, and refused or
+    # decoded as the oracle decodes them
+    streams = damaged_streams(seed, 8, bases=WINDOW_BASES)
+    status, tensor = run_gpu(pp, streams, 0, 64, 64, "f32")
+    check_damaged(streams, status, lambda i, nb: pp.debug_last_coefficients(i, nb), tensor)
+    assert _decoded(pp, len(streams)) == {STREAM_WINDOWS, STREAM_UNJOINED}
