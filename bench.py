@@ -50,12 +50,16 @@ N_STREAMS, STREAM_BATCH = 7, 8
 # scaled by what the same counters read for a plain 256 MiB copy (FETCH_SIZE x 2, WRITE_SIZE x 1).
 # They describe the kernels whose sources hash to MEASURED_SOURCES; for any other sources the
 # figure is reported as null.
-MEASURED_SOURCES = "e3a24c510a1c23b19a27fbc5bd7d4b7cac41e11943365f9eb83ac318856e23a1"
+MEASURED_SOURCES = "a3595b423143f78e437f7150330192da0d47517a24faa23257c2013487855dda"
 MEASURED_TRAFFIC = {
-    2: {"scan": (5419 * 2 + 1265) * 1024, "decode": (7719 * 2 + 289799) * 1024,
-        "reconstruct": (50640 * 2 + 104417) * 1024, "resize": (49121 * 2 + 75264) * 1024},
-    4: {"scan": (23814 * 2 + 575) * 1024, "decode": (28211 * 2 + 620821) * 1024,
-        "reconstruct": (114438 * 2 + 241160) * 1024, "resize": (91697 * 2 + 55296) * 1024},
+    2: {"scan": (5397 * 2 + 1271) * 1024, "decode": (7685 * 2 + 289785) * 1024,
+        "reconstruct": (50666 * 2 + 104422) * 1024, "resize": (49124 * 2 + 75264) * 1024},
+    4: {"scan": (23819 * 2 + 577) * 1024, "decode": (28280 * 2 + 623130) * 1024,
+        "reconstruct": (114445 * 2 + 241166) * 1024, "resize": (92355 * 2 + 55296) * 1024},
+    # (decode: the five kernels of a stream without restart markers)
+    5: {"scan": (2768 * 2 + 2468) * 1024,
+        "decode": ((4455 + 245 + 7964 + 217 + 2356) * 2 + 4865 + 45 + 208560 + 30064) * 1024,
+        "reconstruct": (50785 * 2 + 84861) * 1024, "resize": (54030 * 2 + 150528) * 1024},
 }
 
 
