@@ -56,10 +56,6 @@ MEASURED_TRAFFIC = {
         "reconstruct": (50666 * 2 + 104422) * 1024, "resize": (49124 * 2 + 75264) * 1024},
     4: {"scan": (23819 * 2 + 577) * 1024, "decode": (28280 * 2 + 623130) * 1024,
         "reconstruct": (114445 * 2 + 241166) * 1024, "resize": (92355 * 2 + 55296) * 1024},
-    # (decode: the five kernels of a stream without restart markers)
-    5: {"scan": (2768 * 2 + 2468) * 1024,
-        "decode": ((4455 + 245 + 7964 + 217 + 2356) * 2 + 4865 + 45 + 208560 + 30064) * 1024,
-        "reconstruct": (50785 * 2 + 84861) * 1024, "resize": (54030 * 2 + 150528) * 1024},
 }
 
 
