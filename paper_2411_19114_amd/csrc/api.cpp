@@ -209,6 +209,7 @@ struct Plan {                         // what one call will run
     uint32_t window_bytes = kWindowBytes;  // raw bytes between the decoder's workgroup starts
     uint32_t n_streams = 0;     // windows of the streams without restart markers
     uint32_t row_bytes = kStreamRowBytes;  // clean bytes of a row of such a window
+    bool long_intervals = false;  // which variant of the decoder for large calls: see plan_batch
 };
 
 }  // namespace
@@ -374,7 +375,7 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
     h->table_rep.clear();
     std::fill(h->table_hash.begin(), h->table_hash.end(), 0u);
     Plan P;
-    uint64_t entropy_total = 0;
+    uint64_t entropy_total = 0, long_total = 0;
     StreamCut streams;
     for (int32_t i = 0; i < n; i++) {
         if (offsets[i + 1] < offsets[i]) return PREP_E_INVALID_ARG;
@@ -382,6 +383,8 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
         parse_image(bits + offsets[i], offsets[i + 1] - offsets[i], &pi);
         if (pi.info.status == PREP_OK) {
             entropy_total += pi.info.entropy_bytes;
+            if (pi.info.entropy_bytes > (uint64_t)kLongIntervalBytes * (uint64_t)pi.info.n_intervals)
+                long_total += pi.info.entropy_bytes;
             streams.add(pi);
         }
     }
@@ -391,6 +394,7 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
     // the chip with hypotheses instead of walking whole restart intervals lane by lane
     if (entropy_total <= kSmallCallBytes && !(h->cfg.flags & PREP_FLAG_LARGE_WINDOWS))
         P.window_bytes = entropy_total <= kTinyCallBytes ? kTinyWindowBytes : kSmallWindowBytes;
+    P.long_intervals = 4 * long_total >= entropy_total;
     for (int32_t i = 0; i < n; i++) {
         ParsedImage &pi = h->parsed[(size_t)i];
         prep_image_info &I = pi.info;
@@ -579,7 +583,7 @@ int run_batch(prep_handle *h, const uint8_t *bits_host, const uint8_t *bits_dev,
         launch_decode_entropy(d_bits, s->d_recs, n, P.n_windows, h->d_win_count, h->d_win_first, s->d_data_end,
                               h->d_retry, h->d_coef, (uint32_t)(h->cap_blocks * 64), h->d_status, h->d_tables,
                               P.window_bytes != (uint32_t)kWindowBytes,
-                              P.window_bytes == (uint32_t)kTinyWindowBytes ? 256u : 512u, stream);
+                              P.window_bytes == (uint32_t)kTinyWindowBytes ? 256u : 512u, P.long_intervals, stream);
         launch_finish_streams(s->d_recs, n, P.n_streams, h->d_retry, h->d_streams, h->d_coef,
                               (uint32_t)(h->cap_blocks * 64), stream);
         if (timing) HIP_TRY(hipEventRecord(ev[2], stream));

@@ -32,6 +32,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/prep.h"
 #include "kernels.h"
 #include "prep_internal.h"
@@ -44,42 +46,69 @@ constexpr int kT = kDecodeThreads;
 constexpr int kPadShift = 4;                        // rows of 16 words (= one subsequence) + 1 (copy of the next)
 constexpr int kCleanWords = kChunkRaw / 4 + kT + 16;  // destuffed stream, the rows' last words, zero tail
 constexpr int kMaskWords = kChunkRaw / 32 + 2;      // one bit per clean byte
-constexpr int kSubEntries = 256;                    // second-level lookup entries per table
 constexpr int kMaxBoundaries = 1024;                // listed interval starts per chunk
-constexpr uint32_t kShortInterval = 1024;           // mean clean bytes up to which a lane takes a whole interval
+constexpr uint32_t kShortInterval = kLongIntervalBytes;  // mean clean bytes up to which a lane takes a whole interval
 constexpr uint32_t kNoMarker = 0xFFFFFFFFu;
 constexpr uint32_t kSubBits = kSubseqBytes * 8;
 static_assert(kSubseqBytes == 64 && (kSubseqBytes / 4) == (1 << kPadShift), "one 64-bit keep mask per lane");
 
 // Lookup entry of a Huffman code (16 bits):
-//   bits 15..11 code length + number of appended bits (1..31); 0 = not a code entry
-//   bits 10..4  zig-zag advance - 1 (DC 1, AC run+1, ZRL 16, EOB 128).  Added to the zig-zag
-//               index it gives the index k of the symbol's coefficient, which must not exceed
-//               63 except for EOB, whose coefficient is the block's last: k <= 63 is in order,
-//               64 <= k < 128 is a run past the block's end, k >= 128 is EOB (bit 6 of k tells)
-//   bits 3..0   number of appended bits
-// A first-level entry that is not a code entry refers to the table's second-level pool:
-// bits 10..8 = extra index bits (0..6), bits 7..0 = offset of its block.  Two pool entries are
-// set aside so that every first-level miss is resolved by the same read: entry 0 holds 0 (no
-// such code; the first-level entry is 0 too), entry 1 holds kUseLoop (the table's blocks did
-// not fit the pool: search the canonical code lists instead).
-constexpr uint32_t kUseLoop = 0x07FFu;
-constexpr uint32_t kPoolReserved = 2, kPoolSearchRef = 1;
-constexpr uint32_t kInvalidEntry = (16u << 11) | (127u << 4);  // 16 bits, ends the block
+//   bits 4..0   code length + number of appended bits (1..31); 0 = search the code lists
+//   bits 8..5   number of appended bits
+//   bits 15..9  zig-zag advance - 1 (DC 0, AC run, ZRL 15, EOB 127).  Added to the zig-zag index it
+//               gives the index k of the symbol's coefficient, which must not exceed 63 except
+//               for EOB, whose coefficient is the block's last: k <= 63 is in order, 64 <= k < 128
+//               is a run past the block's end, k >= 128 is EOB (bit 6 of k tells)
+// (the first field shifted to the top of a word leaves nothing of the others: see BitCursor)
+constexpr uint32_t kEobAdvance = 127;
+// bits that are no code word: 16 bits, ends the block, and is refused like a run past its end
+constexpr uint32_t kInvalidEntry = 16u | (64u << 9);
+constexpr uint32_t kSearchEntry = 0;
+// the same in a DC table, where it must not move the index: as many appended bits as no DC code has
+constexpr uint32_t kInvalidDcEntry = 16u | (15u << 5);
+constexpr uint32_t entry_bits(uint32_t e) { return e & 31u; }
+constexpr uint32_t entry_appended(uint32_t e) { return (e >> 5) & 15u; }
+constexpr uint32_t entry_advance(uint32_t e) { return e >> 9; }
 
-struct alignas(16) HuffTables {
-    // first level: entry (prefix << 2) | table for the next kLutBits bits, the four tables
-    // (DC luma, AC luma, DC chroma, AC chroma) interleaved, so that a decoder forms an entry's
-    // address from the bits and its table number with one AND-OR
-    alignas(8) uint16_t lut[4 << kLutBits];
-    uint16_t sub[4 * kSubEntries];   // second level
+// One lookup resolves codes of every length.  Canonical codes grow longer with their value
+// (T.81 Annex C), so the codes of more than ten bits lie at the top of the code space: below
+// kFinePrefixes ten-bit prefixes there is an entry for each prefix, above an entry for each
+// sixteen-bit word.  With a = the next sixteen bits the entry is number max(a / 64, a - 63 *
+// kFinePrefixes): the two meet where the fine part begins, and either side of it the other
+// is the smaller.  Eight fine prefixes: the codes of T.81 Annex K need five of each AC table, codes
+// made for photographs and noise of qualities 50 to 95 at most four.  A prefix below that still
+// begins a longer code (codes far from any image's statistics) has kSearchEntry.
+// With a second level for the codes of more than ten bits, read in a branch of its own, 1.6 % of
+// the symbols took that branch but half of all iterations of a wave of 64 lanes did.
+constexpr uint32_t kFinePrefixes = 1016;
+constexpr uint32_t kLookupEntries = kFinePrefixes + 64u * (1024u - kFinePrefixes);
+
+// What a writing pass needs of an image's four tables
+struct alignas(16) HuffCodes {
+    // the tables (DC luma, AC luma, DC chroma, AC chroma) interleaved: entry (number << 2) | table
+    uint16_t one[4 * kLookupEntries];
     int32_t first[4][17];            // first code of each length
     int32_t count[4][17];            // BITS
     int32_t valptr[4][17];           // index of the first symbol of each length
     uint8_t huffval[4][256];
-    uint32_t sub_used[4];
 };
+// and what the passes that only find states do: entries for as many whole symbols as the ten bits
+// of a prefix hold the codes of (their bits, and their advances together; no values), so that a
+// lookup goes on by 1.6 to 1.9 symbols.  A DC symbol is followed by those of its component's AC
+// table.  The symbols stop
+//   - behind an EOB (the advance is kEobAdvance then),
+//   - where the symbols before the last advance by more than kRunLead together: up to
+//     zig-zag index 62 - kRunLead none of them ends the block,
+//   - with what does not fit the entry's fields.
+// All but the last end within the ten bits.  Prefixes of longer codes have their single symbol.
+struct alignas(16) HuffTables : HuffCodes {
+    uint16_t run[4 * kLookupEntries];
+};
+constexpr int32_t kRunLead = 16;
+constexpr uint32_t kRunLeadBits = 9;  // most bits of the symbols before the last
 
+// kHyp, kRuns: see decode_entropy
+template <bool kHyp, bool kRuns>
 struct DecodeShared {
     // The destuffed stream, big-endian packed (bit 31 of a word is the earliest bit).  In the
     // subsequence passes every 16 words (a subsequence) are followed by a copy of the next
@@ -88,9 +117,16 @@ struct DecodeShared {
     uint32_t clean[kCleanWords];
     uint32_t bmask[kMaskWords];      // bit q set: a restart interval begins at clean byte q
     uint32_t next_boundary[kT + 1];  // first interval start at or after the lane's subsequence
-    uint16_t bpos[kMaxBoundaries];   // interval starts of the chunk in order (clean byte offsets)
-    HuffTables tab;                  // DC luma, AC luma, DC chroma, AC chroma
-    unsigned long long keep[kT];     // which of the lane's 64 raw bytes survived destuffing
+    // Interval starts of the chunk in order (clean byte offsets), for the pass that takes an
+    // interval a lane; the others need to know which of a lane's 64 raw bytes survived destuffing
+    // (and the hypothesis passes use the list's place for states)
+    union {
+        uint16_t bpos[kMaxBoundaries];
+        unsigned long long keep_here[kHyp ? 1 : kT];
+    };
+    std::conditional_t<kRuns, HuffTables, HuffCodes> tab;
+    unsigned long long keep_there[kHyp ? kT : 1];
+    __device__ unsigned long long &keep(int lane) { return kHyp ? keep_there[lane] : keep_here[lane]; }
     uint32_t keep_off[kT + 1];       // clean offset of the lane's first surviving byte
     uint32_t state[kT];              // end state of every subsequence
     uint32_t scan_a[kT / 64 + 1];    // per-wave totals for workgroup scans
@@ -188,9 +224,10 @@ __device__ inline int32_t block_seg_excl_scan(int32_t v, int32_t f, int32_t carr
 // ---- Huffman tables (T.81 Annex C) --------------------------------------------
 
 // canonical search among the code lengths lo..hi for the code that starts `peek16`
-__device__ inline bool canonical_lookup(const HuffTables &T, int t, uint32_t peek16, int lo, int hi,
+__device__ inline bool canonical_lookup(const HuffCodes &T, int t, uint32_t peek16, int lo, int hi,
                                         uint32_t *len, uint32_t *sym)
 {
+#pragma unroll 1
     for (int l = lo; l <= hi; l++) {
         const int32_t c = (int32_t)(peek16 >> (16 - l)) - T.first[t][l];
         if (c >= 0 && c < T.count[t][l]) {
@@ -204,25 +241,30 @@ __device__ inline bool canonical_lookup(const HuffTables &T, int t, uint32_t pee
 
 __device__ inline uint32_t make_entry(bool ac, uint32_t sym, uint32_t len)
 {
-    uint32_t s = sym & 15u, inc;
+    uint32_t s = sym & 15u, advance;
     if (!ac) {
-        if (sym > 11u) return 0u;  // no such DC category in baseline
-        inc = 1;
+        if (sym > 11u) return kSearchEntry;  // no such DC category in baseline
+        advance = 0;
     } else if (s == 0) {
-        inc = (sym >> 4) == 15u ? 16u : 128u;  // ZRL, otherwise end of block
+        advance = (sym >> 4) == 15u ? 15u : kEobAdvance;  // ZRL, otherwise end of block
     } else {
-        inc = (sym >> 4) + 1u;
+        advance = sym >> 4;
     }
-    return ((len + s) << 11) | ((inc - 1u) << 4) | s;
+    return (advance << 9) | (s << 5) | (len + s);
 }
 
-// The first level is filled code by code: canonical codes of one table are consecutive when
-// left-aligned, so the code of length len with value c owns the 2^(kLutBits-len) entries that
-// begin with it.  Entries above the last code of at most kLutBits bits begin longer codes (or
-// nothing): each such prefix gets a block of the second-level pool sized for the longest
-// code that shares it.
+// the run entries, or the single ones where no others are kept
+__device__ __forceinline__ const uint16_t *run_entries(const HuffTables &T) { return T.run; }
+__device__ __forceinline__ const uint16_t *run_entries(const HuffCodes &T) { return T.one; }
+
+// number of the lookup entry for the next bits `win` of the stream
+__device__ __forceinline__ uint32_t lookup_number(uint32_t win)
+{
+    return (uint32_t)max((int32_t)(win >> 22), (int32_t)(win >> 16) - (int32_t)(63u * kFinePrefixes));
+}
+
 // Expands tables t_lo .. t_hi-1 of the four (all lanes of the workgroup must call).
-__device__ inline void build_tables(HuffTables &T, const uint8_t *file, const ImageRec &R, int t_lo = 0,
+__device__ inline void build_tables(HuffCodes &T, const uint8_t *file, const ImageRec &R, int t_lo = 0,
                                     int t_hi = 4)
 {
     const int tid = threadIdx.x;
@@ -242,74 +284,72 @@ __device__ inline void build_tables(HuffTables &T, const uint8_t *file, const Im
             code = (code + c) << 1;
             k += c;
         }
-        T.sub_used[tid] = kPoolReserved;
     }
     for (int t = t_lo; t < t_hi; t++) {
         const uint32_t nval = min(R.dht_nval[t], 256u);
-#pragma unroll
         for (uint32_t i = tid; i < 256u; i += kT) T.huffval[t][i] = i < nval ? file[R.dht_off[t] + 16 + i] : 0;
     }
-    for (int i = t_lo * kSubEntries + tid; i < t_hi * kSubEntries; i += kT) T.sub[i] = 0;
     __syncthreads();
     for (int t = t_lo; t < t_hi; t++) {
-        // codes of at most kLutBits bits: one lane per code
-        const int32_t n_short = min(T.valptr[t][kLutBits] + T.count[t][kLutBits], 256);
-        for (int32_t i = tid; i < n_short; i += kT) {
-            int l = 1;
-            while (l < kLutBits && T.valptr[t][l] + T.count[t][l] <= i) l++;
-            const uint32_t c = (uint32_t)(T.first[t][l] + (i - T.valptr[t][l]));
-            const uint32_t e = make_entry(t & 1, T.huffval[t][i], (uint32_t)l);
-            const uint32_t span = 1u << (kLutBits - l), base = c << (kLutBits - l);
-            if (base + span > (1u << kLutBits)) continue;  // not a prefix code; the parser refuses these
-            for (uint32_t j = 0; j < span; j++) T.lut[((base + j) << 2) | (uint32_t)t] = (uint16_t)e;
-        }
-        // the rest of the first level: beginnings of longer codes, or of none
-        const uint32_t x_lo = min((uint32_t)(T.first[t][kLutBits] + T.count[t][kLutBits]), 1u << kLutBits);
-        for (uint32_t x = x_lo + tid; x < (1u << kLutBits); x += kT) {
-            uint32_t e = 0;
-            // codes of one length are consecutive: which lengths have a code that begins with x?
-            int maxl = 0;
-            for (int l = kLutBits + 1; l <= 16; l++) {
-                const int32_t c = T.count[t][l];
-                if (c == 0) continue;
-                const int32_t lo = T.first[t][l] >> (l - kLutBits);
-                const int32_t hi = (T.first[t][l] + c - 1) >> (l - kLutBits);
-                if ((int32_t)x >= lo && (int32_t)x <= hi) maxl = l;
+        // the sixteen-bit words below end[l - 1] begin with a code of at most l bits
+        uint32_t end[16];
+#pragma unroll
+        for (int l = 1; l <= 16; l++) end[l - 1] = (uint32_t)(T.first[t][l] + T.count[t][l]) << (16 - l);
+        for (uint32_t i = tid; i < kLookupEntries; i += kT) {
+            const bool fine = i >= kFinePrefixes;
+            const uint32_t a = fine ? i + 63u * kFinePrefixes : i << 6;
+            uint32_t l = 1;
+#pragma unroll
+            for (int k = 0; k < 16; k++) l += a >= end[k] ? 1u : 0u;
+            uint32_t e = t & 1 ? kInvalidEntry : kSearchEntry;  // past the last code
+            if (l <= 16u) {
+                const uint32_t c = (a >> (16u - l)) - (uint32_t)T.first[t][l];
+                e = fine || l <= 10u ? make_entry(t & 1, T.huffval[t][((uint32_t)T.valptr[t][l] + c) & 255u], l) : kSearchEntry;
             }
-            if (maxl) {
-                const uint32_t nb = (uint32_t)(maxl - kLutBits), size = 1u << nb;
-                const uint32_t off = atomicAdd(&T.sub_used[t], size);
-                if (off + size <= (uint32_t)kSubEntries) {
-                    e = (nb << 8) | off;
-                    // leave a note for the second-level pass: which prefix owns these entries
-                    for (uint32_t i = 0; i < size; i++)
-                        T.sub[t * kSubEntries + off + i] = (uint16_t)((nb << 11) | x);
-                } else {
-                    e = kPoolSearchRef;
+            T.one[(i << 2) | (uint32_t)t] = (uint16_t)e;
+        }
+    }
+    __syncthreads();
+}
+
+// The run entries of tables t_lo .. t_hi-1 from the single ones of these and, for a DC table, of the
+// AC table behind it (all lanes of the workgroup must call).
+__device__ inline void build_runs(HuffTables &T, int t_lo = 0, int t_hi = 4)
+{
+    for (int t = t_lo; t < t_hi; t++) {
+        for (uint32_t i = threadIdx.x; i < kLookupEntries; i += kT) {
+            uint32_t e = T.one[(i << 2) | (uint32_t)t];
+            if (i < kFinePrefixes && e != kSearchEntry && e != kInvalidEntry) {
+                uint32_t bits = entry_bits(e), advance = entry_advance(e);
+                int32_t lead = 0;  // how far the zig-zag index has come by the symbols so far
+                // (a symbol has at least one bit: the loop ends)
+                while (advance != kEobAdvance && bits <= kRunLeadBits) {
+                    lead = (int32_t)advance + 1;
+                    if (lead > kRunLead) break;
+                    const uint32_t n = T.one[(lookup_number(i << (22 + bits)) << 2) | (uint32_t)(t | 1)];
+                    // the next code lies within the prefix?  (the zeros behind it are not the stream's)
+                    if (n == kSearchEntry || n == kInvalidEntry || bits + entry_bits(n) - entry_appended(n) > 10u) break;
+                    if (bits + entry_bits(n) > 31u) break;
+                    bits += entry_bits(n);
+                    advance = entry_advance(n) == kEobAdvance ? kEobAdvance : (uint32_t)lead + entry_advance(n);
                 }
+                e = (advance << 9) | bits;
             }
-            T.lut[(x << 2) | (uint32_t)t] = (uint16_t)e;
+            T.run[(i << 2) | (uint32_t)t] = (uint16_t)e;
         }
     }
     __syncthreads();
-    // second level: entry i of a block with nb extra bits covers prefix:i:anything
-    for (int t = t_lo; t < t_hi; t++) {
-        const uint32_t used = min(T.sub_used[t], (uint32_t)kSubEntries);
-        for (uint32_t i = tid; i < used; i += kT) {
-            const uint32_t note = T.sub[t * kSubEntries + i];
-            uint32_t e = i == kPoolSearchRef ? kUseLoop : 0u;
-            if (note) {
-                const uint32_t nb = note >> 11, x = note & ((1u << kLutBits) - 1u);
-                const uint32_t off = T.lut[(x << 2) | (uint32_t)t] & 0xFFu;
-                const uint32_t peek = (x << (16 - kLutBits)) | ((i - off) << (16 - kLutBits - nb));
-                uint32_t len, sym;
-                if (canonical_lookup(T, t, peek, kLutBits + 1, kLutBits + (int)nb, &len, &sym))
-                    e = make_entry(t & 1, sym, len);
-            }
-            T.sub[t * kSubEntries + i] = (uint16_t)e;
-        }
-    }
-    __syncthreads();
+}
+
+// the expanded tables of an image with a table slot, or the part of them that a writing pass
+// needs, into LDS (a barrier has to follow)
+template <typename Tables>
+__device__ inline void load_tables(Tables &tab, const uint4 *__restrict__ tables, uint32_t slot)
+{
+    constexpr uint32_t units = sizeof(Tables) / 16, all = sizeof(HuffTables) / 16;
+    uint4 *dst = reinterpret_cast<uint4 *>(&tab);
+#pragma unroll
+    for (uint32_t i = threadIdx.x; i < units; i += kT) dst[i] = tables[(size_t)slot * all + i];
 }
 
 // ---- bit-level decoding ------------------------------------------------------
@@ -345,7 +385,8 @@ __device__ inline uint32_t comp_of_block(const Geometry &g, uint32_t blk_in_mcu)
 }
 
 // first interval start at or after clean byte q (in bits), limit if none
-__device__ inline uint32_t boundary_from(const DecodeShared &S, uint32_t q, uint32_t limit_bits)
+template <bool kHyp, bool kRuns>
+__device__ inline uint32_t boundary_from(const DecodeShared<kHyp, kRuns> &S, uint32_t q, uint32_t limit_bits)
 {
     const uint32_t j = q >> 6;
     if (j >= (uint32_t)kT) return limit_bits;
@@ -367,33 +408,23 @@ struct WriteCtx {
     int32_t bad;
 };
 
-// The rarest part of a lookup: a table whose second level did not fit its pool.  Out of
-// line so that the decode loops stay short.
-__device__ __attribute__((noinline)) uint32_t lookup_by_search(const HuffTables &T, uint32_t tsel,
-                                                               uint32_t win)
+// The rarest part of a lookup: a code that the lookup table refers to the code lists.
+__device__ __forceinline__ uint32_t lookup_by_search(const HuffCodes &T, uint32_t tsel, uint32_t win)
 {
-    uint32_t len, sym;
-    return canonical_lookup(T, (int)tsel, win >> 16, kLutBits + 1, 16, &len, &sym)
-               ? make_entry(tsel & 1u, sym, len) : 0u;
+    uint32_t len, sym, e = kSearchEntry;
+    if (canonical_lookup(T, (int)tsel, win >> 16, 11, 16, &len, &sym)) e = make_entry(tsel & 1u, sym, len);
+    return e != kSearchEntry ? e : (tsel & 1u) ? kInvalidEntry : kInvalidDcEntry;
 }
 
-// Codes longer than the first level covers: e is the first-level entry (not a code entry),
-// win = the next 32 bits of the stream, ts2 = twice the table's number.
-// Returns the second-level entry: a code entry, 0, or kUseLoop.
-__device__ __forceinline__ uint32_t second_level(const HuffTables &T, uint32_t e, uint32_t ts2, uint32_t win)
+// Entry for the next bits `win` in a table of `entries`; tb = twice the table's number
+__device__ __forceinline__ uint32_t look_up(const uint16_t *entries, uint32_t tb, uint32_t win)
 {
-    const uint32_t nbits = e >> 8;
-    // the nbits bits after the first kLutBits; none for nbits = 0
-    const uint32_t idx = __builtin_amdgcn_ubfe(win, 32u - kLutBits - nbits, nbits);
-    return T.sub[(ts2 >> 1) * kSubEntries + (e & 0xFFu) + idx];
+    return *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(entries) + (lookup_number(win) << 3) + tb);
 }
 
-// First-level entry for the next bits `win` in table ts2 / 2: byte offset (prefix << 3) | ts2.
-__device__ __forceinline__ uint32_t first_level(const uint16_t *lut, uint32_t ts2, uint32_t win)
-{
-    const uint32_t at = ((win >> (32 - kLutBits - 3)) & (((1u << kLutBits) - 1u) << 3)) | ts2;
-    return *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(lut) + at);
-}
+// Whether a rare branch is worth entering, or a loop for all lanes is: true if x is for any of the
+// wave's active lanes
+__device__ __forceinline__ bool wave_any(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0; }
 
 // Word w of the destuffed stream lives at index w + (w >> kPadShift) of DecodeShared::clean in
 // the subsequence passes: rows of seventeen words, a subsequence's sixteen and a copy of the
@@ -408,13 +439,37 @@ __device__ __forceinline__ uint32_t clean_row_of_bit(uint32_t p)
     return p >> 9;
 }
 
-// the 32 stream bits from bit position p on, of the two words that hold them and the next:
-// the upper half of the pair shifted left (one instruction less than shifting it right by
-// 32 minus the offset)
-__device__ __forceinline__ uint32_t window_at(uint32_t hi, uint32_t lo, uint32_t p)
-{
-    return (uint32_t)(((((unsigned long long)hi << 32) | lo) << (p & 31u)) >> 32);
-}
+// A place in the stream and the next 32 bits there.  The stream words around it are kept in
+// registers (an entry's bits are fewer than a word's, so at most one new word is needed a symbol, and it
+// is fetched a symbol ahead of its use).  The bit offset is counted down from the next word's
+// first bit, in the top five bits of n32, so that the subtraction of a symbol's bits borrows
+// exactly where a new word begins, and the offset is the shift that V_ALIGNBIT_B32 takes.
+struct BitCursor {
+    uint32_t w;              // ceil(position / 32)
+    uint32_t n32;            // (32 w - position) << 27
+    uint32_t hi, lo, ahead;  // words w - 1, w and w + 1
+    uint32_t win;            // the next 32 bits
+    __device__ __forceinline__ void start(const uint32_t *words, uint32_t p)
+    {
+        w = (p + 31u) >> 5;
+        n32 = (0u - p) << 27;
+        hi = words[p >> 5];  // (word w - 1, or any word where p is a word's first bit)
+        lo = words[w];
+        ahead = words[w + 1];
+        win = __builtin_amdgcn_alignbit(hi, lo, n32 >> 27);
+    }
+    // past the symbol (or symbols) of entry e
+    __device__ __forceinline__ void advance(const uint32_t *words, uint32_t e)
+    {
+        const bool moved = __builtin_sub_overflow(n32, e << 27, &n32);
+        hi = moved ? lo : hi;
+        lo = moved ? ahead : lo;
+        w += moved ? 1u : 0u;
+        win = __builtin_amdgcn_alignbit(hi, lo, n32 >> 27);
+        ahead = words[w + 1];
+    }
+    __device__ __forceinline__ uint32_t position() const { return (w << 5) - (n32 >> 27); }
+};
 
 // value of a stored coefficient: appended bits (T.81 F.2.2.4 RECEIVE) and sign extension
 // (F.2.2.1 EXTEND); adv = code length + s
@@ -427,147 +482,427 @@ __device__ __forceinline__ int32_t coefficient_value(uint32_t win, uint32_t adv,
     return t + (int32_t)((0xFFFFFFFFu << s) ^ (uint32_t)(t >> 31)) + 1;
 }
 
-// Decode from packed state `st` until the bit position reaches end_bit.
-// limit_bits = end of the staged data.  Returns the end state; *nblk = blocks completed.
-// after_boundary: st.p is the first bit of a restart interval (the boundary there is behind
-// us, not ahead).
+// ---- the symbol loops -----------------------------------------------------------
+// One step = one lookup: (writing passes) extract the value and store it, advance position and
+// zig-zag index, look the next bits up.  The state carried from one step to the next is the bit
+// position, block-in-MCU and zig-zag index only.
 //
-// One iteration = one symbol: take the next 32 bits, look them up, (write mode) extract the
-// value and store it, advance position and zig-zag index.  The state carried from one symbol
-// to the next is the bit position, block-in-MCU and zig-zag index only.  A writing pass
-// stores DC *differences*; dc_prefix() turns them into values afterwards.
+// The loops are bound by their instructions: a lone wave issues a dependent one every eight cycles
+// and an independent one every five, and the waves of a SIMD share its issue.  So the steps are
+// written out, in an order in which little waits for the instruction before and a table entry's
+// read is under way while the index and the block are settled, and lanes do not leave one by
+// one: one loop runs while no lane of the wave is near the end of its span or a restart boundary, one
+// that looks at both while none has come there, and all else happens outside, in count_span and
+// write_span.  (The compiler's loop for the former, with its masks, copies and branches, took 42
+// instructions a symbol, half of them again for codes of more than ten bits.)
 //
-// A lone wave issues a dependent instruction only every eight cycles or so and pays a fetch
-// bubble for every taken branch, and a lane that leaves the loop waits for the whole wave to
-// leave it.  So there is one loop, kept short and straight, that every lane stays in until
-// its span is done; the two rare events are branches off it that return to it: a code longer
-// than the first-level table covers, and a symbol that does not fit before the next restart
-// boundary or the end of the data (the bits there are padding, or belong to the next
-// interval), which is where the lane steps over the boundary.
-template <bool kWrite>
-__device__ __forceinline__ uint32_t decode_span(const DecodeShared &S, const Geometry &g, uint32_t st,
-                                                bool after_boundary, uint32_t end_bit,
-                                                uint32_t limit_bits, uint32_t *nblk, WriteCtx *wc)
+// A VALU instruction of gfx950 may read VCC or an SGPR pair that another VALU instruction wrote
+// from the third instruction after it on.
+
+// The lane's state in a symbol loop.
+struct Steps {
+    BitCursor c;
+    uint32_t slot;           // 5 * block in the MCU
+    int32_t k;               // zig-zag index of the coefficient before the next symbol's
+    uint32_t block;          // blocks completed (counting) or block of the image (writing)
+    uint32_t e;              // entry of the next bits
+    uint32_t end_bit, nb;    // end of the span; next restart boundary, or the end of the data
+    int32_t near_w;          // from this c.w on the lane is near one of them
+    __device__ __forceinline__ bool near() const { return (int32_t)c.w >= near_w; }
+    // twice the number of the next symbol's table
+    __device__ __forceinline__ uint32_t table(const Geometry &g) const
+    {
+        return __builtin_amdgcn_ubfe(g.chroma_at, slot, 3u) + (k >= 0 ? 2u : 0u);
+    }
+    // has the lane to be looked at before the next step?
+    __device__ __forceinline__ bool due() const
+    {
+        const uint32_t p = c.position();
+        return e == kSearchEntry || (near() && (p >= end_bit || p + entry_bits(e) > nb));
+    }
+    // past the entry; returns the index of its (last) symbol's coefficient
+    __device__ __forceinline__ int32_t advance(const uint32_t *words, const Geometry &g)
+    {
+        c.advance(words, e);
+        const int32_t at = k + 1 + (int32_t)entry_advance(e);
+        const bool endb = at >= 63;
+        slot = endb ? __builtin_amdgcn_ubfe(g.next_slot, slot, 5u) : slot;
+        k = endb ? -1 : at;
+        block += endb ? 1u : 0u;
+        return at;
+    }
+};
+
+#ifdef __AMDGCN__
+// LDS byte address of what p points to
+__device__ __forceinline__ uint32_t lds_address(const void *p)
 {
-    uint32_t p = st >> 9, slot = slot_of_block((st >> 6) & 7u), zz = st & 63u;
-    uint32_t done = 0;
-    // write mode: first coefficient of the current block, the image's last coefficient,
-    // blocks left in the restart interval
-    uint32_t boff = 0, last = 0;
-    int32_t iv_rem = 0;
-    if (kWrite) {
-        boff = wc->block * 64u;
-        last = g.n_blocks * 64u - 1u;
-        iv_rem = wc->iv_rem;
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
+}
+
+// Parts that the written-out steps share; each leaves in vcc whether the block ends.
+// the words around the position, and the next 32 bits; m1 = the lane is near; t0 = the bit offset
+#define STEP_WORDS                                              \
+    "v_cndmask_b32 %[hi], %[hi], %[lo], vcc\n"                  \
+    "v_cndmask_b32 %[lo], %[lo], %[ahead], vcc\n"               \
+    "v_addc_co_u32 %[w], vcc, 0, %[w], vcc\n"                   \
+    "v_alignbit_b32 %[win], %[hi], %[lo], %[t0]\n"              \
+    "v_lshl_add_u32 %[t2], %[w], 2, %[aheadat]\n"               \
+    "v_cmp_lt_i32 vcc, 62, %[k]\n"                              \
+    "ds_read_b32 %[ahead], %[t2]\n"                             \
+    "v_cmp_ge_i32 %[m1], %[w], %[nearw]\n"
+// t3, t2 = the two candidates of lookup_number; the slot
+#define STEP_NUMBER                                             \
+    "v_lshrrev_b32 %[t3], 22, %[win]\n"                         \
+    "v_add_u32_sdwa %[t2], %[win], %[fine] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD\n" \
+    "v_cndmask_b32 %[slot], %[slot], %[t1], vcc\n"
+// p = the position
+#define STEP_POSITION                                           \
+    "v_lshlrev_b32 %[p], 5, %[w]\n"                             \
+    "v_sub_u32 %[p], %[p], %[t0]\n"
+// leave (to 3:) if a lane is due, stay in loop 2: while a lane is near
+#define STEP_DUE                                                \
+    "v_cmp_ge_u32 %[m2], %[p], %[end]\n"                        \
+    "s_waitcnt lgkmcnt(0)\n"                                    \
+    "v_and_b32 %[t0], 31, %[e]\n"                               \
+    "v_add_u32 %[t0], %[t0], %[p]\n"                            \
+    "v_cmp_gt_u32 %[m0], %[t0], %[nb]\n"                        \
+    "v_cmp_eq_u32 vcc, 0, %[e]\n"                               \
+    "s_or_b64 %[m0], %[m0], %[m2]\n"                            \
+    "s_and_b64 %[m0], %[m0], %[m1]\n"                           \
+    "s_or_b64 vcc, vcc, %[m0]\n"                                \
+    "s_cbranch_vccnz 3f\n"                                      \
+    "s_cmp_lg_u64 %[m1], 0\n"                                   \
+    "s_cbranch_scc1 2b\n"                                       \
+    "3:\n"
+// leave if a lane is near or its entry is kSearchEntry
+#define STEP_NEAR                                               \
+    "s_waitcnt lgkmcnt(0)\n"                                    \
+    "v_cmp_eq_u32 vcc, 0, %[e]\n"                               \
+    "s_or_b64 vcc, vcc, %[m1]\n"                                \
+    "s_cbranch_vccz 1b\n"
+#define STEP_STATE                                                                                                   \
+    [w] "+v"(s.c.w), [n32] "+v"(s.c.n32), [hi] "+v"(s.c.hi), [lo] "+v"(s.c.lo), [ahead] "+v"(s.c.ahead),             \
+        [win] "+v"(s.c.win), [slot] "+v"(s.slot), [k] "+v"(s.k), [block] "+v"(s.block), [e] "+v"(s.e),               \
+        [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2)
+#define STEP_GIVEN                                                                                                   \
+    [nearw] "v"(s.near_w), [aheadat] "v"(ahead_at), [oneac] "v"(one_dc + 2u), [onedc] "v"(one_dc),                   \
+        [next] "s"(g.next_slot), [chroma] "s"(g.chroma_at), [fine] "s"(0u - 63u * kFinePrefixes)
+#endif
+
+// Steps without writing, at least one, until a lane is due or the set of lanes that are near
+// changes from none or to none.  Takes run entries where it may.
+__device__ __forceinline__ void step_count(Steps &s, const uint32_t *words, const uint16_t *one, const uint16_t *run,
+                                           const Geometry &g)
+{
+#ifdef __AMDGCN__
+    const uint32_t ahead_at = lds_address(words) + 4u, one_dc = lds_address(one), run_dc = lds_address(run);
+    uint32_t t0, t1, t2, t3;
+    uint64_t m0, m1, m2;
+#define COUNT_ADVANCE                                           \
+    "v_lshlrev_b32 %[t0], 27, %[e]\n"                           \
+    "v_lshrrev_b32 %[t1], 9, %[e]\n"                            \
+    "v_sub_co_u32 %[n32], vcc, %[n32], %[t0]\n"                 \
+    "v_add3_u32 %[k], %[k], %[t1], 1\n"                         \
+    "v_bfe_u32 %[t1], %[next], %[slot], 5\n"                    \
+    "v_lshrrev_b32 %[t0], 27, %[n32]\n"                         \
+    STEP_WORDS                                                  \
+    "v_cmp_lt_i32 %[m0], %[single], %[k]\n"
+    if (!wave_any(s.near())) {
+        asm volatile(
+            ".p2align 5\n"
+            "1:\n"
+            COUNT_ADVANCE
+            STEP_NUMBER
+            "v_max_i32 %[t3], %[t3], %[t2]\n"
+            "v_cndmask_b32 %[t0], %[runac], %[oneac], %[m0]\n"
+            "v_bfe_u32 %[t1], %[chroma], %[slot], 3\n"
+            "v_lshlrev_b32 %[t3], 3, %[t3]\n"
+            "v_cndmask_b32 %[t0], %[t0], %[rundc], vcc\n"
+            "v_addc_co_u32 %[block], %[m2], 0, %[block], vcc\n"
+            "v_add3_u32 %[t3], %[t3], %[t1], %[t0]\n"
+            "ds_read_u16 %[e], %[t3]\n"
+            "v_cndmask_b32 %[k], %[k], -1, vcc\n"
+            STEP_NEAR
+            : STEP_STATE
+            : STEP_GIVEN, [runac] "v"(run_dc + 2u), [rundc] "v"(run_dc), [single] "n"(62 - kRunLead)
+            : "vcc", "scc", "memory");
+        if (s.near()) s.e = look_up(one, s.table(g), s.c.win);
+    } else {
+        uint32_t p;
+        asm volatile(
+            ".p2align 5\n"
+            "2:\n"
+            COUNT_ADVANCE
+            STEP_POSITION
+            STEP_NUMBER
+            "s_or_b64 %[m0], %[m0], %[m1]\n"
+            "v_max_i32 %[t3], %[t3], %[t2]\n"
+            "v_cndmask_b32 %[t0], %[runac], %[oneac], %[m0]\n"
+            "v_cndmask_b32 %[t2], %[rundc], %[onedc], %[m1]\n"
+            "v_bfe_u32 %[t1], %[chroma], %[slot], 3\n"
+            "v_lshlrev_b32 %[t3], 3, %[t3]\n"
+            "v_cndmask_b32 %[t0], %[t0], %[t2], vcc\n"
+            "v_addc_co_u32 %[block], %[m2], 0, %[block], vcc\n"
+            "v_add3_u32 %[t3], %[t3], %[t1], %[t0]\n"
+            "ds_read_u16 %[e], %[t3]\n"
+            "v_cndmask_b32 %[k], %[k], -1, vcc\n"
+            STEP_DUE
+            : STEP_STATE, [p] "=&v"(p)
+            : STEP_GIVEN, [runac] "v"(run_dc + 2u), [rundc] "v"(run_dc), [single] "n"(62 - kRunLead), [end] "v"(s.end_bit), [nb] "v"(s.nb)
+            : "vcc", "scc", "memory");
     }
-    // next restart boundary ahead (bit position), limit_bits if none
-    uint32_t nb = boundary_from(S, after_boundary ? (p >> 3) + 1u : (p + 7u) >> 3, limit_bits);
-    const uint16_t *lut = S.tab.lut;
-    // tb: twice the number of the current table (DC luma 0, AC luma 2, DC chroma 4, AC chroma 6)
-    const uint32_t ac_bit = 2u;
-    uint32_t tb = __builtin_amdgcn_ubfe(g.chroma_at, slot, 3u) | (zz ? ac_bit : 0u);
-    // what a writing pass has to refuse is gathered without branches in the loop: bit 6 of
-    // over = a coefficient index past its block; sign of late = a symbol where a restart marker
-    // had to come; broken = what the rare branches find
-    int32_t late = 0, broken = 0;
-    uint32_t over = 0;
-    // the stream words that hold bit p, the one after, and the one after that, kept in
-    // registers: a symbol is shorter than a word, so at most one new word is needed per
-    // symbol, and it is fetched one symbol ahead of its use
-    uint32_t w = p >> 5;
-    const uint32_t *row = S.clean + clean_row_of_bit(p);  // the span lies in one subsequence
-    uint32_t hi = row[w], lo = row[w + 1];
-    uint32_t ahead = row[w + 2];
-    // look a symbol up: its table entry, or the invalid entry for bits that are no code word
-    // (an error unless they are the padding before a boundary, which the invalid entry is too
-    // long to fit before)
-    auto lookup = [&](uint32_t win) {
-        uint32_t e = first_level(lut, tb, win);
-        if (__builtin_expect((e >> 11) == 0, 0)) {
-            e = second_level(S.tab, e, tb, win);
-            if (__builtin_expect((e >> 11) == 0, 0)) {
-                if (e == kUseLoop) e = lookup_by_search(S.tab, tb >> 1, win);
-                if ((e >> 11) == 0) {
-                    e = kInvalidEntry;
-                    // (a lookup at or past the span's end is the next span's to judge: this
-                    // one's row holds only part of those bits)
-                    if (kWrite && p < end_bit && p + (kInvalidEntry >> 11) <= nb) broken = 1;
-                }
-            }
+#undef COUNT_ADVANCE
+#else
+    do {
+        s.advance(words, g);
+        s.e = look_up(s.near() || s.k > 62 - kRunLead ? one : run, s.table(g), s.c.win);
+    } while (!s.due());
+#endif
+}
+
+// What a writing pass needs besides.
+struct WriteSteps {
+    int16_t *coef;           // the image's first block
+    uint32_t base;           // element for index 0: the block's, or where its DC difference goes
+    uint32_t side;           // element of block 0's DC difference
+    uint32_t last_block;     // of the image: a stream that runs past it goes on there, the count tells
+    uint32_t over;           // bit 6: an index past its block, or bits that are no code
+    int32_t iv_left, late;   // blocks left in the restart interval, less one; sign of late: a symbol after them
+    bool wide;               // elements that a 32-bit byte offset does not reach
+    __device__ __forceinline__ void place(const Steps &s)
+    {
+        const uint32_t here = min(s.block, last_block);
+        base = s.k < 0 ? side + here : here << 6;
+    }
+};
+
+// Steps with writing, symbol by symbol, until a lane is due or, as above, near.  Every symbol stores: ZRL and
+// EOB carry no appended bits, so their value is 0, and it lands on a coefficient that they
+// declare to be zero (the last of ZRL's sixteen, the last of the block for EOB).
+template <bool kRestart>
+__device__ __forceinline__ void step_write(Steps &s, WriteSteps &ws, const uint32_t *words, const uint16_t *one,
+                                           const Geometry &g)
+{
+#ifdef __AMDGCN__
+    const uint32_t ahead_at = lds_address(words) + 4u, one_dc = lds_address(one);
+    uint32_t t0, t1, t2, t3, t4;
+    uint64_t m0, m1, m2;
+#define WRITE_ADVANCE                                           \
+    "v_lshrrev_b32 %[t1], 9, %[e]\n"                            \
+    "v_sub_u32 %[t2], 0, %[e]\n"                                \
+    "v_bfe_u32 %[t3], %[e], 5, 4\n"                             \
+    "v_lshlrev_b32 %[t0], 27, %[e]\n"                           \
+    "v_add3_u32 %[k], %[k], %[t1], 1\n"                         \
+    "v_bfe_i32 %[t2], %[win], %[t2], %[t3]\n"                   \
+    "v_sub_co_u32 %[n32], vcc, %[n32], %[t0]\n"                 \
+    "v_lshlrev_b32 %[t3], %[t3], -1\n"                          \
+    "v_min_i32 %[t1], 63, %[k]\n"                               \
+    "v_ashrrev_i32 %[t4], 31, %[t2]\n"                          \
+    "v_lshrrev_b32 %[t0], 27, %[n32]\n"                         \
+    "v_xor_b32 %[t3], %[t3], %[t4]\n"                           \
+    "v_add_lshl_u32 %[t1], %[t1], %[base], 1\n"                 \
+    "v_add3_u32 %[t4], %[t2], %[t3], 1\n"                       \
+    "v_or_b32 %[over], %[over], %[k]\n"                         \
+    "global_store_short %[t1], %[t4], %[coef]\n"                \
+    STEP_WORDS                                                  \
+    "v_bfe_u32 %[t1], %[next], %[slot], 5\n"
+#define WRITE_NUMBER                                            \
+    STEP_NUMBER                                                 \
+    "v_addc_co_u32 %[block], %[m2], 0, %[block], vcc\n"         \
+    "v_max_i32 %[t3], %[t3], %[t2]\n"                           \
+    "v_cndmask_b32 %[t0], %[oneac], %[onedc], vcc\n"            \
+    "v_bfe_u32 %[t1], %[chroma], %[slot], 3\n"                  \
+    "v_lshlrev_b32 %[t3], 3, %[t3]\n"                           \
+    "v_min_u32 %[t2], %[block], %[lastblock]\n"                 \
+    "v_add3_u32 %[t3], %[t3], %[t1], %[t0]\n"                   \
+    "ds_read_u16 %[e], %[t3]\n"                                 \
+    "v_lshlrev_b32 %[base], 6, %[t2]\n"                         \
+    "v_add_u32 %[t2], %[side], %[t2]\n"                         \
+    "v_cndmask_b32 %[k], %[k], -1, vcc\n"                       \
+    "v_cndmask_b32 %[base], %[base], %[t2], vcc\n"
+#define WRITE_INTERVAL                                          \
+    "v_or_b32 %[late], %[late], %[left]\n"                      \
+    "v_subb_co_u32 %[left], %[m2], %[left], 0, vcc\n"
+#define WRITE_STATE STEP_STATE, [t4] "=&v"(t4), [base] "+v"(ws.base), [over] "+v"(ws.over)
+#define WRITE_GIVEN STEP_GIVEN, [coef] "s"(ws.coef), [lastblock] "v"(ws.last_block), [side] "v"(ws.side)
+    if (!ws.wide) {
+        if (!wave_any(s.near())) {
+            if constexpr (kRestart)
+                asm volatile(".p2align 5\n"
+                             "1:\n" WRITE_ADVANCE WRITE_NUMBER WRITE_INTERVAL STEP_NEAR
+                             : WRITE_STATE, [late] "+v"(ws.late), [left] "+v"(ws.iv_left)
+                             : WRITE_GIVEN
+                             : "vcc", "scc", "memory");
+            else
+                asm volatile(".p2align 5\n"
+                             "1:\n" WRITE_ADVANCE WRITE_NUMBER STEP_NEAR
+                             : WRITE_STATE
+                             : WRITE_GIVEN
+                             : "vcc", "scc", "memory");
+        } else {
+            uint32_t p;
+            if constexpr (kRestart)
+                asm volatile(".p2align 5\n"
+                             "2:\n" WRITE_ADVANCE STEP_POSITION WRITE_NUMBER WRITE_INTERVAL STEP_DUE
+                             : WRITE_STATE, [late] "+v"(ws.late), [left] "+v"(ws.iv_left), [p] "=&v"(p)
+                             : WRITE_GIVEN, [end] "v"(s.end_bit), [nb] "v"(s.nb)
+                             : "vcc", "scc", "memory");
+            else
+                asm volatile(".p2align 5\n"
+                             "2:\n" WRITE_ADVANCE STEP_POSITION WRITE_NUMBER STEP_DUE
+                             : WRITE_STATE, [p] "=&v"(p)
+                             : WRITE_GIVEN, [end] "v"(s.end_bit), [nb] "v"(s.nb)
+                             : "vcc", "scc", "memory");
         }
-        return e;
-    };
-    if (p < end_bit) {
-        uint32_t win = window_at(hi, lo, p);
-        uint32_t e = lookup(win);
-        do {
-            const uint32_t adv = e >> 11;
-            if (__builtin_expect(p + adv > nb, 0)) {
-                // the symbol does not fit before the next restart boundary / the end of the data
-                if (nb >= limit_bits) {
-                    if (kWrite && (slot != 0 || zz != 0 || limit_bits - p >= 8)) broken = 1;
-                    p = limit_bits;  // >= end_bit: the lane is done
-                } else {
-                    if (kWrite) {
-                        // a boundary comes between MCUs, behind fewer than eight padding bits,
-                        // and after a whole interval (or right where one has just begun)
-                        if (slot != 0 || zz != 0 || nb - p >= 8 || g.ri_blocks == 0 ||
-                            (iv_rem != 0 && iv_rem != (int32_t)g.ri_blocks))
-                            broken = 1;
-                        iv_rem = (int32_t)g.ri_blocks;
-                    }
-                    p = nb;
-                    slot = 0;
-                    zz = 0;
-                    tb = 0;
-                    nb = boundary_from(S, (p >> 3) + 1u, limit_bits);
-                    w = p >> 5;
-                    hi = row[w];
-                    lo = row[w + 1];
-                    ahead = row[w + 2];
+        return;
+    }
+#undef WRITE_ADVANCE
+#undef WRITE_NUMBER
+#undef WRITE_INTERVAL
+#undef WRITE_STATE
+#undef WRITE_GIVEN
+#endif
+    do {
+        const int32_t value = coefficient_value(s.c.win, entry_bits(s.e), entry_appended(s.e));
+        if (kRestart) ws.late |= ws.iv_left;
+        const int32_t at = s.advance(words, g);
+        if (kRestart) ws.iv_left -= at >= 63 ? 1 : 0;
+        ws.coef[ws.base + (uint32_t)min(at, 63)] = (int16_t)value;
+        ws.over |= (uint32_t)at;
+        ws.place(s);
+        s.e = look_up(one, s.table(g), s.c.win);
+    } while (!s.due());
+}
+
+// Decode from packed state `st` until the bit position reaches end_bit, without writing.
+// words = the stream (word w at words[w]), limit_bits = end of its data.  Returns the end state;
+// *nblk = blocks completed.  A symbol that does not fit before the end of the data is padding: the
+// position becomes limit_bits then.  kRestart: the same before the next restart boundary (S lists
+// them), where the lane steps over the boundary and goes on.
+// run = the table of run entries, or that of single ones where there is none.
+// (A run's last symbol, or one that is only counted, may reach past the boundary or the end of the
+// data: then it did not fit.  No sound stream holds such a symbol there, with ten bits and more left.)
+template <bool kRestart, typename Shared>
+__device__ __forceinline__ uint32_t count_span(const Shared &S, const uint32_t *words, const uint16_t *run,
+                                               const Geometry &g, uint32_t st, uint32_t end_bit, uint32_t limit_bits,
+                                               uint32_t *nblk)
+{
+    const uint16_t *one = S.tab.one;
+    uint32_t p = st >> 9;
+    Steps s;
+    s.slot = slot_of_block((st >> 6) & 7u);
+    s.k = (int32_t)(st & 63u) - 1;
+    s.block = 0;
+    s.end_bit = end_bit;
+    s.nb = limit_bits;
+    if constexpr (kRestart) s.nb = boundary_from(S, (p + 7u) >> 3, limit_bits);
+    // far away, all symbols of a run but the last end before the span does
+    auto near_from = [&]() { return ((int32_t)(min(s.end_bit, s.nb) - kRunLeadBits - 1u) >> 5) + 1; };
+    s.near_w = near_from();
+    s.c.start(words, p);
+    s.e = look_up(s.near() || s.k > 62 - kRunLead ? one : run, s.table(g), s.c.win);
+    for (;;) {
+        if (s.e == kSearchEntry) s.e = lookup_by_search(S.tab, s.table(g) >> 1, s.c.win);
+        if (s.near()) {
+            p = s.c.position();
+            while (p > s.nb || (p < end_bit && p + entry_bits(s.e) > s.nb)) {
+                if (!kRestart || s.nb >= limit_bits) {
+                    p = limit_bits;
+                    break;
                 }
-            } else {
-                const uint32_t k = zz + ((e >> 4) & 127u);  // index of the symbol's coefficient
-                if (kWrite) {
-                    // Every symbol stores.  ZRL and EOB carry no appended bits, so their value
-                    // is 0, and it lands on a coefficient that they declare to be zero: the
-                    // last of ZRL's sixteen, the last of the block for EOB.  A stream that runs
-                    // past the image keeps overwriting the image's last coefficient; the block
-                    // count then gives it away.
-                    // A DC difference goes to the block's entry of the side array (dc_prefix turns
-                    // the differences into values and puts those into the blocks).
-                    const uint32_t ci = min(boff + min(k, 63u), last);
-                    wc->coef[zz == 0 ? wc->side_rel + (ci >> 6) : ci] = (int16_t)coefficient_value(win, adv, e & 15u);
-                    over |= k;
-                    late |= iv_rem - 1;
-                }
-                p += adv;
-                {
-                    const bool moved = (p >> 5) != w;
-                    hi = moved ? lo : hi;
-                    lo = moved ? ahead : lo;
-                    w += moved ? 1u : 0u;
-                    ahead = row[w + 2];
-                }
-                const bool endb = k >= 63u;  // zz = k + 1 reaches 64
-                const uint32_t slot1 = __builtin_amdgcn_ubfe(g.next_slot, slot, 5u);
-                zz = endb ? 0u : k + 1u;
-                slot = endb ? slot1 : slot;
-                done += endb ? 1u : 0u;
-                tb = endb ? __builtin_amdgcn_ubfe(g.chroma_at, slot1, 3u) : tb | ac_bit;
-                if (kWrite) {
-                    boff += endb ? 64u : 0u;
-                    iv_rem -= endb ? 1 : 0;
+                if constexpr (kRestart) {
+                    p = s.nb;
+                    s.slot = 0;
+                    s.k = -1;
+                    s.nb = boundary_from(S, (p >> 3) + 1u, limit_bits);
+                    s.near_w = near_from();
+                    s.c.start(words, p);
+                    s.e = look_up(one, 0, s.c.win);
+                    if (s.e == kSearchEntry) s.e = lookup_by_search(S.tab, 0, s.c.win);
                 }
             }
-            // the next symbol's lookup, issued before the loop test
-            win = window_at(hi, lo, p);
-            e = lookup(win);
-        } while (p < end_bit);
+            if (p >= end_bit) break;
+        }
+        step_count(s, words, one, run, g);
     }
-    if (kWrite) wc->bad |= broken | (late < 0 ? 1 : 0) | (int32_t)((over >> 6) & 1u);
-    *nblk = done;
-    return pack_state(p, block_of_slot(slot), zz);
+    *nblk = s.block;
+    return pack_state(p, block_of_slot(s.slot), (uint32_t)(s.k + 1));
+}
+
+// The same with writing: single symbols, exact at every one.  DC *differences* go to the image's
+// side array, one entry per block (dc_prefix turns them into values and puts those into the
+// blocks).  Refuses (wc->bad) what a sound stream cannot hold.
+// Where the end of the span is the end of its restart interval, kRestart = false and limit_bits =
+// end_bit do.
+template <bool kRestart, typename Shared>
+__device__ __forceinline__ uint32_t write_span(const Shared &S, const uint32_t *words, const Geometry &g, uint32_t st,
+                                               uint32_t end_bit, uint32_t limit_bits, uint32_t *nblk, WriteCtx *wc)
+{
+    const uint16_t *one = S.tab.one;
+    uint32_t p = st >> 9;
+    int32_t broken = 0;
+    Steps s;
+    s.slot = slot_of_block((st >> 6) & 7u);
+    s.k = (int32_t)(st & 63u) - 1;
+    s.block = wc->block;
+    s.end_bit = end_bit;
+    s.nb = limit_bits;
+    if constexpr (kRestart) s.nb = boundary_from(S, (p + 7u) >> 3, limit_bits);
+    // far away, any symbol ends before the span does (31 bits at most)
+    auto near_from = [&]() { return ((int32_t)(min(s.end_bit, s.nb) - 32u) >> 5) + 1; };
+    s.near_w = near_from();
+    WriteSteps ws;
+    ws.coef = wc->coef;
+    ws.side = wc->side_rel;
+    ws.last_block = g.n_blocks - 1u;
+    ws.over = 0;
+    ws.iv_left = kRestart ? wc->iv_rem - 1 : 0;
+    ws.late = 0;
+    ws.wide = (((uint64_t)wc->side_rel + g.n_blocks) >> 31) != 0 || ((uint64_t)g.n_blocks >> 25) != 0;
+    ws.place(s);
+    s.c.start(words, p);
+    s.e = look_up(one, s.table(g), s.c.win);
+    for (;;) {
+        if (s.e == kSearchEntry) s.e = lookup_by_search(S.tab, s.table(g) >> 1, s.c.win);
+        if (s.near()) {
+            p = s.c.position();
+            while (p < end_bit && p + entry_bits(s.e) > s.nb) {
+                if (!kRestart || s.nb >= limit_bits) {
+                    // what is left is padding: fewer than eight bits, between MCUs
+                    if (s.slot != 0 || s.k >= 0 || limit_bits - p >= 8) broken = 1;
+                    p = limit_bits;
+                    break;
+                }
+                if constexpr (kRestart) {
+                    // a boundary comes between MCUs, behind fewer than eight padding bits,
+                    // and after a whole interval (or right where one has just begun)
+                    if (s.slot != 0 || s.k >= 0 || s.nb - p >= 8 || g.ri_blocks == 0 ||
+                        (ws.iv_left != -1 && ws.iv_left != (int32_t)g.ri_blocks - 1))
+                        broken = 1;
+                    ws.iv_left = (int32_t)g.ri_blocks - 1;
+                    p = s.nb;
+                    s.slot = 0;
+                    s.k = -1;
+                    s.nb = boundary_from(S, (p >> 3) + 1u, limit_bits);
+                    s.near_w = near_from();
+                    ws.place(s);
+                    s.c.start(words, p);
+                    s.e = look_up(one, 0, s.c.win);
+                    if (s.e == kSearchEntry) s.e = lookup_by_search(S.tab, 0, s.c.win);
+                }
+            }
+            if (p >= end_bit) break;
+        }
+        if (s.e == kInvalidDcEntry) broken = 1;
+        step_write<kRestart>(s, ws, words, one, g);
+    }
+#ifdef __AMDGCN__
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores that the compiler has not seen
+#endif
+    wc->bad |= broken | (ws.late < 0 ? 1 : 0) | (int32_t)((ws.over >> 6) & 1u);
+    *nblk = s.block - wc->block;
+    return pack_state(p, block_of_slot(s.slot), (uint32_t)(s.k + 1));
 }
 
 // Zeros over the blocks [lo, hi) of an image whose coefficients begin at coef, in 16-byte units
@@ -581,86 +916,6 @@ __device__ __attribute__((noinline)) void zero_blocks(int16_t *coef, uint32_t lo
 {
     uint4 *units = reinterpret_cast<uint4 *>(coef);  // eight to a block
     for (uint32_t u = lo * 8u + first; u < hi * 8u; u += step) units[u] = make_uint4(0, 0, 0, 0);
-}
-
-// The short-interval pass: one lane decodes one restart interval from its start state to
-// end_bit, which is the next restart boundary (or the end of the data), and writes its
-// coefficients.  Same symbol loop as decode_span, specialised for what that pass knows: the
-// span's end and the next boundary are the same position, so the loop ends where a symbol no
-// longer fits and never steps over a boundary; the stream is staged without pad words; and
-// the caller's count of the interval's blocks stands in for the running check against
-// restart intervals.  Returns the end state (at end_bit if the stream is sound).
-__device__ __forceinline__ uint32_t decode_interval(const DecodeShared &S, const Geometry &g, uint32_t st,
-                                                    uint32_t end_bit, uint32_t *nblk, WriteCtx *wc)
-{
-    uint32_t p = st >> 9, slot = slot_of_block((st >> 6) & 7u);
-    // Where the next symbol starts counting, as one number: 64 * (block of the image) + zig-zag
-    // index.  A symbol's coefficient index is clamped to 63, so one past the coefficient of a
-    // symbol that ends its block is the first coefficient of the next block by itself.  The
-    // count of completed blocks is how far the block has moved at the end.
-    const uint32_t first_block = wc->block;
-    uint32_t at = (first_block << 6) | (st & 63u);
-    const uint32_t last = g.n_blocks * 64u - 1u;
-    const uint16_t *lut = S.tab.lut;
-    const uint32_t ac_bit = 2u;  // tb: twice the number of the current table, see decode_span
-    uint32_t tb = __builtin_amdgcn_ubfe(g.chroma_at, slot, 3u) | ((st & 63u) ? ac_bit : 0u);
-    int32_t broken = 0;
-    uint32_t over = 0;
-    uint32_t w = p >> 5;
-    uint32_t hi = S.clean[w], lo = S.clean[w + 1], ahead = S.clean[w + 2];
-    // look a symbol up: its table entry, or the invalid entry for bits that are no code word
-    // (an error unless they are the padding before the boundary, which the invalid entry is too
-    // long to fit before)
-    auto lookup = [&](uint32_t win) {
-        uint32_t e = first_level(lut, tb, win);
-        if (__builtin_expect((e >> 11) == 0, 0)) {
-            e = second_level(S.tab, e, tb, win);
-            if (__builtin_expect((e >> 11) == 0, 0)) {
-                if (e == kUseLoop) e = lookup_by_search(S.tab, tb >> 1, win);
-                if ((e >> 11) == 0) {
-                    e = kInvalidEntry;
-                    if (p + (kInvalidEntry >> 11) <= end_bit) broken = 1;
-                }
-            }
-        }
-        return e;
-    };
-    uint32_t win = window_at(hi, lo, p);
-    uint32_t e = lookup(win);
-    // the loop runs while the symbol that was looked up fits before the end: what does not fit
-    // is padding, or nothing at all
-    while (p + (e >> 11) <= end_bit) {
-        const uint32_t adv = e >> 11;
-        const uint32_t k = (at & 63u) + ((e >> 4) & 127u);  // index of the symbol's coefficient
-        // every symbol stores (see decode_span)
-        // (k = 0 is a DC difference: it goes to the side array)
-        const uint32_t here = (at & ~63u) | min(k, 63u);
-        const uint32_t ci = min(here, last);
-        wc->coef[k == 0 ? wc->side_rel + (ci >> 6) : ci] = (int16_t)coefficient_value(win, adv, e & 15u);
-        at = here + 1u;
-        over |= k;
-        p += adv;
-        {
-            const bool moved = (p >> 5) != w;
-            hi = moved ? lo : hi;
-            lo = moved ? ahead : lo;
-            w += moved ? 1u : 0u;
-            ahead = S.clean[w + 2];
-        }
-        const bool endb = k >= 63u;  // the zig-zag index reaches 64
-        const uint32_t slot1 = __builtin_amdgcn_ubfe(g.next_slot, slot, 5u);
-        slot = endb ? slot1 : slot;
-        tb = endb ? __builtin_amdgcn_ubfe(g.chroma_at, slot1, 3u) : tb | ac_bit;
-        win = window_at(hi, lo, p);
-        e = lookup(win);
-    }
-    // the lane must stand between MCUs, fewer than eight (padding) bits before the end
-    const uint32_t zz = at & 63u;
-    if (slot != 0 || zz != 0 || end_bit - p >= 8) broken = 1;
-    else p = end_bit;
-    wc->bad |= broken | (int32_t)((over >> 6) & 1u);
-    *nblk = (at >> 6) - first_block;
-    return pack_state(p, block_of_slot(slot), zz);
 }
 
 // DC differences -> DC values (T.81 F.2.2.1) for blocks [lo, hi) of the image, by the whole
@@ -816,23 +1071,25 @@ __global__ __launch_bounds__(kDecodeThreads) void scan_restart_markers(
         const uint32_t slot = (wg - n_windows) >> 2;
         const int t = (int)((wg - n_windows) & 3u);
         const ImageRec &I = recs[table_rep[slot]];
-        build_tables(tab, bits + I.file_off, I, t, t + 1);
+        build_tables(tab, bits + I.file_off, I, t, (t | 1) + 1);
+        build_runs(tab, t, t + 1);
         const uint32_t *src = reinterpret_cast<const uint32_t *>(&tab);
         uint32_t *dst = reinterpret_cast<uint32_t *>(tables) + (size_t)slot * (sizeof(HuffTables) / 4);
         // the members of table t, as 32-bit words of the struct
-        // (its first-level entries lie among the other tables': they go one by one)
-        uint16_t *dst_lut = reinterpret_cast<uint16_t *>(dst + offsetof(HuffTables, lut) / 4);
-        for (uint32_t i = threadIdx.x; i < (1u << kLutBits); i += kT)
-            dst_lut[(i << 2) | (uint32_t)t] = tab.lut[(i << 2) | (uint32_t)t];
-        const uint32_t part[6][2] = {
-            {(uint32_t)offsetof(HuffTables, sub) + (uint32_t)t * 2u * kSubEntries, 2u * kSubEntries},
-            {(uint32_t)offsetof(HuffTables, first) + (uint32_t)t * 68u, 68u},
-            {(uint32_t)offsetof(HuffTables, count) + (uint32_t)t * 68u, 68u},
-            {(uint32_t)offsetof(HuffTables, valptr) + (uint32_t)t * 68u, 68u},
-            {(uint32_t)offsetof(HuffTables, huffval) + (uint32_t)t * 256u, 256u},
-            {(uint32_t)offsetof(HuffTables, sub_used) + (uint32_t)t * 4u, 4u}};
+        // (its entries lie among the other tables': they go one by one)
+        uint16_t *dst_one = reinterpret_cast<uint16_t *>(dst + offsetof(HuffCodes, one) / 4);
+        uint16_t *dst_run = reinterpret_cast<uint16_t *>(dst + sizeof(HuffCodes) / 4);
+        for (uint32_t i = threadIdx.x; i < kLookupEntries; i += kT) {
+            dst_one[(i << 2) | (uint32_t)t] = tab.one[(i << 2) | (uint32_t)t];
+            dst_run[(i << 2) | (uint32_t)t] = tab.run[(i << 2) | (uint32_t)t];
+        }
+        const uint32_t part[4][2] = {
+            {(uint32_t)offsetof(HuffCodes, first) + (uint32_t)t * 68u, 68u},
+            {(uint32_t)offsetof(HuffCodes, count) + (uint32_t)t * 68u, 68u},
+            {(uint32_t)offsetof(HuffCodes, valptr) + (uint32_t)t * 68u, 68u},
+            {(uint32_t)offsetof(HuffCodes, huffval) + (uint32_t)t * 256u, 256u}};
 #pragma unroll
-        for (int m = 0; m < 6; m++)
+        for (int m = 0; m < 4; m++)
             for (uint32_t i = threadIdx.x; i < part[m][1] / 4; i += kT)
                 dst[part[m][0] / 4 + i] = src[part[m][0] / 4 + i];
         return;
@@ -899,14 +1156,15 @@ __global__ __launch_bounds__(kDecodeThreads) void scan_restart_markers(
 // subsequence is decoded once from each place-in-MCU hypothesis by a lane of its own (the chip
 // is idle otherwise), and once more from the end states those lanes reached in the subsequence
 // before; the true chain then only picks, link by link, the candidate that it equals.
-template <bool kHyp>
-__global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
+template <bool kHyp, bool kRuns>
+__global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
     const uint8_t *__restrict__ bits, const ImageRec *__restrict__ recs, int n_images,
     const uint32_t *__restrict__ win_count, const uint32_t *__restrict__ win_first,
     const uint32_t *__restrict__ data_end, const uint32_t *__restrict__ retry, int16_t *__restrict__ coef_all,
     uint32_t side_off, int32_t *__restrict__ status, const uint4 *__restrict__ tables, uint32_t hyp_span_bits)
 {
-    __shared__ DecodeShared S;
+    __shared__ DecodeShared<kHyp, kRuns> S;
+    const uint16_t *const runs = run_entries(S.tab);
     const int tid = threadIdx.x;
     const uint32_t wg = blockIdx.x;
     const int img = find_image(n_images, wg, [&](int i) { return recs[i].window0; });
@@ -986,12 +1244,11 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
     const uint8_t *file = bits + R.file_off;
     if (R.table_slot != kNoTableSlot) {
         // the tables were expanded once for the batch: copy them
-        constexpr uint32_t units = sizeof(HuffTables) / 16;
-        uint4 *dst = reinterpret_cast<uint4 *>(&S.tab);
-        for (uint32_t i = tid; i < units; i += kT) dst[i] = tables[(size_t)R.table_slot * units + i];
+        load_tables(S.tab, tables, R.table_slot);
         __syncthreads();
     } else {
         build_tables(S.tab, file, R);
+        if constexpr (kRuns) build_runs(S.tab);
     }
 
     const uint8_t *seg = file + R.entropy_rel;
@@ -1060,7 +1317,6 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
                                                 S.scan_a, &totals);
         const uint32_t clean_len = totals & 0xFFFFu, nbnd = totals >> 16;
         const uint32_t my_off = my_pre & 0xFFFFu;
-        S.keep[tid] = keep;
         S.keep_off[tid] = my_off;
         if (tid == 0) S.keep_off[kT] = clean_len;
         // zeros behind the data: the last word is written byte by byte, and lookups near the
@@ -1076,6 +1332,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
                                      nbnd <= (uint32_t)kMaxBoundaries && clean_len <= kShortInterval * (nbnd + 1);
         // the short-interval pass reads the stream without pad words (its lanes start anywhere)
         const uint32_t pad_shift = short_intervals ? 31u : (uint32_t)kPadShift;
+        if (!short_intervals) S.keep(tid) = keep;
         // zeros behind the data: the last word is written byte by byte, and lookups near the
         // end read a few words past it
         {
@@ -1101,7 +1358,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
                         // marker number marker_base + rank of the image must be RST((that) mod 8)
                         if ((((wv[i >> 2] >> (8 * (i & 3))) ^ (marker_base + rank)) & 7u) != 0) bad = 1;
                         atomicOr(&S.bmask[o >> 5], 1u << (o & 31));
-                        if (rank < (uint32_t)kMaxBoundaries) S.bpos[rank] = (uint16_t)o;
+                        if (short_intervals) S.bpos[rank] = (uint16_t)o;  // (at most kMaxBoundaries then)
                         // raw offset just after the last marker of the chunk: where a chunk of
                         // whole intervals would resume
                         if (rank + 1 == nbnd) S.bcast[2] = (uint32_t)(my_lo + 16 * k + i + 1);
@@ -1165,7 +1422,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
                 const uint32_t want = min(k ? g.ri_blocks : rem0, block_end > blk0 ? block_end - blk0 : 0u);
                 wc.block = blk0;
                 uint32_t got;
-                const uint32_t fin = decode_interval(S, g, start, end_bit, &got, &wc);
+                const uint32_t fin = write_span<false>(S, S.clean, g, start, end_bit, end_bit, &got, &wc);
                 // the interval must end on its boundary, between MCUs, with exactly its blocks
                 if (got != want || (fin & 511u) != 0 || (fin >> 9) != end_bit) wc.bad = 1;
             }
@@ -1244,7 +1501,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
                                                         : cand[(uint32_t)tid - H];
                         uint32_t to = from, nb = 0;
                         // (a state past the subsequence's end: the lane before ran through it)
-                        if ((from >> 9) < s_end) to = decode_span<false>(S, g, from, false, s_end, limit_bits, &nb, nullptr);
+                        if ((from >> 9) < s_end) to = count_span<true>(S, S.clean + clean_row_of_bit(from >> 9), runs, g, from, s_end, limit_bits, &nb);
                         if (pass == 0) cand[tid] = to;
                         if (pass == 1 || j == 0) { next[tid] = to; hyp_blocks[tid] = (uint16_t)nb; }
                     }
@@ -1274,7 +1531,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
                     if (j == r) {
                         const uint32_t from = next[(r - 1u) * H + chosen[r - 1u]];
                         uint32_t to = from, nb = 0;
-                        if ((from >> 9) < s_end) to = decode_span<false>(S, g, from, false, s_end, limit_bits, &nb, nullptr);
+                        if ((from >> 9) < s_end) to = count_span<true>(S, S.clean + clean_row_of_bit(from >> 9), runs, g, from, s_end, limit_bits, &nb);
                         next[tid] = to;
                         hyp_blocks[tid] = (uint16_t)nb;
                     }
@@ -1296,7 +1553,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
             if (!active) S.state[tid] = out_state;
         } else {
         // synchronise: iterate end states to their fixed point
-        if (active) out_state = decode_span<false>(S, g, in_state, false, end_bit, limit_bits, &nblk, nullptr);
+        if (active) out_state = count_span<true>(S, S.clean + clean_row_of_bit(in_state >> 9), runs, g, in_state, end_bit, limit_bits, &nblk);
         S.state[tid] = out_state;
         for (uint32_t round = 0; round <= nsub; round++) {
             __syncthreads();
@@ -1307,7 +1564,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
                 in_state = prev_state;
                 uint32_t o = in_state;
                 // a predecessor that already ran past my subsequence leaves me nothing to decode
-                if ((in_state >> 9) < end_bit) o = decode_span<false>(S, g, in_state, false, end_bit, limit_bits, &nblk, nullptr);
+                if ((in_state >> 9) < end_bit) o = count_span<true>(S, S.clean + clean_row_of_bit(in_state >> 9), runs, g, in_state, end_bit, limit_bits, &nblk);
                 else nblk = 0;
                 if (o != out_state) { out_state = o; changed = 1; }
                 S.state[tid] = out_state;
@@ -1338,7 +1595,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
         uint32_t final_state = out_state;
         if (active && (in_state >> 9) < end_bit) {
             uint32_t nb2;
-            final_state = decode_span<true>(S, g, in_state, false, end_bit, limit_bits, &nb2, &wc);
+            final_state = write_span<true>(S, S.clean + clean_row_of_bit(in_state >> 9), g, in_state, end_bit, limit_bits, &nb2, &wc);
             if (final_state != out_state || nb2 != nblk) wc.bad = 1;
         }
         bad |= wc.bad;
@@ -1377,8 +1634,8 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_entropy(
                 atomicAdd(&S.bcast[3], qc - first >= 63u ? (uint32_t)__popcll(m)
                                                          : (uint32_t)__popcll(m & ((2ull << (qc - first)) - 1ull)));
         }
-        if (S.keep_off[tid] <= qc && qc < S.keep_off[tid] + (uint32_t)__popcll(S.keep[tid])) {
-            unsigned long long m = S.keep[tid];
+        if (S.keep_off[tid] <= qc && qc < S.keep_off[tid] + (uint32_t)__popcll(S.keep(tid))) {
+            unsigned long long m = S.keep(tid);
             const uint32_t skip = qc - S.keep_off[tid];
             for (uint32_t i = 0; i < skip; i++) m &= m - 1;  // drop the lowest set bits
             S.bcast[1] = (uint32_t)(my_lo + (int32_t)__builtin_ctzll(m));
@@ -1453,9 +1710,10 @@ static_assert(stream_rows(1) <= stream_rows(3) && stream_rows(4) <= stream_rows(
 static_assert(kStreamWords * 32 < (1 << (kStateBits - 9)) && kStreamMaxRows < (1 << (32 - kStateBits)) && kStreamExtras == 128,
               "a state and its row fit a key, and the table's size wraps by a mask");
 
+template <typename Tables>
 struct StreamShared {
     uint32_t clean[kStreamWords];    // the window's bytes without stuffing, big-endian packed
-    HuffTables tab;
+    Tables tab;
     uint32_t scan_a[kT / 64 + 1];
     uint32_t bcast[4];
 };
@@ -1469,7 +1727,8 @@ struct StreamPart {                  // what staging found
 
 // Stage the raw bytes [w * step, (w + 1) * step) of the segment and enough after them for the
 // overlap rows into S.clean.  All lanes must call.
-__device__ inline StreamPart stage_stream(StreamShared &S, const uint8_t *seg, uint32_t data_len, uint32_t w,
+template <typename Tables>
+__device__ inline StreamPart stage_stream(StreamShared<Tables> &S, const uint8_t *seg, uint32_t data_len, uint32_t w,
                                           uint32_t step, uint32_t row_bytes)
 {
     const int tid = threadIdx.x;
@@ -1555,76 +1814,6 @@ struct StreamRows {
     __device__ inline uint32_t end(uint32_t j) const { return 8u * (j < n_own ? min((j + 1u) * row_bytes, own) : min(own + (j - n_own + 1u) * row_bytes, total)); }
 };
 
-// Decode from packed state `st` until the bit position reaches end_bit, or to limit_bits where no
-// further symbol fits before it (the padding at the end of the data).  The symbol loop of
-// decode_interval for a stream without restart boundaries.  Returns the end state.
-template <bool kWrite>
-__device__ __forceinline__ uint32_t decode_row(const StreamShared &S, const Geometry &g, uint32_t st, uint32_t end_bit,
-                                               uint32_t limit_bits, uint32_t *nblk, WriteCtx *wc)
-{
-    uint32_t p = st >> 9, slot = slot_of_block((st >> 6) & 7u);
-    const uint32_t first_block = kWrite ? wc->block : 0u;
-    uint32_t at = (first_block << 6) | (st & 63u);
-    const uint32_t last = kWrite ? g.n_blocks * 64u - 1u : 0u;
-    const uint16_t *lut = S.tab.lut;
-    const uint32_t ac_bit = 2u;  // tb: twice the number of the current table, see decode_span
-    uint32_t tb = __builtin_amdgcn_ubfe(g.chroma_at, slot, 3u) | ((st & 63u) ? ac_bit : 0u);
-    int32_t broken = 0;
-    uint32_t over = 0;
-    uint32_t w = p >> 5;
-    uint32_t hi = S.clean[w], lo = S.clean[w + 1], ahead = S.clean[w + 2];
-    auto lookup = [&](uint32_t win) {
-        uint32_t e = first_level(lut, tb, win);
-        if (__builtin_expect((e >> 11) == 0, 0)) {
-            e = second_level(S.tab, e, tb, win);
-            if (__builtin_expect((e >> 11) == 0, 0)) {
-                if (e == kUseLoop) e = lookup_by_search(S.tab, tb >> 1, win);
-                if ((e >> 11) == 0) {
-                    e = kInvalidEntry;
-                    if (kWrite && p < end_bit && p + (kInvalidEntry >> 11) <= limit_bits) broken = 1;
-                }
-            }
-        }
-        return e;
-    };
-    uint32_t win = window_at(hi, lo, p);
-    uint32_t e = lookup(win);
-    while (p < end_bit && p + (e >> 11) <= limit_bits) {
-        const uint32_t adv = e >> 11;
-        const uint32_t k = (at & 63u) + ((e >> 4) & 127u);  // index of the symbol's coefficient
-        const uint32_t here = (at & ~63u) | min(k, 63u);
-        if (kWrite) {
-            // every symbol stores (see decode_span); k = 0 is a DC difference: it goes to the side array
-            const uint32_t ci = min(here, last);
-            wc->coef[k == 0 ? wc->side_rel + (ci >> 6) : ci] = (int16_t)coefficient_value(win, adv, e & 15u);
-            over |= k;
-        }
-        at = here + 1u;
-        p += adv;
-        {
-            const bool moved = (p >> 5) != w;
-            hi = moved ? lo : hi;
-            lo = moved ? ahead : lo;
-            w += moved ? 1u : 0u;
-            ahead = S.clean[w + 2];
-        }
-        const bool endb = k >= 63u;  // the zig-zag index reaches 64
-        const uint32_t slot1 = __builtin_amdgcn_ubfe(g.next_slot, slot, 5u);
-        slot = endb ? slot1 : slot;
-        tb = endb ? __builtin_amdgcn_ubfe(g.chroma_at, slot1, 3u) : tb | ac_bit;
-        win = window_at(hi, lo, p);
-        e = lookup(win);
-    }
-    if (p < end_bit) {
-        // what is left is padding: fewer than eight bits, between MCUs
-        if (kWrite && (slot != 0 || (at & 63u) != 0 || limit_bits - p >= 8)) broken = 1;
-        p = limit_bits;
-    }
-    if (kWrite) wc->bad |= broken | (int32_t)((over >> 6) & 1u);
-    *nblk = (at >> 6) - first_block;
-    return pack_state(p, block_of_slot(slot), at & 63u);
-}
-
 __device__ inline void stream_geometry(Geometry &g, const ImageRec &R)
 {
     g.bpm = R.blocks_per_mcu;
@@ -1632,14 +1821,6 @@ __device__ inline void stream_geometry(Geometry &g, const ImageRec &R)
     g.ri_blocks = 0;
     g.set_slots();
     g.n_blocks = R.n_blocks;
-}
-
-// the expanded tables of an image with a table slot, into LDS (a barrier has to follow)
-__device__ inline void load_tables(HuffTables &tab, const uint4 *__restrict__ tables, uint32_t slot)
-{
-    constexpr uint32_t units = sizeof(HuffTables) / 16;
-    uint4 *dst = reinterpret_cast<uint4 *>(&tab);
-    for (uint32_t i = threadIdx.x; i < units; i += kT) dst[i] = tables[(size_t)slot * units + i];
 }
 
 // image of stream window wg: the last one whose first window does not exceed it (images without
@@ -1668,7 +1849,7 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
     const uint32_t *__restrict__ data_end, uint32_t *__restrict__ retry, const uint4 *__restrict__ tables,
     StreamWindow *__restrict__ windows)
 {
-    __shared__ StreamShared S;
+    __shared__ StreamShared<HuffTables> S;
     __shared__ uint32_t cand[kT];              // end states of pass 0
     __shared__ uint32_t node_end[kStreamNodes];
     __shared__ uint16_t node_blocks[kStreamNodes], node_next[kStreamNodes];
@@ -1702,7 +1883,7 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
     const bool mine = j < rows.n && j < stream_rows(H);
     uint32_t state = 0, nb = 0;
     if (mine) {
-        state = decode_row<false>(S, g, pack_state(rows.start(j), h, 0), rows.end(j), rows.limit_bits, &nb, nullptr);
+        state = count_span<false>(S, S.clean, S.tab.run, g, pack_state(rows.start(j), h, 0), rows.end(j), rows.limit_bits, &nb);
         cand[tid] = state;
     }
     __syncthreads();
@@ -1733,7 +1914,7 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
             state = from;
             nb = 0;
             // (a state past the row's end: the row before ran through it)
-            if ((from >> 9) < rows.end(j)) state = decode_row<false>(S, g, from, rows.end(j), rows.limit_bits, &nb, nullptr);
+            if ((from >> 9) < rows.end(j)) state = count_span<false>(S, S.clean, S.tab.run, g, from, rows.end(j), rows.limit_bits, &nb);
         }
         node_end[tid] = state;
         node_blocks[tid] = (uint16_t)nb;
@@ -1756,7 +1937,7 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
         if (key != kNoKey && !mine_done) {
             const uint32_t from = key & ((1u << kStateBits) - 1u), r = key >> kStateBits;
             uint32_t to = from, n = 0;
-            if ((from >> 9) < rows.end(r)) to = decode_row<false>(S, g, from, rows.end(r), rows.limit_bits, &n, nullptr);
+            if ((from >> 9) < rows.end(r)) to = count_span<false>(S, S.clean, S.tab.run, g, from, rows.end(r), rows.limit_bits, &n);
             node_end[kT + tid] = to;
             node_blocks[kT + tid] = (uint16_t)n;
             link((uint32_t)(kT + tid), r, to);
@@ -1891,7 +2072,7 @@ __global__ __launch_bounds__(kDecodeThreads) void write_streams(
     const uint32_t *__restrict__ data_end, uint32_t *__restrict__ retry, const uint4 *__restrict__ tables,
     StreamWindow *__restrict__ windows, int16_t *__restrict__ coef_all, uint32_t side_off)
 {
-    __shared__ StreamShared S;
+    __shared__ StreamShared<HuffCodes> S;
     __shared__ uint32_t node_end[kStreamNodes];
     __shared__ uint16_t node_blocks[kStreamNodes], node_next[kStreamNodes];
     __shared__ uint16_t chain[kStreamMaxRows + 1];
@@ -1974,7 +2155,7 @@ __global__ __launch_bounds__(kDecodeThreads) void write_streams(
     wc.bad = 0;
     if (active) {
         uint32_t fin = in_state, got = 0;
-        if ((in_state >> 9) < rows.end(row)) fin = decode_row<true>(S, g, in_state, rows.end(row), rows.limit_bits, &got, &wc);
+        if ((in_state >> 9) < rows.end(row)) fin = write_span<false>(S, S.clean, g, in_state, rows.end(row), rows.limit_bits, &got, &wc);
         if (fin != out_state || got != nblk) wc.bad = 1;
         // the data end between MCUs
         if (rows.end(row) == rows.limit_bits && ((fin & 511u) != 0 || (fin >> 9) != rows.limit_bits)) wc.bad = 1;
@@ -2032,7 +2213,7 @@ __global__ __launch_bounds__(kDecodeThreads) void finish_streams(
 
 
 size_t huff_tables_bytes() { return sizeof(HuffTables); }
-static_assert(sizeof(HuffTables) % 16 == 0, "table slots are copied in 16-byte units");
+static_assert(sizeof(HuffTables) % 16 == 0 && sizeof(HuffCodes) % 16 == 0 && sizeof(HuffTables) == sizeof(HuffCodes) + sizeof(HuffTables::run), "table slots are copied in 16-byte units");
 
 void launch_scan_restart_markers(const uint8_t *bits, const ImageRec *recs, int n_images,
                                  uint32_t n_windows, uint32_t window_bytes, uint32_t *win_count, uint32_t *win_first,
@@ -2049,17 +2230,17 @@ void launch_scan_restart_markers(const uint8_t *bits, const ImageRec *recs, int 
 void launch_decode_entropy(const uint8_t *bits, const ImageRec *recs, int n_images,
                            uint32_t n_windows, const uint32_t *win_count, const uint32_t *win_first,
                            const uint32_t *data_end, const uint32_t *retry, int16_t *coef, uint32_t side_off, int32_t *status,
-                           const uint8_t *tables, bool small_windows, uint32_t hyp_span_bits, hipStream_t stream)
+                           const uint8_t *tables, bool small_windows, uint32_t hyp_span_bits, bool long_intervals, hipStream_t stream)
 {
     if (n_windows == 0) return;
-    if (small_windows)
-        hipLaunchKernelGGL(decode_entropy<true>, dim3(n_windows), dim3(kDecodeThreads), 0, stream, bits, recs,
-                           n_images, win_count, win_first, data_end, retry, coef, side_off, status,
-                           reinterpret_cast<const uint4 *>(tables), hyp_span_bits);
-    else
-        hipLaunchKernelGGL(decode_entropy<false>, dim3(n_windows), dim3(kDecodeThreads), 0, stream, bits, recs,
-                           n_images, win_count, win_first, data_end, retry, coef, side_off, status,
-                           reinterpret_cast<const uint4 *>(tables), hyp_span_bits);
+    const auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(n_windows), dim3(kDecodeThreads), 0, stream, bits, recs, n_images, win_count,
+                           win_first, data_end, retry, coef, side_off, status, reinterpret_cast<const uint4 *>(tables),
+                           hyp_span_bits);
+    };
+    if (small_windows) launch(decode_entropy<true, true>);
+    else if (long_intervals) launch(decode_entropy<false, true>);
+    else launch(decode_entropy<false, false>);
 }
 
 void launch_decode_streams(const uint8_t *bits, const ImageRec *recs, int n_images, uint32_t n_streams, uint32_t row_bytes,

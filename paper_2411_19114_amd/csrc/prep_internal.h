@@ -28,6 +28,8 @@ constexpr uint64_t kSmallCallBytes = 1536 << 10;            // entropy-coded byt
 // at 32 = 375 KB, even at 48 = 562 KB, worse from there on).
 constexpr int kTinyWindowBytes = 512;
 constexpr uint64_t kTinyCallBytes = 448 << 10;
+// Mean bytes of a restart interval up to which a lane decodes it whole, in large calls (see decode_entropy)
+constexpr int kLongIntervalBytes = 1024;
 // Streams without restart markers are cut into windows too, one workgroup each, where that pays
 // (StreamCut in api.cpp; the kernels: resolve_streams in entropy.hip).  A window is decoded in rows,
 // a lane to a row and hypothesis; its last rows, the overlap, are the first rows of the next window.
@@ -98,7 +100,6 @@ struct StreamWindow {
     int32_t dc_sum[3];                 // sums of these differences per component
     uint32_t pad_;
 };
-constexpr int kLutBits = 10;                                // first-level Huffman lookup width
 // Images of a batch mostly share their Huffman tables (encoders write the tables of T.81
 // Annex K unless asked to optimise): each distinct set of four tables is expanded once per
 // batch into a slot of device memory and copied into LDS by the workgroups that need it.

@@ -170,6 +170,9 @@ inline unsigned long long __ballot(int pred)
     c.wave_bar[wave]->arrive_and_wait();
     return m;
 }
+// asked only whether a rare branch is worth entering, in code that lanes leave one by one: every lane
+// answers for itself
+inline unsigned long long __builtin_amdgcn_ballot_w64(bool pred) { return pred ? 1u : 0u; }
 template <typename T>
 inline T __shfl(T v, int src, int = 64) { return hip_emul::shuffle(v, [src](int) { return src; }); }
 template <typename T>
