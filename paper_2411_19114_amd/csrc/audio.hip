@@ -85,55 +85,140 @@ __global__ __launch_bounds__(256) void resample_kernel(const float *__restrict__
     mid[g] = acc;
 }
 
-// The same sum with the taps in registers: a thread keeps one phase r for all its outputs (the
-// workgroup has a multiple of q threads and steps over whole multiples of q outputs), so its
-// taps are loaded once and only the signal is read in the loop.  tile_start[u] = first
-// workgroup of utterance u; a workgroup makes kTilesPerWg * blockDim.x consecutive outputs.
-constexpr int kMaxTaps = 40;
+// The same sum as a matrix product.  A period is P input and Q output samples, a multiple of p
+// and q.  Sixteen neighbouring phases of a period read one band of 4 S input samples, so
+//   y[a Q + 16 b + j] = sum_n x[a P + first_b + n] T_b[n][j],   n < 4 S, j < 16,
+// is a product of sixteen periods' bands (rows a) with a matrix T_b that holds each phase's taps
+// where they fall in the band, and zeros.  S steps of V_MFMA_F64_16X16X4_F64 make a tile of 256
+// outputs.  The order of the band's samples in the sum is free: step 4 i + e takes sample
+// 16 i + 4 g + e from lane group g = lane / 16, so a lane loads sixteen bytes at a time and
+// four lanes of a row 64 neighbouring bytes.  A wave keeps its T_b, S doubles a lane, for all its
+// tiles, and loads the next tile's samples while it multiplies.  Neighbouring waves of an XCD take the
+// blocks of the same periods, so that most find the samples in its cache.
+//
+// 64 recordings of 1.5 to 35 s (1168 s), 44.1 to 16 kHz: 275 -> 100 us, of which the matrix
+// cores are busy 40.  With a lane per output and its taps in registers 33 samples were loaded and converted
+// per output, here five.  (The same with chunks staged in LDS for
+// all phases, with two barriers each, took 130.)
+typedef double Acc4 __attribute__((ext_vector_type(4)));
+typedef float Quad __attribute__((ext_vector_type(4), aligned(4)));
+constexpr int kBandQuadsMost = 6;                     // S / 4: a band of 96 samples, p / q up to about 3.4
+constexpr int kBandWaves = 8;                         // of a workgroup
+constexpr uint32_t kXcds = 8;                         // (workgroups go to them in turn)
+
+struct BandPlan {
+    int32_t P, Q;          // the period
+    int32_t blocks;        // of sixteen phases
+    int32_t quads;         // S / 4; 0 = the rates are not for this kernel
+};
 // A rate pair p : q (reduced) is accepted up to this size of either term; its tap table has q
 // rows of at most 2 * 6 / 0.99 * max(p / q, 1) + 2 taps, fewer than 14 * max(p, q) + 2 q entries.
 constexpr int kMaxRateTerm = 4096;
 constexpr size_t kMaxTapEntries = 16 * (size_t)kMaxRateTerm;
-constexpr int kTilesPerWg = 8;
 
-__global__ __launch_bounds__(512) void resample_phase_kernel(
+// Entry of `bands` for sample n of block b's band and phase 16 b + j
+__host__ __device__ inline size_t band_entry(int quads, int b, int n, int j)
+{
+    return ((size_t)(b * quads + n / 16) * 4 + (size_t)(n % 4)) * 64 + (size_t)(n % 16 / 4) * 16 + (size_t)j;
+}
+
+// One output by itself, its own taps only.  Out of line: inlined, it cost the kernel that calls
+// it (almost never) its registers.
+__device__ __attribute__((noinline)) double resample_one(const float *x, int64_t from, int64_t in_len, const double *bands,
+                                                         int quads, int b, int j)
+{
+    double y = 0.0;
+    for (int n = 0; n < 16 * quads; n++) {
+        const double w = bands[band_entry(quads, b, n, j)];
+        if (w != 0.0 && from + n >= 0 && from + n < in_len) y = fma((double)x[from + n], w, y);
+    }
+    return y;
+}
+
+// first[b] = first sample of band b, counted from the period's start; tile_start[u] = first tile of
+// utterance u
+template <int kQuads>
+__global__ __launch_bounds__(64 * kBandWaves, 4) void resample_bands_kernel(
     const float *__restrict__ in, const Utterance *__restrict__ utt, const uint64_t *__restrict__ tile_start,
-    int n_utt, const double *__restrict__ taps, const int32_t *__restrict__ first, int p, int q, int n_taps,
+    int n_utt, uint32_t n_tiles, const double *__restrict__ bands, const int32_t *__restrict__ first, BandPlan plan,
     double *__restrict__ mid)
 {
-    int lo = 0, hi = n_utt - 1;
-    while (lo < hi) {
-        const int m = (lo + hi + 1) >> 1;
-        if (tile_start[m] <= blockIdx.x) lo = m; else hi = m - 1;
+    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    // waves that run on one XCD have neighbouring numbers (the grid is a multiple of kXcds)
+    const uint32_t id = ((blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds) * kBandWaves + (uint32_t)wave;
+    const uint32_t turns = gridDim.x * kBandWaves / (uint32_t)plan.blocks;  // tiles that are worked on side by side
+    const int b = (int)(id % (uint32_t)plan.blocks);
+    uint32_t t = id / (uint32_t)plan.blocks;
+    if (t >= turns || t >= n_tiles) return;
+    double tap[4 * kQuads];
+#pragma unroll
+    for (int s = 0; s < 4 * kQuads; s++) tap[s] = bands[((size_t)b * kQuads * 4 + s) * 64 + lane];
+    const int32_t band = first[b];
+    int u = 0;
+    {
+        int hi = n_utt - 1;
+        while (u < hi) {
+            const int m = (u + hi + 1) >> 1;
+            if (tile_start[m] <= t) u = m; else hi = m - 1;
+        }
     }
-    const Utterance u = utt[lo];
-    const uint32_t r = threadIdx.x % (uint32_t)q, sub = threadIdx.x / (uint32_t)q;
-    const uint32_t per_tile = blockDim.x / (uint32_t)q;            // blocks of q outputs per tile
-    double tap[kMaxTaps];
+    uint32_t period = 0;  // the tile's first
+    Quad v[kQuads];
+    // the lane's samples of tile t (of utterance u); zeros where the utterance has none
+    auto load = [&]() {
+        const int64_t len = utt[u].in_len;
+        const float *x = in + utt[u].in_off;
+        period = (t - (uint32_t)tile_start[u]) * 16u;
+        const int64_t at = (int64_t)(period + (uint32_t)j) * plan.P + band + 4 * g;
+        if (at >= 0 && at + 16 * (kQuads - 1) + 4 <= len) {
 #pragma unroll
-    for (int j = 0; j < kMaxTaps; j++) tap[j] = j < n_taps ? taps[(size_t)j * q + r] : 0.0;
-    const float *x = in + u.in_off;
-    double *y = mid + u.mid_off;
-    // a = index of the block of q outputs
-    uint32_t a = ((uint32_t)(blockIdx.x - tile_start[lo]) * kTilesPerWg) * per_tile + sub;
-    const int32_t f = first[r];
-    for (int it = 0; it < kTilesPerWg; it++, a += per_tile) {
-        const uint64_t m = (uint64_t)a * (uint32_t)q + r;
-        if (m >= u.mid_len) break;
-        const int64_t n0 = (int64_t)a * p + f;
-        double acc = 0.0;
-        if (n0 >= 0 && n0 + kMaxTaps <= (int64_t)u.in_len) {
-            const float *xs = x + n0;
-#pragma unroll
-            for (int j = 0; j < kMaxTaps; j++) acc = fma((double)xs[j], tap[j], acc);
+            for (int i = 0; i < kQuads; i++) v[i] = *reinterpret_cast<const Quad *>(x + at + 16 * i);
         } else {
 #pragma unroll
-            for (int j = 0; j < kMaxTaps; j++) {
-                const int64_t n = n0 + j;
-                if (n >= 0 && n < (int64_t)u.in_len) acc = fma((double)x[n], tap[j], acc);
+            for (int i = 0; i < kQuads; i++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const int64_t n = at + 16 * i + e;
+                    v[i][e] = n >= 0 && n < len ? x[n] : 0.0f;
+                }
+        }
+    };
+    load();
+    for (;;) {
+        double x[4 * kQuads];
+#pragma unroll
+        for (int s = 0; s < 4 * kQuads; s++) x[s] = (double)v[s / 4][s % 4];
+        const uint32_t here = period;
+        const int uh = u;
+        t += turns;
+        const bool more = t < n_tiles;
+        if (more) {
+            while (u + 1 < n_utt && tile_start[u + 1] <= t) u++;
+            load();
+        }
+        Acc4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < 4 * kQuads; s++) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[s], tap[s], acc, 0, 0, 0);
+        // acc[i] is output (row g + 4 i, phase j) of the tile
+        const uint32_t len = utt[uh].mid_len;
+        double *y = mid + utt[uh].mid_off;
+        const int phase = 16 * b + j;
+        if (phase < plan.Q) {
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const uint64_t a = here + (uint32_t)(g + 4 * i), m = a * (uint32_t)plan.Q + (uint32_t)phase;
+                // a sample that is no finite number makes all sixteen phases of its band one too: those
+                // whose taps do not reach it are summed without it
+                if (m < len) {
+                    double r = acc[i];
+                    if (!(fabs(r) <= 1.7976931348623157e308))
+                        r = resample_one(in + utt[uh].in_off, (int64_t)a * plan.P + band, utt[uh].in_len, bands, kQuads, b, j);
+                    y[m] = r;
+                }
             }
         }
-        y[m] = acc;
+        if (!more) break;
     }
 }
 
@@ -379,9 +464,11 @@ struct prep_audio {
     double *d_mel_weights = nullptr;
     MelTable mel;
     // interpolation taps of the two rate pairs seen last, in buffers of the largest size a rate
-    // pair can need (reserved in prep_audio_create: a call never allocates or frees)
+    // pair can need (reserved in prep_audio_create: a call never allocates or frees): bands where the
+    // plan has steps, else taps by phase
     struct TapSlot {
         int p = 0, q = 0, n_taps = 0;
+        BandPlan plan = {};
         double *d_taps = nullptr;
         int32_t *d_first = nullptr;
         uint64_t used = 0;       // call counter when the slot served last
@@ -437,6 +524,39 @@ void make_taps(int p, int q, std::vector<double> *taps, std::vector<int32_t> *fi
                 (*taps)[(size_t)j * q + r] = (base / p) * sinc(uarg) * c * c;
             }
         }
+}
+
+// The matrix form of these taps, in place of them, if the rates are for it: the shortest period
+// that fills its blocks of sixteen phases to 98 %, or the one of at most sixteen times p : q that
+// fills them best.
+void make_bands(int p, int q, int n_taps, std::vector<double> *taps, std::vector<int32_t> *first, BandPlan *plan)
+{
+    *plan = BandPlan{};
+    int m = 0;
+    double best = 0.0;
+    for (int k = 1; k <= 16 && best < 0.98; k++) {
+        const double used = (double)q * k / (16.0 * ((q * k + 15) / 16));
+        if (used > best + 1e-9) { best = used; m = k; }
+    }
+    BandPlan t;
+    t.P = p * m;
+    t.Q = q * m;
+    t.blocks = (t.Q + 15) / 16;
+    auto start = [&](int r) { return (*first)[(size_t)(r % q)] + r / q * p; };
+    int width = 0;
+    for (int b = 0; b < t.blocks; b++)
+        width = std::max(width, start(std::min(16 * b + 15, t.Q - 1)) + n_taps - start(16 * b));
+    t.quads = std::max(2, (width + 15) / 16);
+    if (t.quads > kBandQuadsMost || (size_t)t.blocks * (size_t)t.quads * 256 > kMaxTapEntries) return;
+    std::vector<double> bands((size_t)t.blocks * (size_t)t.quads * 256, 0.0);
+    std::vector<int32_t> starts((size_t)t.blocks);
+    for (int b = 0; b < t.blocks; b++) starts[(size_t)b] = start(16 * b);
+    for (int r = 0; r < t.Q; r++)
+        for (int k = 0; k < n_taps; k++)
+            bands[band_entry(t.quads, r / 16, start(r) + k - starts[(size_t)(r / 16)], r % 16)] = (*taps)[(size_t)k * q + r % q];
+    taps->swap(bands);
+    first->swap(starts);
+    *plan = t;
 }
 
 }  // namespace
@@ -569,9 +689,6 @@ int prep_audio_features(prep_audio *h, const float *waveforms, const uint64_t *o
     uint64_t *h_starts = reinterpret_cast<uint64_t *>(h->h_utt + n);
     const uint64_t *d_starts = reinterpret_cast<const uint64_t *>(h->d_utt + n);
     uint64_t mid_total = 0, pairs_total = 0, out_total = 0, tiles_total = 0;
-    // threads per workgroup of the resampler that keeps its taps in registers: a multiple of q
-    const uint32_t phase_threads = q <= 320 ? (uint32_t)q * (uint32_t)std::max(1, 320 / q) : 0u;
-    const uint64_t per_wg = (uint64_t)phase_threads * kTilesPerWg;
     for (int32_t i = 0; i < n; i++) {
         if (offsets[i + 1] < offsets[i] || offsets[i + 1] - offsets[i] > 0xFFFFFFFFull) return PREP_E_INVALID_ARG;
         Utterance &u = h->h_utt[i];
@@ -587,8 +704,6 @@ int prep_audio_features(prep_audio *h, const float *waveforms, const uint64_t *o
         u.pad_ = 0;
         h_starts[i] = mid_total;
         h_starts[(size_t)n + i] = pairs_total;
-        h_starts[2 * (size_t)n + i] = tiles_total;
-        if (per_wg) tiles_total += (len + per_wg - 1) / per_wg;
         mid_total += len;
         pairs_total += (u.frames + 1) / 2;
         out_total += (uint64_t)u.frames * (uint64_t)h->cfg.n_mels;
@@ -607,13 +722,15 @@ int prep_audio_features(prep_audio *h, const float *waveforms, const uint64_t *o
                 // them on the caller's stream, ahead of the kernels that read them (the pinned
                 // staging is free: the call before has been waited for above; so is the slot)
                 if (h->slot[1].used < taps->used) taps = &h->slot[1];
+                taps->p = taps->q = 0;
                 make_taps(p, q, &h->h_taps, &h->h_first, &taps->n_taps);
+                make_bands(p, q, taps->n_taps, &h->h_taps, &h->h_first, &taps->plan);
                 if (h->h_taps.size() > kMaxTapEntries) return PREP_E_TOO_LARGE;
                 memcpy(h->h_taps_pinned, h->h_taps.data(), sizeof(double) * h->h_taps.size());
-                memcpy(h->h_first_pinned, h->h_first.data(), sizeof(int32_t) * (size_t)q);
+                memcpy(h->h_first_pinned, h->h_first.data(), sizeof(int32_t) * h->h_first.size());
                 AUDIO_TRY(hipMemcpyAsync(taps->d_taps, h->h_taps_pinned, sizeof(double) * h->h_taps.size(),
                                          hipMemcpyHostToDevice, stream));
-                AUDIO_TRY(hipMemcpyAsync(taps->d_first, h->h_first_pinned, sizeof(int32_t) * (size_t)q,
+                AUDIO_TRY(hipMemcpyAsync(taps->d_first, h->h_first_pinned, sizeof(int32_t) * h->h_first.size(),
                                          hipMemcpyHostToDevice, stream));
                 taps->p = p;
                 taps->q = q;
@@ -621,14 +738,35 @@ int prep_audio_features(prep_audio *h, const float *waveforms, const uint64_t *o
         }
         taps->used = h->calls;
     }
+    if (p != q && taps->plan.quads) {
+        const uint64_t per_tile = 16ull * (uint64_t)taps->plan.Q;
+        for (int32_t i = 0; i < n; i++) {
+            h_starts[2 * (size_t)n + i] = tiles_total;
+            tiles_total += (h->h_utt[i].mid_len + per_tile - 1) / per_tile;
+        }
+    }
     if (p == q) {
         // same rate: the frames read the input itself; utterance offsets are the input's
         for (int32_t i = 0; i < n; i++) h->h_utt[i].mid_off = h->h_utt[i].in_off;
     }
     AUDIO_TRY(hipMemcpyAsync(h->d_utt, h->h_utt, kRecordBytes * (size_t)n, hipMemcpyHostToDevice, stream));
-    if (p != q && phase_threads && taps->n_taps <= kMaxTaps && tiles_total <= 0x7FFFFFFFull) {
-        hipLaunchKernelGGL(resample_phase_kernel, dim3((unsigned)tiles_total), dim3(phase_threads), 0, stream, waveforms,
-                           h->d_utt, d_starts + 2 * n, n, taps->d_taps, taps->d_first, p, q, taps->n_taps, h->d_mid);
+    if (p != q && taps->plan.quads && tiles_total <= 0x3FFFFFFFull) {
+        const BandPlan &plan = taps->plan;
+        // as many waves as the chip holds, or as there are tiles' blocks, but one for each block at least
+        const uint64_t unit = kXcds * kBandWaves, wanted = (tiles_total * (uint64_t)plan.blocks + unit - 1) / unit * unit;
+        const uint64_t waves = std::max(std::min<uint64_t>(wanted, 256 * 16), ((uint64_t)plan.blocks + unit - 1) / unit * unit);
+        const dim3 grid((unsigned)(waves / kBandWaves));
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(64 * kBandWaves), 0, stream, waveforms, h->d_utt, d_starts + 2 * n, n,
+                               (uint32_t)tiles_total, taps->d_taps, taps->d_first, plan, h->d_mid);
+        };
+        switch (plan.quads) {
+        case 2: launch(resample_bands_kernel<2>); break;
+        case 3: launch(resample_bands_kernel<3>); break;
+        case 4: launch(resample_bands_kernel<4>); break;
+        case 5: launch(resample_bands_kernel<5>); break;
+        default: launch(resample_bands_kernel<kBandQuadsMost>); break;
+        }
     } else if (p != q) {
         hipLaunchKernelGGL(resample_kernel, dim3((unsigned)((mid_total + 255) / 256)), dim3(256), 0, stream, waveforms,
                            h->d_utt, d_starts, n, taps->d_taps, taps->d_first, p, q, taps->n_taps, h->d_mid, mid_total);

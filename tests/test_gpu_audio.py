@@ -134,3 +134,32 @@ def test_frames_in_pairs(prep):
             assert i == 3 or np.array_equal(got[i], plain[i])
     finally:
         ap.close()
+
+
+# rate pairs with a plan for the matrix form: 441 : 160, 3 : 1, 441 : 640 (four groups of workgroups), 3 : 2,
+# 441 : 400, 25 : 8, 4 : 5; and without: 6 : 1 (the band is too long), 1601 : 1600 (a chunk does not fit LDS)
+@pytest.mark.parametrize("rate_in", [44100, 48000, 11025, 24000, 17640, 50000, 12800, 96000, 16010])
+def test_resampled_lengths_at_the_edges_of_chunks(prep, rate_in):
+    """Utterances of one sample more or less than whole chunks and tiles, one that fills none,
+    and one of NaNs beside them, which must not reach its neighbours.  (No shorter ones: the bound
+    above is for deviations of order one.  The two frames of an utterance of 300 samples differ by 0.02
+    in some channels, which makes 1e-4 of a log-Mel value's rounding.)"""
+    import math
+    g = math.gcd(rate_in, 16000)
+    p, q = rate_in // g, 16000 // g
+    period = q if q >= 100 else math.lcm(q, 16)              # outputs of a row of a tile
+    lengths = [n * p // q for n in (1500, 16 * period, 128 * period) if 1500 <= n and n * p // q < 120000]
+    waves = [speech_like(900 + k, rate_in, 8.0)[:n + d] for k, n in enumerate(lengths) for d in (-1, 0, 1)]
+    bad = np.full(len(waves[1]), np.nan, np.float32)
+    ap = prep.AudioPreprocessor(max_batch=16, max_total_samples=sum(len(w) for w in waves) * 3)
+    try:
+        plain = run(ap, waves, rate_in)
+        for w, f in zip(waves, plain):
+            ref = audio.preprocess(w.astype(np.float64), rate_in)
+            assert f.shape == ref.shape and np.abs(f - ref).max() <= FEATURE_TOL
+        got = run(ap, waves[:1] + [bad] + waves[2:], rate_in)
+        assert np.isnan(got[1]).any()
+        for i in range(len(waves)):
+            assert i == 1 or np.array_equal(got[i], plain[i])
+    finally:
+        ap.close()
