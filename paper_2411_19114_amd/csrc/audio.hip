@@ -34,7 +34,7 @@ constexpr double kRolloff = 0.99;
 constexpr float kLogGuard = 5.9604644775390625e-08f;  // 2^-24
 constexpr float kStdGuard = 1e-5f;
 constexpr int kFft = 512;                             // the transform the kernel is built for
-constexpr int kFrameThreads = 128;                    // two pairs of frames per workgroup, one wave each
+constexpr int kFrameThreads = 256;                    // one wave per pair of frames
 constexpr int kMaxMels = 128;
 
 struct Utterance {
@@ -97,9 +97,9 @@ __global__ __launch_bounds__(256) void resample_kernel(const float *__restrict__
 // blocks of the same periods, so that most find the samples in its cache.
 //
 // 64 recordings of 1.5 to 35 s (1168 s), 44.1 to 16 kHz: 275 -> 100 us, of which the matrix
-// cores are busy 40.  With a lane per output and its taps in registers 33 samples were loaded and converted
-// per output, here five.  (The same with chunks staged in LDS for
-// all phases, with two barriers each, took 130.)
+// cores are busy 40.  With a lane per output and its taps in registers 33 samples were loaded and
+// converted per output, here five.  (The same with chunks staged in LDS for all phases, with
+// two barriers each, took 130.)
 typedef double Acc4 __attribute__((ext_vector_type(4)));
 typedef float Quad __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int kBandQuadsMost = 6;                     // S / 4: a band of 96 samples, p / q up to about 3.4
@@ -223,9 +223,41 @@ __global__ __launch_bounds__(64 * kBandWaves, 4) void resample_bands_kernel(
 }
 
 // ---- frames -> log-Mel --------------------------------------------------------------------
-struct MelTable {          // filter m covers bins start[m] .. start[m] + count[m] - 1
-    int32_t start[kMaxMels], count[kMaxMels], first_weight[kMaxMels];
+// The corners of the triangles cut the bins into n_mels + 1 ranges.  In range i lie the rising side of
+// triangle i and the falling one of triangle i - 1 (those that do not exist, at both ends, are summed all the
+// same and not used), so that every bin is read once.  Both sides are linear in the bin: a range needs
+// no table of weights.
+struct MelRange {
+    double rising, falling, step;  // weights of the range's first bin; growth of the former from bin to bin
+    int32_t start, count;          // bins
 };
+
+// ln(x) for x >= 2^-24 from x = 2^e (1 + f), 1 + f in [sqrt 1/2, sqrt 2): ln(1 + f) = 2 artanh(s), s = f / (2 + f),
+// by its series up to s^19 (|s| <= 0.172: what is left out is 1e-16 of the sum).  The quotient is within
+// a few units of 2^-52.  (For the device library's general logarithm the compiler takes twice
+// the instructions.)
+__device__ __forceinline__ double log_of(double x)
+{
+    double m = __builtin_amdgcn_frexp_mant(x);
+    int e = __builtin_amdgcn_frexp_exp(x);
+    const bool low = m < 0.70710678118654752440;
+    m = low ? 2.0 * m : m;
+    e = low ? e - 1 : e;
+    const double f = m - 1.0, d = 2.0 + f;
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    r = fma(fma(-d, r, 1.0), r, r);
+    const double s = f * r, z = s * s;
+    double q = 1.0 / 19.0;
+#pragma unroll
+    for (int k = 17; k >= 3; k -= 2) {
+        double c = 1.0 / k;
+        asm volatile("" : "+s"(c));  // a scalar register pair: the vector registers are needed
+        q = fma(q, z, c);
+    }
+    const double y = fma((double)e, 0.69314718055994530942, fma(2.0 * s * z, q, 2.0 * s));
+    return x <= 1.7976931348623157e308 ? y : x;  // infinity, and no number, as they are
+}
 
 __device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
@@ -274,122 +306,177 @@ constexpr int kFramePadded = kFft + kFft / 8;
 // multiplies by W512^(r k 512 / (8 Ns)), k = j mod Ns, Ns = 8^s, transforms the eight values and
 // writes them Ns apart from (j / Ns) 8 Ns + k), each lane holding eight values in registers; the
 // first pass reads the signal itself.  Its outputs Z hold both spectra of the real frames,
-// A[k] = (Z[k] + conj Z[512 - k]) / 2 and i B[k] = (Z[k] - conj Z[512 - k]) / 2.  Bound by fp64
-// arithmetic and LDS passes, which a pair pays once: 117 000 frames 394 -> 240 us.
+// A[k] = (Z[k] + conj Z[512 - k]) / 2 and i B[k] = (Z[k] - conj Z[512 - k]) / 2.  A wave takes several
+// pairs one after the other (per_wave; one each where there are few): it keeps the last pass's
+// factors, loads the next pair's samples while it sums one's powers, and reads every power
+// once (see MelRange).  117 000 frames 256 -> 140 us, 394 with one frame a transform.  Bound by the
+// latency of its passes through LDS at three waves a SIMD (registers, LDS); the fp64 units are
+// busy a third of the time.
 // The rounding error of a quiet frame's spectrum is relative to its louder neighbour: silence beside a
 // full tone comes out 7e-10 off in the logarithm with samples of up to 2^24, 7e-7 with up to
 // 2^31, where a transform by itself gives the guard exactly.  (The features are rounded to fp32.)
 // A pair never spans two utterances (a NaN would cross over); the last of an odd number of
-// frames is transformed alone.  Two waves a workgroup, so that one utterance of some seconds
-// still has a workgroup for every compute unit.  pair_start[u] = first pair of utterance u among
+// frames is transformed alone.  pair_start[u] = first pair of utterance u among
 // all pairs.  Sample is double for a resampled signal, float where the input is framed as it is.
+constexpr uint32_t kPairsPerWave = 4;  // (140 us for the 117 000 frames; 154 with eight, 171 with sixteen: a last round of waves)
 template <typename Sample>
-__global__ __launch_bounds__(kFrameThreads) void log_mel_kernel(
+__global__ __launch_bounds__(kFrameThreads, 3) void log_mel_kernel(
     const Sample *__restrict__ mid, const Utterance *__restrict__ utt, const uint64_t *__restrict__ pair_start,
-    int n_utt, uint64_t n_pairs, int hop, const double *__restrict__ window, const double2 *__restrict__ twiddle,
-    MelTable mel, const double *__restrict__ mel_weights, int n_mels, float *__restrict__ out)
+    int n_utt, uint64_t n_pairs, uint32_t per_wave, int hop, const double *__restrict__ window,
+    const double2 *__restrict__ twiddle, const MelRange *__restrict__ ranges, int n_mels, float *__restrict__ out)
 {
     __shared__ double2 s_x[kFrameThreads / 64][kFramePadded];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint64_t f = (uint64_t)blockIdx.x * (kFrameThreads / 64) + wave;
-    if (f >= n_pairs) return;    // no workgroup-wide barrier below: a wave works on its own pair
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    uint64_t f = ((uint64_t)blockIdx.x * (kFrameThreads / 64) + (uint64_t)wave) * per_wave;
+    const uint64_t f_end = min(f + per_wave, n_pairs);
+    // the factors of the last two passes (there are 64 of the first of them), the window and the ranges
+    __shared__ double2 s_factor[8 * 8];
+    __shared__ double s_window[kFft];
+    __shared__ MelRange s_range[kMaxMels + 1];
+    double2 factor[8];
+#pragma unroll
+    for (int r = 1; r < 8; r++) factor[r] = twiddle[r * lane];
+    if (threadIdx.x < 64) s_factor[threadIdx.x] = twiddle[(threadIdx.x >> 3) * (threadIdx.x & 7) * (kFft / 64)];
+    for (int i = threadIdx.x; i < kFft; i += kFrameThreads) s_window[i] = window[i];
+    if ((int)threadIdx.x <= n_mels) s_range[threadIdx.x] = ranges[threadIdx.x];
+    static_assert(kMaxMels < kFrameThreads, "a lane copies a range");
+    __syncthreads();
+    if (f >= f_end) return;    // no workgroup-wide barrier below: a wave works on its own pairs
     int lo = 0, hi = n_utt - 1;
     while (lo < hi) {
         const int m = (lo + hi + 1) >> 1;
         if (pair_start[m] <= f) lo = m; else hi = m - 1;
     }
-    const Utterance u = utt[lo];
-    const uint32_t t = 2 * (uint32_t)(f - pair_start[lo]);
-    const bool two = t + 1 < u.frames;
     double2 *x = s_x[wave];
-    // the factors of the last two passes, under way while the signal arrives
-    double2 factor[2][8];
+    // The ranges widen with their number, so a lane takes a narrow one, `lane`, and the wide one that
+    // mirrors it: every busy lane sums about the same number of bins.  (One range is left over where
+    // there are more than 128.)
+    const int n_ranges = n_mels + 1, mirrored = n_ranges - 1 - lane;
+    // the samples of both frames of pair f: loaded while the pair before is summed, where both frames
+    // lie inside the signal
+    uint32_t t = 0, frames = 0;
+    int64_t from = 0;
+    bool inside = false;
+    double ab[2][8];
+    auto load = [&]() {
+        while (lo + 1 < n_utt && pair_start[lo + 1] <= f) lo++;
+        t = 2 * (uint32_t)(f - pair_start[lo]);
+        frames = utt[lo].frames;
+        from = (int64_t)t * hop - kFft / 2;
+        inside = t + 1 < frames && from >= 0 && from + hop + kFft <= (int64_t)utt[lo].mid_len;
+        if (inside) {
+            const Sample *a = mid + utt[lo].mid_off + from, *b = a + hop;
 #pragma unroll
-    for (int pass = 1; pass < 3; pass++) {
-        const int ns = pass == 1 ? 8 : 64, k = lane & (ns - 1);
-#pragma unroll
-        for (int r = 1; r < 8; r++) factor[pass - 1][r] = twiddle[r * k * (kFft / (8 * ns))];
-    }
-    double2 v[8];
-    {
-        const Sample *sig = mid + u.mid_off;
-        const int64_t len = (int64_t)u.mid_len;
-#pragma unroll
-        for (int r = 0; r < 8; r++) {
-            const int j = lane + 64 * r;
-            double ab[2];
-#pragma unroll
-            for (int i = 0; i < 2; i++) {
-                int64_t s = ((int64_t)t + (two ? i : 0)) * hop + j - kFft / 2;
+            for (int r = 0; r < 8; r++) {
+                ab[0][r] = (double)a[lane + 64 * r];
+                ab[1][r] = (double)b[lane + 64 * r];
+            }
+        }
+    };
+    load();
+    for (;;) {
+        const bool two = t + 1 < frames;
+        if (!inside) {
+            const Sample *sig = mid + utt[lo].mid_off;
+            const int64_t len = (int64_t)utt[lo].mid_len;
+            double *staged = reinterpret_cast<double *>(x);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll 1
+            for (int k = lane; k < 2 * kFft; k += 64) {
+                int64_t s = from + (k >= kFft && two ? hop : 0) + (k & (kFft - 1));
                 if (s < 0) s = -s;                       // reflection about the first sample
                 if (s >= len) s = 2 * (len - 1) - s;     // and about the last (len > n_fft / 2)
-                ab[i] = (double)sig[s] * window[j];
+                staged[k] = (double)sig[s];
             }
-            v[r] = make_double2(ab[0], two ? ab[1] : 0.0);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int r = 0; r < 8; r++) {
+                ab[0][r] = staged[lane + 64 * r];
+                ab[1][r] = staged[kFft + lane + 64 * r];
+            }
         }
-    }
-    dft8(v);
+        double2 v[8];
 #pragma unroll
-    for (int r = 0; r < 8; r++) x[padded(lane * 8 + r)] = v[r];
-    // the accesses of one wave to LDS complete in order; the fence keeps the compiler from
-    // moving loads over the stores
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-    for (int pass = 1; pass < 3; pass++) {
-        const int ns = pass == 1 ? 8 : 64;
-        const int k = lane & (ns - 1);
-#pragma unroll
-        for (int r = 0; r < 8; r++) v[r] = x[padded(lane + 64 * r)];
-#pragma unroll
-        for (int r = 1; r < 8; r++) v[r] = cmul(v[r], factor[pass - 1][r]);
+        for (int r = 0; r < 8; r++) {
+            const double win = s_window[lane + 64 * r];
+            v[r] = make_double2(ab[0][r] * win, two ? ab[1][r] * win : 0.0);
+        }
         dft8(v);
-        if (pass == 1) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            const int j0 = (lane >> 3) * 64 + k;
+        // (the accesses of one wave to LDS complete in order; the fences keep the compiler from
+        // moving loads over the stores)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
-            for (int r = 0; r < 8; r++) x[padded(j0 + 8 * r)] = v[r];
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (int r = 0; r < 8; r++) x[padded(lane * 8 + r)] = v[r];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int pass = 1; pass < 3; pass++) {
+            const int ns = pass == 1 ? 8 : 64;
+            const int k = lane & (ns - 1);
+#pragma unroll
+            for (int r = 0; r < 8; r++) v[r] = x[padded(lane + 64 * r)];
+#pragma unroll
+            for (int r = 1; r < 8; r++) v[r] = cmul(v[r], pass == 1 ? s_factor[r * 8 + k] : factor[r]);
+            dft8(v);
+            if (pass == 1) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const int j0 = (lane >> 3) * 64 + k;
+#pragma unroll
+                for (int r = 0; r < 8; r++) x[padded(j0 + 8 * r)] = v[r];
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            }
         }
-    }
-    // After the last pass value r of lane j is Z[j + 64 r].  Z[512 - k] is value 7 - r of lane
-    // 64 - j, in lane 0 its own value 8 - r.  The powers of both frames, bins 0 .. 256, replace
-    // the values of the last pass in LDS (all lanes have read theirs: the fence).
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        // After the last pass value r of lane j is Z[j + 64 r].  Z[512 - k] is value 7 - r of lane
+        // 64 - j, in lane 0 its own value 8 - r.  The powers of both frames, bins 0 .. 256, replace
+        // the values of the last pass in LDS (all lanes have read theirs: the fence).
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
-    for (int r = 0; r < 4; r++) {
-        double2 w = make_double2(__shfl(v[7 - r].x, (64 - lane) & 63), __shfl(v[7 - r].y, (64 - lane) & 63));
-        if (lane == 0) w = v[(8 - r) & 7];
-        const double ax = v[r].x + w.x, ay = v[r].y - w.y, bx = v[r].x - w.x, by = v[r].y + w.y;
-        x[lane + 64 * r] = make_double2(0.25 * (ax * ax + ay * ay), 0.25 * (bx * bx + by * by));
-    }
-    // bin 256 is its own partner: both spectra are real there
-    if (lane == 0) x[kFft / 2] = make_double2(v[4].x * v[4].x, v[4].y * v[4].y);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    // The triangles widen with their number, so a lane takes a narrow one and then the wide one
-    // that mirrors it (m and n_mels - 1 - m): every busy lane sums about the same number of bins.
-    for (int i = lane; i < (n_mels + 1) / 2; i += 64) {
-#pragma unroll
-        for (int side = 0; side < 2; side++) {
-            const int m = side == 0 ? i : n_mels - 1 - i;
-            if (side == 1 && m == i) break;  // the middle one of an odd number
-            const double *w = mel_weights + mel.first_weight[m];
-            const double2 *pw = x + mel.start[m];
-            double a = 0.0, b = 0.0;
+        for (int r = 0; r < 4; r++) {
+            double2 w = make_double2(__shfl(v[7 - r].x, (64 - lane) & 63), __shfl(v[7 - r].y, (64 - lane) & 63));
+            if (lane == 0) w = v[(8 - r) & 7];
+            const double ax = v[r].x + w.x, ay = v[r].y - w.y, bx = v[r].x - w.x, by = v[r].y + w.y;
+            x[lane + 64 * r] = make_double2(0.25 * (ax * ax + ay * ay), 0.25 * (bx * bx + by * by));
+        }
+        // bin 256 is its own partner: both spectra are real there
+        if (lane == 0) x[kFft / 2] = make_double2(v[4].x * v[4].x, v[4].y * v[4].y);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const bool more = f + 1 < f_end;
+        const uint32_t stride = frames;
+        float *o = out + utt[lo].out_off + t;
+        f++;
+        if (more) load();
+        // the sums of the ranges, behind the powers, of both frames
+        double2 *rising = x + kFft / 2 + 1, *falling = rising + kMaxMels + 1;
+        static_assert(kFft / 2 + 1 + 2 * (kMaxMels + 1) <= kFramePadded, "the sums fit behind the powers");
+        auto sum = [&](int m) {
+            const MelRange range = s_range[m];
+            double2 up = make_double2(0.0, 0.0), down = up;
+            double wu = range.rising, wd = range.falling;
+            const double2 *pw = x + range.start;
             // four bins at a time, so that their loads are under way together
-            const int count = mel.count[m];
-            for (int k = 0; k < count; k += 4) {
+            for (int k = 0; k < range.count; k += 4) {
 #pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const int at = min(k + i, count - 1);
-                    const double weight = w[at], wk = k + i < count ? weight : 0.0;
-                    a = fma(wk, pw[at].x, a);
-                    b = fma(wk, pw[at].y, b);
+                for (int e = 0; e < 4; e++) {
+                    const double2 power = pw[min(k + e, range.count - 1)];
+                    const double u = k + e < range.count ? wu : 0.0, d = k + e < range.count ? wd : 0.0;
+                    up = make_double2(fma(u, power.x, up.x), fma(u, power.y, up.y));
+                    down = make_double2(fma(d, power.x, down.x), fma(d, power.y, down.y));
+                    wu += range.step;
+                    wd -= range.step;
                 }
             }
-            float *o = out + u.out_off + (uint64_t)m * u.frames + t;
-            o[0] = (float)log(a + (double)kLogGuard);
-            if (two) o[1] = (float)log(b + (double)kLogGuard);
+            rising[m] = up;
+            falling[m] = down;
+        };
+        if (lane <= mirrored) sum(lane);
+        if (lane < mirrored) sum(mirrored);
+        if (n_ranges > 128 && lane == 0) sum(64);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const double *up = reinterpret_cast<const double *>(rising), *down = reinterpret_cast<const double *>(falling + 1);
+        for (int i = lane; i < 2 * n_mels; i += 64) {   // i = 2 m + frame
+            const float y = (float)log_of(up[i] + down[i] + (double)kLogGuard);
+            if ((i & 1) == 0 || two) o[(uint64_t)(i >> 1) * stride + (i & 1)] = y;
         }
+        if (!more) break;
     }
 }
 
@@ -461,8 +548,7 @@ struct prep_audio {
     // tables on the device
     double *d_window = nullptr;
     double2 *d_twiddle = nullptr;
-    double *d_mel_weights = nullptr;
-    MelTable mel;
+    MelRange *d_ranges = nullptr;
     // interpolation taps of the two rate pairs seen last, in buffers of the largest size a rate
     // pair can need (reserved in prep_audio_create: a call never allocates or frees): bands where the
     // plan has steps, else taps by phase
@@ -527,17 +613,20 @@ void make_taps(int p, int q, std::vector<double> *taps, std::vector<int32_t> *fi
 }
 
 // The matrix form of these taps, in place of them, if the rates are for it: the shortest period
-// that fills its blocks of sixteen phases to 98 %, or the one of at most sixteen times p : q that
-// fills them best.
+// that fills its blocks of sixteen phases to 98 %, or the one of at most sixteen times p : q, with
+// room for its table, that fills them best.
 void make_bands(int p, int q, int n_taps, std::vector<double> *taps, std::vector<int32_t> *first, BandPlan *plan)
 {
     *plan = BandPlan{};
+    const int most = (n_taps + (15 * p + q - 1) / q + 1 + 15) / 16;  // quads of a band
     int m = 0;
     double best = 0.0;
     for (int k = 1; k <= 16 && best < 0.98; k++) {
+        if ((size_t)((q * k + 15) / 16) * (size_t)std::max(2, most) * 256 > kMaxTapEntries) break;
         const double used = (double)q * k / (16.0 * ((q * k + 15) / 16));
         if (used > best + 1e-9) { best = used; m = k; }
     }
+    if (m == 0) return;
     BandPlan t;
     t.P = p * m;
     t.Q = q * m;
@@ -547,7 +636,7 @@ void make_bands(int p, int q, int n_taps, std::vector<double> *taps, std::vector
     for (int b = 0; b < t.blocks; b++)
         width = std::max(width, start(std::min(16 * b + 15, t.Q - 1)) + n_taps - start(16 * b));
     t.quads = std::max(2, (width + 15) / 16);
-    if (t.quads > kBandQuadsMost || (size_t)t.blocks * (size_t)t.quads * 256 > kMaxTapEntries) return;
+    if (t.quads > kBandQuadsMost) return;
     std::vector<double> bands((size_t)t.blocks * (size_t)t.quads * 256, 0.0);
     std::vector<int32_t> starts((size_t)t.blocks);
     for (int b = 0; b < t.blocks; b++) starts[(size_t)b] = start(16 * b);
@@ -595,36 +684,31 @@ int prep_audio_create(prep_audio **out, const prep_audio_config *cfg)
     std::vector<double2> tw((size_t)kFft);  // W^k = exp(-2 pi i k / 512), k = 0 .. 511 (r k reaches 7 * 63)
     for (int k = 0; k < kFft; k++)
         tw[(size_t)k] = make_double2(cos(2.0 * M_PI * k / kFft), -sin(2.0 * M_PI * k / kFft));
-    std::vector<double> weights;
+    std::vector<MelRange> ranges((size_t)cfg->n_mels + 1);
     {
         auto mel_of = [](double f) { return 2595.0 * log10(1.0 + f / 700.0); };
         auto hz_of = [](double m) { return 700.0 * (pow(10.0, m / 2595.0) - 1.0); };
         const double top = mel_of(cfg->rate / 2.0);
         std::vector<double> corner((size_t)cfg->n_mels + 2);
         for (int i = 0; i < cfg->n_mels + 2; i++) corner[(size_t)i] = hz_of(top * i / (cfg->n_mels + 1));
-        for (int m = 0; m < cfg->n_mels; m++) {
-            const double lo = corner[(size_t)m], mid = corner[(size_t)m + 1], hi = corner[(size_t)m + 2];
-            h->mel.start[m] = 0;
-            h->mel.count[m] = 0;
-            h->mel.first_weight[m] = (int32_t)weights.size();
-            for (int k = 0; k <= kFft / 2; k++) {
-                const double f = (double)k * cfg->rate / kFft;
-                const double w = std::max(0.0, std::min((f - lo) / (mid - lo), (hi - f) / (hi - mid)));
-                if (w > 0.0) {
-                    if (h->mel.count[m] == 0) h->mel.start[m] = k;
-                    // zeros between positive weights cannot occur in a triangle
-                    h->mel.count[m] = k - h->mel.start[m] + 1;
-                    weights.push_back(w);
-                }
-            }
+        // range i = the bins from corner i up to corner i + 1 (bin 0 lies on a corner, with no weight)
+        int k = 1;
+        for (int i = 0; i <= cfg->n_mels; i++) {
+            const double lo = corner[(size_t)i], hi = corner[(size_t)i + 1], width = (double)cfg->rate / kFft;
+            MelRange &range = ranges[(size_t)i];
+            range.start = k;
+            range.rising = (k * width - lo) / (hi - lo);
+            range.falling = (hi - k * width) / (hi - lo);
+            range.step = width / (hi - lo);
+            while (k <= kFft / 2 && k * width < hi) k++;
+            range.count = k - range.start;
         }
-        if (weights.empty()) weights.push_back(0.0);
     }
     const size_t n = (size_t)cfg->max_batch;
     bool ok = hipSetDevice(cfg->device) == hipSuccess;
     ok = ok && hipMalloc((void **)&h->d_window, sizeof(double) * kFft) == hipSuccess;
     ok = ok && hipMalloc((void **)&h->d_twiddle, sizeof(double2) * kFft) == hipSuccess;
-    ok = ok && hipMalloc((void **)&h->d_mel_weights, sizeof(double) * weights.size()) == hipSuccess;
+    ok = ok && hipMalloc((void **)&h->d_ranges, sizeof(MelRange) * ranges.size()) == hipSuccess;
     ok = ok && hipMalloc((void **)&h->d_utt, kRecordBytes * n) == hipSuccess;
     ok = ok && hipHostMalloc((void **)&h->h_utt, kRecordBytes * n, hipHostMallocDefault) == hipSuccess;
     // the resampled signal is never longer than max_total_samples scaled by the largest ratio accepted
@@ -638,7 +722,7 @@ int prep_audio_create(prep_audio **out, const prep_audio_config *cfg)
     ok = ok && hipEventCreateWithFlags(&h->done, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipMemcpy(h->d_window, window.data(), sizeof(double) * kFft, hipMemcpyHostToDevice) == hipSuccess;
     ok = ok && hipMemcpy(h->d_twiddle, tw.data(), sizeof(double2) * kFft, hipMemcpyHostToDevice) == hipSuccess;
-    ok = ok && hipMemcpy(h->d_mel_weights, weights.data(), sizeof(double) * weights.size(), hipMemcpyHostToDevice) == hipSuccess;
+    ok = ok && hipMemcpy(h->d_ranges, ranges.data(), sizeof(MelRange) * ranges.size(), hipMemcpyHostToDevice) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         prep_audio_destroy(h);
@@ -655,7 +739,7 @@ int prep_audio_destroy(prep_audio *h)
     if (h->pending) (void)hipEventSynchronize(h->done);
     (void)hipFree(h->d_window);
     (void)hipFree(h->d_twiddle);
-    (void)hipFree(h->d_mel_weights);
+    (void)hipFree(h->d_ranges);
     (void)hipFree(h->d_utt);
     (void)hipFree(h->d_mid);
     for (auto &ts : h->slot) {
@@ -771,16 +855,18 @@ int prep_audio_features(prep_audio *h, const float *waveforms, const uint64_t *o
         hipLaunchKernelGGL(resample_kernel, dim3((unsigned)((mid_total + 255) / 256)), dim3(256), 0, stream, waveforms,
                            h->d_utt, d_starts, n, taps->d_taps, taps->d_first, p, q, taps->n_taps, h->d_mid, mid_total);
     }
-    const uint64_t pairs_per_wg = kFrameThreads / 64;
-    const dim3 pair_grid((unsigned)((pairs_total + pairs_per_wg - 1) / pairs_per_wg));
+    // (from sixteen waves a compute unit on, a wave takes more pairs than one)
+    const uint32_t per_wave = (uint32_t)std::min<uint64_t>(kPairsPerWave, std::max<uint64_t>(1, pairs_total / (256 * 16)));
+    const uint64_t per_wg = (uint64_t)per_wave * (kFrameThreads / 64);
+    const dim3 pair_grid((unsigned)((pairs_total + per_wg - 1) / per_wg));
     if (p == q)
         hipLaunchKernelGGL(log_mel_kernel<float>, pair_grid, dim3(kFrameThreads), 0, stream, waveforms, h->d_utt,
-                           d_starts + n, n, pairs_total, h->cfg.hop, h->d_window, h->d_twiddle, h->mel,
-                           h->d_mel_weights, h->cfg.n_mels, out);
+                           d_starts + n, n, pairs_total, per_wave, h->cfg.hop, h->d_window, h->d_twiddle,
+                           h->d_ranges, h->cfg.n_mels, out);
     else
         hipLaunchKernelGGL(log_mel_kernel<double>, pair_grid, dim3(kFrameThreads), 0, stream, (const double *)h->d_mid,
-                           h->d_utt, d_starts + n, n, pairs_total, h->cfg.hop, h->d_window, h->d_twiddle, h->mel,
-                           h->d_mel_weights, h->cfg.n_mels, out);
+                           h->d_utt, d_starts + n, n, pairs_total, per_wave, h->cfg.hop, h->d_window, h->d_twiddle,
+                           h->d_ranges, h->cfg.n_mels, out);
     hipLaunchKernelGGL(normalize_kernel, dim3((unsigned)n * (unsigned)h->cfg.n_mels), dim3(256), 0, stream, h->d_utt,
                        h->cfg.n_mels, out);
     AUDIO_TRY(hipGetLastError());
