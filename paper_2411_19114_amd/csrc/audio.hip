@@ -702,6 +702,13 @@ int prep_audio_create(prep_audio **out, const prep_audio_config *cfg)
             range.step = width / (hi - lo);
             while (k <= kFft / 2 && k * width < hi) k++;
             range.count = k - range.start;
+            // the falling weights, one after the other as the kernel forms them, stay above zero
+            auto last = [&]() {
+                double w = range.falling;
+                for (int b = 1; b < range.count; b++) w -= range.step;
+                return w;
+            };
+            while (range.count > 0 && last() < 0.0) range.falling = nextafter(range.falling, 2.0);
         }
     }
     const size_t n = (size_t)cfg->max_batch;
