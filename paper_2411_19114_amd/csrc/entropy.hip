@@ -51,6 +51,7 @@ constexpr uint32_t kShortInterval = kLongIntervalBytes;  // mean clean bytes up 
 constexpr uint32_t kNoMarker = 0xFFFFFFFFu;
 constexpr uint32_t kSubBits = kSubseqBytes * 8;
 static_assert(kSubseqBytes == 64 && (kSubseqBytes / 4) == (1 << kPadShift), "one 64-bit keep mask per lane");
+static_assert(kT == 256, "a row's number fits a byte; four waves");
 
 // Lookup entry of a Huffman code (16 bits):
 //   bits 4..0   code length + number of appended bits (1..31); 0 = search the code lists
@@ -107,6 +108,13 @@ struct alignas(16) HuffTables : HuffCodes {
 constexpr int32_t kRunLead = 16;
 constexpr uint32_t kRunLeadBits = 9;  // most bits of the symbols before the last
 
+// Rows (subsequences) that a round of the iteration decodes, and every row's blocks
+struct RowLists {
+    uint32_t from[kT];
+    uint16_t blocks[kT];
+    uint8_t row[kT];
+};
+
 // kHyp, kRuns: see decode_entropy
 template <bool kHyp, bool kRuns>
 struct DecodeShared {
@@ -123,7 +131,14 @@ struct DecodeShared {
     union {
         uint16_t bpos[kMaxBoundaries];
         unsigned long long keep_here[kHyp ? 1 : kT];
+        RowLists rows_here;
     };
+    std::conditional_t<kHyp, uint8_t, RowLists> rows_there;
+    __device__ RowLists &rows()
+    {
+        if constexpr (kHyp) return rows_here;
+        else return rows_there;
+    }
     std::conditional_t<kRuns, HuffTables, HuffCodes> tab;
     unsigned long long keep_there[kHyp ? kT : 1];
     __device__ unsigned long long &keep(int lane) { return kHyp ? keep_there[lane] : keep_here[lane]; }
@@ -1557,25 +1572,49 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
             }
             if (!active) S.state[tid] = out_state;
         } else {
-        // synchronise: iterate end states to their fixed point
+        // synchronise: iterate end states to their fixed point.  After the first round few rows
+        // have a new start state, but up to a round's end they are all over the workgroup: they
+        // are dealt to neighbouring lanes, or three to four waves a round would decode for a few lanes
+        // each (64 full-HD images at quality 95: 11.6 times the waves' work of one decode of all rows, 4
+        // when dealt; kernel ITER_US us).
+        RowLists &rows = S.rows();
         if (active) out_state = count_span<true>(S, S.clean + clean_row_of_bit(in_state >> 9), runs, g, in_state, end_bit, limit_bits, &nblk);
         S.state[tid] = out_state;
+        rows.blocks[tid] = (uint16_t)nblk;
+        __syncthreads();
         for (uint32_t round = 0; round <= nsub; round++) {
-            __syncthreads();
-            int changed = 0;
             const uint32_t prev_state = tid > 0 ? S.state[tid - 1] : st0;
+            const bool again = active && tid > 0 && prev_state != in_state;
+            if (again) in_state = prev_state;
+            const uint64_t ones = __ballot(again);
+            if ((tid & 63) == 0) S.scan_a[tid >> 6] = (uint32_t)__popcll(ones);
             __syncthreads();
-            if (active && tid > 0 && prev_state != in_state) {
-                in_state = prev_state;
-                uint32_t o = in_state;
-                // a predecessor that already ran past my subsequence leaves me nothing to decode
-                if ((in_state >> 9) < end_bit) o = count_span<true>(S, S.clean + clean_row_of_bit(in_state >> 9), runs, g, in_state, end_bit, limit_bits, &nblk);
-                else nblk = 0;
-                if (o != out_state) { out_state = o; changed = 1; }
-                S.state[tid] = out_state;
+            uint32_t at = 0, total = 0;
+            for (int ww = 0; ww < kT / 64; ww++) {
+                if (ww < tid >> 6) at += S.scan_a[ww];
+                total += S.scan_a[ww];
             }
-            if (!__syncthreads_or(changed)) break;
+            if (total == 0) break;  // (uniform over the workgroup)
+            if (again) {
+                at += (uint32_t)__popcll(ones & ((1ull << (tid & 63)) - 1ull));
+                rows.from[at] = in_state;
+                rows.row[at] = (uint8_t)tid;
+            }
+            __syncthreads();
+            // (a workgroup's waves lie on SIMDs of their own: the first in line is another one every round)
+            const uint32_t i = ((uint32_t)tid + 64u * ((wg + round) & 3u)) & (uint32_t)(kT - 1);
+            if (i < total) {
+                const uint32_t row = rows.row[i], from = rows.from[i], row_end = min((row + 1u) * span_bits, own_bits);
+                uint32_t o = from, nb = 0;
+                // a predecessor that already ran past the subsequence leaves nothing to decode
+                if ((from >> 9) < row_end) o = count_span<true>(S, S.clean + clean_row_of_bit(from >> 9), runs, g, from, row_end, limit_bits, &nb);
+                S.state[row] = o;
+                rows.blocks[row] = (uint16_t)nb;
+            }
+            __syncthreads();
         }
+        out_state = S.state[tid];
+        nblk = rows.blocks[tid];
         }
 
         // write: decode once more from the true states
