@@ -928,9 +928,10 @@ __device__ __forceinline__ uint32_t write_span(const Shared &S, const uint32_t *
 // Zeros over the blocks [lo, hi) of an image whose coefficients begin at coef, in 16-byte units
 // first, first + step, ... of the range's eight per block.  Nothing clears the coefficient
 // workspace before the decoder runs, and the writing passes store only the coefficients that
-// symbols name: the blocks that a pass is about to decode get their zeros from here first, in
-// whole 128-byte lines.  Out of line: it runs a few times per chunk and must not add to the
-// registers of the symbol loops.
+// symbols name: a workgroup begins with zeros over all blocks that it is to decode, in whole
+// 128-byte lines, and has barriers before its first coefficient.  (Stored by each lane over its own
+// blocks, right before these, they took a tenth of the time for long intervals.)  Out of line: it
+// must not add to the registers of the symbol loops.
 __device__ __attribute__((noinline)) void zero_blocks(int16_t *coef, uint32_t lo, uint32_t hi, uint32_t first,
                                                       uint32_t step)
 {
@@ -1035,6 +1036,19 @@ __device__ inline int find_image(int n, uint32_t x, F key)
     return lo;
 }
 
+// The same by a whole wave (all lanes must call), in two loads that wait for each other instead
+// of one for every halving: a kernel of many images begins 2 to 3 us earlier.
+template <typename F>
+__device__ inline int find_image_wave(int n, uint32_t x, F key)
+{
+    const int lane = threadIdx.x & 63, s = (n + 63) / 64;
+    if (s > 64) return find_image(n, x, key);
+    int lo = 0;
+    if (s > 1) lo = s * max(0, __popcll(__ballot(lane * s < n && key(min(lane * s, n - 1)) <= x)) - 1);
+    const int i = lo + lane;
+    return lo + max(0, __popcll(__ballot((s == 1 || lane < s) && i < n && key(min(i, n - 1)) <= x)) - 1);
+}
+
 // Which raw bytes of one 16-byte piece are entropy-coded data (keep) and which are the
 // code byte of an RSTn marker (bound).  prev = the byte before the piece, next = the byte
 // after it.  Bytes outside [cs, ce) are neither.  A byte after FF is stuffing or a marker
@@ -1063,6 +1077,44 @@ __device__ inline void classify16(const uint4 v, uint32_t prev, uint32_t nextb, 
     *bound = b;
     *last = prev;
 }
+
+// Packs the bytes that staging keeps into big-endian words, a lane its own piece of the stream.  A lane
+// puts the words whose last byte is its own, with zeros for bytes of the lanes before; its last
+// bytes, fewer than four, are ORed into their word after a barrier.  Words without stuffing or
+// markers in any lane go through whole.  (A byte at a time took 22 of the 177 us that a workgroup
+// spends on a 12 KB restart interval, PACK_US now.)
+struct BytePacker {
+    uint32_t word, n;  // word of the destination, and how many of its bytes precede
+    uint32_t acc = 0;  // the last n bytes, in its low bits
+    __device__ BytePacker(uint32_t byte) : word(byte >> 2), n(byte & 3u) {}
+    __device__ uint32_t at() const { return 4u * word + n; }
+    // the bytes of w (the lowest first) that are set in keep4; put(index, word) stores
+    template <typename Put>
+    __device__ __forceinline__ void add(uint32_t w, uint32_t keep4, Put put)
+    {
+        if (!wave_any(keep4 != 15u)) {
+            const uint32_t v = __builtin_bswap32(w);
+            put(word++, __builtin_amdgcn_alignbit(acc, v, 8u * n));
+            acc = v;
+            return;
+        }
+        uint32_t c = 0, more = 0;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const bool kept = ((keep4 >> i) & 1u) != 0;
+            c = kept ? (c << 8) | ((w >> (8 * i)) & 255u) : c;
+            more += kept ? 1u : 0u;
+        }
+        const uint64_t both = ((uint64_t)acc << (8u * more)) | c;
+        n += more;
+        if (n >= 4u) {
+            n -= 4u;
+            put(word++, (uint32_t)(both >> (8u * n)));
+        }
+        acc = (uint32_t)both;
+    }
+    __device__ uint32_t rest() const { return acc << (32u - 8u * n); }  // (n != 0)
+};
 
 }  // namespace
 
@@ -1114,7 +1166,7 @@ __global__ __launch_bounds__(kDecodeThreads) void scan_restart_markers(
                 dst[part[m][0] / 4 + i] = src[part[m][0] / 4 + i];
         return;
     }
-    const int img = find_image(n_images, wg, [&](int i) { return recs[i].window0; });
+    const int img = find_image_wave(n_images, wg, [&](int i) { return recs[i].window0; });
     const ImageRec &R = recs[img];
     const uint32_t w = wg - R.window0;
     // the per-image verdict starts as the host parser's; the decoder may lower it
@@ -1187,7 +1239,7 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
     const uint16_t *const runs = run_entries(S.tab);
     const int tid = threadIdx.x;
     const uint32_t wg = blockIdx.x;
-    const int img = find_image(n_images, wg, [&](int i) { return recs[i].window0; });
+    const int img = find_image_wave(n_images, wg, [&](int i) { return recs[i].window0; });
     const ImageRec &R = recs[img];
     const uint32_t w = wg - R.window0;
     if (R.status != PREP_OK || w >= R.n_windows) return;
@@ -1337,10 +1389,9 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
                                                 S.scan_a, &totals);
         const uint32_t clean_len = totals & 0xFFFFu, nbnd = totals >> 16;
         const uint32_t my_off = my_pre & 0xFFFFu;
+        if (iter == 0) zero_blocks(coef, block0, block_end, (uint32_t)tid, kT);  // (behind the loads)
         S.keep_off[tid] = my_off;
         if (tid == 0) S.keep_off[kT] = clean_len;
-        // zeros behind the data: the last word is written byte by byte, and lookups near the
-        // end read a few words past it
         // Which of the two passes will decode the chunk is known now.  Intervals 0..n_iv-1 of
         // the chunk end inside it: the first runs from the chunk's start state to the first
         // listed start, interval k > 0 between listed starts k-1 and k, and in the last chunk
@@ -1353,7 +1404,7 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
         // the short-interval pass reads the stream without pad words (its lanes start anywhere)
         const uint32_t pad_shift = short_intervals ? 31u : (uint32_t)kPadShift;
         if (!short_intervals) S.keep(tid) = keep;
-        // zeros behind the data: the last word is written byte by byte, and lookups near the
+        // zeros behind the data: its last word is put together with OR, and lookups near the
         // end read a few words past it
         {
             // (a run of array entries: in the subsequence passes it takes in the rows' last words,
@@ -1362,10 +1413,15 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
             const uint32_t from = !short_intervals && (wd & 15u) == 0 && wd != 0 ? first - 1u : first;
             if (tid < 14) S.clean[from + (uint32_t)tid] = 0;
         }
-        __syncthreads();  // zero fill done before bytes are written
         {
-            uint8_t *cb = reinterpret_cast<uint8_t *>(S.clean);
-            uint32_t o = my_off, rank = my_pre >> 16;
+            BytePacker pack(my_off);
+            uint32_t rank = my_pre >> 16;
+            auto put = [&](uint32_t wq, uint32_t word) {
+                const uint32_t at = wq + (wq >> pad_shift);
+                S.clean[at] = word;
+                // the first word of a subsequence is also the last of the row before
+                if (!short_intervals && (wq & 15u) == 0 && wq != 0) S.clean[at - 1u] = word;
+            };
 #pragma unroll
             for (int k = 0; k < 4; k++) {
                 const uint32_t kp = (uint32_t)(keep >> (16 * k)) & 0xFFFFu;
@@ -1373,26 +1429,30 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
                 if ((kp | bd) == 0) continue;
                 const uint32_t wv[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
 #pragma unroll
-                for (int i = 0; i < 16; i++) {
-                    if ((bd >> i) & 1u) {
+                for (int e = 0; e < 4; e++) {
+                    const uint32_t keep4 = (kp >> (4 * e)) & 15u;
+                    uint32_t marks = (bd >> (4 * e)) & 15u;
+                    while (marks != 0) {
+                        const uint32_t i = (uint32_t)__builtin_ctz(marks);
+                        marks &= marks - 1u;
+                        const uint32_t o = pack.at() + (uint32_t)__popcll(keep4 & ((1u << i) - 1u));
                         // marker number marker_base + rank of the image must be RST((that) mod 8)
-                        if ((((wv[i >> 2] >> (8 * (i & 3))) ^ (marker_base + rank)) & 7u) != 0) bad = 1;
+                        if ((((wv[e] >> (8 * i)) ^ (marker_base + rank)) & 7u) != 0) bad = 1;
                         atomicOr(&S.bmask[o >> 5], 1u << (o & 31));
                         if (short_intervals) S.bpos[rank] = (uint16_t)o;  // (at most kMaxBoundaries then)
                         // raw offset just after the last marker of the chunk: where a chunk of
                         // whole intervals would resume
-                        if (rank + 1 == nbnd) S.bcast[2] = (uint32_t)(my_lo + 16 * k + i + 1);
+                        if (rank + 1 == nbnd) S.bcast[2] = (uint32_t)(my_lo + 16 * k + 4 * e + (int32_t)i + 1);
                         rank++;
                     }
-                    if ((kp >> i) & 1u) {
-                        const uint32_t wq = o >> 2, at = ((wq + (wq >> pad_shift)) << 2) | ((o & 3u) ^ 3u);
-                        const uint8_t byte = (uint8_t)((wv[i >> 2] >> (8 * (i & 3))) & 255u);
-                        cb[at] = byte;
-                        // the first word of a subsequence is also the last of the row before
-                        if (!short_intervals && (wq & 15u) == 0 && wq != 0) cb[at - 4] = byte;
-                        o++;
-                    }
+                    pack.add(wv[e], keep4, put);
                 }
+            }
+            __syncthreads();  // (the words, and the zeros behind the data, are there)
+            if (pack.n != 0) {
+                const uint32_t wq = pack.word, at = wq + (wq >> pad_shift);
+                atomicOr(&S.clean[at], pack.rest());
+                if (!short_intervals && (wq & 15u) == 0 && wq != 0) atomicOr(&S.clean[at - 1u], pack.rest());
             }
         }
         __syncthreads();
@@ -1427,14 +1487,6 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
         // possible and the other waves of the workgroup leave their SIMDs to other workgroups.
         if (short_intervals) {
             const uint32_t rem0 = g.ri_blocks - block_base % g.ri_blocks;  // blocks left in interval 0
-            {
-                // zeros over the blocks of the chunk's intervals: [z_lo, z_hi) of the image (a block
-                // that is under way when the chunk begins was begun, and zeroed, in the chunk before)
-                const uint32_t z_lo = min(block_base + ((st0 & 63u) ? 1u : 0u), g.n_blocks);
-                const uint32_t z_hi = min(min(block_base + rem0 + (n_iv - 1) * g.ri_blocks, block_end), g.n_blocks);
-                zero_blocks(coef, z_lo, z_hi, (uint32_t)tid, kT);
-                __syncthreads();  // (and only then does any lane store a coefficient)
-            }
             for (uint32_t k = (uint32_t)tid; k < n_iv; k += kT) {
                 const uint32_t start = k ? pack_state((uint32_t)S.bpos[k - 1] * 8u, 0, 0) : st0;
                 const uint32_t end_bit = k < nbnd ? (uint32_t)S.bpos[k] * 8u : limit_bits;
@@ -1575,19 +1627,24 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
         // synchronise: iterate end states to their fixed point.  After the first round few rows
         // have a new start state, but up to a round's end they are all over the workgroup: they
         // are dealt to neighbouring lanes, or three to four waves a round would decode for a few lanes
-        // each (64 full-HD images at quality 95: 11.6 times the waves' work of one decode of all rows, 4
-        // when dealt; kernel ITER_US us).
+        // each.  Start states come back, where a row's predecessor is decoded from another state and
+        // falls into step all the same: a row's lane keeps its last three results, and rows are
+        // decoded only once nothing moves by those.  (64 full-HD images at quality 95: 14.4 rounds
+        // a chunk without, 8.2 with three, no fewer with eight; kernel 1358 -> ITER_US us.)
         RowLists &rows = S.rows();
         if (active) out_state = count_span<true>(S, S.clean + clean_row_of_bit(in_state >> 9), runs, g, in_state, end_bit, limit_bits, &nblk);
         S.state[tid] = out_state;
-        rows.blocks[tid] = (uint16_t)nblk;
+        uint32_t in1 = ~0u, out1 = 0, nblk1 = 0, in2 = ~0u, out2 = 0, nblk2 = 0;
         __syncthreads();
-        for (uint32_t round = 0; round <= nsub; round++) {
+        // (the first row whose start state is not final becomes final with every decode, and rows
+        // behind it move by kept results at most once each in between)
+        for (uint32_t round = 0; round <= nsub * nsub; round++) {
             const uint32_t prev_state = tid > 0 ? S.state[tid - 1] : st0;
-            const bool again = active && tid > 0 && prev_state != in_state;
-            if (again) in_state = prev_state;
+            const bool moved = active && tid > 0 && prev_state != in_state;
+            const bool kept = moved && (prev_state == in1 || prev_state == in2), again = moved && !kept;
             const uint64_t ones = __ballot(again);
-            if ((tid & 63) == 0) S.scan_a[tid >> 6] = (uint32_t)__popcll(ones);
+            if (__ballot(kept) != 0 && (tid & 63) == 0) S.scan_a[tid >> 6] = 0x10000u | (uint32_t)__popcll(ones);
+            else if ((tid & 63) == 0) S.scan_a[tid >> 6] = (uint32_t)__popcll(ones);
             __syncthreads();
             uint32_t at = 0, total = 0;
             for (int ww = 0; ww < kT / 64; ww++) {
@@ -1595,6 +1652,19 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
                 total += S.scan_a[ww];
             }
             if (total == 0) break;  // (uniform over the workgroup)
+            if (moved && (kept || total < 0x10000u)) {
+                // the current result becomes the second, an older one the current one
+                const bool second = prev_state == in1;
+                const uint32_t o = second ? out1 : out2, n = second ? nblk1 : nblk2;
+                if (!second) { in2 = in1; out2 = out1; nblk2 = nblk1; }
+                in1 = in_state; out1 = out_state; nblk1 = nblk;
+                in_state = prev_state; out_state = o; nblk = n;
+            }
+            if (total >= 0x10000u) {
+                if (kept) S.state[tid] = out_state;
+                __syncthreads();
+                continue;
+            }
             if (again) {
                 at += (uint32_t)__popcll(ones & ((1ull << (tid & 63)) - 1ull));
                 rows.from[at] = in_state;
@@ -1612,9 +1682,11 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
                 rows.blocks[row] = (uint16_t)nb;
             }
             __syncthreads();
+            if (again) {
+                out_state = S.state[tid];
+                nblk = rows.blocks[tid];
+            }
         }
-        out_state = S.state[tid];
-        nblk = rows.blocks[tid];
         }
 
         // write: decode once more from the true states
@@ -1627,15 +1699,6 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
         const bool boundary_due = (in_state & 511u) == 0 && g.ri_blocks != 0 && my_block % g.ri_blocks == 0 &&
                                   my_block < g.n_blocks && tid != 0;
         wc.iv_rem = boundary_due ? 0 : g.ri_blocks ? (int32_t)(g.ri_blocks - my_block % g.ri_blocks) : 0x7FFFFFFF;
-        // Nothing has cleared the blocks: every lane stores zeros over the blocks whose first
-        // coefficient it will decode (a block that is under way when the lane begins was begun,
-        // and zeroed, by an earlier lane or chunk), and only then does any lane store a coefficient.
-        if (active && (in_state >> 9) < end_bit) {
-            const uint32_t z_lo = my_block + ((in_state & 63u) ? 1u : 0u);
-            const uint32_t z_hi = min(my_block + nblk + ((out_state & 63u) ? 1u : 0u), g.n_blocks);
-            zero_blocks(coef, z_lo, max(z_lo, z_hi), 0, 1);
-        }
-        __syncthreads();
         uint32_t final_state = out_state;
         if (active && (in_state >> 9) < end_bit) {
             uint32_t nb2;
@@ -1816,22 +1879,21 @@ __device__ inline StreamPart stage_stream(StreamShared<Tables> &S, const uint8_t
     const uint32_t before = block_excl_scan(n_all | (n_own << 16), S.scan_a, &totals) & 0xFFFFu;
     part.total = totals & 0xFFFFu;
     part.own = totals >> 16;
-    // zeros behind the data: the last word is written byte by byte, and lookups near the end
+    // zeros behind the data: its last word is put together with OR, and lookups near the end
     // read a few words past it
     if (tid < 6) S.clean[(part.total >> 2) + (uint32_t)tid] = 0;
     part.marker = __syncthreads_or(bound != 0 || bad != 0) != 0;
-    uint8_t *cb = reinterpret_cast<uint8_t *>(S.clean);
-    uint32_t o = before;
+    BytePacker pack(before);
 #pragma unroll
     for (int k = 0; k < 2; k++) {
+        if (keep[k] == 0) continue;
         const uint32_t wv[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
 #pragma unroll
-        for (int i = 0; i < 16; i++)
-            if ((keep[k] >> i) & 1u) {
-                cb[o ^ 3u] = (uint8_t)(wv[i >> 2] >> (8 * (i & 3)));
-                o++;
-            }
+        for (int e = 0; e < 4; e++)
+            pack.add(wv[e], (keep[k] >> (4 * e)) & 15u, [&](uint32_t at, uint32_t word) { S.clean[at] = word; });
     }
+    __syncthreads();
+    if (pack.n != 0) atomicOr(&S.clean[pack.word], pack.rest());
     // Windows are joined at rows that both hold whole, with the bytes of a symbol that begins at
     // their end.  Stuffing leaves at least half of the bytes, which is enough (see ce), but a
     // run of fill bytes (FF FF .. FF 00) may leave any number, behind this window or in it.
@@ -1871,7 +1933,7 @@ __device__ inline void stream_geometry(Geometry &g, const ImageRec &R)
 // stream windows share their number with the next one that has some)
 __device__ inline int image_of_stream(const ImageRec *recs, int n_images, uint32_t wg)
 {
-    return find_image(n_images, wg, [&](int i) { return recs[i].stream0; });
+    return find_image_wave(n_images, wg, [&](int i) { return recs[i].stream0; });
 }
 
 // The extra node of key (see kStateBits), made if there is none yet; x = where to look first.  Out of
