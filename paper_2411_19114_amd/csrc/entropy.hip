@@ -555,26 +555,35 @@ __device__ __forceinline__ uint32_t lds_address(const void *p)
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
 }
 
-// Parts that the written-out steps share; each leaves in vcc whether the block ends.
-// the words around the position, and the next 32 bits; m1 = the lane is near; t0 = the bit offset
+// Parts that the written-out steps share.  What the next entry's address needs comes first; its read is
+// under way while the rest is settled.  (The next stream word's read follows it: reads return in
+// order, so the entry is there when at most one is left.)  vcc = the block ends, carry = a new word begins,
+// t0 = the bit offset.
 #define STEP_WORDS                                              \
-    "v_cndmask_b32 %[hi], %[hi], %[lo], vcc\n"                  \
-    "v_cndmask_b32 %[lo], %[lo], %[ahead], vcc\n"               \
-    "v_addc_co_u32 %[w], vcc, 0, %[w], vcc\n"                   \
+    "s_waitcnt lgkmcnt(0)\n"                                    \
+    "v_cndmask_b32 %[hi], %[hi], %[lo], %[carry]\n"             \
+    "v_cndmask_b32 %[lo], %[lo], %[ahead], %[carry]\n"          \
+    "v_addc_co_u32 %[w], %[m2], 0, %[w], %[carry]\n"            \
     "v_alignbit_b32 %[win], %[hi], %[lo], %[t0]\n"              \
-    "v_lshl_add_u32 %[t2], %[w], 2, %[aheadat]\n"               \
-    "v_cmp_lt_i32 vcc, 62, %[k]\n"                              \
-    "ds_read_b32 %[ahead], %[t2]\n"                             \
-    "v_cmp_ge_i32 %[m1], %[w], %[nearw]\n"
-// t3, t2 = the two candidates of lookup_number; the slot
-#define STEP_NUMBER                                             \
-    "v_lshrrev_b32 %[t3], 22, %[win]\n"                         \
-    "v_add_u32_sdwa %[t2], %[win], %[fine] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD\n" \
     "v_cndmask_b32 %[slot], %[slot], %[t1], vcc\n"
-// p = the position
+// m1 = the lane is near; p = the position
 #define STEP_POSITION                                           \
+    "v_cmp_ge_i32 %[m1], %[w], %[nearw]\n"                      \
     "v_lshlrev_b32 %[p], 5, %[w]\n"                             \
     "v_sub_u32 %[p], %[p], %[t0]\n"
+// t3, t2 = the two candidates of lookup_number
+#define STEP_NUMBER                                             \
+    "v_lshrrev_b32 %[t3], 22, %[win]\n"                         \
+    "v_add_u32_sdwa %[t2], %[win], %[fine] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD\n"
+// from t3, the number, and t0, the table
+#define STEP_LOOK_UP                                            \
+    "v_bfe_u32 %[t1], %[chroma], %[slot], 3\n"                  \
+    "v_lshlrev_b32 %[t3], 3, %[t3]\n"                           \
+    "v_addc_co_u32 %[block], %[m2], 0, %[block], vcc\n"         \
+    "v_add3_u32 %[t3], %[t3], %[t1], %[t0]\n"                   \
+    "ds_read_u16 %[e], %[t3]\n"                                 \
+    "v_lshl_add_u32 %[t2], %[w], 2, %[aheadat]\n"               \
+    "ds_read_b32 %[ahead], %[t2]\n"
 // Lanes that are due are put aside: they wait for the others, and all are looked at together when no
 // other lane is near.  (Spans of the same length end some twenty steps apart.  With a way out of
 // the loop and back for each lane's end a span's end took a third of its time.)
@@ -584,7 +593,7 @@ __device__ __forceinline__ uint32_t lds_address(const void *p)
     "2:\n"
 #define STEP_DUE                                                \
     "v_cmp_ge_u32 %[m2], %[p], %[end]\n"                        \
-    "s_waitcnt lgkmcnt(0)\n"                                    \
+    "s_waitcnt lgkmcnt(1)\n"                                    \
     "v_and_b32 %[t0], 31, %[e]\n"                               \
     "v_add_u32 %[t0], %[t0], %[p]\n"                            \
     "v_cmp_gt_u32 %[m0], %[t0], %[nb]\n"                        \
@@ -595,17 +604,20 @@ __device__ __forceinline__ uint32_t lds_address(const void *p)
     "s_andn2_b64 exec, exec, %[m0]\n"                           \
     "s_and_b64 %[m1], %[m1], exec\n"                            \
     "s_cbranch_scc1 2b\n"                                       \
-    "s_mov_b64 exec, %[all]\n"
+    "s_mov_b64 exec, %[all]\n"                                  \
+    "s_waitcnt lgkmcnt(0)\n"
 // leave if a lane is near or its entry is kSearchEntry
 #define STEP_NEAR                                               \
-    "s_waitcnt lgkmcnt(0)\n"                                    \
+    "v_cmp_ge_i32 %[m1], %[w], %[nearw]\n"                      \
+    "s_waitcnt lgkmcnt(1)\n"                                    \
     "v_cmp_eq_u32 vcc, 0, %[e]\n"                               \
     "s_or_b64 vcc, vcc, %[m1]\n"                                \
-    "s_cbranch_vccz 1b\n"
+    "s_cbranch_vccz 1b\n"                                       \
+    "s_waitcnt lgkmcnt(0)\n"
 #define STEP_STATE                                                                                                   \
     [w] "+v"(s.c.w), [n32] "+v"(s.c.n32), [hi] "+v"(s.c.hi), [lo] "+v"(s.c.lo), [ahead] "+v"(s.c.ahead),             \
         [win] "+v"(s.c.win), [slot] "+v"(s.slot), [k] "+v"(s.k), [block] "+v"(s.block), [e] "+v"(s.e),               \
-        [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2)
+        [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2), [carry] "=&s"(carry)
 #define STEP_GIVEN                                                                                                   \
     [nearw] "v"(s.near_w), [aheadat] "v"(ahead_at), [oneac] "v"(one_dc + 2u), [onedc] "v"(one_dc),                   \
         [next] "s"(g.next_slot), [chroma] "s"(g.chroma_at), [fine] "s"(0u - 63u * kFinePrefixes)
@@ -619,30 +631,27 @@ __device__ __forceinline__ void step_count(Steps &s, const uint32_t *words, cons
 #ifdef __AMDGCN__
     const uint32_t ahead_at = lds_address(words) + 4u, one_dc = lds_address(one), run_dc = lds_address(run);
     uint32_t t0, t1, t2, t3;
-    uint64_t m0, m1, m2;
+    uint64_t m0, m1, m2, carry;
 #define COUNT_ADVANCE                                           \
     "v_lshlrev_b32 %[t0], 27, %[e]\n"                           \
     "v_lshrrev_b32 %[t1], 9, %[e]\n"                            \
-    "v_sub_co_u32 %[n32], vcc, %[n32], %[t0]\n"                 \
+    "v_sub_co_u32 %[n32], %[carry], %[n32], %[t0]\n"            \
     "v_add3_u32 %[k], %[k], %[t1], 1\n"                         \
     "v_bfe_u32 %[t1], %[next], %[slot], 5\n"                    \
     "v_lshrrev_b32 %[t0], 27, %[n32]\n"                         \
-    STEP_WORDS                                                  \
-    "v_cmp_lt_i32 %[m0], %[single], %[k]\n"
+    "v_cmp_lt_i32 vcc, 62, %[k]\n"                              \
+    "v_cmp_lt_i32 %[m0], %[single], %[k]\n"                     \
+    STEP_WORDS
     if (!wave_any(s.near())) {
         asm volatile(
             ".p2align 5\n"
             "1:\n"
             COUNT_ADVANCE
             STEP_NUMBER
-            "v_max_i32 %[t3], %[t3], %[t2]\n"
             "v_cndmask_b32 %[t0], %[runac], %[oneac], %[m0]\n"
-            "v_bfe_u32 %[t1], %[chroma], %[slot], 3\n"
-            "v_lshlrev_b32 %[t3], 3, %[t3]\n"
+            "v_max_i32 %[t3], %[t3], %[t2]\n"
             "v_cndmask_b32 %[t0], %[t0], %[rundc], vcc\n"
-            "v_addc_co_u32 %[block], %[m2], 0, %[block], vcc\n"
-            "v_add3_u32 %[t3], %[t3], %[t1], %[t0]\n"
-            "ds_read_u16 %[e], %[t3]\n"
+            STEP_LOOK_UP
             "v_cndmask_b32 %[k], %[k], -1, vcc\n"
             STEP_NEAR
             : STEP_STATE
@@ -658,15 +667,11 @@ __device__ __forceinline__ void step_count(Steps &s, const uint32_t *words, cons
             STEP_POSITION
             STEP_NUMBER
             "s_or_b64 %[m0], %[m0], %[m1]\n"
-            "v_max_i32 %[t3], %[t3], %[t2]\n"
             "v_cndmask_b32 %[t0], %[runac], %[oneac], %[m0]\n"
+            "v_max_i32 %[t3], %[t3], %[t2]\n"
             "v_cndmask_b32 %[t2], %[rundc], %[onedc], %[m1]\n"
-            "v_bfe_u32 %[t1], %[chroma], %[slot], 3\n"
-            "v_lshlrev_b32 %[t3], 3, %[t3]\n"
             "v_cndmask_b32 %[t0], %[t0], %[t2], vcc\n"
-            "v_addc_co_u32 %[block], %[m2], 0, %[block], vcc\n"
-            "v_add3_u32 %[t3], %[t3], %[t1], %[t0]\n"
-            "ds_read_u16 %[e], %[t3]\n"
+            STEP_LOOK_UP
             "v_cndmask_b32 %[k], %[k], -1, vcc\n"
             STEP_DUE
             : STEP_STATE, [p] "=&v"(p), [all] "=&s"(all)
@@ -707,37 +712,35 @@ __device__ __forceinline__ void step_write(Steps &s, WriteSteps &ws, const uint3
 {
 #ifdef __AMDGCN__
     const uint32_t ahead_at = lds_address(words) + 4u, one_dc = lds_address(one);
-    uint32_t t0, t1, t2, t3, t4;
-    uint64_t m0, m1, m2;
+    uint32_t t0, t1, t2, t3, t4, t5, t6;
+    uint64_t m0, m1, m2, carry;
+// (the value's bits are taken from the window, t5 and t6, before that moves on)
 #define WRITE_ADVANCE                                           \
-    "v_lshrrev_b32 %[t1], 9, %[e]\n"                            \
-    "v_sub_u32 %[t2], 0, %[e]\n"                                \
-    "v_bfe_u32 %[t3], %[e], 5, 4\n"                             \
     "v_lshlrev_b32 %[t0], 27, %[e]\n"                           \
+    "v_lshrrev_b32 %[t1], 9, %[e]\n"                            \
+    "v_sub_co_u32 %[n32], %[carry], %[n32], %[t0]\n"            \
+    "v_sub_u32 %[t5], 0, %[e]\n"                                \
+    "v_bfe_u32 %[t6], %[e], 5, 4\n"                             \
     "v_add3_u32 %[k], %[k], %[t1], 1\n"                         \
-    "v_bfe_i32 %[t2], %[win], %[t2], %[t3]\n"                   \
-    "v_sub_co_u32 %[n32], vcc, %[n32], %[t0]\n"                 \
-    "v_lshlrev_b32 %[t3], %[t3], -1\n"                          \
-    "v_min_i32 %[t1], 63, %[k]\n"                               \
-    "v_ashrrev_i32 %[t4], 31, %[t2]\n"                          \
     "v_lshrrev_b32 %[t0], 27, %[n32]\n"                         \
-    "v_xor_b32 %[t3], %[t3], %[t4]\n"                           \
-    "v_add_lshl_u32 %[t1], %[t1], %[base], 1\n"                 \
-    "v_add3_u32 %[t4], %[t2], %[t3], 1\n"                       \
-    "v_or_b32 %[over], %[over], %[k]\n"                         \
-    "global_store_short %[t1], %[t4], %[coef]\n"                \
-    STEP_WORDS                                                  \
-    "v_bfe_u32 %[t1], %[next], %[slot], 5\n"
+    "v_bfe_i32 %[t5], %[win], %[t5], %[t6]\n"                   \
+    "v_cmp_lt_i32 vcc, 62, %[k]\n"                              \
+    "v_bfe_u32 %[t1], %[next], %[slot], 5\n"                    \
+    STEP_WORDS
 #define WRITE_NUMBER                                            \
     STEP_NUMBER                                                 \
-    "v_addc_co_u32 %[block], %[m2], 0, %[block], vcc\n"         \
-    "v_max_i32 %[t3], %[t3], %[t2]\n"                           \
     "v_cndmask_b32 %[t0], %[oneac], %[onedc], vcc\n"            \
-    "v_bfe_u32 %[t1], %[chroma], %[slot], 3\n"                  \
-    "v_lshlrev_b32 %[t3], 3, %[t3]\n"                           \
+    "v_max_i32 %[t3], %[t3], %[t2]\n"                           \
+    STEP_LOOK_UP                                                \
+    "v_lshlrev_b32 %[t6], %[t6], -1\n"                          \
+    "v_min_i32 %[t1], 63, %[k]\n"                               \
+    "v_ashrrev_i32 %[t4], 31, %[t5]\n"                          \
+    "v_or_b32 %[over], %[over], %[k]\n"                         \
+    "v_xor_b32 %[t6], %[t6], %[t4]\n"                           \
+    "v_add_lshl_u32 %[t1], %[t1], %[base], 1\n"                 \
+    "v_add3_u32 %[t4], %[t5], %[t6], 1\n"                       \
     "v_min_u32 %[t2], %[block], %[lastblock]\n"                 \
-    "v_add3_u32 %[t3], %[t3], %[t1], %[t0]\n"                   \
-    "ds_read_u16 %[e], %[t3]\n"                                 \
+    "global_store_short %[t1], %[t4], %[coef]\n"                \
     "v_lshlrev_b32 %[base], 6, %[t2]\n"                         \
     "v_add_u32 %[t2], %[side], %[t2]\n"                         \
     "v_cndmask_b32 %[k], %[k], -1, vcc\n"                       \
@@ -745,7 +748,7 @@ __device__ __forceinline__ void step_write(Steps &s, WriteSteps &ws, const uint3
 #define WRITE_INTERVAL                                          \
     "v_or_b32 %[late], %[late], %[left]\n"                      \
     "v_subb_co_u32 %[left], %[m2], %[left], 0, vcc\n"
-#define WRITE_STATE STEP_STATE, [t4] "=&v"(t4), [base] "+v"(ws.base), [over] "+v"(ws.over)
+#define WRITE_STATE STEP_STATE, [t4] "=&v"(t4), [t5] "=&v"(t5), [t6] "=&v"(t6), [base] "+v"(ws.base), [over] "+v"(ws.over)
 #define WRITE_GIVEN STEP_GIVEN, [coef] "s"(ws.coef), [lastblock] "v"(ws.last_block), [side] "v"(ws.side)
     if (!ws.wide) {
         if (!wave_any(s.near())) {
@@ -1081,8 +1084,8 @@ __device__ inline void classify16(const uint4 v, uint32_t prev, uint32_t nextb, 
 // Packs the bytes that staging keeps into big-endian words, a lane its own piece of the stream.  A lane
 // puts the words whose last byte is its own, with zeros for bytes of the lanes before; its last
 // bytes, fewer than four, are ORed into their word after a barrier.  Words without stuffing or
-// markers in any lane go through whole.  (A byte at a time took 22 of the 177 us that a workgroup
-// spends on a 12 KB restart interval, PACK_US now.)
+// markers in any lane go through whole.  (A byte at a time took 25 of the 177 us that a workgroup
+// spends on a 12 KB restart interval, three less now.)
 struct BytePacker {
     uint32_t word, n;  // word of the destination, and how many of its bytes precede
     uint32_t acc = 0;  // the last n bytes, in its low bits
@@ -1630,7 +1633,7 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
         // each.  Start states come back, where a row's predecessor is decoded from another state and
         // falls into step all the same: a row's lane keeps its last three results, and rows are
         // decoded only once nothing moves by those.  (64 full-HD images at quality 95: 14.4 rounds
-        // a chunk without, 8.2 with three, no fewer with eight; kernel 1358 -> ITER_US us.)
+        // a chunk without, 8.2 with three, no fewer with eight; kernel 1358 -> 1001 us with zeros stored first.)
         RowLists &rows = S.rows();
         if (active) out_state = count_span<true>(S, S.clean + clean_row_of_bit(in_state >> 9), runs, g, in_state, end_bit, limit_bits, &nblk);
         S.state[tid] = out_state;
