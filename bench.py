@@ -216,7 +216,7 @@ def algorithmic_bytes(infos, pr):
 def stage_report(stage_ms, work, entropy_bytes, sym_per_byte, workload=None):
     names = ["scan", "decode", "reconstruct", "resize"]
     # (workload 5's streams have no restart markers: they are decoded in windows)
-    decoder = "resolve_streams, chain_streams, write_streams, decode_entropy, finish_streams" if workload == 5 else "decode_entropy"
+    decoder = "resolve_streams, chain_streams, write_streams, decode_entropy" if workload == 5 else "decode_entropy"
     kernels = ["scan_restart_markers (+ expanding the Huffman tables)", decoder, "reconstruct_rgb",
                "resize_crop_normalize"]
     stages = []

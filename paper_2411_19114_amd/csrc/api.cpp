@@ -583,9 +583,8 @@ int run_batch(prep_handle *h, const uint8_t *bits_host, const uint8_t *bits_dev,
         launch_decode_entropy(d_bits, s->d_recs, n, P.n_windows, h->d_win_count, h->d_win_first, s->d_data_end,
                               h->d_retry, h->d_coef, (uint32_t)(h->cap_blocks * 64), h->d_status, h->d_tables,
                               P.window_bytes != (uint32_t)kWindowBytes,
-                              P.window_bytes == (uint32_t)kTinyWindowBytes ? 256u : 512u, P.long_intervals, stream);
-        launch_finish_streams(s->d_recs, n, P.n_streams, h->d_retry, h->d_streams, h->d_coef,
-                              (uint32_t)(h->cap_blocks * 64), stream);
+                              P.window_bytes == (uint32_t)kTinyWindowBytes ? 256u : 512u, P.long_intervals,
+                              P.n_streams, h->d_streams, stream);
         if (timing) HIP_TRY(hipEventRecord(ev[2], stream));
     }
     launch_reconstruct(d_bits, s->d_recs, reinterpret_cast<const uint32_t *>(s->d_recs + n), n, P.recon_wgs,

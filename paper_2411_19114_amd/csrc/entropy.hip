@@ -1119,6 +1119,48 @@ struct BytePacker {
     __device__ uint32_t rest() const { return acc << (32u - 8u * n); }  // (n != 0)
 };
 
+__device__ inline void stream_geometry(Geometry &g, const ImageRec &R)
+{
+    g.bpm = R.blocks_per_mcu;
+    g.n_luma = (uint32_t)(luma_h(R.sampling) * luma_v(R.sampling));
+    g.ri_blocks = 0;
+    g.set_slots();
+    g.n_blocks = R.n_blocks;
+}
+
+// image of stream window wg: the last one whose first window does not exceed it (images without
+// stream windows share their number with the next one that has some)
+__device__ inline int image_of_stream(const ImageRec *recs, int n_images, uint32_t wg)
+{
+    return find_image_wave(n_images, wg, [&](int i) { return recs[i].stream0; });
+}
+
+// DC differences -> DC values of the blocks whose DC was decoded in stream window wg (all lanes of the
+// workgroup must call).
+__device__ inline void finish_window(const ImageRec *__restrict__ recs, int n_images, uint32_t wg,
+                                     const uint32_t *__restrict__ retry, const StreamWindow *__restrict__ windows,
+                                     int16_t *__restrict__ coef_all, uint32_t side_off, uint32_t *scan_a, int32_t *dc_val,
+                                     int32_t *dc_flag)
+{
+    const int img = image_of_stream(recs, n_images, wg);
+    const ImageRec &R = recs[img];
+    const uint32_t w = wg - R.stream0;
+    if (w >= R.n_streams || R.status != PREP_OK || retry[img] != 0) return;
+    const StreamWindow *W = windows + R.stream0;
+    if (W[w].dc_hi <= W[w].dc_lo) return;
+    uint32_t before[3] = {0, 0, 0};
+    for (uint32_t i = threadIdx.x; i < w; i += kT)
+#pragma unroll
+        for (int c = 0; c < 3; c++) before[c] += (uint32_t)W[i].dc_sum[c];
+    int32_t carry[3];
+#pragma unroll
+    for (int c = 0; c < 3; c++) carry[c] = (int32_t)block_sum(before[c], scan_a);
+    Geometry g;
+    stream_geometry(g, R);
+    int16_t *coef = coef_all + (size_t)R.coef_block0 * 64;
+    dc_prefix(dc_val, dc_flag, g, coef, coef + (side_off + R.coef_block0 - R.coef_block0 * 64u), W[w].dc_lo, W[w].dc_hi, carry);
+}
+
 }  // namespace
 
 // ---- kernel 1: restart markers per window -----------------------------------
@@ -1231,17 +1273,25 @@ __global__ __launch_bounds__(kDecodeThreads) void scan_restart_markers(
 // subsequence is decoded once from each place-in-MCU hypothesis by a lane of its own (the chip
 // is idle otherwise), and once more from the end states those lanes reached in the subsequence
 // before; the true chain then only picks, link by link, the candidate that it equals.
+// Workgroups from n_windows on finish the stream windows that write_streams wrote, one each: they
+// share nothing with the others (an image is decoded in windows or here), and a kernel of their own
+// costs a call with one image 5 us.
 template <bool kHyp, bool kRuns>
 __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
     const uint8_t *__restrict__ bits, const ImageRec *__restrict__ recs, int n_images,
     const uint32_t *__restrict__ win_count, const uint32_t *__restrict__ win_first,
     const uint32_t *__restrict__ data_end, const uint32_t *__restrict__ retry, int16_t *__restrict__ coef_all,
-    uint32_t side_off, int32_t *__restrict__ status, const uint4 *__restrict__ tables, uint32_t hyp_span_bits)
+    uint32_t side_off, int32_t *__restrict__ status, const uint4 *__restrict__ tables, uint32_t hyp_span_bits,
+    uint32_t n_windows, const StreamWindow *__restrict__ windows)
 {
     __shared__ DecodeShared<kHyp, kRuns> S;
     const uint16_t *const runs = run_entries(S.tab);
     const int tid = threadIdx.x;
     const uint32_t wg = blockIdx.x;
+    if (wg >= n_windows) {
+        finish_window(recs, n_images, wg - n_windows, retry, windows, coef_all, side_off, S.scan_a, S.dc_val, S.dc_flag);
+        return;
+    }
     const int img = find_image_wave(n_images, wg, [&](int i) { return recs[i].window0; });
     const ImageRec &R = recs[img];
     const uint32_t w = wg - R.window0;
@@ -1787,7 +1837,7 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
 //       entry (overlap row, hypothesis) leads to an exit of the same form and a count of blocks.
 //   chain_streams    follows the entries from window to window of an image: the true chain.
 //   write_streams    decodes every window's rows once more, from the true states.
-//   finish_streams   DC differences -> DC values.
+//   finish_window    DC differences -> DC values (in decode_entropy's launch).
 //
 // Whatever does not fit this scheme (a chain that meets no hypothesis within the overlap, markers
 // inside the data, a stream that ends in the wrong state) is set in retry[], and decode_entropy
@@ -1922,22 +1972,6 @@ struct StreamRows {
     __device__ inline uint32_t start(uint32_t j) const { return 8u * (j < n_own ? j * row_bytes : own + (j - n_own) * row_bytes); }
     __device__ inline uint32_t end(uint32_t j) const { return 8u * (j < n_own ? min((j + 1u) * row_bytes, own) : min(own + (j - n_own + 1u) * row_bytes, total)); }
 };
-
-__device__ inline void stream_geometry(Geometry &g, const ImageRec &R)
-{
-    g.bpm = R.blocks_per_mcu;
-    g.n_luma = (uint32_t)(luma_h(R.sampling) * luma_v(R.sampling));
-    g.ri_blocks = 0;
-    g.set_slots();
-    g.n_blocks = R.n_blocks;
-}
-
-// image of stream window wg: the last one whose first window does not exceed it (images without
-// stream windows share their number with the next one that has some)
-__device__ inline int image_of_stream(const ImageRec *recs, int n_images, uint32_t wg)
-{
-    return find_image_wave(n_images, wg, [&](int i) { return recs[i].stream0; });
-}
 
 // The extra node of key (see kStateBits), made if there is none yet; x = where to look first.  Out of
 // line: inlined, it cost resolve_streams 3 % in calls that need few.
@@ -2088,18 +2122,19 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
 
 // One workgroup per image: which entry of each window the image's true chain takes, and the block
 // there.  Windows are taken kChainTile at a time; within a tile, lane (s, e) follows segment s from
-// entry e, one lane strings the segments together, and a lane per segment goes over it again.
-// An image of many windows is bound by the latency of each tile's loads (12 a lane, in calls with
-// little data 21), so twelve of them are under way before the first is stored: a full-HD still of
-// 630 windows 51 -> 36 us.
-constexpr int kChainTile = 128;
-constexpr int kChainLoads = 12;
-__global__ __launch_bounds__(kDecodeThreads) void chain_streams(
+// entry e, one lane strings the segments together, and a lane per segment goes over it again: as many
+// segments as a segment has windows, so that no stage is much longer than the others.  Bound by the
+// latency of these walks and of the tile's loads (24 entries a window, in calls with little data 42), which
+// are under way together: a full-HD still of 630 windows 32 -> 24 us with sixteen waves instead of four.
+constexpr int kChainThreads = 1024;
+constexpr int kChainTile = 256;
+constexpr int kChainLoads = (kChainTile * kStreamEntries + kChainThreads - 1) / kChainThreads;
+__global__ __launch_bounds__(kChainThreads) void chain_streams(
     const ImageRec *__restrict__ recs, uint32_t row_bytes, uint32_t *__restrict__ retry, StreamWindow *__restrict__ windows)
 {
     __shared__ uint32_t through[kChainTile * kStreamEntries];
-    __shared__ uint32_t seg_way[kT], seg_blocks[kT];
-    __shared__ uint32_t seg_entry[kT], seg_block[kT];
+    __shared__ uint32_t seg_way[kChainThreads], seg_blocks[kChainThreads];
+    __shared__ uint32_t seg_entry[kChainThreads], seg_block[kChainThreads];
     __shared__ uint32_t s_entry, s_block;
     const ImageRec &R = recs[blockIdx.x];
     const int tid = threadIdx.x;
@@ -2107,24 +2142,24 @@ __global__ __launch_bounds__(kDecodeThreads) void chain_streams(
     if (n == 0 || R.status != PREP_OK) return;
     const bool redo = retry[blockIdx.x] != 0;
     StreamWindow *W = windows + R.stream0;
-    const uint32_t E = stream_overlap(row_bytes) * R.blocks_per_mcu, n_seg = (uint32_t)kT / E;
+    const uint32_t E = stream_overlap(row_bytes) * R.blocks_per_mcu;
     if (tid == 0) {
         s_entry = redo ? kNoWay : 0u;
         s_block = 0;
     }
     for (uint32_t w0 = 0; w0 < n; w0 += kChainTile) {
         const uint32_t cnt = min(n - w0, (uint32_t)kChainTile);
-        for (uint32_t i0 = (uint32_t)tid; i0 < cnt * E; i0 += kChainLoads * kT) {
-            uint32_t v[kChainLoads];
+        uint32_t v[kChainLoads];
 #pragma unroll
-            for (int k = 0; k < kChainLoads; k++) {
-                const uint32_t i = min(i0 + (uint32_t)(k * kT), cnt * E - 1u);
-                v[k] = W[w0 + i / E].through[i % E];
-            }
-#pragma unroll
-            for (int k = 0; k < kChainLoads; k++)
-                if (i0 + (uint32_t)(k * kT) < cnt * E) through[i0 + (uint32_t)(k * kT)] = v[k];
+        for (int k = 0; k < kChainLoads; k++) {
+            const uint32_t i = min((uint32_t)(tid + k * kChainThreads), cnt * E - 1u);
+            if ((uint32_t)(k * kChainThreads) < cnt * E) v[k] = W[w0 + i / E].through[i % E];
         }
+#pragma unroll
+        for (int k = 0; k < kChainLoads; k++)
+            if ((uint32_t)(tid + k * kChainThreads) < cnt * E) through[tid + k * kChainThreads] = v[k];
+        uint32_t n_seg = 1;
+        while (n_seg * n_seg < cnt && (n_seg + 1u) * E <= (uint32_t)kChainThreads) n_seg++;
         __syncthreads();
         const uint32_t len = (cnt + n_seg - 1) / n_seg;
         const uint32_t s = (uint32_t)tid / E, e = (uint32_t)tid - s * E;
@@ -2171,7 +2206,7 @@ __global__ __launch_bounds__(kDecodeThreads) void chain_streams(
     // the chain has to reach the end of the data with all of the image's blocks
     // (all lanes have come here past the last barrier: they see the same)
     if (s_entry != kToEnd || s_block != R.n_blocks) {
-        for (uint32_t i = (uint32_t)tid; i < n; i += kT) W[i].entry = kNoWay;
+        for (uint32_t i = (uint32_t)tid; i < n; i += kChainThreads) W[i].entry = kNoWay;
         if (tid == 0) retry[blockIdx.x] = 1;
     }
 }
@@ -2293,34 +2328,6 @@ __global__ __launch_bounds__(kDecodeThreads) void write_streams(
     }
 }
 
-// DC differences -> DC values of the blocks whose DC was decoded in each window.
-__global__ __launch_bounds__(kDecodeThreads) void finish_streams(
-    const ImageRec *__restrict__ recs, int n_images, const uint32_t *__restrict__ retry,
-    const StreamWindow *__restrict__ windows, int16_t *__restrict__ coef_all, uint32_t side_off)
-{
-    __shared__ uint32_t scan_a[kT / 64 + 1];
-    __shared__ int32_t dc_val[kT / 64 + 1], dc_flag[kT / 64 + 1];
-    const uint32_t wg = blockIdx.x;
-    const int img = image_of_stream(recs, n_images, wg);
-    const ImageRec &R = recs[img];
-    const uint32_t w = wg - R.stream0;
-    if (w >= R.n_streams || R.status != PREP_OK || retry[img] != 0) return;
-    const StreamWindow *W = windows + R.stream0;
-    if (W[w].dc_hi <= W[w].dc_lo) return;
-    uint32_t before[3] = {0, 0, 0};
-    for (uint32_t i = threadIdx.x; i < w; i += kT)
-#pragma unroll
-        for (int c = 0; c < 3; c++) before[c] += (uint32_t)W[i].dc_sum[c];
-    int32_t carry[3];
-#pragma unroll
-    for (int c = 0; c < 3; c++) carry[c] = (int32_t)block_sum(before[c], scan_a);
-    Geometry g;
-    stream_geometry(g, R);
-    int16_t *coef = coef_all + (size_t)R.coef_block0 * 64;
-    dc_prefix(dc_val, dc_flag, g, coef, coef + (side_off + R.coef_block0 - R.coef_block0 * 64u), W[w].dc_lo, W[w].dc_hi, carry);
-}
-
-
 size_t huff_tables_bytes() { return sizeof(HuffTables); }
 static_assert(sizeof(HuffTables) % 16 == 0 && sizeof(HuffCodes) % 16 == 0 && sizeof(HuffTables) == sizeof(HuffCodes) + sizeof(HuffTables::run), "table slots are copied in 16-byte units");
 
@@ -2339,13 +2346,14 @@ void launch_scan_restart_markers(const uint8_t *bits, const ImageRec *recs, int 
 void launch_decode_entropy(const uint8_t *bits, const ImageRec *recs, int n_images,
                            uint32_t n_windows, const uint32_t *win_count, const uint32_t *win_first,
                            const uint32_t *data_end, const uint32_t *retry, int16_t *coef, uint32_t side_off, int32_t *status,
-                           const uint8_t *tables, bool small_windows, uint32_t hyp_span_bits, bool long_intervals, hipStream_t stream)
+                           const uint8_t *tables, bool small_windows, uint32_t hyp_span_bits, bool long_intervals,
+                           uint32_t n_streams, const StreamWindow *win, hipStream_t stream)
 {
     if (n_windows == 0) return;
     const auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(n_windows), dim3(kDecodeThreads), 0, stream, bits, recs, n_images, win_count,
+        hipLaunchKernelGGL(kernel, dim3(n_windows + n_streams), dim3(kDecodeThreads), 0, stream, bits, recs, n_images, win_count,
                            win_first, data_end, retry, coef, side_off, status, reinterpret_cast<const uint4 *>(tables),
-                           hyp_span_bits);
+                           hyp_span_bits, n_windows, win);
     };
     if (small_windows) launch(decode_entropy<true, true>);
     else if (long_intervals) launch(decode_entropy<false, true>);
@@ -2360,17 +2368,9 @@ void launch_decode_streams(const uint8_t *bits, const ImageRec *recs, int n_imag
     const uint4 *tab = reinterpret_cast<const uint4 *>(tables);
     hipLaunchKernelGGL(resolve_streams, dim3(n_streams), dim3(kDecodeThreads), 0, stream, bits, recs, n_images, row_bytes,
                        data_end, retry, tab, win);
-    hipLaunchKernelGGL(chain_streams, dim3(n_images), dim3(kDecodeThreads), 0, stream, recs, row_bytes, retry, win);
+    hipLaunchKernelGGL(chain_streams, dim3(n_images), dim3(kChainThreads), 0, stream, recs, row_bytes, retry, win);
     hipLaunchKernelGGL(write_streams, dim3(n_streams), dim3(kDecodeThreads), 0, stream, bits, recs, n_images, row_bytes,
                        data_end, retry, tab, win, coef, side_off);
-}
-
-void launch_finish_streams(const ImageRec *recs, int n_images, uint32_t n_streams, const uint32_t *retry,
-                           const StreamWindow *win, int16_t *coef, uint32_t side_off, hipStream_t stream)
-{
-    if (n_streams == 0) return;
-    hipLaunchKernelGGL(finish_streams, dim3(n_streams), dim3(kDecodeThreads), 0, stream, recs, n_images, retry, win, coef,
-                       side_off);
 }
 
 }  // namespace prep

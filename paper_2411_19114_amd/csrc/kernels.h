@@ -26,19 +26,19 @@ void launch_scan_restart_markers(const uint8_t *bits, const ImageRec *recs, int 
 // step of the same launch); side_off plus the number of blocks must stay below 2^32;
 // small_windows: the windows are small (the decoder variant for small calls), and
 // hyp_span_bits = what a lane of its hypothesis passes takes, 512 or 256 bits; long_intervals: much of
-// the data lies in restart intervals too long for a lane each, or in streams that are not cut
+// the data lies in restart intervals too long for a lane each, or in streams that are not cut;
+// n_streams, win: the stream windows that launch_decode_streams wrote, whose DC differences become values
 void launch_decode_entropy(const uint8_t *bits, const ImageRec *recs, int n_images,
                            uint32_t n_windows, const uint32_t *win_count, const uint32_t *win_first,
                            const uint32_t *data_end, const uint32_t *retry, int16_t *coef, uint32_t side_off, int32_t *status,
-                           const uint8_t *tables, bool small_windows, uint32_t hyp_span_bits, bool long_intervals, hipStream_t stream);
+                           const uint8_t *tables, bool small_windows, uint32_t hyp_span_bits, bool long_intervals,
+                           uint32_t n_streams, const StreamWindow *win, hipStream_t stream);
 // The images whose ImageRec counts stream windows (n_streams of all images): three kernels before
-// launch_decode_entropy, which then does the images that they set in retry[] from the start, and
-// one after it.  row_bytes = kStreamRowBytes or kStreamTinyRowBytes.
+// launch_decode_entropy, which finishes them and does the images that they set in retry[] from the
+// start.  row_bytes = kStreamRowBytes or kStreamTinyRowBytes.
 void launch_decode_streams(const uint8_t *bits, const ImageRec *recs, int n_images, uint32_t n_streams, uint32_t row_bytes,
                            const uint32_t *data_end, uint32_t *retry, StreamWindow *win, int16_t *coef, uint32_t side_off,
                            const uint8_t *tables, hipStream_t stream);
-void launch_finish_streams(const ImageRec *recs, int n_images, uint32_t n_streams, const uint32_t *retry,
-                           const StreamWindow *win, int16_t *coef, uint32_t side_off, hipStream_t stream);
 
 // reconstruct.hip
 // chroma: nullptr = subsampled chroma is replicated; else the workspace of the interpolating
