@@ -1885,42 +1885,59 @@ struct StreamPart {                  // what staging found
                                      // is left between long runs of fill bytes
 };
 
-// Stage the raw bytes [w * step, (w + 1) * step) of the segment and enough after them for the
-// overlap rows into S.clean.  All lanes must call.
+// The raw bytes [w * step, (w + 1) * step) of the segment and enough after them for the overlap rows,
+// on their way into registers: 16-byte aligned parts that cover them, one or two to a lane, with
+// the byte before each part (the segment's first byte has none) and the one after it.  They
+// are asked for as long as the host found the segment to be, before anything is known of where the
+// data end in it.  (A workgroup that waits for its tables, its window's record and these one after
+// the other spends a third of its time waiting where all are asked for together.)
+struct StreamLoads {
+    int32_t cs, my_lo, per;
+    uint4 v[2];
+    uint32_t prev[2], after[2];
+    __device__ inline StreamLoads(const uint8_t *seg, uint32_t entropy_len, uint32_t w, uint32_t step, uint32_t row_bytes)
+    {
+        cs = (int32_t)(w * step);
+        const int32_t ce = (int32_t)min(w * step + step + 2u * stream_overlap(row_bytes) * row_bytes + kStreamSlack, entropy_len);
+        const int32_t a0 = cs - (int32_t)((uintptr_t)(seg + cs) & 15u);
+        per = (ce - a0 + 15) >> 4 > kT ? 2 : 1;
+        static_assert(kStreamWords * 4 <= 2 * kT * 16, "two parts a lane hold a window");
+        my_lo = a0 + (int32_t)threadIdx.x * per * 16;
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            const int32_t plo = my_lo + 16 * k;
+            v[k] = make_uint4(0, 0, 0, 0);
+            prev[k] = after[k] = 0;
+            if (k < per && plo < ce) {
+                v[k] = *reinterpret_cast<const uint4 *>(seg + plo);
+                if (plo > 0) prev[k] = load_byte(seg + plo - 1);
+                if (plo + 16 < (int32_t)entropy_len) after[k] = load_byte(seg + plo + 16);
+            }
+        }
+    }
+};
+
+// Stage them in S.clean.  All lanes must call.
 template <typename Tables>
-__device__ inline StreamPart stage_stream(StreamShared<Tables> &S, const uint8_t *seg, uint32_t data_len, uint32_t w,
-                                          uint32_t step, uint32_t row_bytes)
+__device__ inline StreamPart stage_stream(StreamShared<Tables> &S, const StreamLoads &loads, uint32_t data_len, uint32_t step,
+                                          uint32_t row_bytes)
 {
     const int tid = threadIdx.x;
-    const int32_t cs = (int32_t)(w * step), own_end = (int32_t)min(w * step + step, data_len);
-    const int32_t ce = (int32_t)min(w * step + step + 2u * stream_overlap(row_bytes) * row_bytes + kStreamSlack, data_len);
+    const int32_t cs = loads.cs, own_end = (int32_t)min((uint32_t)cs + step, data_len);
+    const int32_t ce = (int32_t)min((uint32_t)cs + step + 2u * stream_overlap(row_bytes) * row_bytes + kStreamSlack, data_len);
     StreamPart part;
     part.to_end = ce == (int32_t)data_len;
-    // 16-byte aligned parts that cover [cs, ce), one or two to a lane
-    const int32_t a0 = cs - (int32_t)((uintptr_t)(seg + cs) & 15u);
-    const int32_t n_parts = (ce - a0 + 15) >> 4;
-    const int32_t per = n_parts > kT ? 2 : 1;
-    static_assert(kStreamWords * 4 <= 2 * kT * 16, "two parts a lane hold a window");
-    uint4 v[2];
     uint32_t keep[2] = {0, 0}, bound = 0;
     int32_t bad = 0;
-    const int32_t my_lo = a0 + tid * per * 16;
-#pragma unroll
-    for (int k = 0; k < 2; k++) {
-        const int32_t plo = my_lo + 16 * k;
-        v[k] = make_uint4(0, 0, 0, 0);
-        if (k < per && plo < ce) v[k] = *reinterpret_cast<const uint4 *>(seg + plo);
-    }
     uint32_t n_own = 0, n_all = 0;
 #pragma unroll
     for (int k = 0; k < 2; k++) {
-        const int32_t plo = my_lo + 16 * k;
-        if (k < per && plo < ce) {
-            // the byte before the part (the segment's first byte has none) and the one after it
-            // (at the end of the data, the FF of the marker there)
-            uint32_t prev = plo > 0 ? load_byte(seg + plo - 1) : 0u, b = 0;
-            const uint32_t after = plo + 16 < (int32_t)data_len ? load_byte(seg + plo + 16) : 0xFFu;
-            classify16(v[k], prev, after, plo, cs, ce, &keep[k], &b, &prev, &bad);
+        const int32_t plo = loads.my_lo + 16 * k;
+        if (k < loads.per && plo < ce) {
+            // (after the data's last byte comes the FF of the marker there)
+            const uint32_t after = plo + 16 < (int32_t)data_len ? loads.after[k] : 0xFFu;
+            uint32_t b = 0, last;
+            classify16(loads.v[k], loads.prev[k], after, plo, cs, ce, &keep[k], &b, &last, &bad);
             bound |= b;
             const int32_t left = own_end - plo;
             const uint32_t mine = left >= 16 ? 0xFFFFu : left > 0 ? (1u << left) - 1u : 0u;
@@ -1940,7 +1957,7 @@ __device__ inline StreamPart stage_stream(StreamShared<Tables> &S, const uint8_t
 #pragma unroll
     for (int k = 0; k < 2; k++) {
         if (keep[k] == 0) continue;
-        const uint32_t wv[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+        const uint32_t wv[4] = {loads.v[k].x, loads.v[k].y, loads.v[k].z, loads.v[k].w};
 #pragma unroll
         for (int e = 0; e < 4; e++)
             pack.add(wv[e], (keep[k] >> (4 * e)) & 15u, [&](uint32_t at, uint32_t word) { S.clean[at] = word; });
@@ -2007,6 +2024,7 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
     Geometry g;
     stream_geometry(g, R);
     const uint32_t H = g.bpm, step = stream_window_bytes(H, row_bytes);
+    const StreamLoads loads(bits + R.file_off + R.entropy_rel, R.entropy_len, w, step, row_bytes);
     const uint32_t data_len = min(R.entropy_len, data_end[img]);
     StreamWindow &W = windows[wg];
     if (w * step >= data_len) {
@@ -2016,9 +2034,13 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
         return;
     }
     load_tables(S.tab, tables, R.table_slot);
-    if (tid < kStreamExtras) extra_key[tid] = kNoKey;
+    if (tid < kStreamExtras) {
+        extra_key[tid] = kNoKey;
+        node_next[kT + tid] = kNodeNoWay;
+        node_blocks[kT + tid] = 0;
+    }
     if (tid == 0) n_extra = 0;
-    const StreamPart part = stage_stream(S, bits + R.file_off + R.entropy_rel, data_len, w, step, row_bytes);
+    const StreamPart part = stage_stream(S, loads, data_len, step, row_bytes);
     if (part.marker && tid == 0) retry[img] = 1;
     const StreamRows rows(part, row_bytes);
 
@@ -2089,31 +2111,56 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
         done = have;
         __syncthreads();
     }
-    for (uint32_t i = (uint32_t)tid; i < (uint32_t)kStreamNodes; i += kT) {
-        if (i >= (uint32_t)kT && extra_key[i - (uint32_t)kT] == kNoKey) continue;
-        W.end[i] = node_end[i];
-        W.blocks[i] = node_blocks[i];
-        W.next[i] = node_next[i];
+    static_assert(kStreamNodes <= 2 * kT, "a lane has two nodes");
+    const uint32_t other = (uint32_t)(kT + tid);  // this lane's extra node, if tid < kStreamExtras
+    W.end[tid] = node_end[tid];
+    W.blocks[tid] = node_blocks[tid];
+    W.next[tid] = node_next[tid];
+    if (tid < kStreamExtras && extra_key[tid] != kNoKey) {
+        W.end[other] = node_end[other];
+        W.blocks[other] = node_blocks[other];
+        W.next[other] = node_next[other];
     }
+    // From every node to the end of its chain, by twice as many nodes a round (a chain has at most one
+    // node per row): node_next leads there, node_end becomes the blocks on the way.  (One lane an entry, node
+    // by node, took 5 of the 27 us of a call with one photograph.)
+    node_end[tid] = node_blocks[tid];
+    if (tid < kStreamExtras) node_end[other] = node_blocks[other];
+    for (uint32_t reach = 1; reach < rows.n; reach *= 2) {
+        __syncthreads();
+        uint32_t next[2] = {kNodeNoWay, kNodeNoWay}, more[2] = {0, 0};
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            if (k == 1 && tid >= kStreamExtras) continue;
+            next[k] = node_next[tid + k * kT];
+            if (next[k] < (uint32_t)kStreamNodes) {
+                more[k] = node_end[next[k]];
+                next[k] = node_next[next[k]];
+            }
+        }
+        __syncthreads();
+        node_next[tid] = (uint16_t)next[0];
+        node_end[tid] += more[0];
+        if (tid < kStreamExtras) {
+            node_next[other] = (uint16_t)next[1];
+            node_end[other] += more[1];
+        }
+    }
+    __syncthreads();
     if (tid < kStreamEntries) {
         // entry e = (overlap row i, hypothesis k) goes on with node (i + 1, k) here; window 0 is
         // entered by node 0
         const uint32_t e = (uint32_t)tid;
-        uint32_t at = w == 0 ? 0u : e + H, way = kNoWay, blocks = 0;
+        const uint32_t at = w == 0 ? 0u : e + H;
+        uint32_t way = kNoWay, blocks = 0;
         if (e < (w == 0 ? 1u : stream_overlap(row_bytes) * H)) {
             W.entry_state[e] = w == 0 ? 0u : cand[e];
             if (w != 0 && e / H + 1u >= rows.n) {
                 way = rows.to_end ? kToEnd : kNoWay;  // no such row: all was decoded in the window before
             } else {
-                // (a chain has at most one node per row)
-                for (uint32_t r = 0; r <= (uint32_t)kStreamMaxRows; r++) {
-                    const uint32_t to = node_next[at];
-                    blocks += node_blocks[at];
-                    if (to == kNodeNoWay) break;
-                    if (to == kNodeToEnd) { way = kToEnd; break; }
-                    if (to & kExit) { way = to & ~kExit; break; }
-                    at = to;
-                }
+                const uint32_t to = node_next[at];
+                blocks = node_end[at];
+                way = to == kNodeToEnd ? kToEnd : to != kNodeNoWay && (to & kExit) != 0 ? to & ~kExit : kNoWay;
             }
         }
         W.through[e] = (blocks << 8) | way;
@@ -2227,7 +2274,17 @@ __global__ __launch_bounds__(kDecodeThreads) void write_streams(
     const uint32_t w = wg - R.stream0;
     if (w >= R.n_streams || R.status != PREP_OK) return;
     StreamWindow &W = windows[wg];
-    const uint32_t H = R.blocks_per_mcu, entry = W.entry;
+    const uint32_t H = R.blocks_per_mcu, entry = W.entry, block0 = W.block;
+    const uint32_t step = stream_window_bytes(H, row_bytes);
+    const StreamLoads loads(bits + R.file_off + R.entropy_rel, R.entropy_len, w, step, row_bytes);
+    uint32_t end[2], blocks[2], next[2];
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+        const int i = min(tid + k * kT, kStreamNodes - 1);
+        end[k] = W.end[i];
+        blocks[k] = W.blocks[i];
+        next[k] = W.next[i];
+    }
     // An image that is to be decoded in one piece is left alone.  Other windows of it may find that
     // out only now and set retry[img]: that is for the next kernels to read.  Here the waves of this
     // workgroup would read it at different times, and some would leave where others go on to
@@ -2241,15 +2298,17 @@ __global__ __launch_bounds__(kDecodeThreads) void write_streams(
     }
     Geometry g;
     stream_geometry(g, R);
-    const uint32_t step = stream_window_bytes(H, row_bytes);
+    const uint32_t entry_state = W.entry_state[entry];
     const uint32_t data_len = min(R.entropy_len, data_end[img]);
     load_tables(S.tab, tables, R.table_slot);
-    for (uint32_t i = (uint32_t)tid; i < (uint32_t)kStreamNodes; i += kT) {
-        node_end[i] = W.end[i];
-        node_blocks[i] = W.blocks[i];
-        node_next[i] = W.next[i];
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+        const int i = min(tid + k * kT, kStreamNodes - 1);
+        node_end[i] = end[k];
+        node_blocks[i] = (uint16_t)blocks[k];
+        node_next[i] = (uint16_t)next[k];
     }
-    const StreamPart part = stage_stream(S, bits + R.file_off + R.entropy_rel, data_len, w, step, row_bytes);
+    const StreamPart part = stage_stream(S, loads, data_len, step, row_bytes);
     const StreamRows rows(part, row_bytes);
     const uint32_t row0 = w == 0 ? 0u : entry / H + 1u;  // first row of the chain
     if (tid == 0) {
@@ -2265,7 +2324,6 @@ __global__ __launch_bounds__(kDecodeThreads) void write_streams(
     const uint32_t cnt = S.bcast[0];
     const bool active = (uint32_t)tid < cnt;
     const uint32_t row = row0 + (uint32_t)tid;
-    const uint32_t entry_state = W.entry_state[entry];
     uint32_t nblk = 0, in_state = 0, out_state = 0;
     if (active) {
         in_state = tid == 0 ? entry_state : node_end[chain[tid - 1]];
@@ -2273,7 +2331,6 @@ __global__ __launch_bounds__(kDecodeThreads) void write_streams(
         nblk = node_blocks[chain[tid]];
     }
     uint32_t total_blocks;
-    const uint32_t block0 = W.block;
     const uint32_t my_block = block0 + block_excl_scan(nblk, S.scan_a, &total_blocks);
     const uint32_t exit_state = cnt ? node_end[chain[cnt - 1]] : entry_state;
     int16_t *coef = coef_all + (size_t)R.coef_block0 * 64;
