@@ -1724,10 +1724,8 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
                 rows.row[at] = (uint8_t)tid;
             }
             __syncthreads();
-            // (a workgroup's waves lie on SIMDs of their own: the first in line is another one every round)
-            const uint32_t i = ((uint32_t)tid + 64u * ((wg + round) & 3u)) & (uint32_t)(kT - 1);
-            if (i < total) {
-                const uint32_t row = rows.row[i], from = rows.from[i], row_end = min((row + 1u) * span_bits, own_bits);
+            if ((uint32_t)tid < total) {
+                const uint32_t row = rows.row[tid], from = rows.from[tid], row_end = min((row + 1u) * span_bits, own_bits);
                 uint32_t o = from, nb = 0;
                 // a predecessor that already ran past the subsequence leaves nothing to decode
                 if ((from >> 9) < row_end) o = count_span<true>(S, S.clean + clean_row_of_bit(from >> 9), runs, g, from, row_end, limit_bits, &nb);
