@@ -278,12 +278,11 @@ __device__ __forceinline__ uint32_t lookup_number(uint32_t win)
     return (uint32_t)max((int32_t)(win >> 22), (int32_t)(win >> 16) - (int32_t)(63u * kFinePrefixes));
 }
 
-// Expands tables t_lo .. t_hi-1 of the four (all lanes of the workgroup must call).
-__device__ inline void build_tables(HuffCodes &T, const uint8_t *file, const ImageRec &R, int t_lo = 0,
-                                    int t_hi = 4)
+// Expands the four tables (all lanes of the workgroup must call).
+__device__ inline void build_tables(HuffCodes &T, const uint8_t *file, const ImageRec &R)
 {
     const int tid = threadIdx.x;
-    if (tid >= t_lo && tid < t_hi) {
+    if (tid < 4) {
         const uint8_t *b = file + R.dht_off[tid];
         int32_t bits[16];
 #pragma unroll
@@ -300,12 +299,12 @@ __device__ inline void build_tables(HuffCodes &T, const uint8_t *file, const Ima
             k += c;
         }
     }
-    for (int t = t_lo; t < t_hi; t++) {
+    for (int t = 0; t < 4; t++) {
         const uint32_t nval = min(R.dht_nval[t], 256u);
         for (uint32_t i = tid; i < 256u; i += kT) T.huffval[t][i] = i < nval ? file[R.dht_off[t] + 16 + i] : 0;
     }
     __syncthreads();
-    for (int t = t_lo; t < t_hi; t++) {
+    for (int t = 0; t < 4; t++) {
         // the sixteen-bit words below end[l - 1] begin with a code of at most l bits
         uint32_t end[16];
 #pragma unroll
@@ -327,33 +326,106 @@ __device__ inline void build_tables(HuffCodes &T, const uint8_t *file, const Ima
     __syncthreads();
 }
 
-// The run entries of tables t_lo .. t_hi-1 from the single ones of these and, for a DC table, of the
-// AC table behind it (all lanes of the workgroup must call).
-__device__ inline void build_runs(HuffTables &T, int t_lo = 0, int t_hi = 4)
+// The run entry of prefix i from its single entry e; one(n) = single entry number n of the table that the
+// prefix's further symbols are of.
+template <typename One>
+__device__ __forceinline__ uint32_t run_entry(uint32_t e, uint32_t i, One one)
 {
-    for (int t = t_lo; t < t_hi; t++) {
+    if (e == kSearchEntry || e == kInvalidEntry) return e;
+    uint32_t bits = entry_bits(e), advance = entry_advance(e);
+    // (a symbol has at least one bit: the loop ends)
+    while (advance != kEobAdvance && bits <= kRunLeadBits) {
+        const int32_t lead = (int32_t)advance + 1;  // how far the zig-zag index has come by the symbols so far
+        if (lead > kRunLead) break;
+        const uint32_t n = one(lookup_number(i << (22 + bits)));
+        // the next code lies within the prefix?  (the zeros behind it are not the stream's)
+        if (n == kSearchEntry || n == kInvalidEntry || bits + entry_bits(n) - entry_appended(n) > 10u) break;
+        if (bits + entry_bits(n) > 31u) break;
+        bits += entry_bits(n);
+        advance = entry_advance(n) == kEobAdvance ? kEobAdvance : (uint32_t)lead + entry_advance(n);
+    }
+    return (advance << 9) | bits;
+}
+
+// The run entries of all tables from the single ones of these and, for a DC table, of the AC table
+// behind it (all lanes of the workgroup must call).
+__device__ inline void build_runs(HuffTables &T)
+{
+    for (int t = 0; t < 4; t++) {
         for (uint32_t i = threadIdx.x; i < kLookupEntries; i += kT) {
             uint32_t e = T.one[(i << 2) | (uint32_t)t];
-            if (i < kFinePrefixes && e != kSearchEntry && e != kInvalidEntry) {
-                uint32_t bits = entry_bits(e), advance = entry_advance(e);
-                int32_t lead = 0;  // how far the zig-zag index has come by the symbols so far
-                // (a symbol has at least one bit: the loop ends)
-                while (advance != kEobAdvance && bits <= kRunLeadBits) {
-                    lead = (int32_t)advance + 1;
-                    if (lead > kRunLead) break;
-                    const uint32_t n = T.one[(lookup_number(i << (22 + bits)) << 2) | (uint32_t)(t | 1)];
-                    // the next code lies within the prefix?  (the zeros behind it are not the stream's)
-                    if (n == kSearchEntry || n == kInvalidEntry || bits + entry_bits(n) - entry_appended(n) > 10u) break;
-                    if (bits + entry_bits(n) > 31u) break;
-                    bits += entry_bits(n);
-                    advance = entry_advance(n) == kEobAdvance ? kEobAdvance : (uint32_t)lead + entry_advance(n);
-                }
-                e = (advance << 9) | bits;
-            }
+            if (i < kFinePrefixes) e = run_entry(e, i, [&](uint32_t n) { return (uint32_t)T.one[(n << 2) | (uint32_t)(t | 1)]; });
             T.run[(i << 2) | (uint32_t)t] = (uint16_t)e;
         }
     }
     __syncthreads();
+}
+
+// Part `part` of an image's table t (lookup and run entries, code lists), straight from the DHT bytes
+// into a slot of expanded tables, an entry a lane.  A run's further symbols are found among the codes like
+// its first, so that no lane waits for the others' entries.  (One workgroup a table, entries looked up in
+// those made before, was what small calls waited for in this kernel: 11.5 us, 5.2 now; 33 sets of
+// tables 13.8 -> 11.2, 64 16.1 -> 12.0 against whole tables made like this.)  All lanes of the workgroup
+// must call.
+constexpr uint32_t kTableParts = (kLookupEntries + kT - 1) / kT;
+struct CodeLists {
+    int32_t first[17], count[17], valptr[17];
+    uint32_t end[16];  // the sixteen-bit words below end[l - 1] begin with a code of at most l bits
+    uint8_t huffval[256];
+};
+__device__ inline void expand_table(const uint8_t *file, const ImageRec &R, int t, uint32_t part, HuffTables *dst)
+{
+    __shared__ CodeLists lists[2];  // of table t, and of the AC table behind it
+    const int tid = threadIdx.x;
+    for (int k = 0; k < 2; k++) {
+        const int of = k ? t | 1 : t;
+        lists[k].huffval[tid] = (uint32_t)tid < min(R.dht_nval[of], 256u) ? file[R.dht_off[of] + 16 + tid] : 0;
+    }
+    if (tid < 2) {
+        const uint8_t *b = file + R.dht_off[tid ? t | 1 : t];
+        CodeLists &L = lists[tid];
+        int32_t bits[16];
+#pragma unroll
+        for (int l = 0; l < 16; l++) bits[l] = b[l];
+        int32_t code = 0, k = 0;
+        L.first[0] = L.count[0] = L.valptr[0] = 0;
+#pragma unroll
+        for (int l = 1; l <= 16; l++) {
+            const int32_t c = bits[l - 1];
+            L.first[l] = code;
+            L.count[l] = c;
+            L.valptr[l] = k;
+            L.end[l - 1] = (uint32_t)(code + c) << (16 - l);
+            code = (code + c) << 1;
+            k += c;
+        }
+    }
+    __syncthreads();
+    // lookup entry number i of table t or t | 1
+    auto entry = [&](const CodeLists &L, int ac, uint32_t i) -> uint32_t {
+        const bool fine = i >= kFinePrefixes;
+        const uint32_t a = fine ? i + 63u * kFinePrefixes : i << 6;
+        uint32_t l = 1;
+#pragma unroll
+        for (int k = 0; k < 16; k++) l += a >= L.end[k] ? 1u : 0u;
+        if (l > 16u) return ac ? kInvalidEntry : kSearchEntry;  // past the last code
+        const uint32_t c = (a >> (16u - l)) - (uint32_t)L.first[l];
+        return fine || l <= 10u ? make_entry(ac != 0, L.huffval[((uint32_t)L.valptr[l] + c) & 255u], l) : kSearchEntry;
+    };
+    const uint32_t i = part * (uint32_t)kT + (uint32_t)tid;
+    if (i < kLookupEntries) {
+        const uint32_t e = entry(lists[0], t & 1, i);
+        dst->one[(i << 2) | (uint32_t)t] = (uint16_t)e;
+        dst->run[(i << 2) | (uint32_t)t] =
+            (uint16_t)(i < kFinePrefixes ? run_entry(e, i, [&](uint32_t n) { return entry(lists[1], 1, n); }) : e);
+    }
+    if (part != 0) return;
+    if (tid < 17) {
+        dst->first[t][tid] = lists[0].first[tid];
+        dst->count[t][tid] = lists[0].count[tid];
+        dst->valptr[t][tid] = lists[0].valptr[tid];
+    }
+    dst->huffval[t][tid] = lists[0].huffval[tid];
 }
 
 // the expanded tables of an image with a table slot, or the part of them that a writing pass
@@ -1171,8 +1243,8 @@ __device__ inline void finish_window(const ImageRec *__restrict__ recs, int n_im
 // EOI marker, which it finds from the file's end) and leaves as the offset of the first EOI
 // marker in it: FF D9 cannot occur inside entropy-coded data (T.81 F.1.2.3), so where a file
 // goes on after its image (a second image, a preview) the data end there.
-// Workgroups from n_windows on do something else: workgroup n_windows + 4 s + t expands
-// Huffman table t of image table_rep[s] into slot s of `tables`.
+// Workgroups from n_windows on do something else: workgroup n_windows + 4 (kTableParts s + p) + t
+// expands part p of Huffman table t of image table_rep[s] into slot s of `tables`.
 __global__ __launch_bounds__(kDecodeThreads) void scan_restart_markers(
     const uint8_t *__restrict__ bits, const ImageRec *__restrict__ recs, int n_images,
     uint32_t n_windows, uint32_t window_bytes, uint32_t *__restrict__ win_count,
@@ -1182,33 +1254,9 @@ __global__ __launch_bounds__(kDecodeThreads) void scan_restart_markers(
     __shared__ uint32_t s_cnt[kT / 64], s_first[kT / 64];
     const uint32_t wg = blockIdx.x;
     if (wg >= n_windows) {
-        // four workgroups per slot, one table each, so that the expansion is not the longest
-        // thing this kernel does
-        __shared__ HuffTables tab;
-        const uint32_t slot = (wg - n_windows) >> 2;
-        const int t = (int)((wg - n_windows) & 3u);
+        const uint32_t id = wg - n_windows, slot = id / (4u * kTableParts);
         const ImageRec &I = recs[table_rep[slot]];
-        build_tables(tab, bits + I.file_off, I, t, (t | 1) + 1);
-        build_runs(tab, t, t + 1);
-        const uint32_t *src = reinterpret_cast<const uint32_t *>(&tab);
-        uint32_t *dst = reinterpret_cast<uint32_t *>(tables) + (size_t)slot * (sizeof(HuffTables) / 4);
-        // the members of table t, as 32-bit words of the struct
-        // (its entries lie among the other tables': they go one by one)
-        uint16_t *dst_one = reinterpret_cast<uint16_t *>(dst + offsetof(HuffCodes, one) / 4);
-        uint16_t *dst_run = reinterpret_cast<uint16_t *>(dst + sizeof(HuffCodes) / 4);
-        for (uint32_t i = threadIdx.x; i < kLookupEntries; i += kT) {
-            dst_one[(i << 2) | (uint32_t)t] = tab.one[(i << 2) | (uint32_t)t];
-            dst_run[(i << 2) | (uint32_t)t] = tab.run[(i << 2) | (uint32_t)t];
-        }
-        const uint32_t part[4][2] = {
-            {(uint32_t)offsetof(HuffCodes, first) + (uint32_t)t * 68u, 68u},
-            {(uint32_t)offsetof(HuffCodes, count) + (uint32_t)t * 68u, 68u},
-            {(uint32_t)offsetof(HuffCodes, valptr) + (uint32_t)t * 68u, 68u},
-            {(uint32_t)offsetof(HuffCodes, huffval) + (uint32_t)t * 256u, 256u}};
-#pragma unroll
-        for (int m = 0; m < 4; m++)
-            for (uint32_t i = threadIdx.x; i < part[m][1] / 4; i += kT)
-                dst[part[m][0] / 4 + i] = src[part[m][0] / 4 + i];
+        expand_table(bits + I.file_off, I, (int)(id & 3u), id / 4u % kTableParts, reinterpret_cast<HuffTables *>(tables) + slot);
         return;
     }
     const int img = find_image_wave(n_images, wg, [&](int i) { return recs[i].window0; });
@@ -1234,16 +1282,22 @@ __global__ __launch_bounds__(kDecodeThreads) void scan_restart_markers(
             const uint32_t after = load_byte(seg + min(plo + 16, (int32_t)R.entropy_len));
             const uint32_t wv[5] = {v.x, v.y, v.z, v.w, after};
 #pragma unroll
-            for (int i = 0; i < 16; i++) {
-                const uint32_t cur = (wv[i >> 2] >> (8 * (i & 3))) & 255u;
-                const uint32_t nxt = (wv[(i + 1) >> 2] >> (8 * ((i + 1) & 3))) & 255u;
-                const int32_t pos = plo + i;
-                if (cur == 0xFFu && nxt >= 0xD0u && nxt <= 0xD9u && nxt != 0xD8u && pos >= lo && pos < hi) {
-                    if (nxt == 0xD9u) {
-                        eoi = min(eoi, (uint32_t)pos);
-                    } else if (count_rst) {
-                        cnt++;
-                        first = min(first, (uint32_t)pos);
+            for (int e = 0; e < 4; e++) {
+                // a byte FF before one of D0 to DF, four at a time: a zero byte here
+                const uint32_t next = __builtin_amdgcn_alignbit(wv[e + 1], wv[e], 8u);
+                const uint32_t z = ~wv[e] | ((next & 0xF0F0F0F0u) ^ 0xD0D0D0D0u);
+                if (((z - 0x01010101u) & ~z & 0x80808080u) == 0) continue;
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const uint32_t cur = (wv[e] >> (8 * i)) & 255u, nxt = (next >> (8 * i)) & 255u;
+                    const int32_t pos = plo + 4 * e + i;
+                    if (cur == 0xFFu && nxt >= 0xD0u && nxt <= 0xD9u && nxt != 0xD8u && pos >= lo && pos < hi) {
+                        if (nxt == 0xD9u) {
+                            eoi = min(eoi, (uint32_t)pos);
+                        } else if (count_rst) {
+                            cnt++;
+                            first = min(first, (uint32_t)pos);
+                        }
                     }
                 }
             }
@@ -2393,7 +2447,7 @@ void launch_scan_restart_markers(const uint8_t *bits, const ImageRec *recs, int 
                                  uint8_t *tables, hipStream_t stream)
 {
     if (n_windows == 0) return;
-    hipLaunchKernelGGL(scan_restart_markers, dim3(n_windows + 4 * n_tables), dim3(kDecodeThreads), 0, stream,
+    hipLaunchKernelGGL(scan_restart_markers, dim3(n_windows + 4 * kTableParts * n_tables), dim3(kDecodeThreads), 0, stream,
                        bits, recs, n_images, n_windows, window_bytes, win_count, win_first, data_end, retry, status, table_rep,
                        reinterpret_cast<uint4 *>(tables));
 }
