@@ -1897,11 +1897,12 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
 //
 // The work is 2 H + 1 decodes of every byte (H = blocks per MCU) against about ten by iteration
 // over 4:2:0, but none waits for another for longer than a row.  Whole calls, one workgroup per
-// image against windows: a 44 KB photograph 1099 -> 132 us, a 760 KB full-HD still 14 639 -> 175 us,
-// 128 photographs (5 MB) 1879 -> 455 us, 512 thumbnails of 4:4:4, 4:2:0 and gray (5.6 MB)
-// 1062 -> 443 us.  Where windows do not pay, api.cpp does not cut (StreamCut).  resolve_streams and
-// write_streams are bound by a lane's dependent symbols (about 0.1 us each when the chip is idle)
-// and, where the chip is full, by instruction issue: 182 and 94 us of the 128 photographs' 455.
+// image against windows: a 44 KB photograph 1099 -> 93 us, a 760 KB full-HD still 14 639 -> 124 us,
+// 128 photographs (5 MB) 1879 -> 371 us, 512 thumbnails of 4:4:4, 4:2:0 and gray (5.6 MB)
+// 1062 -> 369 us.  Where windows do not pay, api.cpp does not cut (StreamCut).  resolve_streams and
+// write_streams are bound by a lane's dependent symbols (about 0.1 us each when the chip is idle) and,
+// a third of their time where it is full, by waiting for a window's records, tables and bytes:
+// 114 and 79 us of the 128 photographs' 371.
 
 namespace {
 
