@@ -163,3 +163,32 @@ def test_resampled_lengths_at_the_edges_of_chunks(prep, rate_in):
             assert i == 1 or np.array_equal(got[i], plain[i])
     finally:
         ap.close()
+
+
+@pytest.mark.parametrize("n_mels", [1, 2, 63, 64, 127, 128])
+def test_numbers_of_triangles(prep, n_mels):
+    # one range more than triangles: an even or odd number of them, and one more than two a lane
+    rate = 16000
+    w = speech_like(40 + n_mels, rate, 1.3)
+    ap = prep.AudioPreprocessor(max_batch=1, max_total_samples=len(w), n_mels=n_mels)
+    try:
+        g, = run(ap, [w], rate)
+        ref = audio.preprocess(w.astype(np.float64), rate, n_mels=n_mels)
+        assert g.shape == ref.shape and np.abs(g - ref).max() <= FEATURE_TOL
+    finally:
+        ap.close()
+
+
+def test_waves_that_take_several_pairs(prep):
+    """From 8192 pairs of frames on a wave takes more than one, across the utterances' borders: the
+    features are those of the utterances by themselves, bit for bit."""
+    rate = 16000
+    waves = [speech_like(500 + k % 7, rate, 4.2)[:60000 + 1111 * (k % 7)] for k in range(48)]
+    ap = prep.AudioPreprocessor(max_batch=48, max_total_samples=sum(map(len, waves)))
+    try:
+        assert sum((1 + len(w) // 160 + 1) // 2 for w in waves) >= 8192
+        alone = [run(ap, [w], rate)[0] for w in waves[:7]]
+        for k, g in enumerate(run(ap, waves, rate)):
+            assert np.array_equal(g, alone[k % 7])
+    finally:
+        ap.close()

@@ -138,3 +138,20 @@ def test_random_damage(pp, seed):
     status, tensor = run_gpu(pp, streams, 0, 64, 64, "f32")
     check_damaged(streams, status, lambda i, nb: pp.debug_last_coefficients(i, nb), tensor)
     assert _decoded(pp, len(streams)) == {STREAM_WINDOWS, STREAM_UNJOINED}
+
+
+# windows of 1.3 KB in these calls (at most 1 MiB of data): one image of more windows than the larger
+# tile of chain_streams holds, and one of more than the smaller tile's beside many of one window, which keep it small
+@pytest.mark.parametrize("n_small,w,h", [(0, 1600, 1400), (8, 1100, 800)])
+def test_chains_longer_than_a_tile(n_small, w, h):
+    import paper_2411_19114_amd as prep
+    files = [_file(77, w, h, 94, MODE_420, sigma=9.0)] + [_file(80 + k, 24, 16, 60, MODE_420) for k in range(n_small)]
+    windows = len(files[0]) // ((42 - 7) * 36)  # (42 rows of 36 bytes, seven of which overlap the next window)
+    assert sum(map(len, files)) < 1 << 20 and windows > (640 if n_small == 0 else 256)
+    h = prep.Preprocessor(device=0, max_batch=len(files), max_width=w, max_height=h, max_bitstream_bytes=1 << 20,
+                          flags=prep.FLAG_FULL_RGB)
+    try:
+        check_against_oracle(h, files, 0, 1, 1, "f32")
+        assert _decoded(h, len(files)) == {STREAM_WINDOWS}
+    finally:
+        h.close()
