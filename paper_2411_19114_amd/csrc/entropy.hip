@@ -127,10 +127,10 @@ struct DecodeShared {
     uint32_t next_boundary[kT + 1];  // first interval start at or after the lane's subsequence
     // Interval starts of the chunk in order (clean byte offsets), for the pass that takes an
     // interval a lane; the others need to know which of a lane's 64 raw bytes survived destuffing
-    // (and the hypothesis passes use the list's place for states)
+    // (and the hypothesis passes use the list's place for states: there a lane keeps it in registers)
     union {
         uint16_t bpos[kMaxBoundaries];
-        unsigned long long keep_here[kHyp ? 1 : kT];
+        unsigned long long keep[kHyp ? 1 : kT];
         RowLists rows_here;
     };
     std::conditional_t<kHyp, uint8_t, RowLists> rows_there;
@@ -140,8 +140,6 @@ struct DecodeShared {
         else return rows_there;
     }
     std::conditional_t<kRuns, HuffTables, HuffCodes> tab;
-    unsigned long long keep_there[kHyp ? kT : 1];
-    __device__ unsigned long long &keep(int lane) { return kHyp ? keep_there[lane] : keep_here[lane]; }
     uint32_t keep_off[kT + 1];       // clean offset of the lane's first surviving byte
     uint32_t state[kT];              // end state of every subsequence
     uint32_t scan_a[kT / 64 + 1];    // per-wave totals for workgroup scans
@@ -149,6 +147,9 @@ struct DecodeShared {
     int32_t dc_flag[kT / 64 + 1];
     uint32_t bcast[8];
 };
+
+// Workgroups that a compute unit's 160 KB of LDS hold: they get theirs in units of 1280 bytes
+constexpr uint32_t workgroups_by_lds(size_t bytes) { return (160u << 10) / 1280u / (uint32_t)((bytes + 1279u) / 1280u); }
 
 __device__ inline uint32_t pack_state(uint32_t p, uint32_t blk, uint32_t zz)
 {
@@ -1339,6 +1340,7 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
     uint32_t n_windows, const StreamWindow *__restrict__ windows)
 {
     __shared__ DecodeShared<kHyp, kRuns> S;
+    static_assert(kHyp || workgroups_by_lds(sizeof(S)) >= (kRuns ? 3u : 4u), "as many as the launch bounds say");
     const uint16_t *const runs = run_entries(S.tab);
     const int tid = threadIdx.x;
     const uint32_t wg = blockIdx.x;
@@ -1510,7 +1512,8 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
                                      nbnd <= (uint32_t)kMaxBoundaries && clean_len <= kShortInterval * (nbnd + 1);
         // the short-interval pass reads the stream without pad words (its lanes start anywhere)
         const uint32_t pad_shift = short_intervals ? 31u : (uint32_t)kPadShift;
-        if (!short_intervals) S.keep(tid) = keep;
+        if constexpr (!kHyp)
+            if (!short_intervals) S.keep[tid] = keep;
         // zeros behind the data: its last word is put together with OR, and lookups near the
         // end read a few words past it
         {
@@ -1657,6 +1660,10 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
             uint32_t *cand = reinterpret_cast<uint32_t *>(S.bpos);  // (the list of interval starts
             uint32_t *next = cand + kT;                             // is of no use to these passes)
             static_assert(sizeof(S.bpos) >= 2 * kT * sizeof(uint32_t), "cand[] and next[] fit");
+            // (With 2 KB more only two workgroups fitted, which the compiler's occupancy of three does not tell:
+            // calls of gray images that make more than 512 of them took 133 us instead of 89.)
+            static_assert(workgroups_by_lds(sizeof(S) + sizeof(hyp_blocks) + sizeof(link) + sizeof(chosen)) >= 3 || !kHyp,
+                          "three workgroups a compute unit, as the launch bounds say");
             constexpr uint32_t kNoLink = 255;
             const uint32_t H = g.bpm, per = (uint32_t)kT / H;
             const uint32_t j = (uint32_t)tid / H, h = (uint32_t)tid - j * H;
@@ -1846,8 +1853,9 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
                 atomicAdd(&S.bcast[3], qc - first >= 63u ? (uint32_t)__popcll(m)
                                                          : (uint32_t)__popcll(m & ((2ull << (qc - first)) - 1ull)));
         }
-        if (S.keep_off[tid] <= qc && qc < S.keep_off[tid] + (uint32_t)__popcll(S.keep(tid))) {
-            unsigned long long m = S.keep(tid);
+        if constexpr (!kHyp) keep = S.keep[tid];
+        if (S.keep_off[tid] <= qc && qc < S.keep_off[tid] + (uint32_t)__popcll(keep)) {
+            unsigned long long m = keep;
             const uint32_t skip = qc - S.keep_off[tid];
             for (uint32_t i = 0; i < skip; i++) m &= m - 1;  // drop the lowest set bits
             S.bcast[1] = (uint32_t)(my_lo + (int32_t)__builtin_ctzll(m));
