@@ -1449,6 +1449,14 @@ __global__ __launch_bounds__(kDecodeThreads, kRuns ? 3 : 4) void decode_entropy(
 
     const uint32_t max_chunks = (range_hi - range_lo) / 64u + 2;
     for (uint32_t iter = 0; iter < max_chunks && cs < rhi; iter++) {
+        // what a chunk hands on to the next came through LDS: the same in every lane, but the compiler does
+        // not know, and of the 128 vector registers of the variant for short intervals none are spare
+        cs = __builtin_amdgcn_readfirstlane(cs);
+        st0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)st0);
+        block_base = (uint32_t)__builtin_amdgcn_readfirstlane((int)block_base);
+        marker_base = (uint32_t)__builtin_amdgcn_readfirstlane((int)marker_base);
+#pragma unroll
+        for (int c = 0; c < 3; c++) dc_carry[c] = __builtin_amdgcn_readfirstlane(dc_carry[c]);
         // ---- stage: destuff raw bytes [cs, ce) into S.clean --------------------------
         // lanes own 64-byte pieces (four 16-byte parts) of the 16-byte aligned span that
         // contains cs
