@@ -578,10 +578,13 @@ int run_batch(prep_handle *h, const uint8_t *bits_host, const uint8_t *bits_dev,
                                     h->d_status, reinterpret_cast<const uint32_t *>(s->d_recs + n) + n,
                                     P.n_tables, h->d_tables, stream);
         if (timing) HIP_TRY(hipEventRecord(ev[1], stream));
+        // the DC differences go behind the blocks of this call, not behind those that the handle has room for: up to
+        // 2^25 blocks a call the written-out symbol loops reach both with one 32-bit offset (see WriteSteps)
+        const uint32_t side_off = (uint32_t)(P.n_blocks * 64);
         launch_decode_streams(d_bits, s->d_recs, n, P.n_streams, P.row_bytes, s->d_data_end, h->d_retry, h->d_streams,
-                              h->d_coef, (uint32_t)(h->cap_blocks * 64), h->d_tables, stream);
+                              h->d_coef, side_off, h->d_tables, stream);
         launch_decode_entropy(d_bits, s->d_recs, n, P.n_windows, h->d_win_count, h->d_win_first, s->d_data_end,
-                              h->d_retry, h->d_coef, (uint32_t)(h->cap_blocks * 64), h->d_status, h->d_tables,
+                              h->d_retry, h->d_coef, side_off, h->d_status, h->d_tables,
                               P.window_bytes != (uint32_t)kWindowBytes,
                               P.window_bytes == (uint32_t)kTinyWindowBytes ? 256u : 512u, P.long_intervals,
                               P.n_streams, h->d_streams, stream);
