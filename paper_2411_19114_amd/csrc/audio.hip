@@ -115,6 +115,9 @@ struct BandPlan {
 // rows of at most 2 * 6 / 0.99 * max(p / q, 1) + 2 taps, fewer than 14 * max(p, q) + 2 q entries.
 constexpr int kMaxRateTerm = 4096;
 constexpr size_t kMaxTapEntries = 16 * (size_t)kMaxRateTerm;
+// Samples that a handle may be asked to hold: more than any device's memory takes (8 bytes each), and few enough
+// that their sizes fit 64 bits and the tiles of resample_bands_kernel (at least 128 samples each) 30.
+constexpr uint64_t kMaxSamples = 1ull << 36;
 
 // Entry of `bands` for sample n of block b's band and phase 16 b + j
 __host__ __device__ inline size_t band_entry(int quads, int b, int n, int j)
@@ -668,6 +671,7 @@ int prep_audio_create(prep_audio **out, const prep_audio_config *cfg)
         cfg->win_length > cfg->n_fft || cfg->hop < 1 || cfg->n_mels < 1 || cfg->n_mels > kMaxMels ||
         cfg->max_total_samples < 1)
         return PREP_E_INVALID_ARG;
+    if (cfg->max_total_samples > kMaxSamples) return PREP_E_NOMEM;
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || cfg->device < 0 || cfg->device >= ndev) {
         (void)hipGetLastError();
@@ -841,7 +845,8 @@ int prep_audio_features(prep_audio *h, const float *waveforms, const uint64_t *o
         for (int32_t i = 0; i < n; i++) h->h_utt[i].mid_off = h->h_utt[i].in_off;
     }
     AUDIO_TRY(hipMemcpyAsync(h->d_utt, h->h_utt, kRecordBytes * (size_t)n, hipMemcpyHostToDevice, stream));
-    if (p != q && taps->plan.quads && tiles_total <= 0x3FFFFFFFull) {
+    if (p != q && taps->plan.quads) {
+        // (a slot with a plan holds its taps in that form only, so there is no other way for it)
         const BandPlan &plan = taps->plan;
         // as many waves as the chip holds, or as there are tiles' blocks, but one for each block at least
         const uint64_t unit = kXcds * kBandWaves, wanted = (tiles_total * (uint64_t)plan.blocks + unit - 1) / unit * unit;

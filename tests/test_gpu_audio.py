@@ -111,6 +111,11 @@ def test_argument_errors(prep):
         ap.close()
     with pytest.raises(prep.PrepError):
         prep.AudioPreprocessor(max_batch=1, max_total_samples=1000, n_fft=1024)
+    # more than the device holds, and more than the sizes in bytes hold
+    for samples in (1 << 37, 1 << 61, (1 << 64) - 1):
+        with pytest.raises(prep.PrepError) as e:
+            prep.AudioPreprocessor(max_batch=1, max_total_samples=samples)
+        assert e.value.code == prep.E_NOMEM
 
 
 def test_frames_in_pairs(prep):
