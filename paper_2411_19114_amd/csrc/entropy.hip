@@ -687,9 +687,10 @@ __device__ __forceinline__ uint32_t lds_address(const void *p)
     "s_or_b64 vcc, vcc, %[m1]\n"                                \
     "s_cbranch_vccz 1b\n"                                       \
     "s_waitcnt lgkmcnt(0)\n"
+// (All that a step writes is marked as written early: a step reads what STEP_GIVEN lists after that.)
 #define STEP_STATE                                                                                                   \
-    [w] "+v"(s.c.w), [n32] "+v"(s.c.n32), [hi] "+v"(s.c.hi), [lo] "+v"(s.c.lo), [ahead] "+v"(s.c.ahead),             \
-        [win] "+v"(s.c.win), [slot] "+v"(s.slot), [k] "+v"(s.k), [block] "+v"(s.block), [e] "+v"(s.e),               \
+    [w] "+&v"(s.c.w), [n32] "+&v"(s.c.n32), [hi] "+&v"(s.c.hi), [lo] "+&v"(s.c.lo), [ahead] "+&v"(s.c.ahead),             \
+        [win] "+&v"(s.c.win), [slot] "+&v"(s.slot), [k] "+&v"(s.k), [block] "+&v"(s.block), [e] "+&v"(s.e),               \
         [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2), [carry] "=&s"(carry)
 #define STEP_GIVEN                                                                                                   \
     [nearw] "v"(s.near_w), [aheadat] "v"(ahead_at), [oneac] "v"(one_dc + 2u), [onedc] "v"(one_dc),                   \
@@ -821,14 +822,14 @@ __device__ __forceinline__ void step_write(Steps &s, WriteSteps &ws, const uint3
 #define WRITE_INTERVAL                                          \
     "v_or_b32 %[late], %[late], %[left]\n"                      \
     "v_subb_co_u32 %[left], %[m2], %[left], 0, vcc\n"
-#define WRITE_STATE STEP_STATE, [t4] "=&v"(t4), [t5] "=&v"(t5), [t6] "=&v"(t6), [base] "+v"(ws.base), [over] "+v"(ws.over)
+#define WRITE_STATE STEP_STATE, [t4] "=&v"(t4), [t5] "=&v"(t5), [t6] "=&v"(t6), [base] "+&v"(ws.base), [over] "+&v"(ws.over)
 #define WRITE_GIVEN STEP_GIVEN, [coef] "s"(ws.coef), [lastblock] "v"(ws.last_block), [side] "v"(ws.side)
     if (!ws.wide) {
         if (!wave_any(s.near())) {
             if constexpr (kRestart)
                 asm volatile(".p2align 5\n"
                              "1:\n" WRITE_ADVANCE WRITE_NUMBER WRITE_INTERVAL STEP_NEAR
-                             : WRITE_STATE, [late] "+v"(ws.late), [left] "+v"(ws.iv_left)
+                             : WRITE_STATE, [late] "+&v"(ws.late), [left] "+&v"(ws.iv_left)
                              : WRITE_GIVEN
                              : "vcc", "scc", "memory");
             else
@@ -842,7 +843,7 @@ __device__ __forceinline__ void step_write(Steps &s, WriteSteps &ws, const uint3
             uint64_t all;
             if constexpr (kRestart)
                 asm volatile(STEP_DUE_BEGIN WRITE_ADVANCE STEP_POSITION WRITE_NUMBER WRITE_INTERVAL STEP_DUE
-                             : WRITE_STATE, [late] "+v"(ws.late), [left] "+v"(ws.iv_left), [p] "=&v"(p), [all] "=&s"(all)
+                             : WRITE_STATE, [late] "+&v"(ws.late), [left] "+&v"(ws.iv_left), [p] "=&v"(p), [all] "=&s"(all)
                              : WRITE_GIVEN, [end] "v"(s.end_bit), [nb] "v"(s.nb)
                              : "vcc", "scc", "memory");
             else
