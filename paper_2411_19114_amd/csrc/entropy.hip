@@ -2242,10 +2242,12 @@ __global__ __launch_bounds__(kDecodeThreads) void resolve_streams(
 // entry e, one lane strings the segments together, and a lane per segment goes over it again: as many
 // segments as a segment has windows, so that no stage is much longer than the others.  Bound by the
 // latency of these walks and of the tile's loads (24 entries a window, in calls with little data 42), which
-// are under way together: a full-HD still of 630 windows 32 -> 19 us with sixteen waves instead of four and
-// one tile.
+// are under way together: a full-HD still of 600 windows 32 -> 20 us with sixteen waves instead of four and
+// one tile; one of 795 windows 28.6 with a tile of 640, 24.3 with one for all.
 constexpr int kChainThreads = 1024;
-constexpr int kChainTile = 256, kChainLargeTile = 640;  // windows: 43 and 108 KB of LDS
+constexpr int kChainTile = 256;  // windows: 43 KB of LDS
+// the larger: all windows that an image can have in a call with short rows (833 of six blocks per MCU: 140 KB)
+constexpr int kChainLargeTile = (int)(kStreamTinyBytes / stream_window_bytes(6, kStreamTinyRowBytes)) + 1;
 template <int kTile>
 __global__ __launch_bounds__(kChainThreads) void chain_streams(
     const ImageRec *__restrict__ recs, uint32_t row_bytes, uint32_t *__restrict__ retry, StreamWindow *__restrict__ windows)
@@ -2255,6 +2257,7 @@ __global__ __launch_bounds__(kChainThreads) void chain_streams(
     __shared__ uint32_t seg_way[kChainThreads], seg_blocks[kChainThreads];
     __shared__ uint32_t seg_entry[kChainThreads], seg_block[kChainThreads];
     __shared__ uint32_t s_entry, s_block;
+    static_assert(workgroups_by_lds(sizeof(through) + 4 * sizeof(seg_way) + 8) >= 1, "a tile fits");
     const ImageRec &R = recs[blockIdx.x];
     const int tid = threadIdx.x;
     const uint32_t n = R.n_streams;
@@ -2497,7 +2500,7 @@ void launch_decode_streams(const uint8_t *bits, const ImageRec *recs, int n_imag
     const uint4 *tab = reinterpret_cast<const uint4 *>(tables);
     hipLaunchKernelGGL(resolve_streams, dim3(n_streams), dim3(kDecodeThreads), 0, stream, bits, recs, n_images, row_bytes,
                        data_end, retry, tab, win);
-    // the larger tile where images have more windows than half the smaller one (630 windows 24 -> 19 us; 128
+    // the larger tile where images have more windows than half the smaller one (600 windows 24 -> 20 us; 128
     // images of 16 windows 4.8 -> 5.1) and a compute unit has no other image to follow
     if (n_images <= 256 && n_streams > (uint32_t)n_images * (kChainTile / 2))
         hipLaunchKernelGGL(chain_streams<kChainLargeTile>, dim3(n_images), dim3(kChainThreads), 0, stream, recs, row_bytes, retry, win);

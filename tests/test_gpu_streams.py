@@ -140,8 +140,9 @@ def test_random_damage(pp, seed):
     assert _decoded(pp, len(streams)) == {STREAM_WINDOWS, STREAM_UNJOINED}
 
 
-# windows of 1.3 KB in these calls (at most 1 MiB of data): one image of more windows than the larger
-# tile of chain_streams holds, and one of more than the smaller tile's beside many of one window, which keep it small
+# windows of 1.3 KB in these calls (at most 1 MiB of data): one image of most of the windows that such a call can have,
+# which the larger tile of chain_streams holds, and one of more than the smaller tile's beside many of one window, which
+# keep it small
 @pytest.mark.parametrize("n_small,w,h", [(0, 1600, 1400), (8, 1100, 800)])
 def test_chains_longer_than_a_tile(n_small, w, h):
     import paper_2411_19114_amd as prep
@@ -153,5 +154,18 @@ def test_chains_longer_than_a_tile(n_small, w, h):
     try:
         check_against_oracle(h, files, 0, 1, 1, "f32")
         assert _decoded(h, len(files)) == {STREAM_WINDOWS}
+    finally:
+        h.close()
+
+
+def test_more_windows_than_the_larger_tile():
+    # windows of 2.6 KB (more than 1 MiB of data): a full tile of 833 of them, and some
+    import paper_2411_19114_amd as prep
+    f = _file(41, 2800, 2500, 93, MODE_420, sigma=8.0)
+    assert 834 < len(f) // ((42 - 4) * 68) < 2 * 833
+    h = prep.Preprocessor(device=0, max_batch=1, max_width=2800, max_height=2500, max_bitstream_bytes=len(f))
+    try:
+        check_against_oracle(h, [f], 0, 64, 64, "f32")
+        assert _decoded(h, 1) == {STREAM_WINDOWS}
     finally:
         h.close()
