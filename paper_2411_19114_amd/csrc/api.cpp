@@ -375,7 +375,7 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
     h->table_rep.clear();
     std::fill(h->table_hash.begin(), h->table_hash.end(), 0u);
     Plan P;
-    uint64_t entropy_total = 0, long_total = 0;
+    uint64_t entropy_total = 0, long_total = 0, busy_workgroups = 0;
     StreamCut streams;
     for (int32_t i = 0; i < n; i++) {
         if (offsets[i + 1] < offsets[i]) return PREP_E_INVALID_ARG;
@@ -394,7 +394,6 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
     // the chip with hypotheses instead of walking whole restart intervals lane by lane
     if (entropy_total <= kSmallCallBytes && !(h->cfg.flags & PREP_FLAG_LARGE_WINDOWS))
         P.window_bytes = entropy_total <= kTinyCallBytes ? kTinyWindowBytes : kSmallWindowBytes;
-    P.long_intervals = 4 * long_total >= entropy_total;
     for (int32_t i = 0; i < n; i++) {
         ParsedImage &pi = h->parsed[(size_t)i];
         prep_image_info &I = pi.info;
@@ -428,6 +427,7 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
                 const uint32_t step = stream_window_bytes((uint32_t)I.blocks_per_mcu, P.row_bytes);
                 R.n_streams = (uint32_t)std::max<uint64_t>((I.entropy_bytes + step - 1) / step, 1);
             }
+            if (R.n_streams == 0) busy_workgroups += std::min<uint64_t>(R.n_windows, std::max(I.n_intervals, 1));
             for (int c = 0; c < 3; c++) R.dqt_off[c] = pi.dqt_off[c];
             R.width = (uint16_t)I.width;
             R.height = (uint16_t)I.height;
@@ -478,6 +478,17 @@ int plan_batch(prep_handle *h, const uint8_t *bits, const uint64_t *offsets, int
         P.n_windows += R.n_windows;
         P.n_streams += R.n_streams;
     }
+    // Which variant of the decoder for large calls.  Its iteration over long intervals goes 1.3 times as fast with run
+    // entries, whose tables leave room for three workgroups a compute unit; without them it is four.  So calls
+    // with much data in long intervals take the former unless just the latter does them in one round (decode stage,
+    // us, with / without: unmarked gray images of 96 x 96, 760 of them 60 / 70, 800 110 / 71, 1000 110 / 73, 1030 110 / 131,
+    // 2000 164 / 157; 4:2:0 of 128 x 128 138 / 196, 243 / 197, 257 / 198, 256 / 332, 389 / 417).  Much = a quarter: photographs with a marker
+    // every eight MCUs and a part of the bytes in rows of 1.5 to 2.5 KB, 1100 to 1800 workgroups, 444 at 0.35 312 / 332, 422 at 0.33
+    // 267 / 312.  (Up to 768 workgroups the former is also faster with less, 96 such 4:2:0 images at 0.15 230 / 309.)  Streams that
+    // are cut into windows count: where one's windows cannot be joined the call waits for its iteration (128
+    // photographs, one of them such: 566 / 672; none: 306 / 304).
+    const bool one_round_of_four = busy_workgroups > 3 * kComputeUnits && busy_workgroups <= 4 * kComputeUnits;
+    P.long_intervals = 4 * long_total >= entropy_total && !one_round_of_four;
     P.n_tables = (uint32_t)h->table_rep.size();
     // A reconstruction workgroup takes several groups of its image when there are plenty, so
     // that it can fetch one while it works on another; group0 counts workgroups.

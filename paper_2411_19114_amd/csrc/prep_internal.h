@@ -5,6 +5,8 @@
 
 namespace prep {
 
+constexpr uint32_t kComputeUnits = 256;                     // of the device
+
 // ---- entropy decoder geometry -------------------------------------------
 // One workgroup owns a contiguous run of restart intervals of one image and
 // decodes it chunk by chunk.  A chunk is kChunkRaw raw bytes staged into LDS

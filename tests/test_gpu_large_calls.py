@@ -1,11 +1,12 @@
 """Calls of more than 2^25 blocks, whose first images lie so far from their DC differences that the decoder
-takes the form of its symbol loops with 64-bit addresses; and handles with room for such calls."""
+takes the form of its symbol loops with 64-bit addresses; handles with room for such calls; and calls of about as
+many workgroups as the chip holds."""
 import numpy as np
 import pytest
 
 import oracle
 import synth
-from helpers import check_damaged, damaged_streams, run_gpu, WINDOW_BASES
+from helpers import check_against_oracle, check_damaged, damaged_streams, run_gpu, WINDOW_BASES
 from oracle import MODE_420, MODE_422, MODE_444, MODE_GRAY
 from paper_2411_19114_amd import STREAM_WHOLE, STREAM_WINDOWS
 
@@ -79,3 +80,58 @@ def test_a_handle_with_room_to_spare_is_as_fast():
         for h in handles:
             h.close()
     assert best[1] <= 1.12 * best[0], best
+
+
+def _whole_streams(n, mode=MODE_GRAY):
+    """n unmarked streams of one chunk, more of them than are cut into windows, with more than 1.5 MiB of data."""
+    files = [oracle.encode(_image(300 + k, 128 - k % 3, 128, 8.0), 88, mode, 0, table_mode=k % 5 == 4)[0] for k in range(20)]
+    files = (files * (n // 20 + 1))[:n]
+    assert sum(map(len, files)) > 3 << 19
+    return files
+
+
+# 768 and 1024 workgroups: as many as the chip holds of the decoder's variant with run entries, and of the one without
+@pytest.mark.parametrize("mode,n", [(MODE_GRAY, 768), (MODE_GRAY, 769), (MODE_GRAY, 1024), (MODE_GRAY, 1025), (MODE_444, 900),
+                                    (MODE_422, 1000)])
+def test_calls_of_about_one_round(mode, n):
+    import paper_2411_19114_amd as prep
+    files = _whole_streams(n, mode)
+    h = prep.Preprocessor(device=0, max_batch=n, max_width=128, max_height=128, max_bitstream_bytes=sum(map(len, files)))
+    try:
+        # (damage in between: both variants refuse, or decode, what the oracle does)
+        bad = [s for s in damaged_streams(23, 4, n_bases=4) if b"\xff\xff\x00" not in s]
+        mixed = files[:n // 2] + bad + files[n // 2:n - len(bad)]
+        status, tensor = run_gpu(h, mixed, 0, 16, 16, "f32")
+        assert [status[i] for i in (0, n // 2 - 1, n - 1)] == [0, 0, 0]
+        check_damaged(mixed[n // 2:n // 2 + len(bad)], status[n // 2:], lambda i, nb: h.debug_last_coefficients(n // 2 + i, nb),
+                      tensor[n // 2:])
+        check_against_oracle(h, files, 0, 16, 16, "f32")
+        assert {h.debug_last_stream(i) for i in range(n)} == {STREAM_WHOLE}
+    finally:
+        h.close()
+
+
+def test_a_thousand_streams_take_one_round():
+    """The decoder's time for 1000 streams that a workgroup takes each is that for 750 and a little (73 against 60 us with
+    the variant of which the chip holds 1024; 110 with the other, which does them in two rounds)."""
+    import torch
+    import paper_2411_19114_amd as prep
+    from paper_2411_19114_amd.binding import make_params
+    params = make_params(32, 32, 32, "f16", synth.IMAGENET_MEAN, synth.IMAGENET_STD)
+    took = []
+    for n in (750, 1000):
+        files = _whole_streams(n)
+        blob, offsets = synth.pack(files)
+        bits = torch.from_numpy(blob).to("cuda:0")
+        out = torch.empty((n, 3, 32, 32), dtype=torch.float16, device="cuda:0")
+        h = prep.Preprocessor(device=0, max_batch=n, max_width=128, max_height=128, max_bitstream_bytes=sum(map(len, files)))
+        try:
+            h.set_timing(True)
+            for _ in range(30):
+                h.decode_resize_batch_resident(blob, bits.data_ptr(), offsets, params, out.data_ptr(),
+                                               torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            took.append(min(h.stage_ms(k)[1] for k in range(20)))
+        finally:
+            h.close()
+    assert took[1] <= 1.5 * took[0], took
