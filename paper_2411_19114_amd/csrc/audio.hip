@@ -23,6 +23,7 @@
 #include <algorithm>
 #include <new>
 #include <numeric>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/prep.h"
@@ -336,25 +337,30 @@ __global__ __launch_bounds__(kFrameThreads, 3) void log_mel_kernel(
     __shared__ double2 s_factor[8 * 8];
     __shared__ double s_window[kFft];
     __shared__ MelRange s_range[kMaxMels + 1];
+    static_assert(kFft == 2 * kFrameThreads && kMaxMels < kFrameThreads, "a lane copies two window values, and a range");
     double2 factor[8];
 #pragma unroll
     for (int r = 1; r < 8; r++) factor[r] = twiddle[r * lane];
-    if (threadIdx.x < 64) s_factor[threadIdx.x] = twiddle[(threadIdx.x >> 3) * (threadIdx.x & 7) * (kFft / 64)];
-    for (int i = threadIdx.x; i < kFft; i += kFrameThreads) s_window[i] = window[i];
-    if ((int)threadIdx.x <= n_mels) s_range[threadIdx.x] = ranges[threadIdx.x];
-    static_assert(kMaxMels < kFrameThreads, "a lane copies a range");
-    __syncthreads();
-    if (f >= f_end) return;    // no workgroup-wide barrier below: a wave works on its own pairs
-    int lo = 0, hi = n_utt - 1;
-    while (lo < hi) {
-        const int m = (lo + hi + 1) >> 1;
-        if (pair_start[m] <= f) lo = m; else hi = m - 1;
+    // (asked for here, put into LDS when the samples have been asked for too)
+    const double2 some_factor = twiddle[(lane >> 3) * (lane & 7) * (kFft / 64)];
+    const double some_window[2] = {window[threadIdx.x], window[threadIdx.x + kFrameThreads]};
+    const MelRange some_range = ranges[min((int)threadIdx.x, n_mels)];
+    int lo = 0;
+    if (f < f_end) {
+        int hi = n_utt - 1;
+        while (lo < hi) {
+            const int m = (lo + hi + 1) >> 1;
+            if (pair_start[m] <= f) lo = m; else hi = m - 1;
+        }
     }
     double2 *x = s_x[wave];
-    // The ranges widen with their number, so a lane takes a narrow one, `lane`, and the wide one that
-    // mirrors it: every busy lane sums about the same number of bins.  (One range is left over where
-    // there are more than 128.)
+    // The ranges widen with their number, so where there are more than 64 a lane takes a narrow one, `lane`,
+    // and the wide one that mirrors it: every busy lane sums about the same number of bins.  (One range is
+    // left over where there are more than 128.)  Up to 64 have a lane each, or, a power of two of them, several: one
+    // channel, two ranges, 8 utterances of 5 s 60 -> 16 us.
     const int n_ranges = n_mels + 1, mirrored = n_ranges - 1 - lane;
+    int log_parts = 0;
+    while ((n_ranges << (log_parts + 1)) <= 64) log_parts++;
     // the samples of both frames of pair f: loaded while the pair before is summed, where both frames
     // lie inside the signal
     uint32_t t = 0, frames = 0;
@@ -376,7 +382,13 @@ __global__ __launch_bounds__(kFrameThreads, 3) void log_mel_kernel(
             }
         }
     };
-    load();
+    if (f < f_end) load();
+    if (threadIdx.x < 64) s_factor[threadIdx.x] = some_factor;
+    s_window[threadIdx.x] = some_window[0];
+    s_window[threadIdx.x + kFrameThreads] = some_window[1];
+    if ((int)threadIdx.x <= n_mels) s_range[threadIdx.x] = some_range;
+    __syncthreads();
+    if (f >= f_end) return;    // no workgroup-wide barrier below: a wave works on its own pairs
     for (;;) {
         const bool two = t + 1 < frames;
         if (!inside) {
@@ -450,29 +462,50 @@ __global__ __launch_bounds__(kFrameThreads, 3) void log_mel_kernel(
         // the sums of the ranges, behind the powers, of both frames
         double2 *rising = x + kFft / 2 + 1, *falling = rising + kMaxMels + 1;
         static_assert(kFft / 2 + 1 + 2 * (kMaxMels + 1) <= kFramePadded, "the sums fit behind the powers");
-        auto sum = [&](int m) {
+        // part = [first, last) of range m's bins; a part's weights are not those that the host has looked at
+        auto sum = [&](int m, auto part, int first, int last) {
             const MelRange range = s_range[m];
             double2 up = make_double2(0.0, 0.0), down = up;
             double wu = range.rising, wd = range.falling;
+            if constexpr (part) {
+                wu += first * range.step;
+                wd -= first * range.step;
+            } else {
+                first = 0;
+                last = range.count;
+            }
             const double2 *pw = x + range.start;
             // four bins at a time, so that their loads are under way together
-            for (int k = 0; k < range.count; k += 4) {
+            for (int k = first; k < last; k += 4) {
 #pragma unroll
                 for (int e = 0; e < 4; e++) {
-                    const double2 power = pw[min(k + e, range.count - 1)];
-                    const double u = k + e < range.count ? wu : 0.0, d = k + e < range.count ? wd : 0.0;
+                    const double2 power = pw[min(k + e, last - 1)];
+                    const double u = k + e < last ? wu : 0.0, d = k + e < last ? (part ? fmax(wd, 0.0) : wd) : 0.0;
                     up = make_double2(fma(u, power.x, up.x), fma(u, power.y, up.y));
                     down = make_double2(fma(d, power.x, down.x), fma(d, power.y, down.y));
                     wu += range.step;
                     wd -= range.step;
                 }
             }
+            if constexpr (part) {
+                for (int i = 1; i < 1 << log_parts; i *= 2) {
+                    up = cadd(up, make_double2(__shfl_xor(up.x, i), __shfl_xor(up.y, i)));
+                    down = cadd(down, make_double2(__shfl_xor(down.x, i), __shfl_xor(down.y, i)));
+                }
+                if (lane & ((1 << log_parts) - 1)) return;
+            }
             rising[m] = up;
             falling[m] = down;
         };
-        if (lane <= mirrored) sum(lane);
-        if (lane < mirrored) sum(mirrored);
-        if (n_ranges > 128 && lane == 0) sum(64);
+        if (n_ranges > 64) {
+            if (lane <= mirrored) sum(lane, std::false_type(), 0, 0);
+            if (lane < mirrored) sum(mirrored, std::false_type(), 0, 0);
+            if (n_ranges > 128 && lane == 0) sum(64, std::false_type(), 0, 0);
+        } else if (lane >> log_parts < n_ranges) {
+            const int m = lane >> log_parts, count = s_range[m].count;
+            const int each = (count + (1 << log_parts) - 1) >> log_parts, first = (lane & ((1 << log_parts) - 1)) * each;
+            sum(m, std::true_type(), min(first, count), min(first + each, count));
+        }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         const double *up = reinterpret_cast<const double *>(rising), *down = reinterpret_cast<const double *>(falling + 1);
         for (int i = lane; i < 2 * n_mels; i += 64) {   // i = 2 m + frame

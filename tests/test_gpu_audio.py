@@ -184,6 +184,26 @@ def test_numbers_of_triangles(prep, n_mels):
         ap.close()
 
 
+# the last number of triangles, and the first, whose ranges have 2^k lanes each; and as many ranges as lanes
+@pytest.mark.parametrize("n_mels", [3, 4, 7, 8, 15, 16, 31, 32, 62])
+def test_ranges_of_several_lanes(prep, n_mels):
+    """Two utterances, one of an odd number of frames; a full tone and silence in the other, where a weight
+    that rounded below zero would show."""
+    rate = 16000
+    t = np.arange(rate) / rate
+    loud = np.concatenate([np.zeros(4000), 1e9 * np.sin(2 * np.pi * 3000.0 * t), np.zeros(4000)]).astype(np.float32)
+    waves = [speech_like(60 + n_mels, rate, 0.9)[:160 * 80 + 11], loud]
+    ap = prep.AudioPreprocessor(max_batch=2, max_total_samples=sum(map(len, waves)), n_mels=n_mels)
+    try:
+        got = run(ap, waves, rate)
+        ref = audio.preprocess(waves[0].astype(np.float64), rate, n_mels=n_mels)
+        assert got[0].shape == ref.shape and np.abs(got[0] - ref).max() <= FEATURE_TOL
+        ref = audio.preprocess(waves[1].astype(np.float64), rate, n_mels=n_mels)
+        assert np.isfinite(got[1]).all() and np.abs(got[1] - ref).max() <= FEATURE_TOL
+    finally:
+        ap.close()
+
+
 def test_waves_that_take_several_pairs(prep):
     """From 8192 pairs of frames on a wave takes more than one, across the utterances' borders: the
     features are those of the utterances by themselves, bit for bit."""
