@@ -583,11 +583,12 @@ int run_batch(prep_handle *h, const uint8_t *bits_host, const uint8_t *bits_dev,
             HIP_TRY(hipMemcpyAsync(h->d_coef, coef_host, P.n_blocks * 128, hipMemcpyHostToDevice, stream));
         if (timing) { HIP_TRY(hipEventRecord(ev[1], stream)); HIP_TRY(hipEventRecord(ev[2], stream)); }
     } else {
+        const bool small_windows = P.window_bytes != (uint32_t)kWindowBytes;
         // (P.n_windows >= n > 0: the scan also sets every image's status)
         launch_scan_restart_markers(d_bits, s->d_recs, n, P.n_windows, P.window_bytes, h->d_win_count, h->d_win_first,
                                     s->d_data_end, h->d_retry,
                                     h->d_status, reinterpret_cast<const uint32_t *>(s->d_recs + n) + n,
-                                    P.n_tables, h->d_tables, stream);
+                                    P.n_tables, small_windows || P.long_intervals || P.n_streams != 0, h->d_tables, stream);
         if (timing) HIP_TRY(hipEventRecord(ev[1], stream));
         // the DC differences go behind the blocks of this call, not behind those that the handle has room for: up to
         // 2^25 blocks a call the written-out symbol loops reach both with one 32-bit offset (see WriteSteps)
@@ -596,8 +597,7 @@ int run_batch(prep_handle *h, const uint8_t *bits_host, const uint8_t *bits_dev,
                               h->d_coef, side_off, h->d_tables, stream);
         launch_decode_entropy(d_bits, s->d_recs, n, P.n_windows, h->d_win_count, h->d_win_first, s->d_data_end,
                               h->d_retry, h->d_coef, side_off, h->d_status, h->d_tables,
-                              P.window_bytes != (uint32_t)kWindowBytes,
-                              P.window_bytes == (uint32_t)kTinyWindowBytes ? 256u : 512u, P.long_intervals,
+                              small_windows, P.window_bytes == (uint32_t)kTinyWindowBytes ? 256u : 512u, P.long_intervals,
                               P.n_streams, h->d_streams, stream);
         if (timing) HIP_TRY(hipEventRecord(ev[2], stream));
     }

@@ -366,15 +366,15 @@ __device__ inline void build_runs(HuffTables &T)
 // into a slot of expanded tables, an entry a lane.  A run's further symbols are found among the codes like
 // its first, so that no lane waits for the others' entries.  (One workgroup a table, entries looked up in
 // those made before, was what small calls waited for in this kernel: 11.5 us, 5.2 now; 33 sets of
-// tables 13.8 -> 11.2, 64 16.1 -> 12.0 against whole tables made like this.)  All lanes of the workgroup
-// must call.
+// tables 13.8 -> 11.2, 64 16.1 -> 12.0 against whole tables made like this.)  Run entries cost most and are left
+// out where no kernel of the call reads them.  All lanes of the workgroup must call.
 constexpr uint32_t kTableParts = (kLookupEntries + kT - 1) / kT;
 struct CodeLists {
     int32_t first[17], count[17], valptr[17];
     uint32_t end[16];  // the sixteen-bit words below end[l - 1] begin with a code of at most l bits
     uint8_t huffval[256];
 };
-__device__ inline void expand_table(const uint8_t *file, const ImageRec &R, int t, uint32_t part, HuffTables *dst)
+__device__ inline void expand_table(const uint8_t *file, const ImageRec &R, int t, uint32_t part, bool runs, HuffTables *dst)
 {
     __shared__ CodeLists lists[2];  // of table t, and of the AC table behind it
     const int tid = threadIdx.x;
@@ -417,8 +417,9 @@ __device__ inline void expand_table(const uint8_t *file, const ImageRec &R, int 
     if (i < kLookupEntries) {
         const uint32_t e = entry(lists[0], t & 1, i);
         dst->one[(i << 2) | (uint32_t)t] = (uint16_t)e;
-        dst->run[(i << 2) | (uint32_t)t] =
-            (uint16_t)(i < kFinePrefixes ? run_entry(e, i, [&](uint32_t n) { return entry(lists[1], 1, n); }) : e);
+        if (runs)
+            dst->run[(i << 2) | (uint32_t)t] =
+                (uint16_t)(i < kFinePrefixes ? run_entry(e, i, [&](uint32_t n) { return entry(lists[1], 1, n); }) : e);
     }
     if (part != 0) return;
     if (tid < 17) {
@@ -1251,14 +1252,15 @@ __global__ __launch_bounds__(kDecodeThreads) void scan_restart_markers(
     const uint8_t *__restrict__ bits, const ImageRec *__restrict__ recs, int n_images,
     uint32_t n_windows, uint32_t window_bytes, uint32_t *__restrict__ win_count,
     uint32_t *__restrict__ win_first, uint32_t *__restrict__ data_end, uint32_t *__restrict__ retry,
-    int32_t *__restrict__ status, const uint32_t *__restrict__ table_rep, uint4 *__restrict__ tables)
+    int32_t *__restrict__ status, const uint32_t *__restrict__ table_rep, bool runs, uint4 *__restrict__ tables)
 {
     __shared__ uint32_t s_cnt[kT / 64], s_first[kT / 64];
     const uint32_t wg = blockIdx.x;
     if (wg >= n_windows) {
         const uint32_t id = wg - n_windows, slot = id / (4u * kTableParts);
         const ImageRec &I = recs[table_rep[slot]];
-        expand_table(bits + I.file_off, I, (int)(id & 3u), id / 4u % kTableParts, reinterpret_cast<HuffTables *>(tables) + slot);
+        expand_table(bits + I.file_off, I, (int)(id & 3u), id / 4u % kTableParts, runs,
+                     reinterpret_cast<HuffTables *>(tables) + slot);
         return;
     }
     const int img = find_image_wave(n_images, wg, [&](int i) { return recs[i].window0; });
@@ -2467,12 +2469,12 @@ void launch_scan_restart_markers(const uint8_t *bits, const ImageRec *recs, int 
                                  uint32_t n_windows, uint32_t window_bytes, uint32_t *win_count, uint32_t *win_first,
                                  uint32_t *data_end, uint32_t *retry,
                                  int32_t *status, const uint32_t *table_rep, uint32_t n_tables,
-                                 uint8_t *tables, hipStream_t stream)
+                                 bool runs, uint8_t *tables, hipStream_t stream)
 {
     if (n_windows == 0) return;
     hipLaunchKernelGGL(scan_restart_markers, dim3(n_windows + 4 * kTableParts * n_tables), dim3(kDecodeThreads), 0, stream,
                        bits, recs, n_images, n_windows, window_bytes, win_count, win_first, data_end, retry, status, table_rep,
-                       reinterpret_cast<uint4 *>(tables));
+                       runs, reinterpret_cast<uint4 *>(tables));
 }
 
 void launch_decode_entropy(const uint8_t *bits, const ImageRec *recs, int n_images,

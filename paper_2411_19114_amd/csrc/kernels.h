@@ -15,12 +15,13 @@ size_t huff_tables_bytes();
 // table_rep[s] = an image whose tables go into slot s of `tables` (n_tables slots);
 // window_bytes = raw bytes between workgroup starts (the ImageRecs' n_windows count such windows);
 // data_end[i] = length of image i's entropy-coded segment as the host found it, lowered by the
-// kernel to the offset of the first EOI marker inside it; retry[i] = 0
+// kernel to the offset of the first EOI marker inside it; retry[i] = 0;
+// runs: the decoder's kernels of this call read the tables' run entries
 void launch_scan_restart_markers(const uint8_t *bits, const ImageRec *recs, int n_images,
                                  uint32_t n_windows, uint32_t window_bytes, uint32_t *win_count, uint32_t *win_first,
                                  uint32_t *data_end, uint32_t *retry,
                                  int32_t *status, const uint32_t *table_rep, uint32_t n_tables,
-                                 uint8_t *tables, hipStream_t stream);
+                                 bool runs, uint8_t *tables, hipStream_t stream);
 // coef + side_off: one int16 per block of the coefficient workspace, in the same allocation
 // behind the coefficients (the DC differences, which the decoder turns into values in a second
 // step of the same launch); side_off plus the number of blocks must stay below 2^32;

@@ -135,3 +135,29 @@ def test_a_thousand_streams_take_one_round():
         finally:
             h.close()
     assert took[1] <= 1.5 * took[0], took
+
+
+def test_run_entries_are_made_where_they_are_read():
+    """300 images with tables of their own, in turn with restart intervals for a lane each, whose decoder reads no run
+    entries, and with one for the image, whose decoder does: right on one handle either way, and the former does
+    not wait for the entries (the scan stage took as long for both, 0.7 of it now)."""
+    import torch
+    import paper_2411_19114_amd as prep
+    n = 300
+    images = [_image(400 + k, 96, 96, 6.0 + k % 5) for k in range(n)]
+    calls = [[oracle.encode(im, 84 + k % 9, MODE_444, dri)[0] for k, im in enumerate(images)] for dri in (8, 400)]
+    # (windows as in large calls)
+    h = prep.Preprocessor(device=0, max_batch=n, max_width=96, max_height=96, flags=prep.FLAG_LARGE_WINDOWS,
+                          max_bitstream_bytes=max(sum(map(len, c)) for c in calls))
+    h.set_timing(True)
+    took = [[], []]
+    try:
+        for k in (0, 1, 0, 1):
+            check_against_oracle(h, calls[k], 0, 16, 16, "f32")
+        for k in (0, 1) * 10:
+            run_gpu(h, calls[k], 0, 16, 16, "f32", resident=True)
+            torch.cuda.synchronize()
+            took[k].append(h.stage_ms()[0])
+    finally:
+        h.close()
+    assert min(took[0]) <= 0.88 * min(took[1]), took
