@@ -65,7 +65,7 @@ def sources_hash():
     h = hashlib.sha256()
     for f in sorted(glob.glob(os.path.join(ROOT, "paper_2411_19114_amd", "csrc", "*"))):
         # the image path's sources (the audio path and the batching server have no part in it)
-        if f.endswith((".hip", ".cpp", ".h")) and os.path.basename(f) not in ("audio.hip", "batcher.cpp"):
+        if f.endswith((".hip", ".cpp", ".h")) and os.path.basename(f) not in ("audio.hip", "audio_plan.h", "batcher.cpp"):
             h.update(os.path.basename(f).encode())
             with open(f, "rb") as fh:
                 h.update(fh.read())
@@ -556,7 +556,7 @@ def run_audio(args, torch, prep):
                    "input_generation_s": round(gen_s, 2)},
         "roofline": {"bound": "alu", "achieved": flops / (ms * 1e-3) / 1e12, "peak": 78.6, "unit": "TFLOP/s",
                      "frac": flops / (ms * 1e-3) / 1e12 / 78.6, "traffic": None,
-                     "kernel": "whole step (resample_phase_kernel, log_mel_kernel, normalize_kernel)",
+                     "kernel": "whole step (resample_bands_kernel, log_mel_kernel, normalize_kernel)",
                      "algorithmic_bytes": traffic, "hbm_frac_by_algorithmic_bytes": traffic / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS},
         "cpu_baseline": cpu,
     }

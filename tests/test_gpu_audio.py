@@ -141,11 +141,16 @@ def test_frames_in_pairs(prep):
         ap.close()
 
 
-# rate pairs with a plan for the matrix form: 441 : 160, 3 : 1, 441 : 640 (four groups of workgroups), 3 : 2,
-# 441 : 400, 25 : 8, 4 : 5; and without: 6 : 1 (the band is too long), 1601 : 1600 (a chunk does not fit LDS)
-@pytest.mark.parametrize("rate_in", [44100, 48000, 11025, 24000, 17640, 50000, 12800, 96000, 16010])
+# rate pairs that take the matrix form: 441 : 160, 3 : 1, 441 : 640, 3 : 2, 441 : 400, 25 : 8, 4 : 5, 1601 : 1600; and those
+# that take a lane per output: 6 : 1 and 441 : 80 (the band is too long), 3201 : 3200 (the table is too large)
+# (tests/test_audio_plan.py holds both lists to it)
+MATRIX_RATES = [44100, 48000, 11025, 24000, 17640, 50000, 12800, 16010]
+PHASE_RATES = [96000, 88200, 16005]
+
+
+@pytest.mark.parametrize("rate_in", MATRIX_RATES + PHASE_RATES)
 def test_resampled_lengths_at_the_edges_of_chunks(prep, rate_in):
-    """Utterances of one sample more or less than whole chunks and tiles, one that fills none,
+    """Utterances of one sample more or less than whole periods and tiles, one that fills none,
     and one of NaNs beside them, which must not reach its neighbours.  (No shorter ones: the bound
     above is for deviations of order one.  The two frames of an utterance of 300 samples differ by 0.02
     in some channels, which makes 1e-4 of a log-Mel value's rounding.)"""
@@ -166,6 +171,29 @@ def test_resampled_lengths_at_the_edges_of_chunks(prep, rate_in):
         assert np.isnan(got[1]).any()
         for i in range(len(waves)):
             assert i == 1 or np.array_equal(got[i], plain[i])
+    finally:
+        ap.close()
+
+
+@pytest.mark.parametrize("rate_in,bad", [(44100, np.nan), (48000, np.inf), (24000, -np.inf), (11025, np.nan)])
+def test_bad_samples_between_frames(prep, rate_in, bad):
+    """Samples that are no finite numbers reach the outputs whose own taps hold them, not the others of their band:
+    with frames of 512 samples every 1024, those in the middle of a gap reach no frame, and all features are the
+    oracle's.  One stands just so far from a frame that the taps of the nearest output inside end before it."""
+    rate, hop = 16000, 1024
+    good = speech_like(5, rate_in, 3.0)
+    reach = int(np.ceil(6 / 0.99 * max(rate_in, rate) / rate)) + 1             # samples on either side that an output reads
+    bad_at = [int(round((hop * k + 512) * rate_in / rate)) for k in (1, 7, 20)]     # the middles of gaps
+    bad_at += [int(np.ceil((hop * k + 256) * rate_in / rate)) + reach for k in (3, 11)]    # just behind a frame
+    bad_at += [int((hop * k - 257) * rate_in / rate) - reach for k in (5, 13)]             # just before one
+    w = good.copy()
+    w[bad_at] = bad
+    ap = prep.AudioPreprocessor(max_batch=2, max_total_samples=4 * len(w), hop=hop)
+    try:
+        clean, got = run(ap, [good], rate_in)[0], run(ap, [w], rate_in)[0]
+        ref = audio.preprocess(good.astype(np.float64), rate_in, hop=hop)
+        assert clean.shape == ref.shape and np.abs(clean - ref).max() <= FEATURE_TOL
+        assert np.isfinite(got).all() and np.abs(got - ref).max() <= FEATURE_TOL
     finally:
         ap.close()
 
