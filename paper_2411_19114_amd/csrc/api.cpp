@@ -319,15 +319,15 @@ uint32_t table_slot_of(prep_handle *h, const uint8_t *bits, const uint64_t *offs
 //   - A stream is cut only if it is sparse enough for its windows to be joined
 //     (stream_density_limit).  A call with a denser one that is more than a quarter as long as the
 //     longest sparse stream is not cut at all: it waits for that one either way.
-//   - Windows pay by the length of the longest stream (7, 8, 12 and 25 us per KB in one workgroup
-//     with 1, 3, 4 and 6 blocks per MCU) and cost four launches and about 60 us for every MB.  Where no
-//     stream is longer than one chunk, no MCU has six blocks and the streams occupy the chip by
-//     themselves, a workgroup each is faster: batches of 256 gray images of 256 x 256
-//     174 against 219 us (1.6 MB), of 384 4:4:4 images of 192 x 192 238 against 293 us (2.1 MB), of 512
-//     4:2:2 images of 64 x 64 258 against 295 us.  It is not for smaller batches (64 of these:
-//     139 against 129, 152 against 146, 163 against 103 us).
-//   - A stream of one subsequence is decoded by one lane (a gray image of 16 x 16: 45 against 55 us),
-//     and batches of streams of a few wait for their launches (512 4:2:0 images of 32 x 32: 270 against 288).
+//   - Windows pay by the length of the longest stream and cost three launches and about 30 us for every MB.  Where
+//     no stream is longer than one chunk, no MCU has six blocks and the streams occupy the chip by
+//     themselves, a workgroup each is faster.  Decode stage, us, in windows against a workgroup each: 256 gray images of
+//     256 x 256 91 / 69, 384 4:4:4 ones of 192 x 192 116 / 88, 384 4:2:2 ones of 160 x 160 137 / 101.  4:2:0 images
+//     of 256 x 256 78 / 129 (32), 91 / 128 (128), 110 / 130 (256), 158 / 151 (384).  (Since a workgroup's iteration takes half
+//     the time that it took when these lines were drawn, gray and 4:4:4 streams of one chunk would be faster without
+//     windows from far fewer on: 32 of the latter 73 / 68, 128 80 / 72, 128 of the former 67 / 65; 4:2:0 from 384.)
+//   - A stream of one subsequence is decoded by one lane, and batches of streams of a few wait for their
+//     launches (4:2:0 images of 32 x 32 60 / 51 (one), 71 / 64 (256), 78 / 73 (512)).
 struct StreamCut {
     uint32_t n = 0, blocks_per_mcu = 0;  // streams that may be cut, and the most blocks in an MCU of theirs
     uint64_t total = 0, longest = 0, longest_dense = 0;

@@ -22,12 +22,19 @@ constexpr int kWindowBytes = 12288;                         // raw bytes between
 // smaller windows (more workgroups, a few restart intervals each) and its workgroups find the
 // decoder states inside an interval by phase hypotheses instead (see decode_entropy).
 constexpr int kSmallWindowBytes = 2048;
-constexpr uint64_t kSmallCallBytes = 1536 << 10;            // entropy-coded bytes of a call up to which it is cut small
+// Entropy-coded bytes of a call up to which it is cut small.  The chip holds 768 workgroups of that variant, 1.5 MB
+// of windows.  Decode stage, us, cut small against not, images of 480 x 360: a marker a row, 4:2:0 98 / 142 (0.6 MB),
+// 109 / 140 (1.1), 160 / 140 (1.7); 4:2:2 92 / 263 (1.3), 161 / 262 (2.5), 234 / 343 (3.8); gray 79 / 212 (1.5),
+// 149 / 230 (3.1); 4:4:4 80 / 95 (0.5), 88 / 94 (0.9), 135 / 95 (1.8).  Where intervals are much shorter than a
+// window the line lies lower: a marker every eight MCUs, 4:2:0 99 / 137 (1.1), 152 / 137 (1.7), but 4:2:2 98 / 89 (0.3),
+// 4:4:4 102 / 70 (0.5), gray 104 / 51 (0.3): there the cut does not pay at all, and is made all the same.
+constexpr uint64_t kSmallCallBytes = 1536 << 10;
 // The smallest calls (a single image, a batch of a few dozen small ones) still leave most
 // compute units idle with 2 KiB windows: they are cut into windows of about one restart
-// interval of a small image, and a lane of the hypothesis passes takes half a subsequence
-// (measured on batches of 256 x 256 images: 86 against 142 us up to 16 images, 96 against 140
-// at 32 = 375 KB, even at 48 = 562 KB, worse from there on).
+// interval of a small image, and a lane of the hypothesis passes takes half a subsequence.
+// 768 such windows are 384 KB; beyond them the two ways meet (images of 256 x 256, a marker a row, us, these windows
+// against 2 KiB: 4:2:0 56 / 79 at 84 KB, 60 / 80 at 335, 98 / 81 at 503; 4:4:4 61 / 81 at 257, 102 / 82 at 513; gray
+// 58 / 93 at 307, 96 / 93 at 461).
 constexpr int kTinyWindowBytes = 512;
 constexpr uint64_t kTinyCallBytes = 448 << 10;
 // Mean bytes of a restart interval up to which a lane decodes it whole, in large calls (see decode_entropy)
@@ -39,10 +46,10 @@ constexpr int kStreamRowBytes = 68;                         // clean bytes per r
 constexpr int kStreamTinyRowBytes = 36;                     // the same in calls with little data
 // Entropy-coded bytes of such streams in a call up to which rows are short.  Short rows make more
 // workgroups, whose lanes have less to do one after the other; once the chip is full, their longer
-// overlaps only add work.  Whole calls, short against long rows, us: photographs of 44 KB 126
-// against 182 (one), 149 against 197 (1.0 MB), 184 against 212 (1.7 MB), 225 against 216 (2.0 MB);
-// full-HD stills of 0.7 MB 170 against 211 (one), 221 against 215 (two).  (Where fewer hypotheses are
-// decoded, 4:2:2 and 4:4:4, the two meet later, at 2.5 and 4.7 MB: the line is below all of these.)
+// overlaps only add work.  Decode stage, short against long rows, us, images of 480 x 360: 4:2:0 74 against 91 (one,
+// 35 KB), 91 / 93 (0.6 MB), 97 / 98 (0.8), 108 / 99 (1.1), 137 / 107 (1.7).  Where fewer hypotheses are decoded the two
+// meet later: 4:4:4 98 / 109 (1.8), 148 / 132 (3.6); 4:2:2 87 / 97 (1.2), 103 / 101 (1.9); gray 81 / 92 (2.0), 117 / 104
+// (3.1).  One full-HD still of 0.76 MB of noise, near the density limit, loses by them: 146 / 114.
 constexpr uint64_t kStreamTinyBytes = 1024 << 10;
 // Overlap rows.  A decoder that comes out of a window agrees with none of the hypotheses of an
 // overlap row with a probability that falls with the row's length: full-HD stills of quality 95,

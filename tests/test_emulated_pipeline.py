@@ -60,8 +60,8 @@ def test_modes_restart_intervals_and_odd_sizes(windows):
 
 
 def test_tables_whose_codes_are_mostly_sixteen_bits_long():
-    # nearly every AC symbol takes the decoder's second-level lookup, and the table's
-    # second-level blocks do not all fit their pool, so some take the canonical search
+    # most codes begin below the prefixes that have an entry for each sixteen-bit word: nearly
+    # every AC symbol takes the canonical search
     streams = [oracle.encode(_img(40 + k, 70, 45), 88, mode, dri, table_mode=2)[0]
                for k, (mode, dri) in enumerate([(MODE_420, 0), (MODE_420, 2), (MODE_444, 0), (MODE_GRAY, 3)])]
     _check(streams, 0, 1, 1, "f32", flags=2)

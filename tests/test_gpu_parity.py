@@ -201,9 +201,9 @@ def test_extreme_coefficients_and_byte_stuffing(pp):
 
 
 def test_tables_whose_codes_are_mostly_sixteen_bits_long(pp):
-    # oracle table mode 2: 148 of the 162 AC codes are sixteen bits long, so nearly every AC
-    # symbol takes the second-level lookup, and the second-level blocks do not all fit their
-    # pool, so some take the canonical search; short intervals, long ones and none
+    # oracle table mode 2: 148 of the 162 AC codes are sixteen bits long, and most of them begin below the
+    # prefixes that have an entry for each sixteen-bit word, so nearly every AC symbol takes the
+    # canonical search; short intervals, long ones and none
     streams = []
     for k, (mode, dri, size) in enumerate([(MODE_420, 0, (200, 120)), (MODE_420, 2, (200, 120)),
                                            (MODE_444, 0, (90, 70)), (MODE_GRAY, 3, (90, 70)),
