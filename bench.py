@@ -50,12 +50,12 @@ N_STREAMS, STREAM_BATCH = 7, 8
 # scaled by what the same counters read for a plain 256 MiB copy (FETCH_SIZE x 2, WRITE_SIZE x 1).
 # They describe the kernels whose sources hash to MEASURED_SOURCES; for any other sources the
 # figure is reported as null.
-MEASURED_SOURCES = "a3595b423143f78e437f7150330192da0d47517a24faa23257c2013487855dda"
+MEASURED_SOURCES = "4f8804edc0ac6eaa9d56116b9685fbb4c2390bf08f055296221e0c59bdb46753"
 MEASURED_TRAFFIC = {
-    2: {"scan": (5397 * 2 + 1271) * 1024, "decode": (7685 * 2 + 289785) * 1024,
-        "reconstruct": (50666 * 2 + 104422) * 1024, "resize": (49124 * 2 + 75264) * 1024},
-    4: {"scan": (23819 * 2 + 577) * 1024, "decode": (28280 * 2 + 623130) * 1024,
-        "reconstruct": (114445 * 2 + 241166) * 1024, "resize": (92355 * 2 + 55296) * 1024},
+    2: {"scan": (5357 * 2 + 1732) * 1024, "decode": (7826 * 2 + 288417) * 1024,
+        "reconstruct": (50667 * 2 + 104419) * 1024, "resize": (49121 * 2 + 75264) * 1024},
+    4: {"scan": (23781 * 2 + 1135) * 1024, "decode": (29249 * 2 + 945357) * 1024,
+        "reconstruct": (114445 * 2 + 241146) * 1024, "resize": (91248 * 2 + 55296) * 1024},
 }
 
 
